@@ -395,6 +395,14 @@ int q8_conv_f32_ref(const q8_conv_desc *d, const float *x_dev, const float *w_de
                     const float *b_dev, const float *res_dev, float *y_dev,
                     void *stream);
 
+/* The same with the output written at d->out_c_off inside pixels of d->out_c_stride values
+ * (0 = K; x and res dense) and with the running maxima of the calibration text taken on the
+ * way (see q8_calibrate_maxabs; each pointer may be NULL): *maxabs_sum_dev of |conv + bias|
+ * before the residual sum and the ReLU, *maxabs_out_dev of |y| over what this call writes. */
+int q8_conv_f32_observed(const q8_conv_desc *d, const float *x_dev, const float *w_dev,
+                         const float *b_dev, const float *res_dev, float *y_dev,
+                         float *maxabs_sum_dev, float *maxabs_out_dev, void *stream);
+
 /* int8 max-pool over an R x S window; taps outside the image are ignored.         */
 int q8_maxpool_i8(const int8_t *x_dev, int N, int H, int W, int C, int R, int S,
                   int stride, int pad, int Ho, int Wo, int8_t *y_dev, void *stream);

@@ -34,7 +34,7 @@ EXPORTS = [
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8",
-    "q8_conv_f32_ref", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
+    "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
 
@@ -137,6 +137,7 @@ lib.q8_sum_factor.restype = _f
 lib.q8_sum_factor.argtypes = [_f, _f]
 lib.q8_probe_mfma_i8.argtypes = [_i, _i, _vp, _vp]
 lib.q8_conv_f32_ref.argtypes = [_dp, _vp, _vp, _vp, _vp, _vp, _vp]
+lib.q8_conv_f32_observed.argtypes = [_dp] + [_vp] * 8
 lib.q8_maxpool_i8.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
 lib.q8_maxpool_f32.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
 
@@ -506,6 +507,16 @@ def conv_f32_ref(desc, x, w, b=None, res=None, out=None):
     return out
 
 
+def conv_f32_observed(desc, x, w, b, res, out, maxabs_sum, maxabs_out):
+    """conv_f32_ref into a channel slice of ``out``, with the running max-abs of the value before
+    the residual sum and of the output (1-element fp32 device tensors, or None)."""
+    _check(lib.q8_conv_f32_observed(C.byref(desc), _ptr(x, torch.float32), _ptr(w, torch.float32),
+                                    _ptr(b, torch.float32), _ptr(res, torch.float32),
+                                    _ptr(out, torch.float32), _ptr(maxabs_sum, torch.float32),
+                                    _ptr(maxabs_out, torch.float32), _stream()))
+    return out
+
+
 def _pool(fn, dtype, x, R, S, stride, pad, Ho, Wo):
     N, H, W, Cc = x.shape
     y = torch.empty((N, Ho, Wo, Cc), dtype=dtype, device=x.device)
@@ -526,7 +537,7 @@ def pool_i8(x, mode, R, S, stride, pad, Ho, Wo, q_in=1.0, q_out=1.0, out=None, o
     factor ``q_in`` to ``q_out``."""
     N, H, W, Cc = x.shape
     if out is None:
-        out = torch.zeros((N, Ho, Wo, Cc), dtype=torch.int8, device=x.device)
+        out = torch.empty((N, Ho, Wo, Cc), dtype=torch.int8, device=x.device)
     _check(lib.q8_pool_i8(_ptr(x, torch.int8), N, H, W, Cc, 0 if mode == "max" else 1, R, S, stride,
                           pad, Ho, Wo, q_in, q_out, _ptr(out, torch.int8), out.shape[3], out_c_off,
                           _stream()))
@@ -536,7 +547,7 @@ def pool_i8(x, mode, R, S, stride, pad, Ho, Wo, q_in=1.0, q_out=1.0, out=None, o
 def pool_f32(x, mode, R, S, stride, pad, Ho, Wo, out=None, out_c_off=0):
     N, H, W, Cc = x.shape
     if out is None:
-        out = torch.zeros((N, Ho, Wo, Cc), dtype=torch.float32, device=x.device)
+        out = torch.empty((N, Ho, Wo, Cc), dtype=torch.float32, device=x.device)
     _check(lib.q8_pool_f32(_ptr(x, torch.float32), N, H, W, Cc, 0 if mode == "max" else 1, R, S,
                            stride, pad, Ho, Wo, _ptr(out, torch.float32), out.shape[3], out_c_off,
                            _stream()))

@@ -1,0 +1,412 @@
+// fp32 NHWC convolution + bias (+ residual) (+ ReLU): the forward that produces the real-valued
+// activations calibration measures, with the max-abs of what it computes taken on the way.
+// A helper around the quantised path, not part of it.
+//
+// What bounds it: on large layers the fp32 matrix rate (122 of the 153 TF a library product of
+// 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at batch 64); on the layers of a calibration batch
+// of eight (200 - 400 tiles) the operand loads, 15 - 20 bytes per clock and CU from L2.  16
+// reduction bytes per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments
+// straight into the MFMA's register layout (16 rows x 64 bytes a load), two stages ahead of the
+// one it computes: no LDS and no barrier inside the loop.  ResNet-50 calibration on 8 images:
+// 13.9 -> 1.8 ms, with the max-abs taken here instead of in a pass over every tensor and the value
+// in front of a fused sum measured on the way instead of in a second convolution.
+//
+// Small maps have few tiles (7 x 7 at batch 8: 392 pixels): KW groups of wavefronts then share
+// the stages of one tile and add their accumulators through LDS in a fixed order.
+#include "q8_common.h"
+#include "q8_conv_common.h"
+
+namespace q8 {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+struct F32Params {
+  const float* __restrict__ x;
+  const float* __restrict__ w;
+  const float* __restrict__ b;
+  const float* __restrict__ res;
+  float* __restrict__ y;
+  unsigned* __restrict__ obs_sum;      // max |conv + bias| before the residual sum, or null
+  unsigned* __restrict__ obs_out;      // max |y|, or null
+  int N, H, W, C, K, R, S, sh, sw, ph, pw, dh, dw, Ho, Wo, M, rsc, out_cs, out_off, relu;
+  int vec_y, vec_b;                    // output / residual rows, the bias take 16-byte accesses
+  FastDiv by_img, by_row, by_c, by_s;
+  int n_ptiles, n_ctiles;
+};
+
+[[maybe_unused]] constexpr int kOob = (int)0x80000000;   // beyond any descriptor (they span at most 2^31 - 1 bytes)
+
+__device__ __forceinline__ void observe(unsigned* slot, float m) {
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63) == 0) {
+    const unsigned bits = __float_as_uint(m);
+    if (bits > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(slot, bits);
+  }
+}
+
+// WP x WC wavefronts, each TP x TC MFMA tiles of 16 pixels x 16 channels; NC chunks of 64 bytes per
+// row and stage, NB stages in registers.
+// MODE 2: C % (16 NC) == 0, a stage lies in one tap; 1: C % 4 == 0, a 16-byte chunk lies
+// in one tap; 0: any C, four single loads per chunk.
+template <int WP, int WC, int TP, int TC, int KW, int NC, int NB, int MODE>
+__global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(const F32Params p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int BP = WP * TP * 16, BC = WC * TC * 16, NW = WP * WC;
+  constexpr int kXch = KW > 1 ? (KW - 1) * NW * TP * TC * 256 : 4;
+  __shared__ __attribute__((aligned(16))) float xch[kXch];
+  const int nblk = p.n_ptiles * p.n_ctiles;
+  int bid = blockIdx.x;
+  {   // every XCD takes a contiguous run of tiles, channel tile fastest (shared activations)
+    const int xcd = bid % kNumXcd, idx = bid / kNumXcd, base = nblk / kNumXcd, rem = nblk % kNumXcd;
+    bid = xcd * base + (xcd < rem ? xcd : rem) + idx;
+  }
+  const int ptile = bid / p.n_ctiles, ctile = bid - ptile * p.n_ctiles;
+  const int pix0 = ptile * BP, ch0 = ctile * BC;
+  const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kgroup = KW > 1 ? wave_all / NW : 0, wave = KW > 1 ? wave_all % NW : wave_all;
+  const int wave_p = wave % WP, wave_c = wave / WP;
+
+  // the activation descriptor starts at the tile's first image: offsets stay below 2^31
+  // whatever the batch (the host checks the span of a tile's images)
+  const int n0 = fast_div(pix0, p.by_img.m, p.by_img.s);
+  const long img = (long)p.H * p.W * p.C;
+  const long x_left = ((long)p.N - n0) * img * 4;
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(p.x + n0 * img), 0, (int)(x_left < 0x7fffffffL ? x_left : 0x7fffffffL), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      __builtin_amdgcn_make_buffer_rsrc((void*)p.w, 0, p.K * p.rsc * 4, 0x00020000);
+
+  int a_off[TC];
+#pragma unroll
+  for (int i = 0; i < TC; ++i) {
+    // rows are dealt to channels so that a lane's accumulators of the TC tiles are 4 TC
+    // consecutive channels of one pixel
+    const int ch = ch0 + wave_c * TC * 16 + (row >> 2) * 4 * TC + i * 4 + (row & 3);
+    a_off[i] = ch < p.K ? ch * p.rsc * 4 + quarter * 16 : kOob;
+  }
+  int hi0[TP], wi0[TP], base[TP];
+#pragma unroll
+  for (int j = 0; j < TP; ++j) {
+    const int pix = pix0 + (wave_p * TP + j) * 16 + row;
+    hi0[j] = -(1 << 29);               // a pixel beyond M: every tap outside the image
+    wi0[j] = base[j] = 0;
+    if (pix < p.M) {
+      const int n = fast_div(pix, p.by_img.m, p.by_img.s);
+      const int rem = pix - n * (p.Ho * p.Wo);
+      const int ho = fast_div(rem, p.by_row.m, p.by_row.s);
+      hi0[j] = ho * p.sh - p.ph;
+      wi0[j] = (rem - ho * p.Wo) * p.sw - p.pw;
+      base[j] = (((n - n0) * p.H + hi0[j]) * p.W + wi0[j]) * p.C;
+    }
+  }
+
+  v4f acc[TC][TP];
+#pragma unroll
+  for (int i = 0; i < TC; ++i)
+#pragma unroll
+    for (int j = 0; j < TP; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+  v4f af[NB][NC][TC], bf[NB][NC][TP];    // fragments of the stage computed and of NB - 1 in flight
+  auto tap_offset = [&](int kidx, int j) {   // byte offset of reduction index kidx for row j
+    const int tap = fast_div(kidx, p.by_c.m, p.by_c.s), c = kidx - tap * p.C;
+    const int r = fast_div(tap, p.by_s.m, p.by_s.s), s = tap - r * p.S;
+    const bool in = (kidx < p.rsc) & ((unsigned)(hi0[j] + r * p.dh) < (unsigned)p.H) &
+                    ((unsigned)(wi0[j] + s * p.dw) < (unsigned)p.W);
+    return in ? (base[j] + (r * p.dh * p.W + s * p.dw) * p.C + c) * 4 : kOob;
+  };
+  // Always issues the same number of loads (a stage behind the last one reads zeros), so the
+  // waits in front of the MFMAs count exactly the loads of the stage they need.
+  const int n_st = (p.rsc + NC * 16 - 1) / (NC * 16);
+  auto load_stage = [&](int st, auto buf_c) __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf_c)::value;
+#pragma unroll
+    for (int i = 0; i < TC; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        af[BUF][c][i] = __builtin_bit_cast(
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (st < n_st ? a_off[i] : kOob) + c * 64,
+                                                       st * NC * 64, 0));
+#pragma unroll
+    for (int j = 0; j < TP; ++j) {
+      if constexpr (MODE == 2) {
+        const int tap = fast_div(st * NC * 16, p.by_c.m, p.by_c.s), c0 = st * NC * 16 - tap * p.C;
+        const int r = fast_div(tap, p.by_s.m, p.by_s.s), s = tap - r * p.S;
+        const int delta = (r * p.dh * p.W + s * p.dw) * p.C + c0;
+        int off = (base[j] + delta) * 4 + quarter * 16;
+        asm volatile("" : "+v"(off));      // a select, no branch: the stage stays one region
+        const bool in = (st < n_st) & ((unsigned)(hi0[j] + r * p.dh) < (unsigned)p.H) &
+                        ((unsigned)(wi0[j] + s * p.dw) < (unsigned)p.W);
+        off = in ? off : kOob;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          bf[BUF][c][j] = __builtin_bit_cast(
+              v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, off + c * 64, 0, 0));
+      } else {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const int kidx = (st * NC + c) * 16 + quarter * 4;
+          if constexpr (MODE == 1) {
+            bf[BUF][c][j] = __builtin_bit_cast(
+                v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, tap_offset(kidx, j), 0, 0));
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              bf[BUF][c][j][e] = __builtin_bit_cast(
+                  float, __builtin_amdgcn_raw_buffer_load_b32(rsrc_x, tap_offset(kidx + e, j), 0, 0));
+          }
+        }
+      }
+    }
+  };
+  auto mma_stage = [&](auto buf_c) __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf_c)::value;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+          for (int j = 0; j < TP; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[BUF][c][i][e], bf[BUF][c][j][e],
+                                                             acc[i][j], 0, 0, 0);
+  };
+  using std::integral_constant;
+  auto prologue = [&](auto self, auto b_c) __attribute__((always_inline)) -> void {
+    constexpr int BUF = decltype(b_c)::value;
+    if constexpr (BUF < NB - 1) {
+      load_stage(kgroup + BUF * KW, b_c);
+      self(self, integral_constant<int, BUF + 1>{});
+    }
+  };
+  prologue(prologue, integral_constant<int, 0>{});
+  // Full passes over the NB buffers.  The loads of a stage are spread between the MFMAs of the
+  // stage computed meanwhile: a wavefront issues in order, and with 32 rows a load the address
+  // unit takes long enough that a burst of them would keep the matrix unit waiting.
+  const int n_mine = (n_st - kgroup + KW - 1) / KW;
+  int k0 = 0;
+  for (; k0 + NB <= n_mine; k0 += NB) {
+    auto pass = [&](auto self, auto b_c) __attribute__((always_inline)) -> void {
+      constexpr int BUF = decltype(b_c)::value;
+      if constexpr (BUF < NB) {
+        load_stage(kgroup + (k0 + BUF + NB - 1) * KW, integral_constant<int, (BUF + NB - 1) % NB>{});
+        mma_stage(b_c);
+        if constexpr (MODE == 2) {
+          constexpr int kLoads = NC * (TC + TP), kMma = NC * 4 * TC * TP;
+#pragma unroll
+          for (int g = 0; g < kLoads; ++g) {
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                     // one VMEM read
+            __builtin_amdgcn_sched_group_barrier(0x008, kMma / kLoads, 0);         // MFMAs
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        self(self, integral_constant<int, BUF + 1>{});
+      }
+    };
+    pass(pass, integral_constant<int, 0>{});
+  }
+  auto rest = [&](auto self, auto b_c) __attribute__((always_inline)) -> void {
+    constexpr int BUF = decltype(b_c)::value;
+    if constexpr (BUF < NB - 1) {
+      if (k0 + BUF < n_mine) mma_stage(b_c);
+      self(self, integral_constant<int, BUF + 1>{});
+    }
+  };
+  rest(rest, integral_constant<int, 0>{});
+
+  // Units of the tail: one MFMA tile, four consecutive channels of a pixel per lane.  With KW groups
+  // every wavefront hands the units it does not own to their owners through LDS, adds up its
+  // own share and finishes it, so the tail is spread over all of them.
+  constexpr int U = TC * TP, OWN = U / KW;
+  static_assert(U % KW == 0, "every group owns the same number of units");
+  v4f own[OWN], bias[OWN];
+  const int u0 = kgroup * OWN;
+  auto unit_ch = [&](int u) { return ch0 + wave_c * TC * 16 + quarter * 4 * TC + u / TP * 4; };
+#pragma unroll
+  for (int k = 0; k < OWN; ++k) {
+    const int ch = unit_ch(u0 + k);
+    bias[k] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    if (p.b) {
+      if (p.vec_b && ch + 4 <= p.K) {
+        bias[k] = *reinterpret_cast<const v4f*>(p.b + ch);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (ch + e < p.K) bias[k][e] = p.b[ch + e];
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const v4f v = acc[u / TP][u % TP];
+    const int owner = u / OWN;
+    if (kgroup == owner) {
+      own[u % OWN] = v;
+    } else if constexpr (KW > 1) {
+      const int slot = (wave * U + u) * (KW - 1) + (kgroup < owner ? kgroup : kgroup - 1);
+      *reinterpret_cast<v4f*>(xch + (slot * 64 + lane) * 4) = v;
+    }
+  }
+  if constexpr (KW > 1) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < OWN; ++k)
+#pragma unroll
+      for (int g = 0; g < KW - 1; ++g)
+        own[k] += *reinterpret_cast<const v4f*>(xch + (((wave * U + u0 + k) * (KW - 1) + g) * 64 + lane) * 4);
+  }
+
+  float m_sum = 0.0f, m_out = 0.0f;
+#pragma unroll
+  for (int k = 0; k < OWN; ++k) {
+    const int u = u0 + k, ch = unit_ch(u), nvalid = p.K - ch;
+    const int pix = pix0 + (wave_p * TP + u % TP) * 16 + row;
+    if (nvalid <= 0 || pix >= p.M) continue;
+    float* y = p.y + (size_t)pix * p.out_cs + p.out_off + ch;
+    const float* res = p.res ? p.res + (size_t)pix * p.K + ch : nullptr;
+    v4f v = own[k] + bias[k];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < nvalid) m_sum = fmaxf(m_sum, fabsf(v[e]));
+    const bool whole = p.vec_y && nvalid >= 4;
+    if (res) {
+      if (whole) {
+        v += *reinterpret_cast<const v4f*>(res);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < nvalid) v[e] += res[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (p.relu) v[e] = fmaxf(v[e], 0.0f);
+      if (e < nvalid) m_out = fmaxf(m_out, fabsf(v[e]));
+    }
+    if (whole) {
+      *reinterpret_cast<v4f*>(y) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < nvalid) y[e] = v[e];
+    }
+  }
+  if (p.obs_sum) observe(p.obs_sum, m_sum);
+  if (p.obs_out) observe(p.obs_out, m_out);
+#endif
+}
+
+// Any size: one thread per output value.  Only for tensors the 32-bit offsets above cannot
+// address (an image or the filters beyond 2 GiB, 2^31 output pixels).
+__global__ __launch_bounds__(kThreads) void conv_f32_any_kernel(const F32Params p) {
+  const size_t total = (size_t)p.N * p.Ho * p.Wo * p.K;
+  float m_sum = 0.0f, m_out = 0.0f;
+  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < total;
+       i += (size_t)gridDim.x * kThreads) {
+    const int k = (int)(i % p.K);
+    const size_t pix = i / p.K;
+    const int wo = (int)(pix % p.Wo), ho = (int)(pix / p.Wo % p.Ho);
+    const size_t n = pix / p.Wo / p.Ho;
+    float v = 0.0f;
+    for (int r = 0; r < p.R; ++r) {
+      const long hi = (long)ho * p.sh - p.ph + (long)r * p.dh;
+      if (hi < 0 || hi >= p.H) continue;
+      for (int s = 0; s < p.S; ++s) {
+        const long wi = (long)wo * p.sw - p.pw + (long)s * p.dw;
+        if (wi < 0 || wi >= p.W) continue;
+        const float* x = p.x + ((n * p.H + hi) * p.W + wi) * p.C;
+        const float* w = p.w + (((size_t)k * p.R + r) * p.S + s) * p.C;
+        for (int c = 0; c < p.C; ++c) v = fmaf(x[c], w[c], v);
+      }
+    }
+    if (p.b) v += p.b[k];
+    m_sum = fmaxf(m_sum, fabsf(v));
+    if (p.res) v += p.res[pix * p.K + k];
+    if (p.relu) v = fmaxf(v, 0.0f);
+    m_out = fmaxf(m_out, fabsf(v));
+    p.y[pix * p.out_cs + p.out_off + k] = v;
+  }
+  if (p.obs_sum) observe(p.obs_sum, m_sum);
+  if (p.obs_out) observe(p.obs_out, m_out);
+}
+
+template <int WP, int WC, int TP, int TC, int KW, int NC, int NB>
+int launch_f32(F32Params& p, hipStream_t stream) {
+  p.n_ptiles = (p.M + WP * TP * 16 - 1) / (WP * TP * 16);
+  p.n_ctiles = (p.K + WC * TC * 16 - 1) / (WC * TC * 16);
+  const long nblk = (long)p.n_ptiles * p.n_ctiles;
+  if (nblk > 0x7fffffffL) return Q8_EUNSUPPORTED;
+  auto kernel = p.C % (16 * NC) == 0 ? conv_f32_mfma_kernel<WP, WC, TP, TC, KW, NC, NB, 2>
+                : p.C % 4 == 0 ? conv_f32_mfma_kernel<WP, WC, TP, TC, KW, NC, NB, 1>
+                               : conv_f32_mfma_kernel<WP, WC, TP, TC, KW, NC, NB, 0>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(WP * WC * KW * 64), 0, stream, p);
+  return q8_launch_status();
+}
+
+int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float* b, const float* res,
+             float* y, int out_cs, int out_off, float* obs_sum, float* obs_out, hipStream_t stream) {
+  Q8_REQUIRE(d && d->N >= 0 && d->H >= 1 && d->W >= 1 && d->C >= 1 && d->K >= 1 && d->R >= 1 &&
+                 d->S >= 1 && d->stride_h >= 1 && d->stride_w >= 1 && d->pad_h >= 0 &&
+                 d->pad_w >= 0 && d->dil_h >= 1 && d->dil_w >= 1, Q8_EINVAL);
+  F32Params p{};
+  p.Ho = q8_conv_out_h(d); p.Wo = q8_conv_out_w(d);
+  const long M = (long)d->N * p.Ho * p.Wo;
+  if (M == 0) return Q8_OK;
+  Q8_REQUIRE(x && w && y && out_off >= 0 && out_cs >= out_off + d->K, Q8_EINVAL);
+  p.x = x; p.w = w; p.b = b; p.res = res; p.y = y;
+  p.obs_sum = reinterpret_cast<unsigned*>(obs_sum); p.obs_out = reinterpret_cast<unsigned*>(obs_out);
+  p.N = d->N; p.H = d->H; p.W = d->W; p.C = d->C; p.K = d->K; p.R = d->R; p.S = d->S;
+  p.sh = d->stride_h; p.sw = d->stride_w; p.ph = d->pad_h; p.pw = d->pad_w;
+  p.dh = d->dil_h; p.dw = d->dil_w;
+  p.out_cs = out_cs; p.out_off = out_off; p.relu = d->relu ? 1 : 0;
+  p.vec_y = (out_cs % 4 == 0 && out_off % 4 == 0 && q8_aligned(y, 16) &&
+             (!res || (d->K % 4 == 0 && q8_aligned(res, 16)))) ? 1 : 0;
+  p.vec_b = q8_aligned(b, 16) ? 1 : 0;
+  const long rsc = (long)d->R * d->S * d->C, img = (long)d->H * d->W * d->C * 4;
+  const long per_img = (long)p.Ho * p.Wo;
+  // what one tile of at most 128 pixels can reach: its images and the padding around them
+  const long reach = (127 / per_img + 2) * img +
+                     ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + d->S * d->dil_w) * d->C * 4;
+  if (M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || reach > 0x7fffffffL || d->H > (1 << 28) ||
+      (long)d->R * d->dil_h > (1 << 28)) {
+    const size_t total = (size_t)M * d->K;
+    const size_t blocks = (total + kThreads - 1) / kThreads;
+    hipLaunchKernelGGL(conv_f32_any_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)),
+                       dim3(kThreads), 0, stream, p);
+    return q8_launch_status();
+  }
+  p.M = (int)M; p.rsc = (int)rsc;
+  p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
+  p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
+  // The largest tile that still gives every CU one; below that the tile is shared by four
+  // groups of wavefronts (their SIMDs), first 64 x 64, then 32 x 32 where those leave CUs idle.
+  auto tiles = [&](long t) { return (M + t - 1) / t * ((d->K + t - 1) / t); };
+  if (d->K > 64 && tiles(128) >= 256) return launch_f32<2, 2, 4, 4, 1, 1, 3>(p, stream);
+  if (d->K > 32 && tiles(64) >= 192) return launch_f32<1, 1, 4, 4, 4, 1, 3>(p, stream);
+  return launch_f32<1, 1, 2, 2, 4, 2, 3>(p, stream);
+}
+
+}  // namespace
+}  // namespace q8
+
+extern "C" {
+
+int q8_conv_f32_ref(const q8_conv_desc* d, const float* x_dev, const float* w_dev,
+                    const float* b_dev, const float* res_dev, float* y_dev, void* stream) {
+  return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev, d ? d->K : 0, 0, nullptr, nullptr,
+                      (hipStream_t)stream);
+}
+
+int q8_conv_f32_observed(const q8_conv_desc* d, const float* x_dev, const float* w_dev,
+                         const float* b_dev, const float* res_dev, float* y_dev,
+                         float* maxabs_sum_dev, float* maxabs_out_dev, void* stream) {
+  Q8_REQUIRE(q8_aligned(maxabs_sum_dev, 4) && q8_aligned(maxabs_out_dev, 4), Q8_EALIGN);
+  return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev,
+                      d && d->out_c_stride ? d->out_c_stride : (d ? d->K : 0), d ? d->out_c_off : 0,
+                      maxabs_sum_dev, maxabs_out_dev, (hipStream_t)stream);
+}
+
+}  // extern "C"

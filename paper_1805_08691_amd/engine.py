@@ -274,20 +274,56 @@ class Engine:
                     observe(op.dst, t[op.dst])
         return t
 
+    def _observed_forward(self, x, slot):
+        """fp32 forward of the folded network that leaves the running max-abs of every tensor in
+        ``slot`` (one-element device tensors by key).  A convolution takes the maxima of its own
+        output and of its value before a fused sum while it holds them; a stand-alone pooling
+        keeps its input's factor and is not measured."""
+        net, N = self.net, x.shape[0]
+        t = {net.input: x}
+        last_use = {}
+        for i, op in enumerate(net.ops):
+            last_use[op.src] = i
+            if op.kind == "conv" and op.res is not None:
+                last_use[op.res] = i
+        last_write = {op.dst: i for i, op in enumerate(net.ops)}
+        pooled = {op.dst for op in net.ops if op.kind == "pool"
+                  and net.tensors[op.dst].C != net.tensors[op.src].C}
+        for i, op in enumerate(net.ops):
+            d = net.tensors[op.dst]
+            if op.dst not in t:
+                t[op.dst] = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
+            out = t[op.dst]
+            if op.kind == "pool":
+                B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H, d.W, out=out,
+                           out_c_off=op.dst_c_off)
+            else:
+                Wf, bf = self.folded[op.name]
+                desc = self._desc(op, N, framed=False)
+                desc.in_c_stride = desc.res_c_stride = 0
+                desc.out_c_stride = d.C
+                B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
+                                    slot[op.name + ":branch"] if op.res else None, slot[op.dst])
+            if op.dst in pooled and last_write[op.dst] == i:
+                B.calibrate_maxabs(out, slot[op.dst])
+            for name in {op.src, getattr(op, "res", None)}:
+                if name is not None and last_use.get(name) == i:
+                    del t[name]
+
     def calibrate(self, batches):
         """Running max-abs over fp32 forwards of ``batches`` (device fp32 NHWC tensors)."""
-        slots = {}
-
-        def observe(key, tensor):
-            if key not in slots:
-                slots[key] = torch.zeros(1, dtype=torch.float32, device=self.dev)
-            B.calibrate_maxabs(tensor.contiguous(), slots[key])
-
+        keys = [self.net.input]
+        for op in self.net.ops:
+            if op.kind == "conv" and op.res is not None:
+                keys.append(op.name + ":branch")
+            if op.dst not in keys:
+                keys.append(op.dst)
+        slots = torch.zeros(len(keys), dtype=torch.float32, device=self.dev)
+        slot = dict(zip(keys, slots.split(1)))
         for x in batches:
-            observe(self.net.input, x)
-            self.forward_f32(x, observe)
-        keys = list(slots)
-        vals = torch.cat([slots[k] for k in keys]).cpu().numpy()
+            B.calibrate_maxabs(x.contiguous(), slot[self.net.input])
+            self._observed_forward(x.contiguous(), slot)
+        vals = slots.cpu().numpy()
         q = {k: B.qfactor(float(v), 8 if k in self.unsigned else P_ACT)
              for k, v in zip(keys, vals)}
         for op in self.net.ops:

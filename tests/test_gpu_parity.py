@@ -1362,3 +1362,46 @@ def test_gpu_calibration_matches_oracle_closely(B):
     assert set(q_g) == set(q_o)
     for k in q_o:
         assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
+
+
+# the fp32 forward of calibration: every tile build (128 x 128, 64 x 64 and 32 x 32 shared by four
+# wavefront groups), every chunk mode (C % 32, C % 16, C % 4, other), tails in pixels, channels
+# and reduction, stride, dilation, a channel slice
+@pytest.mark.parametrize("geom,res,slice_", [
+    ((1, 5, 7, 3, 20, 3, 3, 1, 1), False, (0, 0)), ((2, 17, 15, 7, 33, 5, 5, 2, 1), True, (0, 0)),
+    ((1, 7, 7, 12, 64, 1, 1, 1, 1), True, (0, 0)), ((3, 9, 11, 20, 70, 3, 3, 1, 2), False, (90, 12)),
+    ((1, 1, 1, 2048, 50, 1, 1, 1, 1), False, (0, 0)), ((2, 28, 28, 48, 192, 3, 3, 1, 1), True, (0, 0)),
+    ((4, 57, 55, 32, 65, 3, 3, 2, 1), True, (0, 0)), ((8, 64, 66, 16, 130, 1, 7, 1, 1), False, (133, 1))])
+def test_conv_f32_tiles(B, geom, res, slice_):
+    import torch
+    N, H, W, Cc, K, R, S, st, dil = geom
+    rng = np.random.default_rng(11)
+    ph, pw = dil * (R - 1) // 2, dil * (S - 1) // 2
+    desc = B.ConvDesc(N, H, W, Cc, K, R, S, st, st, ph, pw, dil, dil, relu=1, out_c_stride=slice_[0],
+                      out_c_off=slice_[1])
+    x = rng.standard_normal((N, H, W, Cc)).astype(np.float32)
+    w = rng.standard_normal((K, R, S, Cc)).astype(np.float32)
+    b = rng.standard_normal(K).astype(np.float32)
+    r = rng.standard_normal((N, desc.Ho, desc.Wo, K)).astype(np.float32) if res else None
+
+    def fp64(x, w, b):
+        y = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2),
+                                       torch.from_numpy(w).double().permute(0, 3, 1, 2),
+                                       torch.from_numpy(b).double() if b is not None else None, st,
+                                       (ph, pw), dil)
+        return y.permute(0, 2, 3, 1).numpy()
+    pre = fp64(x, w, b)
+    want = np.maximum(pre + r if res else pre, 0.0)
+    # any order of n fp32 products and sums: |error| <= (n + 2) 2^-24 sum |x||w| (+ |b| + |r|)
+    bound = (R * S * Cc + 4) * 2.0 ** -24 * (fp64(abs(x), abs(w), abs(b)) + (abs(r) if res else 0))
+    m_sum, m_out = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    out = torch.full((N, desc.Ho, desc.Wo, slice_[0] or K), -7.0, device="cuda")
+    B.conv_f32_observed(desc, dev(x), dev(w), dev(b), dev(r) if res else None, out, m_sum, m_out)
+    got, lo = host(out), slice_[1]
+    assert np.all(abs(got[..., lo:lo + K] - want) <= bound)
+    assert np.all(got[..., :lo] == -7) and np.all(got[..., lo + K:] == -7)
+    assert float(m_out) == got[..., lo:lo + K].max()          # the maximum of what was written
+    assert abs(float(m_sum) - abs(pre).max()) <= bound.max()
+    if slice_ == (0, 0):
+        ref = B.conv_f32_ref(desc, dev(x), dev(w), dev(b), dev(r) if res else None)
+        assert np.array_equal(host(ref), got)                 # the same sums without the maxima
