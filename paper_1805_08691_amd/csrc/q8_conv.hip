@@ -23,6 +23,12 @@ int num_ring_variants();
 int first_pw_variant();
 int first_p3_variant();
 int first_stem_variant();
+int first_direct_variant();
+int ext_variant(int variant);                       // the extended build that stands in for a variant
+void ring_variant_tile(int variant, int* bp, int* bc);
+void halo_variant_tile(int variant, int* bp, int* bc);
+int pick_direct(long M, int K, int red_len, float* us);
+bool direct_applicable(const ConvParams& p);
 int launch_stem_image(ConvParams& p, const StemImage& im, int pool, bool dry_run, hipStream_t stream);
 int first_split_variant();
 int num_split_variants();
@@ -140,8 +146,9 @@ int pick_halo3(const q8_conv_desc* d) {
   return smallest;
 }
 
-// `forced`: -1, or a variant of the main kernel to use where that kernel is applicable.
-int pick_variant(const q8_conv_desc* d, int forced = -1) {
+// Among the tiled kernels.  `forced`: -1, or a variant of the main kernel to use where that kernel
+// is applicable.
+int pick_tiled(const q8_conv_desc* d, int forced = -1) {
   const int mode = conv_mode(d);
   const int tile = d->K > 64 ? 0 : d->K > 32 ? 1 : 2;      // 128x128, 256x64, 256x32
   if (!stream_capable(d)) return kRegBase + 3 * mode + tile;
@@ -207,6 +214,39 @@ int pick_variant(const q8_conv_desc* d, int forced = -1) {
   // Inception-shaped stack), 128 x 64 tiles with a ring of 4
   if (tiles128 <= 160) return 9;
   return tiles128 <= 512 ? 11 : 1;
+}
+
+// Layers with few tiles: the latency family (q8_conv_direct_kernel.h) where its estimate is below
+// that of the tiled build.  The tiled estimates are fits to the same launches: a chain of reduction
+// steps fed at 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail; the 3x3 family
+// by its 64-channel chunks.  The persistent families are only chosen for sizes far above this.
+// ext: unsigned codes or per-channel scales (the extended builds).
+int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1) {
+  const int tiled = pick_tiled(d, forced);
+  if (forced >= 0 || tiled >= kRegBase || conv_mode(d) != 0) return tiled;
+  const int first_halo = q8::num_ring_variants(), first_pw = q8::first_pw_variant();
+  const int ho = out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h);
+  const int wo = out_extent(d->W, d->pad_w, d->dil_w, d->S, d->stride_w);
+  const long M = (long)d->N * ho * wo;
+  const int red_len = d->R * d->S * d->C;
+  int bp = 0, bc = 0;
+  float tiled_us = 0.0f;
+  if (tiled >= first_pw && !ext) return tiled;
+  if (tiled >= first_halo && !ext) {
+    q8::halo_variant_tile(tiled - first_halo, &bp, &bc);
+    const bool two_groups = tiled - first_halo == 12 || tiled - first_halo == 9;
+    const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
+    tiled_us = 4.34f + (two_groups ? 0.668f : 1.58f) * (float)(d->C / 64) * fmaxf(1.0f, wg / 256.0f);
+  } else {
+    q8::ring_variant_tile(ext ? q8::ext_variant(tiled) : tiled, &bp, &bc);
+    const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
+    const float bytes = (float)((long)(bp + bc) * red_len) * 1e-5f * fmaxf(1.0f, wg / 256.0f);
+    tiled_us = d->C % 64 == 0 ? 3.64f + 1.47f * bytes + 0.312f * wg * 0.01f
+                              : 4.22f + 2.05f * bytes + 0.164f * wg * 0.01f;
+  }
+  float us = 0.0f;
+  const int direct = q8::pick_direct(M, d->K, red_len, &us);
+  return us < 0.95f * tiled_us ? q8::first_direct_variant() + direct : tiled;
 }
 
 }  // namespace
@@ -498,7 +538,11 @@ int conv_launch(const q8_conv_desc* d, const U8Flags& u, const int8_t* z_x, cons
     p.vec16_2 = aligned2(16) ? 1 : 0;
     return q8::launch_pair_variant(p, s);
   }
-  int variant = pick_variant(d, u.variant);
+  const bool ext = u.in_u8 || u.out_u8 || u.res_u8 || u.m_vec;
+  int variant = pick_variant(d, ext, u.variant);
+  if (u.variant < 0 && variant >= q8::first_direct_variant() && variant < kRegBase &&
+      !q8::direct_applicable(p))
+    variant = pick_tiled(d);
   p.n_split = 1;
   p.ws_counters = nullptr;
   p.ws_slabs = nullptr;

@@ -61,6 +61,10 @@ int launch_halo_variant(int variant, ConvParams& p, hipStream_t stream) {
 const char* halo_variant_name(int variant) {
   return variant >= 0 && variant < kNumHaloVariants ? kHaloVariants[variant].name : "unsupported";
 }
+void halo_variant_tile(int variant, int* bp, int* bc) {
+  *bp = kHaloVariants[variant].bp;
+  *bc = kHaloVariants[variant].bc;
+}
 int halo_variant_max_w(int variant) {
   return variant >= 0 && variant < kNumHaloVariants ? kHaloVariants[variant].max_w : 0;
 }

@@ -9,10 +9,11 @@ namespace {
 struct RingVariant {
   const char* name;
   int (*launch)(ConvParams&, hipStream_t);
+  int bp, bc;
 };
 #define Q8_RING_ROW(I, WP, WC, TP, TC, BK, ST) \
   { "conv_i8_ring_kernel<" #WP "," #WC "," #TP "," #TC "," #BK "," #ST ">", \
-    &launch_ring<WP, WC, TP, TC, BK, ST, 0> },
+    &launch_ring<WP, WC, TP, TC, BK, ST, 0>, WP * TP * 32, WC * TC * 32 },
 const RingVariant kRingVariants[] = {
     Q8_RING_EXT_LIST(Q8_RING_ROW)          //  0 .. 11: also in the extended build
     Q8_RING_ROW(12, 4, 2, 1, 2, 64, 3)     // 12: 128 x 128, eight wavefronts of 32 x 64
@@ -59,17 +60,33 @@ int num_stem_variants();
 int launch_stem_variant(int variant, ConvParams& p, hipStream_t stream);
 const char* stem_variant_name(int variant);
 
+// ... and the latency family (q8_conv_direct.hip)
+int num_direct_variants();
+bool direct_applicable(const ConvParams& p);
+int launch_direct_variant(int variant, ConvParams& p, hipStream_t stream);
+const char* direct_variant_name(int variant);
+
 int num_ring_variants() { return kNumRingVariants; }
+void ring_variant_tile(int variant, int* bp, int* bc) {
+  *bp = kRingVariants[variant].bp;
+  *bc = kRingVariants[variant].bc;
+}
+int ext_variant(int variant) { return variant < kNumRingExtVariants ? variant : 1; }
 int first_pw_variant() { return kNumRingVariants + num_halo_variants(); }
 int first_split_variant() { return first_pw_variant() + num_pw_variants(); }
 int first_p3_variant() { return first_split_variant() + num_split_variants(); }
 int first_stem_variant() { return first_p3_variant() + num_p3_variants(); }
-int num_stream_variants() { return first_stem_variant() + num_stem_variants(); }
+int first_direct_variant() { return first_stem_variant() + num_stem_variants(); }
+int num_stream_variants() { return first_direct_variant() + num_direct_variants(); }
 int launch_stream_variant(int variant, ConvParams& p, hipStream_t stream) {
   if (variant < 0 || variant >= num_stream_variants()) return Q8_EINVAL;
+  if (variant >= first_direct_variant()) {
+    if (!direct_applicable(p)) variant = 1;        // odd channel counts: the general kernel
+    else return launch_direct_variant(variant - first_direct_variant(), p, stream);
+  }
   if (p.in_u8 | p.out_u8 | p.res_u8 | (p.m_vec != nullptr)) {
     // variants without an extended build fall back to the 128 x 128 ring of 3
-    return launch_ring_ext_variant(variant < kNumRingExtVariants ? variant : 1, p, stream);
+    return launch_ring_ext_variant(ext_variant(variant), p, stream);
   }
   if (variant >= first_stem_variant())
     return launch_stem_variant(variant - first_stem_variant(), p, stream);
@@ -81,6 +98,7 @@ int launch_stream_variant(int variant, ConvParams& p, hipStream_t stream) {
   return kRingVariants[variant].launch(p, stream);
 }
 const char* stream_variant_name(int variant) {
+  if (variant >= first_direct_variant()) return direct_variant_name(variant - first_direct_variant());
   if (variant >= first_stem_variant()) return stem_variant_name(variant - first_stem_variant());
   if (variant >= first_p3_variant()) return p3_variant_name(variant - first_p3_variant());
   if (variant >= first_split_variant()) return split_variant_name(variant - first_split_variant());

@@ -1405,3 +1405,23 @@ def test_conv_f32_tiles(B, geom, res, slice_):
     if slice_ == (0, 0):
         ref = B.conv_f32_ref(desc, dev(x), dev(w), dev(b), dev(r) if res else None)
         assert np.array_equal(host(ref), got)                 # the same sums without the maxima
+
+
+# the latency family: one pixel, one reduction step, more steps than a wavefront keeps in flight,
+# channel counts that end inside a group of four, taps per 16-byte chunk, a dilated filter
+DIRECT_CASES = [
+    dict(N=1, H=1, W=1, C=64, K=16, R=1, S=1), dict(N=1, H=1, W=1, C=2048, K=50, R=1, S=1),
+    dict(N=3, H=5, W=3, C=16, K=126, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=1, H=17, W=17, C=160, K=48, R=1, S=7, pad_w=3), dict(N=1, H=7, W=9, C=512, K=20, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=2, H=19, W=19, C=64, K=36, R=3, S=3, pad_h=6, pad_w=6, dil_h=6, dil_w=6),
+    dict(N=2, H=9, W=9, C=128, K=33, R=1, S=1, stride_h=2, stride_w=2)]
+
+
+@pytest.mark.parametrize("idx", range(len(DIRECT_CASES)))
+def test_conv_latency_family(B, idx):
+    names = [B.lib.q8_conv_variant_name(v).decode() for v in range(B.conv_num_variants())]
+    variants = [v for v, n in enumerate(names) if "direct" in n]
+    assert variants and "direct" in B.conv_variant(B.ConvDesc(**DIRECT_CASES[idx]))
+    for v in variants:
+        _run_conv_case(B, DIRECT_CASES[idx], relu=bool(v % 2), with_res=bool(idx % 2), with_bias=True,
+                       seed=31 * v + idx, variant=v)
