@@ -325,6 +325,54 @@ size_t q8_conv_chain_static_workspace_limit(void);
 int q8_conv_chain_int8_static(const void *plan_host, const void *plan_dev, void *stream);
 int q8_conv_chain_static_status(int32_t *status_host);
 
+/* ---- a list of calls as one ------------------------------------------------------------
+ * A program that runs the same layers again and again (a network's step) describes its calls
+ * once as an array of q8_op in HOST memory and enqueues them with one q8_run_ops: the results
+ * are those of the calls one after the other, without the per-call cost of a language binding.
+ * Each op names the entry point it stands for and holds its arguments:
+ *   Q8_OP_CONV        q8_conv_int8 / q8_conv_u8 / q8_conv_int8_per_channel /
+ *                     q8_conv_int8_real_output / q8_conv_int8_dequantized, by `flags`:
+ *                     d, x, w, bias, q_x, q_w, q_out, residual, q_res, y; aux = start table
+ *                     (Q8_OPF_IN_U8) or per-channel scales (Q8_OPF_PER_CHANNEL); y_f32 = the
+ *                     fp32 output (Q8_OPF_REAL) or Eq. D beside the codes (Q8_OPF_DEQUANT)
+ *   Q8_OP_HEAD        q8_conv_image_f32_int8: d, x, H, W, C, top, left, q_x, p, w, bias, q_w,
+ *                     q_out, y, and Q8_OPF_POOL
+ *   Q8_OP_POOL        q8_pool_i8: x, d.N, H, W, C, mode, R, S, stride, pad, Ho, Wo, q_x (q_in),
+ *                     q_out, y, d.out_c_stride, d.out_c_off
+ *   Q8_OP_MAXPOOL     q8_maxpool_i8: x, d.N, H, W, C, R, S, stride, pad, Ho, Wo, y
+ *   Q8_OP_QUANTIZE    q8_quantize: x, n, q_x, p, y
+ *   Q8_OP_QUANTIZE_PAD    q8_quantize_pad_channels: x, n (pixels), C, Ho (C_pad), q_x, p, y
+ *   Q8_OP_QUANTIZE_IMAGE  q8_quantize_image: x, d.N, H, W, C, q_x, p, y, Ho (Hs), Wo (Ws), top, left
+ *   Q8_OP_DEQUANTIZE  q8_dequantize (or _u8 with Q8_OPF_IN_U8): x, n, q_x, y_f32
+ * `stream` is an index into `streams`.  Ops are enqueued in order.  Neighbours with the same
+ * nonzero `group` (and stream) must not depend on each other; the library may then run several
+ * of them as one launch.  Neighbouring Q8_OP_DEQUANTIZE ops never depend on each other.
+ * Returns the first error; ops behind it are not enqueued.                               */
+enum {
+  Q8_OP_CONV = 0, Q8_OP_HEAD, Q8_OP_POOL, Q8_OP_MAXPOOL, Q8_OP_QUANTIZE, Q8_OP_QUANTIZE_PAD,
+  Q8_OP_QUANTIZE_IMAGE, Q8_OP_DEQUANTIZE
+};
+enum {
+  Q8_OPF_IN_U8 = 1, Q8_OPF_OUT_U8 = 2, Q8_OPF_RES_U8 = 4, Q8_OPF_PER_CHANNEL = 8, Q8_OPF_REAL = 16,
+  Q8_OPF_DEQUANT = 32, Q8_OPF_POOL = 64
+};
+typedef struct q8_op {
+  int32_t kind, flags, group, stream;
+  q8_conv_desc d;
+  int32_t H, W, C, mode, R, S, stride, pad, Ho, Wo, top, left, p;
+  const void *x, *w, *bias, *residual, *aux;
+  void *y;
+  float *y_f32;
+  float q_x, q_w, q_out, q_res;
+  size_t n;
+} q8_op;
+int q8_run_ops(const q8_op *ops, int n_ops, void *const *streams, int n_streams);
+
+/* Estimated duration in us of one launch of this layer on an otherwise idle chip (host
+ * arithmetic; what the library chooses kernels by): for programs that order independent
+ * layers.  0 if the layer is unsupported.                                               */
+float q8_conv_estimate_us(const q8_conv_desc *d);
+
 /* Name of the kernel variant (tile shape) q8_conv_int8 picks for this geometry, as it
  * appears in a profiler's kernel trace; "unsupported" if the call would be rejected.
  * For measurement code that groups launches by kernel.                              */

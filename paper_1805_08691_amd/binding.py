@@ -33,7 +33,7 @@ EXPORTS = [
     "q8_conv_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
-    "q8_probe_mfma_i8",
+    "q8_probe_mfma_i8", "q8_run_ops", "q8_conv_estimate_us",
     "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
@@ -75,6 +75,20 @@ class ChainLayer(C.Structure):
                 ("z_y", C.c_void_p), ("src_layer", C.c_int32), ("res_layer", C.c_int32),
                 ("variant", C.c_int32)]
 
+
+class Op(C.Structure):
+    """Mirror of ``q8_op``: one call of a q8_run_ops list."""
+    _fields_ = ([(n, C.c_int32) for n in ("kind", "flags", "group", "stream")] + [("d", ConvDesc)] +
+                [(n, C.c_int32) for n in ("H", "W", "C", "mode", "R", "S", "stride", "pad", "Ho", "Wo",
+                                          "top", "left", "p")] +
+                [(n, C.c_void_p) for n in ("x", "w", "bias", "residual", "aux", "y", "y_f32")] +
+                [(n, C.c_float) for n in ("q_x", "q_w", "q_out", "q_res")] + [("n", C.c_size_t)])
+
+
+(OP_CONV, OP_HEAD, OP_POOL, OP_MAXPOOL, OP_QUANTIZE, OP_QUANTIZE_PAD, OP_QUANTIZE_IMAGE,
+ OP_DEQUANTIZE) = range(8)
+(OPF_IN_U8, OPF_OUT_U8, OPF_RES_U8, OPF_PER_CHANNEL, OPF_REAL, OPF_DEQUANT,
+ OPF_POOL) = (1 << i for i in range(7))
 
 _vp, _sz, _f, _i = C.c_void_p, C.c_size_t, C.c_float, C.c_int
 _dp = C.POINTER(ConvDesc)
@@ -133,6 +147,9 @@ lib.q8_conv_int8_variant.argtypes = [_dp, _vp, _vp, _vp, _f, _f, _f, _vp, _f, _v
 lib.q8_conv_int8_dequantized.argtypes = [_dp, _vp, _vp, _vp, _f, _f, _f, _vp, _f, _vp, _vp, _vp]
 lib.q8_conv_image_f32_supported.argtypes = [_dp, _i, _i, _i, _i, _i, _i]
 lib.q8_conv_image_f32_int8.argtypes = [_dp, _vp, _i, _i, _i, _i, _i, _f, _i, _vp, _vp, _f, _f, _i, _vp, _vp]
+lib.q8_run_ops.argtypes = [_vp, _i, _vp, _i]
+lib.q8_conv_estimate_us.restype = _f
+lib.q8_conv_estimate_us.argtypes = [_dp]
 lib.q8_sum_factor.restype = _f
 lib.q8_sum_factor.argtypes = [_f, _f]
 lib.q8_probe_mfma_i8.argtypes = [_i, _i, _vp, _vp]
@@ -476,6 +493,11 @@ class ConvChain:
         v = C.c_int32(-1)
         _check(lib.q8_conv_chain_static_status(C.byref(v)))
         return v.value
+
+
+def conv_estimate_us(desc):
+    """Estimated duration of one launch of the layer (what the library chooses kernels by)."""
+    return lib.q8_conv_estimate_us(C.byref(desc))
 
 
 def conv_variant(desc):

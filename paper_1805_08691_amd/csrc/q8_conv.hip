@@ -29,6 +29,7 @@ void ring_variant_tile(int variant, int* bp, int* bc);
 void halo_variant_tile(int variant, int* bp, int* bc);
 int pick_direct(long M, int K, int red_len, float* us);
 bool direct_applicable(const ConvParams& p);
+int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us);
 int launch_stem_image(ConvParams& p, const StemImage& im, int pool, bool dry_run, hipStream_t stream);
 int first_split_variant();
 int num_split_variants();
@@ -221,8 +222,10 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1) {
 // steps fed at 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail; the 3x3 family
 // by its 64-channel chunks.  The persistent families are only chosen for sizes far above this.
 // ext: unsigned codes or per-channel scales (the extended builds).
-int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1) {
+int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float* est_us = nullptr) {
   const int tiled = pick_tiled(d, forced);
+  if (est_us)
+    *est_us = 4.0f + (float)d->N * (float)d->H * (float)d->W * (float)d->K * (float)(d->R * d->S * d->C) * 2e-9f;
   if (forced >= 0 || tiled >= kRegBase || conv_mode(d) != 0) return tiled;
   const int first_halo = q8::num_ring_variants(), first_pw = q8::first_pw_variant();
   const int ho = out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h);
@@ -231,6 +234,7 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1) {
   const int red_len = d->R * d->S * d->C;
   int bp = 0, bc = 0;
   float tiled_us = 0.0f;
+  if (est_us) *est_us = 3.0f + (float)M * (float)d->K * (float)red_len * 1.1e-9f;   // ~ 1.8 POP/s
   if (tiled >= first_pw && !ext) return tiled;
   if (tiled >= first_halo && !ext) {
     q8::halo_variant_tile(tiled - first_halo, &bp, &bc);
@@ -246,7 +250,9 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1) {
   }
   float us = 0.0f;
   const int direct = q8::pick_direct(M, d->K, red_len, &us);
-  return us < 0.95f * tiled_us ? q8::first_direct_variant() + direct : tiled;
+  const bool take_direct = us < 0.95f * tiled_us;
+  if (est_us) *est_us = take_direct ? us : tiled_us;
+  return take_direct ? q8::first_direct_variant() + direct : tiled;
 }
 
 }  // namespace
@@ -538,11 +544,8 @@ int conv_launch(const q8_conv_desc* d, const U8Flags& u, const int8_t* z_x, cons
     p.vec16_2 = aligned2(16) ? 1 : 0;
     return q8::launch_pair_variant(p, s);
   }
-  const bool ext = u.in_u8 || u.out_u8 || u.res_u8 || u.m_vec;
-  int variant = pick_variant(d, ext, u.variant);
-  if (u.variant < 0 && variant >= q8::first_direct_variant() && variant < kRegBase &&
-      !q8::direct_applicable(p))
-    variant = pick_tiled(d);
+  float us = 0.0f;
+  int variant = u.variant >= 0 ? pick_variant(d, false, u.variant) : q8::conv_choose(d, p, &us);
   p.n_split = 1;
   p.ws_counters = nullptr;
   p.ws_slabs = nullptr;
@@ -567,6 +570,50 @@ int conv_launch(const q8_conv_desc* d, const U8Flags& u, const int8_t* z_x, cons
 }  // namespace
 
 namespace q8 {
+// The arguments of a Q8_OP_CONV op, checked and in the kernels' form.
+int conv_fill_op(const q8_op* o, ConvParams& p, bool* empty) {
+  const int f = o->flags;
+  U8Flags u{f & Q8_OPF_IN_U8 ? 1 : 0, f & Q8_OPF_OUT_U8 ? 1 : 0, f & Q8_OPF_RES_U8 ? 1 : 0, nullptr};
+  float q_x = o->q_x, q_w = o->q_w, q_out = o->q_out;
+  if (u.in_u8) {
+    Q8_REQUIRE(o->bias != nullptr, Q8_EINVAL);
+    u.tap_sums = static_cast<const int32_t*>(o->aux);
+  }
+  if (f & Q8_OPF_PER_CHANNEL) {
+    Q8_REQUIRE(o->aux != nullptr, Q8_EINVAL);
+    u.m_vec = static_cast<const float*>(o->aux);
+    q_x = q_w = 1.0f;
+  }
+  int8_t* y = static_cast<int8_t*>(o->y);
+  if (f & Q8_OPF_REAL) {
+    u.y_f32 = o->y_f32;
+    q_out = 1.0f;
+    y = nullptr;
+  }
+  if (f & Q8_OPF_DEQUANT) {
+    Q8_REQUIRE(o->y_f32 != nullptr, Q8_EINVAL);
+    u.y_deq = o->y_f32;
+  }
+  return conv_fill(&o->d, u, static_cast<const int8_t*>(o->x), o->w,
+                   static_cast<const int32_t*>(o->bias), q_x, q_w, q_out,
+                   static_cast<const int8_t*>(o->residual), o->q_res, y, nullptr, p, empty);
+}
+
+// What one layer would be launched as on its own, and the estimate; launches it.
+int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
+  *us = 0.0f;
+  const bool ext = p.in_u8 || p.out_u8 || p.res_u8 || p.m_vec;
+  const int v = pick_variant(d, ext, -1, us);
+  return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d) : v;
+}
+int conv_launch_chosen(int variant, ConvParams& p, hipStream_t s) {
+  p.n_split = 1;
+  p.ws_counters = nullptr;
+  p.ws_slabs = nullptr;
+  return variant >= kRegBase ? launch_reg_variant(variant - kRegBase, p, s)
+                             : launch_stream_variant(variant, p, s);
+}
+
 int conv_fill_plain(const q8_conv_desc* d, const int8_t* z_x, const void* z_w_packed,
                     const int32_t* bias_i32, float q_x, float q_w, float q_out,
                     const int8_t* residual, float q_res, int8_t* z_y, ConvParams& p, bool* empty) {
@@ -822,6 +869,13 @@ int q8_conv_int8_variant(const q8_conv_desc* d, const int8_t* z_x, const void* z
   u.workspace_bytes = workspace_bytes;
   return conv_launch(d, u, z_x, z_w_packed, bias_i32, q_x, q_w, q_out, residual, q_res, z_y,
                      acc_dump, stream);
+}
+
+float q8_conv_estimate_us(const q8_conv_desc* d) {
+  if (!desc_sane(d) || conv_mode(d) < 0) return 0.0f;
+  float us = 0.0f;
+  pick_variant(d, false, -1, &us);
+  return us;
 }
 
 const char* q8_conv_variant(const q8_conv_desc* d) {

@@ -27,7 +27,26 @@ DirectParams direct_params(const ConvParams& p) {
   d.acc_dump = p.acc_dump;
   d.start_bytes = (p.tap_sums ? (p.R + 1) * (p.R + 1) * (p.S + 1) * (p.S + 1) : p.bias ? 1 : 0) * p.K * 4;
   d.res_bytes = p.res ? p.res_bytes : 0;
+  d.mode = p.C % 64 != 0 ? 0 : p.R * p.S == 1 && (p.pad_h | p.pad_w) == 0 ? 2 : 1;
   return d;
+}
+
+template <int TP, int TC, int KW, int NB>
+int launch_direct_group(const ConvParams* const* p, int n, hipStream_t stream) {
+  DirectGroup g;
+  g.n = n;
+  long blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    DirectParams& d = g.layer[i] = direct_params(*p[i]);
+    d.n_ptiles = (d.M + TP * 16 - 1) / (TP * 16);
+    d.n_ctiles = (d.K + TC * 16 - 1) / (TC * 16);
+    g.first[i] = (int)blocks;
+    blocks += (long)d.n_ptiles * d.n_ctiles;
+    if (blocks > 0x7fffffffL) return Q8_EUNSUPPORTED;
+  }
+  hipLaunchKernelGGL((conv_i8_direct_group_kernel<TP, TC, KW, NB>), dim3((unsigned)blocks), dim3(KW * 64),
+                     0, stream, g);
+  return q8_launch_status();
 }
 
 template <int TP, int TC, int KW, int NB>
@@ -37,9 +56,8 @@ int launch_direct(const ConvParams& p, hipStream_t stream) {
   d.n_ctiles = (p.K + TC * 16 - 1) / (TC * 16);
   const long nblk = (long)d.n_ptiles * d.n_ctiles;
   if (nblk > 0x7fffffffL) return Q8_EUNSUPPORTED;
-  const bool pointwise = p.R * p.S == 1 && (p.pad_h | p.pad_w) == 0;
-  auto kernel = p.C % 64 != 0 ? conv_i8_direct_kernel<TP, TC, KW, NB, 0>
-                : pointwise   ? conv_i8_direct_kernel<TP, TC, KW, NB, 2>
+  auto kernel = d.mode == 0   ? conv_i8_direct_kernel<TP, TC, KW, NB, 0>
+                : d.mode == 2 ? conv_i8_direct_kernel<TP, TC, KW, NB, 2>
                               : conv_i8_direct_kernel<TP, TC, KW, NB, 1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(KW * 64), 0, stream, d);
   return q8_launch_status();
@@ -53,12 +71,13 @@ int launch_direct(const ConvParams& p, hipStream_t stream) {
 struct DirectVariant {
   const char* name;
   int (*launch)(const ConvParams&, hipStream_t);
+  int (*launch_group)(const ConvParams* const*, int, hipStream_t);
   int bp, bc;
   float base, per_wg, per_byte;
 };
 #define Q8_DIRECT_ROW(TP, TC, KW, NB, A, B, C) \
-  { "conv_i8_direct_kernel<" #TP "," #TC "," #KW "," #NB ">", &launch_direct<TP, TC, KW, NB>, TP * 16, \
-    TC * 16, A, B, C },
+  { "conv_i8_direct_kernel<" #TP "," #TC "," #KW "," #NB ">", &launch_direct<TP, TC, KW, NB>, \
+    &launch_direct_group<TP, TC, KW, NB>, TP * 16, TC * 16, A, B, C },
 const DirectVariant kDirectVariants[] = {
     Q8_DIRECT_ROW(1, 1, 8, 8, 2.70f, 0.178f, 2.32f)   // 0: 16 pixels x 16 channels, eight wavefronts
     Q8_DIRECT_ROW(1, 1, 4, 8, 2.69f, 0.024f, 2.36f)   // 1
@@ -87,6 +106,31 @@ int pick_direct(long M, int K, int red_len, float* us) {
     if (best < 0 || t < *us) { best = v; *us = t; }
   }
   return best;
+}
+// The same for several independent layers in one launch: the busiest CU has the largest tile, or
+// its share of all of them.
+int pick_direct_group(const ConvParams* const* p, int n, float* us) {
+  int best = -1;
+  for (int v = 0; v < kNumDirectVariants; ++v) {
+    const DirectVariant& d = kDirectVariants[v];
+    float wg = 0.0f, bytes = 0.0f, largest = 0.0f;
+    for (int i = 0; i < n; ++i) {
+      const float w = (float)(((p[i]->M + d.bp - 1) / d.bp) * (long)((p[i]->K + d.bc - 1) / d.bc));
+      const float b = (float)((long)(d.bp + d.bc) * p[i]->red_len);
+      wg += w;
+      bytes += w * b;
+      largest = b > largest ? b : largest;
+    }
+    const float share = bytes / 256.0f;
+    const float t = d.base + 0.3f + d.per_wg * (wg > 256.0f ? wg - 256.0f : 0.0f) * 0.01f +
+                    d.per_byte * 1e-5f * (wg > 256.0f ? share + 0.5f * largest : largest);
+    if (best < 0 || t < *us) { best = v; *us = t; }
+  }
+  return best;
+}
+int launch_direct_group_variant(int variant, const ConvParams* const* p, int n, hipStream_t stream) {
+  if (variant < 0 || variant >= kNumDirectVariants || n < 1 || n > kMaxGroup) return Q8_EINVAL;
+  return kDirectVariants[variant].launch_group(p, n, stream);
 }
 const char* direct_variant_name(int variant) {
   return variant >= 0 && variant < kNumDirectVariants ? kDirectVariants[variant].name : "unsupported";

@@ -30,7 +30,7 @@ struct DirectParams {
   int Wo, HoWo, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w;
   FastDiv by_img, by_row, by_c, by_s;
   int n_ptiles, n_ctiles, ptile_fastest;
-  int R;
+  int R, mode;                    // mode: the addressing build the layer takes in a group
   int start_bytes, res_bytes;     // descriptor sizes: start values (bias or table), residual
   const int32_t* bias;
   const int8_t* res;
@@ -44,6 +44,14 @@ struct DirectParams {
   float* y_deq;
   float q_deq;
   int32_t* acc_dump;
+};
+
+// Independent layers in one launch: workgroup b belongs to the last layer l with first[l] <= b.
+constexpr int kMaxGroup = 8;
+struct DirectGroup {
+  int n;
+  int first[kMaxGroup];
+  DirectParams layer[kMaxGroup];
 };
 
 namespace {
@@ -337,6 +345,20 @@ __global__ __launch_bounds__(KW * 64) void conv_i8_direct_kernel(const DirectPar
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(16))) int lds[TP * TC * KW * 256];
   conv_tile_direct<TP, TC, KW, NB, MODE>(p, blockIdx.x, lds);
+#endif
+}
+
+template <int TP, int TC, int KW, int NB>
+__global__ __launch_bounds__(KW * 64) void conv_i8_direct_group_kernel(const DirectGroup g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(16))) int lds[TP * TC * KW * 256];
+  int l = 0;
+  for (int i = 1; i < g.n; ++i) l = (int)blockIdx.x >= g.first[i] ? i : l;
+  const DirectParams& p = g.layer[l];
+  const int bid = blockIdx.x - g.first[l];
+  if (p.mode == 2) conv_tile_direct<TP, TC, KW, NB, 2>(p, bid, lds);
+  else if (p.mode == 1) conv_tile_direct<TP, TC, KW, NB, 1>(p, bid, lds);
+  else conv_tile_direct<TP, TC, KW, NB, 0>(p, bid, lds);
 #endif
 }
 

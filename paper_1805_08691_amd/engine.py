@@ -10,6 +10,8 @@ Online step:
   run_step(x, dequant) Q on the input image, one fused conv launch per layer (Eq. A'), D on the
                        outputs that leave the int8 domain; forward(x) is run_step without D.
 """
+import ctypes
+
 import numpy as np
 import torch
 
@@ -130,6 +132,7 @@ class Engine:
         self.act = {}         # tensor name -> int8 device buffer [N, H, W, C_stored]
         self.desc = {}        # conv name -> ConvDesc
         self.graph = None
+        self._plans = {}      # (real-valued batch given, tensors dequantised) -> planned step
         for op in net.ops:
             if op.kind == "conv":
                 self.desc[op.name] = self._desc(op, batch)
@@ -333,9 +336,11 @@ class Engine:
             if op.kind == "pool" and self.net.tensors[op.dst].C == self.net.tensors[op.src].C:
                 q[op.dst] = q[op.src]       # a stand-alone pool keeps its input's factor
         self.q = q
+        self._plans.clear()
         return q
 
     def set_factors(self, q):
+        self._plans.clear()
         self.q = {k: float(v) for k, v in q.items()}
 
     def quantize_weights_per_channel(self):
@@ -350,6 +355,7 @@ class Engine:
             self.m_vec[op.name] = B.requant_scales(self.q[op.src], q_w, self.q[op.dst])
 
     def quantize_weights(self):
+        self._plans.clear()
         if self.per_channel:
             return self.quantize_weights_per_channel()
         slots = {}
@@ -374,6 +380,7 @@ class Engine:
 
     # ------------------------------------------------------------------ online step
     def allocate(self):
+        self._plans.clear()
         for name, t in self.net.tensors.items():
             H, W = t.H, t.W
             if name == self.net.input and self.in_frame:
@@ -406,9 +413,10 @@ class Engine:
         else:
             B.quantize(x, self.q[self.net.input], P_ACT, out=z)
 
-    def _dequant_writer(self, name):
-        """The convolution that can write Eq. D of tensor ``name`` beside its codes, or None."""
-        if not self.fuse_dequant or self.unsigned or self.per_channel or name in self.real:
+    def _dequant_writer(self, name, any_engine=False):
+        """The convolution that writes Eq. D of tensor ``name`` beside its codes (in an engine with
+        ``fuse_dequant``; ``any_engine``: the one that could), or None."""
+        if not (self.fuse_dequant or any_engine) or self.unsigned or self.per_channel or name in self.real:
             return None
         writers = [o for o in self.net.ops if o.dst == name]
         if len(writers) != 1 or writers[0].kind != "conv":
@@ -585,13 +593,238 @@ class Engine:
                 self.run_ops([ops[i]], 0, self.N)
                 i += 1
 
+    # ------------------------------------------------------------------ the planned step
+    # A step is described once as an array of library calls (binding.Op) and enqueued with one
+    # call per stream segment; only the pointers of the real-valued batch and of the fp32
+    # outputs are filled in per step.
+    def _op_conv(self, op, lo, n, deq):
+        packed, bias = self.wq[op.name]
+        U, o = self.unsigned, B.Op()
+        o.kind, o.d = B.OP_CONV, self.conv_desc(op, n)
+        src, dst = self.act[op.src], self.act[op.dst]
+        o.x = src.data_ptr() + lo * src.stride(0)
+        o.w, o.bias = packed.data_ptr(), bias.data_ptr()
+        o.y = dst.data_ptr() + lo * dst.stride(0)
+        o.q_x, o.q_out = self.q[op.src], self.q[op.dst]
+        o.q_w = 1.0 if self.per_channel else self.qw[op.name]
+        if op.res:
+            res = self.act[op.res]
+            o.residual, o.q_res = res.data_ptr() + lo * res.stride(0), self.q[op.res]
+        if op.dst in self.real:
+            out = self.act_f32[op.dst]
+            o.flags, o.y_f32 = B.OPF_REAL, out.data_ptr() + 4 * lo * out.stride(0)
+        elif self.per_channel:
+            o.flags, o.aux = B.OPF_PER_CHANNEL, self.m_vec[op.name].data_ptr()
+        elif op.src in U or op.dst in U or op.res in U:
+            o.flags = (B.OPF_IN_U8 * (op.src in U) | B.OPF_OUT_U8 * (op.dst in U) |
+                       B.OPF_RES_U8 * (op.res in U))
+            if op.src in U:
+                o.aux = self.taps[op.name].data_ptr()
+        elif deq:
+            o.flags = B.OPF_DEQUANT
+        return o
+
+    def _op_pool(self, op, lo, n):
+        s, d = self.net.tensors[op.src], self.net.tensors[op.dst]
+        src, dst, o = self.act[op.src], self.act[op.dst], B.Op()
+        exact = op.mode == "max" and self.q[op.src] == self.q[op.dst] and _pad_c(d.C) == _pad_c(s.C)
+        o.kind = B.OP_MAXPOOL if exact else B.OP_POOL
+        o.x, o.y = src.data_ptr() + lo * src.stride(0), dst.data_ptr() + lo * dst.stride(0)
+        o.d.N, o.H, o.W, o.C = n, s.H, s.W, _pad_c(s.C)
+        o.mode = 0 if op.mode == "max" else 1
+        o.R, o.S, o.stride, o.pad, o.Ho, o.Wo = op.R, op.S, op.stride, op.pad, d.H, d.W
+        o.q_x, o.q_out = self.q[op.src], self.q[op.dst]
+        o.d.out_c_stride, o.d.out_c_off = _pad_c(d.C), op.dst_c_off
+        return o
+
+    def _op_quantize(self, n):
+        t, z, o = self.net.tensors[self.net.input], self.act[self.net.input], B.Op()
+        o.q_x, o.p, o.y = self.q[self.net.input], P_ACT, z.data_ptr()
+        if self.in_frame:
+            o.kind, o.d.N, o.H, o.W, o.C = B.OP_QUANTIZE_IMAGE, n, t.H, t.W, t.C
+            o.top, o.left, o.Ho, o.Wo = self.in_frame
+        elif _pad_c(t.C) != t.C:
+            o.kind, o.n, o.C, o.Ho = B.OP_QUANTIZE_PAD, n * t.H * t.W, t.C, _pad_c(t.C)
+        else:
+            o.kind, o.n = B.OP_QUANTIZE, n * t.H * t.W * t.C
+        return o
+
+    def _op_head(self, lo, n):
+        conv, pool = self.head
+        packed, bias = self.wq[conv.name]
+        t, o = self.net.tensors[self.net.input], B.Op()
+        dst = self.act[pool.dst if pool else conv.dst]
+        o.kind, o.flags, o.d = B.OP_HEAD, B.OPF_POOL if pool else 0, self.conv_desc(conv, n)
+        o.H, o.W, o.C = t.H, t.W, t.C
+        o.top, o.left = self.in_frame[:2]
+        o.q_x, o.p, o.q_w, o.q_out = self.q[self.net.input], P_ACT, self.qw[conv.name], self.q[conv.dst]
+        o.w, o.bias, o.y = packed.data_ptr(), bias.data_ptr(), dst.data_ptr() + lo * dst.stride(0)
+        return o
+
+    def _levels(self, ops, n, dst_of):
+        """Level of every op: one more than its producers', and for an op that nothing waits for at
+        once the level between its earliest and latest where it adds least (it then shares a
+        launch, or the idle part of the chip, with the ops there)."""
+        writers, early, late, us, share = {}, [], {}, [], []
+        for i, op in enumerate(ops):
+            level = 0
+            for name in (op.src, getattr(op, "res", None)):
+                for j in writers.get(name, ()):
+                    level = max(level, early[j] + 1)
+            early.append(level)
+            writers.setdefault(dst_of(op), []).append(i)
+            d = self.net.tensors[op.dst]
+            us.append(B.conv_estimate_us(self.conv_desc(op, n)) if op.kind == "conv" else 3.0)
+            work = n * d.H * d.W * (op.K if op.kind == "conv" else d.C)
+            share.append(min(1.0, work / 65536.0))     # tiles of 16 x 16 against 256 CUs
+        depth = max(early) + 1
+        for i in reversed(range(len(ops))):
+            readers = [late[j] for j, o in enumerate(ops) if j > i
+                       and dst_of(ops[i]) in (o.src, getattr(o, "res", None))]
+            late[i] = min(readers) - 1 if readers else depth - 1
+        members = [[] for _ in range(depth)]
+        cost = lambda m: (max([us[i] for i in m] + [2.7 + sum((us[i] - 2.7) * share[i] for i in m)])
+                          if m else 0.0)
+        loose = []
+        for i in range(len(ops)):
+            # only ops that no other op reads: moving one never moves another
+            if late[i] > early[i] and late[i] == depth - 1 and not any(
+                    dst_of(ops[i]) in (o.src, getattr(o, "res", None)) for o in ops):
+                loose.append(i)
+            else:
+                members[early[i]].append(i)
+        for i in sorted(loose, key=lambda i: -us[i]):
+            best = min(range(early[i], depth), key=lambda l: cost(members[l] + [i]) - cost(members[l]))
+            members[best].append(i)
+        return members
+
+    def _plan(self, with_x, names):
+        """The planned step: (ops before the pipelines fork, ops of the pipelines, ops behind the
+        join, where the batch's and the outputs' pointers go)."""
+        net, part_ops = self.net, []
+        ops = list(net.ops)
+        if with_x and self.head:
+            ops = [o for o in ops if o is not self.head[1]]
+        fused = {name: self._dequant_writer(name) for name in names}
+        # Eq. D inside the launch that writes the tensor: asked for, or free (a launch of the
+        # latency family finishes four channels per lane whatever it writes)
+        for name in names:
+            w = self._dequant_writer(name, any_engine=True)
+            if fused[name] is None and w is not None and \
+                    "direct" in B.conv_variant(self.conv_desc(w, self.N)):
+                fused[name] = w
+        fused = {name: w for name, w in fused.items() if w is not None}
+        parts = self.parts
+        if len(parts) > 1 and not self._pipelines_pay(ops):
+            parts = [(0, self.N)]
+        x_slots, out_slots = [], []
+
+        def add(into, o, stream=0, group=0):
+            o.stream, o.group = stream, group
+            into.append(o)
+            return len(into) - 1
+
+        pre, body, post = [], [], []
+        t_in = net.tensors[net.input]
+        image = 4 * t_in.H * t_in.W * t_in.C
+        if with_x and not self.head:
+            x_slots.append((0, add(pre, self._op_quantize(self.N)), 0))
+
+        def emit(op, k, group):
+            lo, n = parts[k]
+            if with_x and self.head and op is self.head[0]:
+                x_slots.append((1, add(body, self._op_head(lo, n), k, group), image * lo))
+            elif op.kind == "pool":
+                add(body, self._op_pool(op, lo, n), k, group)
+            else:
+                deq = fused.get(op.dst) is op
+                i = add(body, self._op_conv(op, lo, n, deq), k, group)
+                if deq:
+                    out_slots.append((1, i, op.dst, 4 * lo * self.act[op.dst].stride(0)))
+        if len(parts) == 1:
+            pooled_head = with_x and self.head and self.head[1]
+            dst_of = lambda o: self.head[1].dst if pooled_head and o is self.head[0] else o.dst
+            for level, members in enumerate(self._levels(ops, self.N, dst_of)):
+                for i in sorted(members):
+                    emit(ops[i], 0, level + 1)
+        else:
+            # layer by layer, alternating between the pipelines: a captured graph hands its nodes
+            # to the GPU in the order they were recorded, and a pipeline recorded whole before
+            # the next one starts that much earlier and runs alone meanwhile
+            for op in ops:
+                for k in list(range(1, len(parts))) + [0]:
+                    emit(op, k, 0)
+        for name in names:
+            if name in fused:
+                continue
+            o, z = B.Op(), self.act[name]
+            o.kind, o.flags = B.OP_DEQUANTIZE, B.OPF_IN_U8 if name in self.unsigned else 0
+            o.x, o.n, o.q_x = z.data_ptr(), z.numel(), self.q[name]
+            out_slots.append((2, add(post, o), name, 0))
+        segments = [(B.Op * len(s))(*s) for s in (pre, body, post)]
+        return segments, x_slots, out_slots, len(parts)
+
+    def _pipelines_pay(self, ops):
+        """Concurrent pipelines hide one launch's latency and tail behind the other's work, and cost
+        a second set of launches (in a recorded graph also a dependency per launch): worth it
+        where the average launch on the whole batch is well above its latency."""
+        us = sum(B.conv_estimate_us(self.conv_desc(o, self.N)) for o in ops if o.kind == "conv")
+        return us > 8.5 * len(ops)
+
+    def _plannable(self, dequant):
+        return not (self.chain or self.pairs or self.duals or any(
+            name in self.real for name in dequant))
+
+    def _run_planned(self, x, dequant):
+        names = tuple(name for name, out in dequant.items() if out is not None)
+        key = (x is not None, names)
+        plan = self._plans.get(key)
+        if plan is None:
+            plan = self._plans[key] = self._plan(*key)
+        segments, x_slots, out_slots, n_parts = plan
+        if x is not None:
+            t = self.net.tensors[self.net.input]
+            assert tuple(x.shape) == (self.N, t.H, t.W, t.C), "the real-valued batch [N, H, W, C]"
+            base = B._ptr(x, torch.float32)
+            for s, i, off in x_slots:
+                segments[s][i].x = base + off
+        for s, i, name, off in out_slots:
+            out = dequant[name]
+            assert out.numel() == self.act[name].numel()
+            segments[s][i].y_f32 = B._ptr(out, torch.float32) + off
+        main = torch.cuda.current_stream()
+        streams = (ctypes.c_void_p * n_parts)(main.cuda_stream,
+                                              *(s.cuda_stream for s in self.side[:n_parts - 1]))
+        run = B.lib.q8_run_ops
+        if n_parts == 1:
+            for ops in segments:
+                if len(ops):
+                    B._check(run(ops, len(ops), streams, 1))
+            return
+        pre, body, post = segments
+        if len(pre):
+            B._check(run(pre, len(pre), streams, 1))
+        for side in self.side[:n_parts - 1]:
+            side.wait_stream(main)
+        B._check(run(body, len(body), streams, n_parts))
+        for side in self.side[:n_parts - 1]:
+            main.wait_stream(side)
+        if len(post):
+            B._check(run(post, len(post), streams, 1))
+
     def run_step(self, x=None, dequant=None, serial=False):
         """One pass over the batch: Eq. Q on ``x`` (if given), every layer, Eq. D on the
         tensors named in ``dequant`` ({name: fp32 output buffer}).  With two streams the
         layers of each half batch form a pipeline of their own between the (whole-batch)
-        quantise and dequantise launches -- splitting those two as well was slower;
-        ``serial`` issues the same launches one pipeline after the other on the caller's
-        stream."""
+        quantise and dequantise launches -- splitting those two as well was slower -- where
+        the batch is large enough for that to pay; ``serial`` issues the launches of every
+        part one pipeline after the other on the caller's stream."""
+        if not serial and self._plannable(dequant or {}):
+            self._run_planned(x, dequant or {})
+            for name, out in (dequant or {}).items():
+                if out is None:
+                    self.dequantize(name)
+            return
         self._x = None
         if x is not None:
             self.set_input(x)
@@ -607,9 +840,6 @@ class Engine:
             main = torch.cuda.current_stream()
             for side in self.side:
                 side.wait_stream(main)
-            # layer by layer, alternating between the pipelines: a captured graph hands its
-            # nodes to the GPU in the order they were recorded, and a pipeline recorded whole
-            # before the next one starts that much earlier and runs alone meanwhile
             for op in self.net.ops:
                 for side, part in zip(self.side, self.parts[1:]):
                     with torch.cuda.stream(side):

@@ -1425,3 +1425,30 @@ def test_conv_latency_family(B, idx):
     for v in variants:
         _run_conv_case(B, DIRECT_CASES[idx], relu=bool(v % 2), with_res=bool(idx % 2), with_bias=True,
                        seed=31 * v + idx, variant=v)
+
+
+def test_run_ops_groups_equal_single_calls(B):
+    """Independent layers of one group (joined into one launch) and a list of tensors to dequantise
+    give the bits of the calls one by one."""
+    import ctypes
+    rng = np.random.default_rng(5)
+    geoms = [dict(N=1, H=17, W=17, C=64, K=48, R=1, S=1), dict(N=1, H=17, W=17, C=64, K=50, R=3, S=3, pad_h=1, pad_w=1),
+             dict(N=1, H=17, W=17, C=48, K=16, R=1, S=7, pad_w=3), dict(N=1, H=9, W=5, C=256, K=33, R=1, S=1)]
+    ops, keep, want = (B.Op * (2 * len(geoms)))(), [], []
+    for i, geom in enumerate(geoms):
+        d = B.ConvDesc(relu=i % 2, **geom)
+        x = dev(rng.integers(-128, 128, (d.N, d.H, d.W, d.C)).astype(np.int8))
+        w = B.pack_weights(d, dev(rng.integers(-128, 128, (d.K, d.R, d.S, d.C)).astype(np.int8)))
+        b = dev(rng.integers(-2000, 2000, d.K).astype(np.int32))
+        want.append(B.conv_int8(d, x, w, b, 0.01, 0.01, 0.5))
+        y, r = torch.zeros_like(want[-1]), torch.zeros(want[-1].shape, device="cuda")
+        o, q = ops[i], ops[len(geoms) + i]
+        o.kind, o.group, o.d, o.x, o.w, o.bias, o.y = B.OP_CONV, 1, d, x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr()
+        o.q_x, o.q_w, o.q_out = 0.01, 0.01, 0.5
+        q.kind, q.flags, q.x, q.n, q.q_x, q.y_f32 = B.OP_DEQUANTIZE, B.OPF_IN_U8 * (i % 2), y.data_ptr(), y.numel(), 0.5, r.data_ptr()
+        keep.append((x, w, b, y, r))
+    streams = (ctypes.c_void_p * 1)(torch.cuda.current_stream().cuda_stream)
+    assert B.lib.q8_run_ops(ops, len(ops), streams, 1) == 0
+    for i, (x, w, b, y, r) in enumerate(keep):
+        assert np.array_equal(host(y), host(want[i]))
+        assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
