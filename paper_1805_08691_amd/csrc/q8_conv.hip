@@ -235,8 +235,8 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
   int bp = 0, bc = 0;
   float tiled_us = 0.0f;
   if (est_us) *est_us = 3.0f + (float)M * (float)d->K * (float)red_len * 1.1e-9f;   // ~ 1.8 POP/s
-  if (tiled >= first_pw && !ext) return tiled;
-  if (tiled >= first_halo && !ext) {
+  if (tiled >= first_pw) return tiled;
+  if (tiled >= first_halo) {
     q8::halo_variant_tile(tiled - first_halo, &bp, &bc);
     const bool two_groups = tiled - first_halo == 12 || tiled - first_halo == 9;
     const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
@@ -602,8 +602,7 @@ int conv_fill_op(const q8_op* o, ConvParams& p, bool* empty) {
 // What one layer would be launched as on its own, and the estimate; launches it.
 int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
   *us = 0.0f;
-  const bool ext = p.in_u8 || p.out_u8 || p.res_u8 || p.m_vec;
-  const int v = pick_variant(d, ext, -1, us);
+  const int v = pick_variant(d, is_extended(p), -1, us);
   return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d) : v;
 }
 int conv_launch_chosen(int variant, ConvParams& p, hipStream_t s) {

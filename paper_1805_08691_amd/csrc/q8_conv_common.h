@@ -383,6 +383,26 @@ __device__ __forceinline__ void finish16_fast(const ConvParams& p, int pix, int 
       codes16_fast<HAS_RES, U8, RES_U8, PC>(p, v, rw, mv);
 }
 
+// The codes of a complete group in a build that is plain (EXT = 0) or takes unsigned codes and
+// per-channel scales by run-time flags (EXT = 1).
+template <int EXT>
+__device__ __forceinline__ v4i codes16_build(const ConvParams& p, const int (&v)[16],
+                                             const int (&rw)[4], const float (&mv)[16], bool has_res) {
+  if constexpr (EXT) {
+    if (p.m_vec)
+      return has_res ? codes16_fast<true, false, false, true>(p, v, rw, mv)
+                     : codes16_fast<false, false, false, true>(p, v, rw, mv);
+    if (!has_res) return codes16_fast<false, true>(p, v, rw, mv);
+    return p.res_u8 ? codes16_fast<true, true, true>(p, v, rw, mv)
+                    : codes16_fast<true, true, false>(p, v, rw, mv);
+  } else {
+    return has_res ? codes16_fast<true>(p, v, rw, mv) : codes16_fast<false>(p, v, rw, mv);
+  }
+}
+__host__ __device__ inline bool is_extended(const ConvParams& p) {
+  return p.in_u8 || p.out_u8 || p.res_u8 || p.m_vec != nullptr;
+}
+
 // Whole epilogue in one go (register-staged kernel).
 __device__ __forceinline__ void epilogue16(const ConvParams& p, int pix, int ch, int (&v)[16]) {
   int b[16], rw[4];

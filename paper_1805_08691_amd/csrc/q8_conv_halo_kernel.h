@@ -58,7 +58,9 @@ struct HaloShape {
   static constexpr int max_w() { return (PATCH_ROWS - BP - 2) / 2; }
 };
 
-template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3>
+// EXT = 1: unsigned activation codes (a pixel's accumulators start at the row of its rectangle of
+// taps inside the image, see u8_start_index) and per-channel scales.
+template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3, int EXT = 0>
 __device__ __forceinline__ void conv_tile_halo3(const ConvParams& p, const int ptile,
                                                 const int ctile, int8_t* const lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -149,6 +151,19 @@ __device__ __forceinline__ void conv_tile_halo3(const ConvParams& p, const int p
     for (int j = 0; j < TP; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = kgroup == 0 ? b[e] : 0;
+  }
+  if (EXT && p.tap_sums && kgroup == 0) {
+#pragma unroll
+    for (int j = 0; j < TP; ++j) {
+      const int idx = u8_start_index(p, pix0 + (wave_p * TP + j) * 32 + frag_row);
+#pragma unroll
+      for (int i = 0; i < TC; ++i) {
+        int b[16];
+        load_start16(p, idx, ch0 + (wave_c * TC + i) * 32 + 16 * (lane >> 5), b);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = b[e];
+      }
+    }
   }
   int res_w[TC][TP][4];
   auto fetch_residual = [&]() {
@@ -338,11 +353,11 @@ __device__ __forceinline__ void conv_tile_halo3(const ConvParams& p, const int p
         }
   }
 
-  finish_tile<TP, TC, 0>(p, acc, res_w, pix0, ch0, BP, BC, wave_p, wave_c, lane);
+  finish_tile<TP, TC, EXT>(p, acc, res_w, pix0, ch0, BP, BC, wave_p, wave_c, lane);
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
-template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3>
+template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3, int EXT = 0>
 __global__ __launch_bounds__(WP * WC * KW * 64) void conv_i8_halo3_kernel(const ConvParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
@@ -358,7 +373,7 @@ __global__ __launch_bounds__(WP * WC * KW * 64) void conv_i8_halo3_kernel(const 
 #endif
   const int ptile = p.ptile_fastest ? bid % p.n_ptiles : bid / p.n_ctiles;
   const int ctile = p.ptile_fastest ? bid / p.n_ptiles : bid % p.n_ctiles;
-  conv_tile_halo3<WP, WC, TP, TC, PL, KW, ST>(p, ptile, ctile, lds);
+  conv_tile_halo3<WP, WC, TP, TC, PL, KW, ST, EXT>(p, ptile, ctile, lds);
 #ifdef Q8_TRACE
   q8_trace_record(p, q8_t0);
 #endif
@@ -370,18 +385,17 @@ template <int WP, int WC, int TP, int TC, int PL, int KW = 1>
 bool halo3_applicable(const ConvParams& p) {
   return (p.C / 64) % KW == 0 && p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 &&
          p.dil_w == 1 && p.pad_h == 1 && p.pad_w == 1 && p.C % 64 == 0 && p.S4 == 0 &&
-         p.W <= HaloShape<WP, WC, TP, TC, PL>::max_w() && !p.in_u8 && !p.out_u8 && !p.res_u8 &&
-         !p.m_vec && !p.w2;
+         p.W <= HaloShape<WP, WC, TP, TC, PL>::max_w() && !p.w2;
 }
 
-template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3>
+template <int WP, int WC, int TP, int TC, int PL, int KW = 1, int ST = 3, int EXT = 0>
 int launch_halo3(ConvParams& p, hipStream_t stream) {
   using Sh = HaloShape<WP, WC, TP, TC, PL, KW, ST>;
   p.n_ptiles = (p.M + Sh::BP - 1) / Sh::BP;
   p.n_ctiles = (p.K + Sh::BC - 1) / Sh::BC;
   const long nblk = (long)p.n_ptiles * p.n_ctiles;
   if (nblk > 0x7fffffffL) return Q8_EUNSUPPORTED;
-  auto kernel = conv_i8_halo3_kernel<WP, WC, TP, TC, PL, KW, ST>;
+  auto kernel = conv_i8_halo3_kernel<WP, WC, TP, TC, PL, KW, ST, EXT>;
   if constexpr (Sh::LDS_BYTES > 65536) {
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

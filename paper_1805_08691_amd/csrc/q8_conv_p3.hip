@@ -14,7 +14,7 @@ int launch_p3_or_generic(ConvParams& p, hipStream_t stream) {
 }
 
 int launch_p3b_or_generic(ConvParams& p, hipStream_t stream) {
-  if (p3b_applicable(p)) return launch_p3b(p, stream);
+  if (p3b_applicable(p)) return launch_p3b<0>(p, stream);
   return launch_ring<2, 2, 2, 2, 64, 3, 0>(p, stream);
 }
 

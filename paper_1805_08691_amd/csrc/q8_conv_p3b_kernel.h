@@ -33,6 +33,7 @@ struct P3bShape {
 };
 
 // p.n_ptiles = tiles in all (N * tiles_h * tiles_w), p.n_ctiles = tiles_w (set by launch_p3b).
+template <int EXT>
 __global__ __launch_bounds__(256) void conv_i8_p3b_kernel(const ConvParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = P3bShape;
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(256) void conv_i8_p3b_kernel(const ConvParams p) {
   const int a_foff0 = frag_row * 64 + swz<4>(frag_row, frag_half) * 16 + wave_c * 32 * 64;
   int bias_v[16];
   load_bias16(p, wave_c * 32 + 16 * (lane >> 5), bias_v);
-  const float no_scales[16] = {};
+  float scales[16] = {};
+  if (EXT && p.m_vec) load_scale16(p, wave_c * 32 + 16 * (lane >> 5), scales);
 
   // patch offsets of this lane's fragments, per tap, half step and pixel tile of the wave: the
   // same in every tile
@@ -147,6 +149,20 @@ __global__ __launch_bounds__(256) void conv_i8_p3b_kernel(const ConvParams p) {
     for (int j = 0; j < TP; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[j][e] = bias_v[e];
+    if (EXT && p.tap_sums) {        // unsigned input codes: the start values of the pixel's rectangle
+      int n, h0, w0;
+      tile_origin(tile, n, h0, w0);
+#pragma unroll
+      for (int j = 0; j < TP; ++j) {
+        const int i = (wave_p * TP + j) * 32 + frag_row, h = h0 + i / TW, w = w0 + i % TW;
+        const int r_lo = h == 0, r_hi = h + 1 < H ? 3 : 2, s_lo = w == 0, s_hi = w + 1 < W ? 3 : 2;
+        const int idx = h < H && w < W ? ((r_lo * 4 + r_hi) * 4 + s_lo) * 4 + s_hi : 0;
+        int b[16];
+        load_start16(p, idx, wave_c * 32 + 16 * (lane >> 5), b);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = b[e];
+      }
+    }
     const int8_t* const pbase = patch + buf * Sh::PATCH_BYTES;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
@@ -174,7 +190,7 @@ __global__ __launch_bounds__(256) void conv_i8_p3b_kernel(const ConvParams p) {
         for (int e = 0; e < 16; ++e) v[e] = acc[j][e];
         const int rw[4] = {0, 0, 0, 0};
         *reinterpret_cast<v4i*>(stage + row * BC + ((slot ^ swz_out<SLOTS>(row)) << 4)) =
-            codes16_fast<false>(p, v, rw, no_scales);
+            codes16_build<EXT>(p, v, rw, scales, false);
       }
     }
     __syncthreads();
@@ -205,19 +221,19 @@ __global__ __launch_bounds__(256) void conv_i8_p3b_kernel(const ConvParams p) {
 inline bool p3b_applicable(const ConvParams& p) {
   return p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 &&
          p.dil_w == 1 && p.pad_h == 1 && p.pad_w == 1 && p.C == 64 && p.S4 == 0 && p.K <= 64 &&
-         (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.in_u8 &&
-         !p.out_u8 && !p.res_u8 && !p.m_vec && !p.w2 && !p.tap_sums &&
+         (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
          (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
-inline int launch_p3b(ConvParams& p, hipStream_t stream) {
+template <int EXT>
+int launch_p3b(ConvParams& p, hipStream_t stream) {
   using Sh = P3bShape;
   const long tiles_w = (p.W + Sh::TW - 1) / Sh::TW, tiles_h = (p.H + Sh::TH - 1) / Sh::TH;
   const long tiles = (long)p.N * tiles_h * tiles_w;
   if (tiles > 0x7fffffffL) return Q8_EUNSUPPORTED;
   p.n_ptiles = (int)tiles;
   p.n_ctiles = (int)tiles_w;
-  auto kernel = conv_i8_p3b_kernel;
+  auto kernel = conv_i8_p3b_kernel<EXT>;
   static const hipError_t attr = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
       Sh::LDS_BYTES);

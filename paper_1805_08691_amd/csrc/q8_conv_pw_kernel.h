@@ -34,7 +34,7 @@ struct PwShape {
   static constexpr int LDS_BYTES = A_BYTES + 2 * B_BYTES + 2 * S_BYTES;
 };
 
-template <int TC, int KS>
+template <int TC, int KS, int EXT>
 __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = PwShape<TC, KS>;
@@ -142,7 +142,11 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 
   int ptile = group;
   if (ptile < p.n_ptiles) issue_tile(ptile, 0);
-  const float no_scales[16] = {};
+  float scales[TC][16] = {};
+  if (EXT && p.m_vec) {
+#pragma unroll
+    for (int i = 0; i < TC; ++i) load_scale16(p, ch0 + (wave_c * TC + i) * 32 + 16 * (lane >> 5), scales[i]);
+  }
   for (int it = 0; ptile < p.n_ptiles; ++it, ptile += n_groups) {
     const int buf = it & 1;
     const int next = ptile + n_groups;
@@ -197,10 +201,10 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
         if (has_res) {
           const v4i r = *cell;
           const int rw[4] = {r[0], r[1], r[2], r[3]};
-          *cell = codes16_fast<true>(p, v, rw, no_scales);
+          *cell = codes16_build<EXT>(p, v, rw, scales[i], true);
         } else {
           const int rw[4] = {0, 0, 0, 0};
-          *cell = codes16_fast<false>(p, v, rw, no_scales);
+          *cell = codes16_build<EXT>(p, v, rw, scales[i], false);
         }
       }
     }
@@ -229,17 +233,17 @@ bool pw_applicable(const ConvParams& p) {
   const bool pointwise = p.R == 1 && p.S == 1 && p.stride_h == 1 && p.stride_w == 1 &&
                          p.pad_h == 0 && p.pad_w == 0;
   return pointwise && p.S4 == 0 && p.C == KS * 64 && (p.K & 15) == 0 && p.vec16 && !p.acc_dump &&
-         !p.y_f32 && !p.y_deq && !p.in_u8 && !p.out_u8 && !p.res_u8 && !p.m_vec && !p.w2 &&
+         !p.y_f32 && !p.y_deq && !p.w2 &&
          (!p.res || (p.res_bytes > 0 && (long)p.M * p.res_cs < 0x7fffffffL)) &&
          (long)p.M * p.in_cs < 0x7fffffffL;
 }
 
-template <int TC, int KS>
+template <int TC, int KS, int EXT>
 int launch_pw(ConvParams& p, hipStream_t stream) {
   using Sh = PwShape<TC, KS>;
   p.n_ptiles = (p.M + Sh::BP - 1) / Sh::BP;
   p.n_ctiles = (p.K + Sh::BC - 1) / Sh::BC;
-  auto kernel = conv_i8_pw_kernel<TC, KS>;
+  auto kernel = conv_i8_pw_kernel<TC, KS, EXT>;
   if constexpr (Sh::LDS_BYTES > 65536) {
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

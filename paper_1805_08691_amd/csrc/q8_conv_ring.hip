@@ -60,6 +60,11 @@ int num_stem_variants();
 int launch_stem_variant(int variant, ConvParams& p, hipStream_t stream);
 const char* stem_variant_name(int variant);
 
+// ... whose extended builds are in q8_conv_ext.hip
+int launch_halo_ext(int family, ConvParams& p, hipStream_t stream);
+int launch_p3_ext(int family, ConvParams& p, hipStream_t stream);
+int launch_pw_ext(int family, ConvParams& p, hipStream_t stream);
+
 // ... and the latency family (q8_conv_direct.hip)
 int num_direct_variants();
 bool direct_applicable(const ConvParams& p);
@@ -71,7 +76,9 @@ void ring_variant_tile(int variant, int* bp, int* bc) {
   *bp = kRingVariants[variant].bp;
   *bc = kRingVariants[variant].bc;
 }
-int ext_variant(int variant) { return variant < kNumRingExtVariants ? variant : 1; }
+int ext_variant(int variant) {
+  return variant < kNumRingExtVariants || variant == 13 || variant == 21 ? variant : 1;
+}
 int first_pw_variant() { return kNumRingVariants + num_halo_variants(); }
 int first_split_variant() { return first_pw_variant() + num_pw_variants(); }
 int first_p3_variant() { return first_split_variant() + num_split_variants(); }
@@ -84,8 +91,16 @@ int launch_stream_variant(int variant, ConvParams& p, hipStream_t stream) {
     if (!direct_applicable(p)) variant = 1;        // odd channel counts: the general kernel
     else return launch_direct_variant(variant - first_direct_variant(), p, stream);
   }
-  if (p.in_u8 | p.out_u8 | p.res_u8 | (p.m_vec != nullptr)) {
-    // variants without an extended build fall back to the 128 x 128 ring of 3
+  if (is_extended(p)) {
+    // the other families' extended builds; variants without one fall back to the 128 x 128 ring of 3
+    int rc = Q8_EUNSUPPORTED;
+    if (variant >= first_stem_variant())
+      rc = launch_stem_variant(variant - first_stem_variant(), p, stream);
+    else if (variant >= first_p3_variant()) rc = launch_p3_ext(variant - first_p3_variant(), p, stream);
+    else if (variant >= first_split_variant()) {}
+    else if (variant >= first_pw_variant()) rc = launch_pw_ext(variant - first_pw_variant(), p, stream);
+    else if (variant >= kNumRingVariants) rc = launch_halo_ext(variant - kNumRingVariants, p, stream);
+    if (rc != Q8_EUNSUPPORTED) return rc;
     return launch_ring_ext_variant(ext_variant(variant), p, stream);
   }
   if (variant >= first_stem_variant())

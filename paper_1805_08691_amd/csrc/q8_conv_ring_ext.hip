@@ -12,6 +12,10 @@ int launch_ring_ext_variant(int variant, ConvParams& p, hipStream_t stream) {
     return launch_ring<WP, WC, TP, TC, BK, ST, 1>(p, stream);
     Q8_RING_EXT_LIST(Q8_RING_CASE)
 #undef Q8_RING_CASE
+    case 13:
+      return launch_ring<4, 2, 2, 2, 64, 3, 1>(p, stream);
+    case 21:
+      return launch_ring<2, 2, 1, 1, 128, 4, 1>(p, stream);
     default:
       return Q8_EINVAL;
   }

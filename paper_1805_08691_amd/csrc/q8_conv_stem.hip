@@ -9,6 +9,11 @@ namespace {
 
 int launch_stem_or_generic(ConvParams& p, hipStream_t stream) {
   const StemImage none{};
+  if (is_extended(p)) {        // unsigned output codes, per-channel scales
+    if (stem_applicable<2>(p)) return launch_stem<2, false, false, 1>(p, none, stream);
+    if (stem_applicable<1>(p)) return launch_stem<1, false, false, 1>(p, none, stream);
+    return launch_ring_ext_variant(8, p, stream);
+  }
   if (stem_applicable<2>(p)) return launch_stem<2, false, false>(p, none, stream);
   if (stem_applicable<1>(p)) return launch_stem<1, false, false>(p, none, stream);
   return launch_ring<2, 2, 2, 1, 64, 2, 0>(p, stream);

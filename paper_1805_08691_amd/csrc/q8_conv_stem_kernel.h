@@ -63,7 +63,7 @@ __device__ __forceinline__ unsigned join_bytes(SplitBytes s) {
 
 // p.n_ptiles = strips per image, p.n_ctiles = output rows (POOL: pooled rows) per strip, set by
 // launch_stem.  SH: the vertical stride (the number of image rows a new output row adds).
-template <int SH, bool F32IN, bool POOL>
+template <int SH, bool F32IN, bool POOL, int EXT = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void conv_i8_stem_kernel(const ConvParams p, const StemImage im) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = StemShape;
@@ -190,6 +190,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int e = 0; e < 16; ++e) bias_v[tc][e] = b[e];
   }
+  float scales[2][16] = {};
+  if (EXT && p.m_vec) {
+#pragma unroll
+    for (int tc = 0; tc < 2; ++tc) load_scale16(p, tc * 32 + 16 * (lane >> 5), scales[tc]);
+  }
   const float code_lo = p.relu ? 0.0f : -128.0f;          // ReLU folded into the lower bound
   constexpr float kMagic = 12582912.0f;                   // 1.5 * 2^23: t + kMagic rounds t to an
                                                           // integer, held in the low mantissa bits
@@ -292,13 +297,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
         for (int e = 0; e < 16; ++e)
           t[e] = __float_as_uint(
-              __builtin_amdgcn_fmed3f((float)acc[tc][e] * p.m, code_lo, 127.0f) + kMagic);
+              __builtin_amdgcn_fmed3f((float)acc[tc][e] * (EXT && p.m_vec ? scales[tc][e] : p.m),
+                                      EXT && p.out_u8 ? 0.0f : code_lo,
+                                      EXT && p.out_u8 ? 255.0f : 127.0f) + kMagic);
         v4i out;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const unsigned w01 = __builtin_amdgcn_perm(t[4 * a + 1], t[4 * a], 0x0c0c0400u);
           const unsigned w23 = __builtin_amdgcn_perm(t[4 * a + 3], t[4 * a + 2], 0x0c0c0400u);
-          out[a] = (int)__builtin_amdgcn_perm(w23, w01, 0x05040100u);
+          out[a] = (int)(__builtin_amdgcn_perm(w23, w01, 0x05040100u) ^
+                         (EXT && p.out_u8 ? 0x80808080u : 0u));       // unsigned codes minus 128
         }
         *reinterpret_cast<v4i*>(stage + row * BC + ((slot ^ swz_out<SLOTS>(row)) << 4)) = out;
       }
@@ -381,14 +389,14 @@ bool stem_applicable(const ConvParams& p) {
   return p.stride_h == SH && p.R + 2 * SH <= 16 && p.S4 == 2 && p.S == 1 && p.C == 32 &&
          p.in_cs == 4 && p.R <= 8 && p.K <= 64 && (p.K & 15) == 0 && p.Wo <= 128 && p.W <= 240 &&
          p.stride_w <= 2 && p.pad_h == 0 && p.pad_w == 0 && p.vec16 && !p.res && !p.acc_dump &&
-         !p.y_f32 && !p.y_deq && !p.in_u8 && !p.out_u8 && !p.res_u8 && !p.m_vec && !p.w2 && !p.tap_sums &&
+         !p.y_f32 && !p.y_deq && !p.in_u8 && !p.res_u8 && !p.w2 && !p.tap_sums &&
          (long)p.N * p.H * p.W * 4 < 0x7fffffffL && (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
-template <int SH, bool F32IN, bool POOL>
+template <int SH, bool F32IN, bool POOL, int EXT = 0>
 int launch_stem(ConvParams& p, const StemImage& im, hipStream_t stream) {
   using Sh = StemShape;
-  auto kernel = conv_i8_stem_kernel<SH, F32IN, POOL>;
+  auto kernel = conv_i8_stem_kernel<SH, F32IN, POOL, EXT>;
   static const hipError_t attr = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
       Sh::LDS_BYTES);

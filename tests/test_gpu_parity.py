@@ -1452,3 +1452,48 @@ def test_run_ops_groups_equal_single_calls(B):
     for i, (x, w, b, y, r) in enumerate(keep):
         assert np.array_equal(host(y), host(want[i]))
         assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
+
+
+# one layer per tiled family with a build for unsigned codes and per-channel scales: 3x3 tiles of
+# each split, the persistent 3x3 and 1x1 kernels, the ring of K = 128 rows, the image rows; channel counts that
+# end inside a tile and images that end inside one
+EXT_CASES = [
+    dict(N=16, H=28, W=28, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1), dict(N=5, H=29, W=23, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=8, H=28, W=28, C=128, K=192, R=3, S=3, pad_h=1, pad_w=1), dict(N=8, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=2, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1), dict(N=16, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=16, H=55, W=57, C=128, K=144, R=3, S=3, pad_h=1, pad_w=1), dict(N=12, H=55, W=57, C=64, K=64, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=24, H=55, W=57, C=64, K=64, R=1, S=1), dict(N=24, H=37, W=35, C=128, K=128, R=1, S=1, stride_h=2, stride_w=2),
+    dict(N=16, H=37, W=35, C=512, K=80, R=1, S=1), dict(N=8, H=117, W=117, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)]
+
+
+@pytest.mark.parametrize("idx", range(len(EXT_CASES)))
+def test_conv_extended_builds(B, idx):
+    d = B.ConvDesc(relu=1, **EXT_CASES[idx])
+    image = d.C == 3
+    rng = np.random.default_rng(900 + idx)
+    w = rng.integers(-128, 128, (d.K, d.R, d.S, d.C)).astype(np.int8)
+    b = rng.integers(-20000, 20000, d.K).astype(np.int32)
+    x = rng.integers(0, 128 if image else 256, (d.N, d.H, d.W, d.in_c_stride or d.C)).astype(np.uint8)
+    res = None if idx in (7, 8, 11) else rng.integers(0, 256, (d.N, d.Ho, d.Wo, d.K)).astype(np.uint8)
+
+    def accumulate(codes):            # whole numbers below 2^53: exact in fp64
+        acc = torch.nn.functional.conv2d(
+            torch.from_numpy(codes[..., :d.C].astype(np.float64)).permute(0, 3, 1, 2),
+            torch.from_numpy(w.astype(np.float64)).permute(0, 3, 1, 2), torch.from_numpy(b.astype(np.float64)),
+            (d.stride_h, d.stride_w), (d.pad_h, d.pad_w))
+        return acc.permute(0, 2, 3, 1).contiguous().numpy().astype(np.int32)
+
+    packed = B.pack_weights(d, dev(w))
+    scale = np.float32(60.0 / (74.0 * 147.0 * np.sqrt(d.R * d.S * d.C)))
+    m_r, acc = np.float32(0.4), accumulate(x)
+    taps, bias = (None, dev(b)) if image else B.u8_prepare(d, dev(w), dev(b))
+    got = B.conv_u8(d, not image, 1, res is not None, dev(x.astype(np.int8) if image else _stored(x)), packed, bias,
+                    taps, 1.0, float(scale), 1.0, None if res is None else dev(_stored(res)), float(m_r))
+    assert np.array_equal(host(got), _stored(orc.requant_mixed(
+        acc, orc.requant_scale(1.0, scale, 1.0), True, res, orc.residual_scale(m_r, 1.0), out_unsigned=True)))
+
+    x_s, res_s = _stored(x) if not image else x.astype(np.int8), None if res is None else _stored(res)
+    m = (scale * rng.uniform(0.3, 3.0, d.K)).astype(np.float32)
+    got = B.conv_int8_per_channel(d, dev(x_s), packed, dev(b), dev(m), 1.0, None if res is None else dev(res_s), 0.4)
+    acc = accumulate(x_s) if not image else acc
+    assert np.array_equal(host(got), orc.requant_pc(acc, m, True, res_s, np.float32(0.4)))
