@@ -792,16 +792,16 @@ class Engine:
             out = dequant[name]
             assert out.numel() == self.act[name].numel()
             segments[s][i].y_f32 = B._ptr(out, torch.float32) + off
-        main = torch.cuda.current_stream()
-        streams = (ctypes.c_void_p * n_parts)(main.cuda_stream,
-                                              *(s.cuda_stream for s in self.side[:n_parts - 1]))
         run = B.lib.q8_run_ops
+        streams = (ctypes.c_void_p * n_parts)(B._stream(),
+                                              *(s.cuda_stream for s in self.side[:n_parts - 1]))
         if n_parts == 1:
             for ops in segments:
                 if len(ops):
                     B._check(run(ops, len(ops), streams, 1))
             return
         pre, body, post = segments
+        main = torch.cuda.current_stream()
         if len(pre):
             B._check(run(pre, len(pre), streams, 1))
         for side in self.side[:n_parts - 1]:
