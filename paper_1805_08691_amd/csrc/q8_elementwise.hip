@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* __restr
   const size_t tid = (size_t)blockIdx.x * kThreads + threadIdx.x;
   const size_t body = (n - head) / 4;
   const size_t tail0 = head + body * 4;
-  if (tid < head) z[tid] = (int8_t)Q(r[tid]);
+  for (size_t k = tid; k < head; k += (size_t)gridDim.x * kThreads) z[k] = (int8_t)Q(r[k]);
   if (tid < n - tail0) z[tail0 + tid] = (int8_t)Q(r[tail0 + tid]);
   const f4_nt* __restrict__ r4 = reinterpret_cast<const f4_nt*>(r + head);
   unsigned* __restrict__ z4 = reinterpret_cast<unsigned*>(z + head);
@@ -617,9 +617,7 @@ int q8_quantize_u8(const float* r_dev, size_t n, float q, int8_t* z_dev, void* s
   size_t head = head_elems(r_dev, 4, n);
   if (!q8_aligned(z_dev + head, 4)) head = n;
   hipLaunchKernelGGL((q8_recip_normal(q) ? quantize_kernel<true, true> : quantize_kernel<true, false>),
-                     dim3(head == n ? (unsigned)((n + kThreads - 1) / kThreads)
-                                                           : (unsigned)blocks_for((n + 15) / 16)),
-                     dim3(kThreads), 0, (hipStream_t)stream, r_dev, n, head, q, 0.0f, 255.0f, z_dev);
+                     dim3((unsigned)blocks_for(head == n ? n : (n + 15) / 16)), dim3(kThreads), 0, (hipStream_t)stream, r_dev, n, head, q, 0.0f, 255.0f, z_dev);
   return q8_launch_status();
 }
 
