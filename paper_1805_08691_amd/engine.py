@@ -344,6 +344,7 @@ class Engine:
         self.q = {k: float(v) for k, v in q.items()}
 
     def quantize_weights_per_channel(self):
+        self._plans.clear()
         for op in self.net.convs():
             Wf, bf = self.folded[op.name]
             q_w, z_w = B.quantize_weights_per_channel(Wf, P_W)
@@ -771,20 +772,25 @@ class Engine:
         us = sum(B.conv_estimate_us(self.conv_desc(o, self.N)) for o in ops if o.kind == "conv")
         return us > 8.5 * len(ops)
 
-    def _plannable(self, dequant):
+    def _plannable(self, x, dequant):
+        """Not with the multi-layer kernels, and only for a batch of exactly the net's shape (the
+        plan holds one pointer to it; layer by layer takes a longer or flattened one too)."""
+        t = self.net.tensors[self.net.input]
         return not (self.chain or self.pairs or self.duals or any(
-            name in self.real for name in dequant))
+            name in self.real for name in dequant)) and (
+                x is None or tuple(x.shape) == (self.N, t.H, t.W, t.C))
 
     def _run_planned(self, x, dequant):
         names = tuple(name for name, out in dequant.items() if out is not None)
         key = (x is not None, names)
-        plan = self._plans.get(key)
-        if plan is None:
-            plan = self._plans[key] = self._plan(*key)
+        # the factors and the switch are attributes a program may set between steps
+        given = (self.fuse_dequant, *self.q.values())
+        plan, planned_for = self._plans.get(key, (None, None))
+        if planned_for != given:
+            plan = self._plan(*key)
+            self._plans[key] = plan, given
         segments, x_slots, out_slots, n_parts = plan
         if x is not None:
-            t = self.net.tensors[self.net.input]
-            assert tuple(x.shape) == (self.N, t.H, t.W, t.C), "the real-valued batch [N, H, W, C]"
             base = B._ptr(x, torch.float32)
             for s, i, off in x_slots:
                 segments[s][i].x = base + off
@@ -819,7 +825,7 @@ class Engine:
         quantise and dequantise launches -- splitting those two as well was slower -- where
         the batch is large enough for that to pay; ``serial`` issues the launches of every
         part one pipeline after the other on the caller's stream."""
-        if not serial and self._plannable(dequant or {}):
+        if not serial and self._plannable(x, dequant or {}):
             self._run_planned(x, dequant or {})
             for name, out in (dequant or {}).items():
                 if out is None:

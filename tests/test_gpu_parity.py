@@ -1112,6 +1112,34 @@ def test_run_step_one_and_two_pipelines_and_serial(B):
         assert np.array_equal(got, host(eng.dequantize(o)))       # fused or not: the same bits
 
 
+def test_planned_step_follows_the_engine(B):
+    """The planned step equals the layer-by-layer one (``serial``) with the pipelines forced, after
+    a factor was set between two steps, and for a batch longer than the engine's."""
+    from paper_1805_08691_amd.engine import Engine
+    net, params, x, folded, q, *_ = _oracle_pipeline(2, 7, True)
+    o = net.outputs[0]
+    for n_streams in (1, 2, 3):
+        eng = Engine(net, 7, n_streams=n_streams)
+        eng._pipelines_pay = lambda ops: True
+        eng.load_params(params)
+        eng.fold()
+        eng.set_factors(q)
+        eng.quantize_weights()
+        eng.allocate()
+        out = torch.empty(eng.act[o].shape, dtype=torch.float32, device="cuda")
+        longer = torch.cat([dev(x), dev(x[:1])])
+        for factor, batch in ((1.0, dev(x)), (2.0, dev(x)), (1.0, longer)):
+            eng.q[o] = q[o] * factor
+            got = []
+            for serial in (True, False):
+                eng.act[o].fill_(55)
+                eng.run_step(batch, {o: out}, serial=serial)
+                torch.cuda.synchronize()
+                got.append((host(eng.act[o]).copy(), host(out).copy()))
+            assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+            assert len(np.unique(got[1][0])) > 16
+
+
 def _sampled_images_check(B, cfg_id, batch, picks, n_cal, cal_batch, n_streams=2, unsigned=False,
                           per_channel=False, real_outputs=False, own_sum_factor=False,
                           fuse_pairs=False, chain=False, chain_variants=None, fuse_duals=False,
