@@ -125,10 +125,18 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
 #pragma unroll
     for (int i = 0; i < TC; ++i)
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
+      for (int c = 0; c < NC; ++c) {
+        // behind the end of a filter stands the next one, whose values must not meet this one's
+        // sums, not even times zero (an infinity there)
+        const int left = MODE == 2 ? 4 : p.rsc - (st * NC + c) * 16 - quarter * 4;
         af[BUF][c][i] = __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (st < n_st ? a_off[i] : kOob) + c * 64,
-                                                       st * NC * 64, 0));
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                     rsrc_w, ((st < n_st) & (left > 0) ? a_off[i] : kOob) + c * 64, st * NC * 64, 0));
+        if constexpr (MODE == 0) {
+#pragma unroll
+          for (int e = 1; e < 4; ++e) af[BUF][c][i][e] = e < left ? af[BUF][c][i][e] : 0.0f;
+        }
+      }
 #pragma unroll
     for (int j = 0; j < TP; ++j) {
       if constexpr (MODE == 2) {

@@ -1435,6 +1435,20 @@ def test_conv_f32_tiles(B, geom, res, slice_):
         assert np.array_equal(host(ref), got)                 # the same sums without the maxima
 
 
+@pytest.mark.parametrize("C, R, K", [(3, 7, 8), (20, 1, 50), (5, 1, 33), (24, 3, 40)])
+def test_conv_f32_keeps_filters_apart(B, C, R, K):
+    """An infinity in one filter stays in its own channel, where the reduction ends inside a stage."""
+    rng = np.random.default_rng(C)
+    d = B.ConvDesc(N=1, H=9, W=9, C=C, K=K, R=R, S=R, pad_h=R // 2, pad_w=R // 2)
+    x = dev(rng.standard_normal((1, 9, 9, C)).astype(np.float32))
+    w = rng.standard_normal((K, R, R, C)).astype(np.float32)
+    clean = host(B.conv_f32_ref(d, x, dev(w)))
+    w[1] = np.inf
+    got = host(B.conv_f32_ref(d, x, dev(w)))
+    others = np.arange(K) != 1
+    assert np.array_equal(got[..., others], clean[..., others]) and not np.isfinite(got[..., 1]).all()
+
+
 # the latency family: one pixel, one reduction step, more steps than a wavefront keeps in flight,
 # channel counts that end inside a group of four, taps per 16-byte chunk, a dilated filter
 DIRECT_CASES = [
