@@ -783,12 +783,15 @@ class Engine:
     def _run_planned(self, x, dequant):
         names = tuple(name for name, out in dequant.items() if out is not None)
         key = (x is not None, names)
-        # the factors and the switch are attributes a program may set between steps
-        given = (self.fuse_dequant, *self.q.values())
-        plan, planned_for = self._plans.get(key, (None, None))
+        # factors, switch, filters and buffers are attributes a program may set between steps; the
+        # plan keeps the objects that its pointers lead into, so none is freed or its id reused
+        objects = [*self.wq.values(), *self.act.values(), *self.act_f32.values(), *self.m_vec.values(),
+                   *self.taps.values(), *self.qw.values()]
+        given = (self.fuse_dequant, *self.q.values(), *map(id, objects))
+        plan, planned_for, _ = self._plans.get(key, (None, None, None))
         if planned_for != given:
             plan = self._plan(*key)
-            self._plans[key] = plan, given
+            self._plans[key] = plan, given, objects
         segments, x_slots, out_slots, n_parts = plan
         if x is not None:
             base = B._ptr(x, torch.float32)

@@ -1140,6 +1140,33 @@ def test_planned_step_follows_the_engine(B):
             assert len(np.unique(got[1][0])) > 16
 
 
+def test_planned_step_follows_other_buffers(B):
+    """A program may put other filters, factors of them and buffers in the place of the engine's:
+    the planned step takes them, as the layer-by-layer one (``serial``) does."""
+    from paper_1805_08691_amd.engine import Engine
+    net, params, x, folded, q, *_ = _oracle_pipeline(2, 7, True)
+    o, name = net.outputs[0], net.convs()[-1].name
+    eng = Engine(net, 7)
+    eng.load_params(params)
+    eng.fold()
+    eng.set_factors(q)
+    eng.quantize_weights()
+    eng.allocate()
+    out, codes = torch.empty(eng.act[o].shape, dtype=torch.float32, device="cuda"), []
+    (packed, bias), q_w = eng.wq[name], eng.qw[name]
+    for filters, factor in ((packed, q_w), (torch.flip(packed, (0,)), q_w), (packed, 2 * q_w)):
+        eng.wq[name], eng.qw[name] = (filters, bias), factor
+        eng.act[o] = torch.full_like(eng.act[o], 55)
+        got = []
+        for serial in (False, True):
+            eng.run_step(dev(x), {o: out}, serial=serial)
+            torch.cuda.synchronize()
+            got.append((host(eng.act[o]).copy(), host(out).copy()))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+        codes.append(got[0][0])
+    assert not np.array_equal(codes[0], codes[1]) and not np.array_equal(codes[0], codes[2])
+
+
 def _sampled_images_check(B, cfg_id, batch, picks, n_cal, cal_batch, n_streams=2, unsigned=False,
                           per_channel=False, real_outputs=False, own_sum_factor=False,
                           fuse_pairs=False, chain=False, chain_variants=None, fuse_duals=False,
