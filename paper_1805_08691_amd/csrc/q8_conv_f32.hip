@@ -191,6 +191,28 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
     }
   };
   prologue(prologue, integral_constant<int, 0>{});
+  // The residual values of the units this wavefront finishes, requested together: inside the tail
+  // they were one trip to memory behind another (64 -> 256 channels on 56 x 56 x 8: 16 trips).
+  // Lanes outside the output read the tensor's first values.  Behind the first operands where the
+  // registers allow it, else behind the last.
+  constexpr int U = TC * TP, OWN = U / KW;       // units: see the tail
+  static_assert(U % KW == 0, "every group owns the same number of units");
+  const int u0 = kgroup * OWN;
+  auto unit_ch = [&](int u) { return ch0 + wave_c * TC * 16 + quarter * 4 * TC + u / TP * 4; };
+  auto unit_pix = [&](int u) { return pix0 + (wave_p * TP + u % TP) * 16 + row; };
+  const bool vec_res = p.res && p.vec_y;         // (then K % 4 == 0)
+  v4f res_v[OWN];
+  auto load_res = [&]() __attribute__((always_inline)) {
+    if (vec_res) {
+#pragma unroll
+      for (int k = 0; k < OWN; ++k) {
+        const int ch = unit_ch(u0 + k), pix = unit_pix(u0 + k);
+        res_v[k] = *reinterpret_cast<const v4f*>(p.res + (ch < p.K && pix < p.M ? (size_t)pix * p.K + ch : 0));
+      }
+    }
+  };
+  constexpr bool kEarlyRes = OWN <= 4;
+  if constexpr (kEarlyRes) load_res();
   // Full passes over the NB buffers.  The loads of a stage are spread between the MFMAs of the
   // stage computed meanwhile: a wavefront issues in order, and with 32 rows a load the address
   // unit takes long enough that a burst of them would keep the matrix unit waiting.
@@ -228,11 +250,8 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
   // Units of the tail: one MFMA tile, four consecutive channels of a pixel per lane.  With KW groups
   // every wavefront hands the units it does not own to their owners through LDS, adds up its
   // own share and finishes it, so the tail is spread over all of them.
-  constexpr int U = TC * TP, OWN = U / KW;
-  static_assert(U % KW == 0, "every group owns the same number of units");
+  if constexpr (!kEarlyRes) load_res();
   v4f own[OWN], bias[OWN];
-  const int u0 = kgroup * OWN;
-  auto unit_ch = [&](int u) { return ch0 + wave_c * TC * 16 + quarter * 4 * TC + u / TP * 4; };
 #pragma unroll
   for (int k = 0; k < OWN; ++k) {
     const int ch = unit_ch(u0 + k);
@@ -271,23 +290,21 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
 #pragma unroll
   for (int k = 0; k < OWN; ++k) {
     const int u = u0 + k, ch = unit_ch(u), nvalid = p.K - ch;
-    const int pix = pix0 + (wave_p * TP + u % TP) * 16 + row;
+    const int pix = unit_pix(u);
     if (nvalid <= 0 || pix >= p.M) continue;
     float* y = p.y + (size_t)pix * p.out_cs + p.out_off + ch;
-    const float* res = p.res ? p.res + (size_t)pix * p.K + ch : nullptr;
     v4f v = own[k] + bias[k];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (e < nvalid) m_sum = fmaxf(m_sum, fabsf(v[e]));
     const bool whole = p.vec_y && nvalid >= 4;
-    if (res) {
-      if (whole) {
-        v += *reinterpret_cast<const v4f*>(res);
-      } else {
+    if (vec_res) {
+      v += res_v[k];
+    } else if (p.res) {
+      const float* res = p.res + (size_t)pix * p.K + ch;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e < nvalid) v[e] += res[e];
-      }
+      for (int e = 0; e < 4; ++e)
+        if (e < nvalid) v[e] += res[e];
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -375,8 +392,8 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.vec_b = q8_aligned(b, 16) ? 1 : 0;
   const long rsc = (long)d->R * d->S * d->C, img = (long)d->H * d->W * d->C * 4;
   const long per_img = (long)p.Ho * p.Wo;
-  // what one tile of at most 128 pixels can reach: its images and the padding around them
-  const long reach = (127 / per_img + 2) * img +
+  // what one tile of at most 256 pixels can reach: its images and the padding around them
+  const long reach = (255 / per_img + 2) * img +
                      ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + d->S * d->dil_w) * d->C * 4;
   if (M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || reach > 0x7fffffffL || d->H > (1 << 28) ||
       (long)d->R * d->dil_h > (1 << 28)) {
@@ -392,6 +409,11 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   // The largest tile that still gives every CU one; below that the tile is shared by four
   // groups of wavefronts (their SIMDs), first 64 x 64, then 32 x 32 where those leave CUs idle.
   auto tiles = [&](long t) { return (M + t - 1) / t * ((d->K + t - 1) / t); };
+  // (Short reductions shared by two groups of a 128 x 64 tile, or by none of a 64 x 64 tile of four
+  // wavefronts, are slower: 128 -> 512 on 28 x 28 x 8 48 and 50 us against 38.)
+  // Up to 64 channels and many tiles: no sharing, whose exchange of accumulators then costs more
+  // than it hides (7x7 on 224 x 224 x 8, 1568 tiles of 64 x 64: 64 -> 46 us).
+  if (d->K <= 64 && d->K > 32 && tiles(64) >= 1024) return launch_f32<4, 1, 4, 4, 1, 1, 3>(p, stream);
   if (d->K > 64 && tiles(128) >= 256) return launch_f32<2, 2, 4, 4, 1, 1, 3>(p, stream);
   if (d->K > 32 && tiles(64) >= 192) return launch_f32<1, 1, 4, 4, 4, 1, 3>(p, stream);
   return launch_f32<1, 1, 2, 2, 4, 2, 3>(p, stream);
