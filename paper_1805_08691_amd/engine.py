@@ -294,9 +294,13 @@ class Engine:
                   and net.tensors[op.dst].C != net.tensors[op.src].C}
         for i, op in enumerate(net.ops):
             d = net.tensors[op.dst]
-            if op.dst not in t:
-                t[op.dst] = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
-            out = t[op.dst]
+            width = op.K if op.kind == "conv" else net.tensors[op.src].C
+            if d.C == width:        # written whole
+                out = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
+            else:                   # a slice: the channels that no op writes are zeros
+                out = t.get(op.dst)
+                if out is None:
+                    out = torch.zeros((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
             if op.kind == "pool":
                 B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H, d.W, out=out,
                            out_c_off=op.dst_c_off)
@@ -309,6 +313,7 @@ class Engine:
                                     slot[op.name + ":branch"] if op.res else None, slot[op.dst])
             if op.dst in pooled and last_write[op.dst] == i:
                 B.calibrate_maxabs(out, slot[op.dst])
+            t[op.dst] = out
             for name in {op.src, getattr(op, "res", None)}:
                 if name is not None and last_use.get(name) == i:
                     del t[name]

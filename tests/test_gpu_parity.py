@@ -1419,6 +1419,40 @@ def test_gpu_calibration_matches_oracle_closely(B):
         assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
 
 
+def _padded_concat_net():
+    """Two branches and a pooling of the image's map side by side in a tensor that is padded to 48
+    channels, read by another layer."""
+    net = wl.Network("padded_concat", "x")
+    net.tensor("x", 9, 11, 16)
+    net.tensor("cat", 9, 11, 48)
+    wl._conv(net, "a", "x", 8, 1, 1, dst="cat", dst_c_off=0)
+    wl._conv(net, "b", "x", 12, 3, 3, dst="cat", dst_c_off=12)
+    wl._pool(net, "p", "x", 3, 1, 1, dst="cat", dst_c_off=24)
+    net.outputs = [wl._conv(net, "c", "cat", 32, 3, 3, relu=False)]
+    return net
+
+
+def test_gpu_calibration_of_partly_written_tensors(B):
+    """Channels of a tensor that no op writes are zeros in the fp32 forward, whatever the memory
+    held before."""
+    from paper_1805_08691_amd.engine import Engine
+    net = _padded_concat_net()
+    params = {op.name: wl.conv_params(2, i, op) for i, op in enumerate(net.convs())}
+    rng = np.random.default_rng(3)
+    xs = [rng.standard_normal((4, 9, 11, 16)).astype(np.float32) for _ in range(2)]
+    q_o = onet.calibrate(net, onet.fold_all(net, params), xs)
+    eng = Engine(net, 4)
+    eng.load_params(params)
+    eng.fold()
+    dirt = [torch.full((4, 9, 11, n), 1e6, device="cuda") for n in (16, 32, 48) for _ in range(4)]
+    torch.cuda.synchronize()
+    del dirt                       # what the allocator hands out next
+    q_g = eng.calibrate([dev(x) for x in xs])
+    assert set(q_g) == set(q_o)
+    for k in q_o:
+        assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
+
+
 # the fp32 forward of calibration: every tile build (128 x 128, 64 x 64 and 32 x 32 shared by four
 # wavefront groups), every chunk mode (C % 32, C % 16, C % 4, other), tails in pixels, channels
 # and reduction, stride, dilation, a channel slice
