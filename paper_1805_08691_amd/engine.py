@@ -319,7 +319,8 @@ class Engine:
                     del t[name]
 
     def calibrate(self, batches):
-        """Running max-abs over fp32 forwards of ``batches`` (device fp32 NHWC tensors)."""
+        """Running max-abs over fp32 forwards of ``batches`` (device fp32 NHWC tensors, at least
+        one)."""
         keys = [self.net.input]
         for op in self.net.ops:
             if op.kind == "conv" and op.res is not None:
@@ -328,9 +329,13 @@ class Engine:
                 keys.append(op.dst)
         slots = torch.zeros(len(keys), dtype=torch.float32, device=self.dev)
         slot = dict(zip(keys, slots.split(1)))
+        n_batches = 0
         for x in batches:
             B.calibrate_maxabs(x.contiguous(), slot[self.net.input])
             self._observed_forward(x.contiguous(), slot)
+            n_batches += 1
+        if not n_batches:
+            raise ValueError("calibrate: no batches")     # every factor would be 1
         vals = slots.cpu().numpy()
         q = {k: B.qfactor(float(v), 8 if k in self.unsigned else P_ACT)
              for k, v in zip(keys, vals)}
