@@ -808,9 +808,7 @@ class Engine:
             for s, i, off in x_slots:
                 segments[s][i].x = base + off
         for s, i, name, off in out_slots:
-            out = dequant[name]
-            assert out.numel() == self.act[name].numel()
-            segments[s][i].y_f32 = B._ptr(out, torch.float32) + off
+            segments[s][i].y_f32 = B._ptr(dequant[name], torch.float32) + off
         run = B.lib.q8_run_ops
         streams = (ctypes.c_void_p * n_parts)(B._stream(),
                                               *(s.cuda_stream for s in self.side[:n_parts - 1]))
@@ -833,11 +831,14 @@ class Engine:
 
     def run_step(self, x=None, dequant=None, serial=False):
         """One pass over the batch: Eq. Q on ``x`` (if given), every layer, Eq. D on the
-        tensors named in ``dequant`` ({name: fp32 output buffer}).  With two streams the
+        tensors named in ``dequant`` ({name: fp32 output buffer, of the batch or longer}).  With two streams the
         layers of each half batch form a pipeline of their own between the (whole-batch)
         quantise and dequantise launches -- splitting those two as well was slower -- where
         the batch is large enough for that to pay; ``serial`` issues the launches of every
         part one pipeline after the other on the caller's stream."""
+        for name, out in (dequant or {}).items():
+            if out is not None and out.numel() < self.act[name].numel():
+                raise ValueError(f"run_step: the buffer of {name} is shorter than the tensor")
         if not serial and self._plannable(x, dequant or {}):
             self._run_planned(x, dequant or {})
             for name, out in (dequant or {}).items():

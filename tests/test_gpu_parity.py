@@ -1140,6 +1140,39 @@ def test_planned_step_follows_the_engine(B):
             assert len(np.unique(got[1][0])) > 16
 
 
+@pytest.mark.parametrize("fuse_dequant", [False, True])
+def test_planned_step_and_other_output_buffers(B, fuse_dequant):
+    """Buffers longer than the batch and flattened ones take the dequantised batch as they do layer by layer (``serial``); shorter ones are refused."""
+    from paper_1805_08691_amd.engine import Engine
+    net, params, x, folded, q, *_ = _oracle_pipeline(2, 2, True)
+    o = net.outputs[0]
+    for batch, n_streams in ((2, 1), (2, 2), (1, 1)):
+        eng = Engine(net, batch, n_streams=n_streams, fuse_dequant=fuse_dequant)
+        eng._pipelines_pay = lambda ops: True
+        eng.load_params(params)
+        eng.fold()
+        eng.set_factors(q)
+        eng.quantize_weights()
+        eng.allocate()
+        N, H, W, K = eng.act[o].shape
+        want = torch.empty((N, H, W, K), device="cuda")
+        eng.run_step(dev(x[:N]), {o: want}, serial=True)
+        buffers = [torch.full((N + 3, H, W, K), -7.0, device="cuda")]
+        if not fuse_dequant:
+            buffers.append(torch.full((N * H * W * K,), -7.0, device="cuda"))
+        for out in buffers:
+            eng.run_step(dev(x[:N]), {o: out})
+            torch.cuda.synchronize()
+            got = out if out.dim() == 1 else out[:N]
+            assert torch.equal(got.reshape(want.shape), want)
+            assert out.dim() == 1 or bool((out[N:] == -7).all())
+        with pytest.raises(ValueError):
+            eng.run_step(dev(x[:N]), {o: torch.empty((N, H, W, K - 1), device="cuda")})
+        if N > 1 and n_streams == 1:            # images that lie apart are refused, as before
+            with pytest.raises(AssertionError):
+                eng.run_step(dev(x[:N]), {o: torch.empty((N, 2, H, W, K), device="cuda")[:, 0]})
+
+
 def test_planned_step_follows_other_buffers(B):
     """A program may put other filters, factors of them and buffers in the place of the engine's:
     the planned step takes them, as the layer-by-layer one (``serial``) does."""
