@@ -783,12 +783,14 @@ class Engine:
         return us > 8.5 * len(ops)
 
     def _plannable(self, x, dequant):
-        """Not with the multi-layer kernels, and only for a batch of exactly the net's shape (the
-        plan holds one pointer to it; layer by layer takes a longer or flattened one too)."""
+        """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and
+        for contiguous buffers (the plan holds one pointer to each; layer by layer takes a longer
+        or flattened batch too, and buffers of which only the images it writes are contiguous)."""
         t = self.net.tensors[self.net.input]
         return not (self.chain or self.pairs or self.duals or any(
-            name in self.real for name in dequant)) and (
-                x is None or tuple(x.shape) == (self.N, t.H, t.W, t.C))
+            name in self.real or (out is not None and not out.is_contiguous())
+            for name, out in dequant.items())) and (
+                x is None or (tuple(x.shape) == (self.N, t.H, t.W, t.C) and x.is_contiguous()))
 
     def _run_planned(self, x, dequant):
         names = tuple(name for name, out in dequant.items() if out is not None)

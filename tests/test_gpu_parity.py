@@ -1142,7 +1142,8 @@ def test_planned_step_follows_the_engine(B):
 
 @pytest.mark.parametrize("fuse_dequant", [False, True])
 def test_planned_step_and_other_output_buffers(B, fuse_dequant):
-    """Buffers longer than the batch and flattened ones take the dequantised batch as they do layer by layer (``serial``); shorter ones are refused."""
+    """Buffers longer than the batch, flattened ones and ones whose images lie apart take the
+    dequantised batch as they do layer by layer (``serial``); shorter ones are refused."""
     from paper_1805_08691_amd.engine import Engine
     net, params, x, folded, q, *_ = _oracle_pipeline(2, 2, True)
     o = net.outputs[0]
@@ -1160,6 +1161,8 @@ def test_planned_step_and_other_output_buffers(B, fuse_dequant):
         buffers = [torch.full((N + 3, H, W, K), -7.0, device="cuda")]
         if not fuse_dequant:
             buffers.append(torch.full((N * H * W * K,), -7.0, device="cuda"))
+        if N == 1:
+            buffers.append(torch.full((3, 2, H, W, K), -7.0, device="cuda")[:, 0])
         for out in buffers:
             eng.run_step(dev(x[:N]), {o: out})
             torch.cuda.synchronize()
@@ -1171,6 +1174,28 @@ def test_planned_step_and_other_output_buffers(B, fuse_dequant):
         if N > 1 and n_streams == 1:            # images that lie apart are refused, as before
             with pytest.raises(AssertionError):
                 eng.run_step(dev(x[:N]), {o: torch.empty((N, 2, H, W, K), device="cuda")[:, 0]})
+
+
+def test_fused_head_takes_images_that_lie_apart(B):
+    """Each pipeline's part of the batch has to be contiguous, the batch has not."""
+    from paper_1805_08691_amd.engine import Engine
+    net = wl.resnet50(image=160)
+    eng = Engine(net, 2, n_streams=2, fuse_head=True)
+    assert eng.head
+    eng.load_params({op.name: wl.conv_params(3, i, op) for i, op in enumerate(net.convs())})
+    eng.fold()
+    x = dev(wl.input_batch(3, net, 2))
+    eng.calibrate([x])
+    eng.quantize_weights()
+    eng.allocate()
+    o = net.outputs[0]
+    eng.run_step(x)
+    want = eng.act[o].clone()
+    eng.act[o].fill_(55)
+    apart = torch.stack([x, x + 1], 1)[:, 0]
+    assert not apart.is_contiguous()
+    eng.run_step(apart)
+    assert torch.equal(eng.act[o], want) and len(torch.unique(want)) > 16
 
 
 def test_planned_step_follows_other_buffers(B):
