@@ -673,34 +673,38 @@ class Engine:
         return o
 
     def _levels(self, ops, n, dst_of):
-        """Level of every op: one more than its producers', and for an op that nothing waits for at
-        once the level between its earliest and latest where it adds least (it then shares a
-        launch, or the idle part of the chip, with the ops there)."""
-        writers, early, late, us, share = {}, [], {}, [], []
+        """Level of every op: one more than the ops' it waits for (those that wrote what it reads,
+        and where it writes over a tensor, those that read or wrote it before), and for an op that
+        nothing waits for the level from that one on where it adds least (it then shares a launch,
+        or the idle part of the chip, with the ops there)."""
+        writers, readers, early, us, share = {}, {}, [], [], []
+        waited_for = [False] * len(ops)
         for i, op in enumerate(ops):
-            level = 0
-            for name in (op.src, getattr(op, "res", None)):
-                for j in writers.get(name, ()):
-                    level = max(level, early[j] + 1)
-            early.append(level)
-            writers.setdefault(dst_of(op), []).append(i)
-            d = self.net.tensors[op.dst]
+            d, dst = self.net.tensors[op.dst], dst_of(op)
+            reads = {op.src, getattr(op, "res", None)} - {None}
+            lo = op.dst_c_off
+            hi = lo + (op.K if op.kind == "conv" else _pad_c(self.net.tensors[op.src].C))
+            waits = {j for name in reads for j, _, _ in writers.get(name, ())}
+            waits.update(readers.get(dst, ()))
+            # (slices of one tensor side by side do not wait for each other)
+            waits.update(j for j, a, b in writers.get(dst, ()) if a < hi and lo < b)
+            early.append(1 + max((early[j] for j in waits), default=-1))
+            for j in waits:
+                waited_for[j] = True
+            for name in reads:
+                readers.setdefault(name, []).append(i)
+            writers.setdefault(dst, []).append((i, lo, hi))
             us.append(B.conv_estimate_us(self.conv_desc(op, n)) if op.kind == "conv" else 3.0)
             work = n * d.H * d.W * (op.K if op.kind == "conv" else d.C)
             share.append(min(1.0, work / 65536.0))     # tiles of 16 x 16 against 256 CUs
         depth = max(early) + 1
-        for i in reversed(range(len(ops))):
-            readers = [late[j] for j, o in enumerate(ops) if j > i
-                       and dst_of(ops[i]) in (o.src, getattr(o, "res", None))]
-            late[i] = min(readers) - 1 if readers else depth - 1
         members = [[] for _ in range(depth)]
         cost = lambda m: (max([us[i] for i in m] + [2.7 + sum((us[i] - 2.7) * share[i] for i in m)])
                           if m else 0.0)
         loose = []
         for i in range(len(ops)):
-            # only ops that no other op reads: moving one never moves another
-            if late[i] > early[i] and late[i] == depth - 1 and not any(
-                    dst_of(ops[i]) in (o.src, getattr(o, "res", None)) for o in ops):
+            # only ops that no other op waits for: moving one never moves another
+            if early[i] < depth - 1 and not waited_for[i]:
                 loose.append(i)
             else:
                 members[early[i]].append(i)

@@ -14,3 +14,52 @@ def test_calibration_without_a_batch_is_refused(batches):
     with pytest.raises(ValueError):
         eng.calibrate(batches)
     assert eng.q == {"x": 0.5}
+
+
+def _reused_names():
+    """Networks that give a tensor's name a second time, in the three ways that orders matter."""
+    def net(*layers):
+        n = wl.Network("reuse", "x")
+        n.tensor("x", 7, 9, 64)
+        for name in ("t", "u", "v", "cat"):
+            n.tensor(name, 7, 9, 64)
+        for name, src, dst, K, off, res in layers:
+            wl._conv(n, name, src, K, 1, 1, res=res, dst=dst, dst_c_off=off)
+        n.outputs = [layers[-1][2]]
+        return n
+    return [
+        # t is read by b, then written over by a layer that reads the image alone
+        net(("a", "x", "t", 64, 0, None), ("b", "t", "u", 64, 0, None), ("c", "x", "t", 64, 0, None),
+            ("d", "t", "v", 64, 0, "u")),
+        # t is written twice with nothing between; a residual reads the second
+        net(("a", "x", "t", 64, 0, None), ("b", "x", "u", 64, 0, None), ("c", "u", "v", 64, 0, None),
+            ("d", "x", "t", 64, 0, None), ("e", "v", "u", 64, 0, "t")),
+        # slices: side by side, then one written over, the last layers read by nothing
+        net(("a", "x", "cat", 32, 0, None), ("b", "x", "cat", 32, 32, None), ("c", "cat", "t", 64, 0, None),
+            ("d", "x", "cat", 48, 16, None), ("e", "t", "u", 64, 0, None), ("f", "u", "v", 64, 0, None)),
+    ]
+
+
+def _waits(net, a, b):
+    """Whether op b, behind op a in the list, has to come after it."""
+    def reads(o):
+        return {o.src, getattr(o, "res", None)} - {None}
+
+    def slice_(o):
+        return o.dst_c_off, o.dst_c_off + (o.K if o.kind == "conv" else net.tensors[o.src].C)
+    (a0, a1), (b0, b1) = slice_(a), slice_(b)
+    return a.dst in reads(b) or b.dst in reads(a) or (a.dst == b.dst and a0 < b1 and b0 < a1)
+
+
+@pytest.mark.parametrize("net", _reused_names() + [wl.bottleneck_block(), wl.resnet50(), wl.inception_v3(),
+                                                   wl.ssd300_vgg16()], ids=lambda n: n.name)
+def test_levels_keep_the_order_of_dependent_layers(net):
+    eng = Engine(net, 1, device="cpu")
+    members = eng._levels(net.ops, 1, lambda o: o.dst)
+    level = {i: lv for lv, m in enumerate(members) for i in m}
+    assert sorted(level) == list(range(len(net.ops)))
+    for j, b in enumerate(net.ops):
+        for i, a in enumerate(net.ops[:j]):
+            assert not _waits(net, a, b) or level[i] < level[j], (a.name, b.name)
+    if len(net.ops) > 10:                # independent layers do share a level
+        assert len(members) < len(net.ops)
