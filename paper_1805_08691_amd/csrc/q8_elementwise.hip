@@ -412,7 +412,10 @@ int dequantize_list(const q8_op* ops, int n, hipStream_t stream) {
         need > 0x3fffffff) {
       const int rc = o.flags & Q8_OPF_IN_U8 ? q8_dequantize_u8(z, o.n, o.q_x, o.y_f32, stream)
                                             : q8_dequantize(z, o.n, o.q_x, o.y_f32, stream);
-      if (rc != Q8_OK) return rc;
+      if (rc != Q8_OK) {
+        flush();               // the tensors in front of the refused one
+        return rc;
+      }
       continue;
     }
     if (l.n == kDeqMax || blocks + need > 0x3fffffff) {

@@ -1615,6 +1615,40 @@ def test_run_ops_groups_equal_single_calls(B):
         assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
 
 
+def _dequantize_ops(B, n, lengths, offset_of=()):
+    """A list of Q8_OP_DEQUANTIZE ops over int8 tensors of ``lengths``, those in ``offset_of`` one
+    value behind an aligned address; (ops, tensors, outputs, factors)."""
+    rng = np.random.default_rng(n)
+    ops, zs, outs, factors = (B.Op * n)(), [], [], []
+    for i in range(n):
+        off = 1 if i in offset_of else 0
+        zs.append(dev(rng.integers(-128, 128, lengths[i] + off).astype(np.int8))[off:])
+        outs.append(torch.full((lengths[i] + off,), -7.0, device="cuda")[off:])
+        factors.append(0.125 * (i + 1))
+        o = ops[i]
+        o.kind, o.flags, o.q_x = B.OP_DEQUANTIZE, B.OPF_IN_U8 * (i % 3 == 1), factors[i]
+        o.x, o.n, o.y_f32 = zs[i].data_ptr(), lengths[i], outs[i].data_ptr()
+    return ops, zs, outs, factors
+
+
+def _run_ops(B, ops):
+    import ctypes
+    streams = (ctypes.c_void_p * 1)(torch.cuda.current_stream().cuda_stream)
+    rc = B.lib.q8_run_ops(ops, len(ops), streams, 1)
+    torch.cuda.synchronize()
+    return rc
+
+
+def test_run_ops_dequantises_what_stands_in_front_of_a_refused_op(B):
+    lengths = [5000, 64, 1, 300, 77]
+    ops, zs, outs, factors = _dequantize_ops(B, 5, lengths)
+    ops[3].q_x = -1.0
+    assert _run_ops(B, ops) == -1
+    for i in range(5):
+        want = factors[i] * (zs[i].float() + 128 * (i % 3 == 1)) if i < 3 else torch.full_like(outs[i], -7.0)
+        assert torch.equal(outs[i], want), i
+
+
 # one layer per tiled family with a build for unsigned codes and per-channel scales: 3x3 tiles of
 # each split, the persistent 3x3 and 1x1 kernels, the ring of K = 128 rows, the image rows; channel counts that
 # end inside a tile and images that end inside one
