@@ -55,23 +55,35 @@ int run_one(const q8_op& o, void* stream) {
 }
 
 // A run of independent ops on one stream.  The convolutions that would be launched as the latency
-// family anyway go together, or all of them do, or none: whatever is estimated shortest.
+// family anyway go together, or all of them do, or none: whatever is estimated shortest.  Ops in
+// front of a refused one are enqueued, those behind it are not: the convolutions, whose arguments
+// are checked without a launch, therefore go behind the others.
 int run_group(const q8_op* ops, int n, void* stream) {
   ConvParams p[kMaxGroup];
   const ConvParams *small[kMaxGroup], *all[kMaxGroup];
-  int variant[kMaxGroup], n_small = 0, n_all = 0;
-  bool is_small[kMaxGroup] = {}, launched[kMaxGroup] = {};
+  int variant[kMaxGroup], n_small = 0, n_all = 0, n_conv = 0, refused = Q8_OK;
+  bool is_small[kMaxGroup] = {}, waiting[kMaxGroup] = {};
   float us_each[kMaxGroup], us_small = 0.0f, us_all = 0.0f;
   const int first = first_direct_variant(), last = first + num_direct_variants();
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < n && refused == Q8_OK; ++i) {
     if (ops[i].kind != Q8_OP_CONV) continue;
     bool empty = false;
-    const int rc = conv_fill_op(&ops[i], p[i], &empty);
-    if (rc != Q8_OK) return rc;
-    launched[i] = true;
-    if (empty) continue;
+    refused = conv_fill_op(&ops[i], p[i], &empty);
+    if (refused != Q8_OK) n = i;
+    else waiting[i] = !empty;
+  }
+  for (int i = 0; i < n; ++i) {
+    if (ops[i].kind == Q8_OP_CONV) continue;
+    const int rc = run_one(ops[i], stream);
+    if (rc != Q8_OK) {
+      refused = rc;
+      n = i;
+    }
+  }
+  for (int i = 0; i < n; ++i) {
+    if (!waiting[i]) continue;
+    ++n_conv;
     variant[i] = conv_choose(&ops[i].d, p[i], &us_each[i]);
-    launched[i] = false;
     us_all += us_each[i];
     if (direct_applicable(p[i]) && p[i].S4 == 0) all[n_all++] = &p[i];
     if (variant[i] >= first && variant[i] < last) {
@@ -80,28 +92,25 @@ int run_group(const q8_op* ops, int n, void* stream) {
       small[n_small++] = &p[i];
     }
   }
-  int n_conv = 0;
-  for (int i = 0; i < n; ++i) n_conv += ops[i].kind == Q8_OP_CONV && !launched[i];
   float us_g = 0.0f, us_a = 0.0f;
   const int vs = n_small >= 2 ? pick_direct_group(small, n_small, &us_g) : -1;
   const int va = n_all >= 2 && n_all == n_conv ? pick_direct_group(all, n_all, &us_a) : -1;
   const float saved_small = vs >= 0 ? us_small - us_g : 0.0f, saved_all = va >= 0 ? us_all - us_a : 0.0f;
   if (saved_all > 0.0f && saved_all >= saved_small) {
     const int rc = launch_direct_group_variant(va, all, n_all, (hipStream_t)stream);
-    if (rc != Q8_OK) return rc;
-    for (int i = 0; i < n; ++i) launched[i] = launched[i] || ops[i].kind == Q8_OP_CONV;
-  } else if (saved_small > 0.0f) {
+    return rc != Q8_OK ? rc : refused;
+  }
+  if (saved_small > 0.0f) {
     const int rc = launch_direct_group_variant(vs, small, n_small, (hipStream_t)stream);
     if (rc != Q8_OK) return rc;
-    for (int i = 0; i < n; ++i) launched[i] = launched[i] || is_small[i];
+    for (int i = 0; i < n; ++i) waiting[i] = waiting[i] && !is_small[i];
   }
   for (int i = 0; i < n; ++i) {
-    if (launched[i]) continue;
-    const int rc = ops[i].kind == Q8_OP_CONV ? conv_launch_chosen(variant[i], p[i], (hipStream_t)stream)
-                                             : run_one(ops[i], stream);
+    if (!waiting[i]) continue;
+    const int rc = conv_launch_chosen(variant[i], p[i], (hipStream_t)stream);
     if (rc != Q8_OK) return rc;
   }
-  return Q8_OK;
+  return refused;
 }
 
 }  // namespace

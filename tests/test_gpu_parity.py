@@ -1649,6 +1649,33 @@ def test_run_ops_dequantises_what_stands_in_front_of_a_refused_op(B):
         assert torch.equal(outs[i], want), i
 
 
+@pytest.mark.parametrize("refused", [1, 2, 3, None])
+def test_run_ops_group_with_a_refused_op(B, refused):
+    """Of a group of independent layers and poolings, those in front of the op that is refused for
+    its arguments run and those behind it do not."""
+    rng = np.random.default_rng(9)
+    x = dev(rng.integers(-128, 128, (1, 9, 9, 64)).astype(np.int8))
+    d = B.ConvDesc(N=1, H=9, W=9, C=64, K=32, R=1, S=1)
+    w = B.pack_weights(d, dev(rng.integers(-128, 128, (32, 1, 1, 64)).astype(np.int8)))
+    conv, pool = B.conv_int8(d, x, w, None, 0.01, 0.01, 0.5), B.pool_i8(x, "avg", 3, 3, 1, 1, 9, 9)
+    ops, outs = (B.Op * 5)(), []
+    for i, o in enumerate(ops):
+        is_conv = i % 2 == 0
+        outs.append(torch.full_like(conv if is_conv else pool, 55))
+        o.group, o.x, o.y, o.q_x, o.q_out = 1, x.data_ptr(), outs[i].data_ptr(), 1.0, 1.0
+        if is_conv:
+            o.kind, o.d, o.w, o.q_x, o.q_w, o.q_out = B.OP_CONV, d, w.data_ptr(), 0.01, 0.01, 0.5
+        else:
+            o.kind, o.H, o.W, o.C, o.mode, o.d.N = B.OP_POOL, 9, 9, 64, 1, 1
+            o.R, o.S, o.stride, o.pad, o.Ho, o.Wo, o.d.out_c_stride = 3, 3, 1, 1, 9, 9, 64
+    if refused is not None:
+        ops[refused].q_out = -1.0
+    assert _run_ops(B, ops) == (0 if refused is None else -1)
+    for i, out in enumerate(outs):
+        ran = refused is None or i < refused
+        assert torch.equal(out, (pool if i % 2 else conv) if ran else torch.full_like(out, 55)), i
+
+
 # one layer per tiled family with a build for unsigned codes and per-channel scales: 3x3 tiles of
 # each split, the persistent 3x3 and 1x1 kernels, the ring of K = 128 rows, the image rows; channel counts that
 # end inside a tile and images that end inside one
