@@ -195,6 +195,10 @@ __device__ __forceinline__ void conv_tile_direct(const DirectParams& p, const in
   v4i af[NB][TC], bf[NB][TP];
   auto load_step = [&](int st, auto buf_c) __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf_c)::value;
+    // Steps behind the last one read filter values from beyond the descriptor, zeros.  Their scalar
+    // offset is that of the first step: whichever way the range check counts a scalar offset, none
+    // leads behind a pixel's channels or a filter.
+    const int step_off = st < nk ? st * 64 : 0;
     if constexpr (MODE == 0) {
       const int k = st * 64 + quarter * 16;       // the lane's own 16-byte chunk and its tap
       const int tap = fast_div(k, p.by_c.m, p.by_c.s), c = k - tap * p.C;
@@ -213,13 +217,13 @@ __device__ __forceinline__ void conv_tile_direct(const DirectParams& p, const in
 #pragma unroll
       for (int i = 0; i < TC; ++i)
         af[BUF][i] = __builtin_bit_cast(
-            v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, k_in ? a_off[i] : kDirectOob, st * 64, 0));
+            v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, k_in ? a_off[i] : kDirectOob, step_off, 0));
     } else {
       if constexpr (MODE == 2) {
 #pragma unroll
         for (int j = 0; j < TP; ++j)
           bf[BUF][j] = __builtin_bit_cast(
-              v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, base[j], st * 64, 0));
+              v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, base[j], step_off, 0));
       } else {
         const int tap = fast_div(st * 64, p.by_c.m, p.by_c.s), c = st * 64 - tap * p.C;
         const int r = fast_div(tap, p.by_s.m, p.by_s.s), s = tap - r * p.S;
@@ -237,7 +241,7 @@ __device__ __forceinline__ void conv_tile_direct(const DirectParams& p, const in
 #pragma unroll
       for (int i = 0; i < TC; ++i)
         af[BUF][i] = __builtin_bit_cast(
-            v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, st < nk ? a_off[i] : kDirectOob, st * 64, 0));
+            v4i, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, st < nk ? a_off[i] : kDirectOob, step_off, 0));
     }
   };
   v4i acc[TC][TP];
@@ -265,8 +269,8 @@ __device__ __forceinline__ void conv_tile_direct(const DirectParams& p, const in
     rec(rec, integral_constant<int, 0>{});
   };
   // The first NB steps of this wavefront are requested at once.  A wavefront with more of them
-  // keeps NB in flight (steps behind the last read zeros there, so the loop issues the same
-  // loads on every path and its waits are exact); one with fewer issues what it has.
+  // keeps NB in flight (steps behind the last add nothing, so the loop issues the same loads on
+  // every path and its waits are exact); one with fewer issues what it has.
   // (may be zero or negative: nothing to do)
   const int n_mine = (nk - wave + KW - 1) / KW;
   each_buf([&](auto b_c) __attribute__((always_inline)) {

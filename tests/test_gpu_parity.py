@@ -1568,14 +1568,17 @@ def test_conv_f32_keeps_filters_apart(B, C, R, K):
     assert np.array_equal(got[..., others], clean[..., others]) and not np.isfinite(got[..., 1]).all()
 
 
-# the latency family: one pixel, one reduction step, more steps than a wavefront keeps in flight,
-# channel counts that end inside a group of four, taps per 16-byte chunk, a dilated filter
+# the latency family: one pixel, one reduction step, more steps than a wavefront keeps in flight (also
+# of a single pixel and filter, which the steps behind the last one would lead out of), channel counts
+# that end inside a group of four, taps per 16-byte chunk, a dilated filter
 DIRECT_CASES = [
     dict(N=1, H=1, W=1, C=64, K=16, R=1, S=1), dict(N=1, H=1, W=1, C=2048, K=50, R=1, S=1),
     dict(N=3, H=5, W=3, C=16, K=126, R=3, S=3, pad_h=1, pad_w=1),
     dict(N=1, H=17, W=17, C=160, K=48, R=1, S=7, pad_w=3), dict(N=1, H=7, W=9, C=512, K=20, R=3, S=3, pad_h=1, pad_w=1),
     dict(N=2, H=19, W=19, C=64, K=36, R=3, S=3, pad_h=6, pad_w=6, dil_h=6, dil_w=6),
-    dict(N=2, H=9, W=9, C=128, K=33, R=1, S=1, stride_h=2, stride_w=2)]
+    dict(N=2, H=9, W=9, C=128, K=33, R=1, S=1, stride_h=2, stride_w=2),
+    dict(N=1, H=1, W=1, C=4160, K=1, R=1, S=1), dict(N=1, H=1, W=1, C=4176, K=1, R=1, S=1),
+    dict(N=1, H=1, W=1, C=512, K=1, R=3, S=3, pad_h=1, pad_w=1)]
 
 
 @pytest.mark.parametrize("idx", range(len(DIRECT_CASES)))
