@@ -11,6 +11,8 @@ Online step:
                        outputs that leave the int8 domain; forward(x) is run_step without D.
 """
 import ctypes
+import itertools
+import operator
 
 import numpy as np
 import torch
@@ -799,15 +801,18 @@ class Engine:
     def _run_planned(self, x, dequant):
         names = tuple(name for name, out in dequant.items() if out is not None)
         key = (x is not None, names)
-        # factors, switch, filters and buffers are attributes a program may set between steps; the
-        # plan keeps the objects that its pointers lead into, so none is freed or its id reused
-        objects = [*self.wq.values(), *self.act.values(), *self.act_f32.values(), *self.m_vec.values(),
-                   *self.taps.values(), *self.qw.values()]
-        given = (self.fuse_dequant, *self.q.values(), *map(id, objects))
-        plan, planned_for, _ = self._plans.get(key, (None, None, None))
-        if planned_for != given:
+        # factors, switch, filters and buffers are attributes a program may set between steps, and a
+        # tensor's storage may be another than it was: the plan holds for the same names, the same
+        # objects (whose types and strides were checked) and the addresses that they have now
+        tensors = [t for t in itertools.chain(*self.wq.values(), self.act.values(), self.act_f32.values(),
+                                              self.m_vec.values(), self.taps.values()) if t is not None]
+        q_w = () if self.per_channel else self.qw.values()
+        given = (self.fuse_dequant, *self.q, *self.q.values(), *self.wq, *self.act, *self.taps, *self.m_vec, *q_w,
+                 *map(torch.Tensor.data_ptr, tensors))
+        plan, planned_for, planned_with = self._plans.get(key, (None, None, None))
+        if planned_for != given or not all(map(operator.is_, planned_with, tensors)):
             plan = self._plan(*key)
-            self._plans[key] = plan, given, objects
+            self._plans[key] = plan, given, tensors
         segments, x_slots, out_slots, n_parts = plan
         if x is not None:
             base = B._ptr(x, torch.float32)

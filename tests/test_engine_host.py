@@ -1,5 +1,6 @@
 """Host-side checks of the engine: what it refuses and how it orders layers (no GPU)."""
 import pytest
+import torch
 
 B = pytest.importorskip("paper_1805_08691_amd.binding")
 
@@ -63,3 +64,59 @@ def test_levels_keep_the_order_of_dependent_layers(net):
             assert not _waits(net, a, b) or level[i] < level[j], (a.name, b.name)
     if len(net.ops) > 10:                # independent layers do share a level
         assert len(members) < len(net.ops)
+
+
+@pytest.fixture
+def recorded(monkeypatch):
+    """Engines on host memory, whose planned steps are recorded and not run: recorded(net, batch,
+    **options) -> (engine, step), and step(x, dequant) the ops of one step."""
+    def ptr(t, dtype=None):               # the checks of the binding, without a device
+        if t is None:
+            return None
+        assert t.is_contiguous() and (dtype is None or t.dtype is dtype)
+        return t.data_ptr()
+    ops = []
+
+    def run(arr, n, streams, n_streams):
+        for o in arr:
+            ops.append(B.Op.from_buffer_copy(o))
+        return 0
+    monkeypatch.setattr(B, "_ptr", ptr)
+    monkeypatch.setattr(B, "_stream", lambda: 0)
+    monkeypatch.setattr(B.lib, "q8_run_ops", run)
+
+    def make(net, batch, **options):
+        eng = Engine(net, batch, device="cpu", **options)
+        eng.set_factors({name: 2.0 ** -i for i, name in enumerate(net.tensors)})
+        for o in net.convs():
+            eng.wq[o.name] = (torch.zeros(B.packed_weight_bytes(eng.desc[o.name]), dtype=torch.int8),
+                              torch.zeros(o.K, dtype=torch.int32))
+            eng.qw[o.name] = 0.5
+        eng.allocate()
+
+        def step(x=None, dequant=None):
+            ops.clear()
+            eng.run_step(x, dequant)
+            assert ops
+            return list(ops)
+        return eng, step
+    return make
+
+
+def test_planned_step_follows_storage_and_names(recorded):
+    """A tensor may be given other storage, and a table the same values under other names."""
+    net = wl.bottleneck_block()
+    eng, step = recorded(net, 2)
+    conv, out = net.convs()[-1], net.outputs[0]
+    first = step()[-1]
+    assert first.w == eng.wq[conv.name][0].data_ptr() and first.y == eng.act[out].data_ptr()
+    moved = [*eng.wq[conv.name], eng.act[out]]
+    for t in moved:
+        t.data = t.clone()
+    o = step()[-1]
+    assert [o.w, o.bias, o.y] == [t.data_ptr() for t in moved] and o.w != first.w
+    names = [n for n in eng.q if n not in (conv.src, out)] + [conv.src, out]
+    for order in (names, names[:-2] + [out, conv.src]):
+        eng.q = dict(zip(order, (2.0 ** -i for i in range(len(names)))))
+        o = step()[-1]
+        assert (o.q_x, o.q_out) == (eng.q[conv.src], eng.q[out])
