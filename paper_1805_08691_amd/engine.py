@@ -610,39 +610,42 @@ class Engine:
     # A step is described once as an array of library calls (binding.Op) and enqueued with one
     # call per stream segment; only the pointers of the real-valued batch and of the fp32
     # outputs are filled in per step.
+    # (every address goes through the checks that the layer calls make)
+    def _codes(self, name, lo, n):
+        return B._ptr(self.act[name][lo:lo + n], torch.int8)
+
     def _op_conv(self, op, lo, n, deq):
         packed, bias = self.wq[op.name]
         U, o = self.unsigned, B.Op()
         o.kind, o.d = B.OP_CONV, self.conv_desc(op, n)
-        src, dst = self.act[op.src], self.act[op.dst]
-        o.x = src.data_ptr() + lo * src.stride(0)
-        o.w, o.bias = packed.data_ptr(), bias.data_ptr()
-        o.y = dst.data_ptr() + lo * dst.stride(0)
+        o.x, o.y = self._codes(op.src, lo, n), self._codes(op.dst, lo, n)
+        o.w, o.bias = B._ptr(packed, torch.int8), B._ptr(bias, torch.int32)
         o.q_x, o.q_out = self.q[op.src], self.q[op.dst]
         o.q_w = 1.0 if self.per_channel else self.qw[op.name]
         if op.res:
-            res = self.act[op.res]
-            o.residual, o.q_res = res.data_ptr() + lo * res.stride(0), self.q[op.res]
+            o.residual, o.q_res = self._codes(op.res, lo, n), self.q[op.res]
         if op.dst in self.real:
-            out = self.act_f32[op.dst]
-            o.flags, o.y_f32 = B.OPF_REAL, out.data_ptr() + 4 * lo * out.stride(0)
+            o.flags, o.y_f32 = B.OPF_REAL, B._ptr(self.act_f32[op.dst][lo:lo + n], torch.float32)
         elif self.per_channel:
-            o.flags, o.aux = B.OPF_PER_CHANNEL, self.m_vec[op.name].data_ptr()
+            o.flags, o.aux = B.OPF_PER_CHANNEL, B._ptr(self.m_vec[op.name], torch.float32)
         elif op.src in U or op.dst in U or op.res in U:
             o.flags = (B.OPF_IN_U8 * (op.src in U) | B.OPF_OUT_U8 * (op.dst in U) |
                        B.OPF_RES_U8 * (op.res in U))
             if op.src in U:
-                o.aux = self.taps[op.name].data_ptr()
+                o.aux = B._ptr(self.taps.get(op.name), torch.int32)
         elif deq:
             o.flags = B.OPF_DEQUANT
         return o
 
     def _op_pool(self, op, lo, n):
         s, d = self.net.tensors[op.src], self.net.tensors[op.dst]
-        src, dst, o = self.act[op.src], self.act[op.dst], B.Op()
+        o = B.Op()
         exact = op.mode == "max" and self.q[op.src] == self.q[op.dst] and _pad_c(d.C) == _pad_c(s.C)
         o.kind = B.OP_MAXPOOL if exact else B.OP_POOL
-        o.x, o.y = src.data_ptr() + lo * src.stride(0), dst.data_ptr() + lo * dst.stride(0)
+        if exact:            # (run_pool checks nothing there either)
+            o.x, o.y = self.act[op.src][lo:lo + n].data_ptr(), self.act[op.dst][lo:lo + n].data_ptr()
+        else:
+            o.x, o.y = self._codes(op.src, lo, n), self._codes(op.dst, lo, n)
         o.d.N, o.H, o.W, o.C = n, s.H, s.W, _pad_c(s.C)
         o.mode = 0 if op.mode == "max" else 1
         o.R, o.S, o.stride, o.pad, o.Ho, o.Wo = op.R, op.S, op.stride, op.pad, d.H, d.W
@@ -651,8 +654,8 @@ class Engine:
         return o
 
     def _op_quantize(self, n):
-        t, z, o = self.net.tensors[self.net.input], self.act[self.net.input], B.Op()
-        o.q_x, o.p, o.y = self.q[self.net.input], P_ACT, z.data_ptr()
+        t, o = self.net.tensors[self.net.input], B.Op()
+        o.q_x, o.p, o.y = self.q[self.net.input], P_ACT, self._codes(self.net.input, 0, n)
         if self.in_frame:
             o.kind, o.d.N, o.H, o.W, o.C = B.OP_QUANTIZE_IMAGE, n, t.H, t.W, t.C
             o.top, o.left, o.Ho, o.Wo = self.in_frame
@@ -666,12 +669,12 @@ class Engine:
         conv, pool = self.head
         packed, bias = self.wq[conv.name]
         t, o = self.net.tensors[self.net.input], B.Op()
-        dst = self.act[pool.dst if pool else conv.dst]
         o.kind, o.flags, o.d = B.OP_HEAD, B.OPF_POOL if pool else 0, self.conv_desc(conv, n)
         o.H, o.W, o.C = t.H, t.W, t.C
         o.top, o.left = self.in_frame[:2]
         o.q_x, o.p, o.q_w, o.q_out = self.q[self.net.input], P_ACT, self.qw[conv.name], self.q[conv.dst]
-        o.w, o.bias, o.y = packed.data_ptr(), bias.data_ptr(), dst.data_ptr() + lo * dst.stride(0)
+        o.w, o.bias = B._ptr(packed, torch.int8), B._ptr(bias, torch.int32)
+        o.y = self._codes(pool.dst if pool else conv.dst, lo, n)
         return o
 
     def _levels(self, ops, n, dst_of):
@@ -776,7 +779,7 @@ class Engine:
                 continue
             o, z = B.Op(), self.act[name]
             o.kind, o.flags = B.OP_DEQUANTIZE, B.OPF_IN_U8 if name in self.unsigned else 0
-            o.x, o.n, o.q_x = z.data_ptr(), z.numel(), self.q[name]
+            o.x, o.n, o.q_x = B._ptr(z, torch.int8), z.numel(), self.q[name]
             out_slots.append((2, add(post, o), name, 0))
         segments = [(B.Op * len(s))(*s) for s in (pre, body, post)]
         return segments, x_slots, out_slots, len(parts)

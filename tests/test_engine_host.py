@@ -120,3 +120,23 @@ def test_planned_step_follows_storage_and_names(recorded):
         eng.q = dict(zip(order, (2.0 ** -i for i in range(len(names)))))
         o = step()[-1]
         assert (o.q_x, o.q_out) == (eng.q[conv.src], eng.q[out])
+
+
+def test_planned_step_refuses_what_the_layer_calls_refuse(recorded):
+    """Buffers of another type or with gaps are refused, layers without a bias are not."""
+    net = wl.bottleneck_block()
+    conv, out = net.convs()[-1], net.outputs[0]
+    eng, step = recorded(net, 2)
+    packed, bias = eng.wq[conv.name]
+    eng.wq[conv.name] = packed, None
+    assert step()[-1].bias is None
+    for other in ((packed.view(torch.uint8), bias), (packed.repeat(2)[::2], bias), (packed, bias.long())):
+        eng.wq[conv.name] = other
+        with pytest.raises(AssertionError):
+            step()
+    eng.wq[conv.name] = packed, bias
+    codes = eng.act[out]
+    for other in (codes.float(), codes.repeat(1, 1, 1, 2)[..., ::2]):
+        eng.act[out] = other
+        with pytest.raises(AssertionError):
+            step()
