@@ -760,7 +760,7 @@ class Engine:
                 deq = fused.get(op.dst) is op
                 i = add(body, self._op_conv(op, lo, n, deq), k, group)
                 if deq:
-                    out_slots.append((1, i, op.dst, 4 * lo * self.act[op.dst].stride(0)))
+                    out_slots.append((1, i, op.dst, 4 * lo * self.act[op.dst].shape[1:].numel()))
         if len(parts) == 1:
             pooled_head = with_x and self.head and self.head[1]
             dst_of = lambda o: self.head[1].dst if pooled_head and o is self.head[0] else o.dst
@@ -777,7 +777,7 @@ class Engine:
         for name in names:
             if name in fused:
                 continue
-            o, z = B.Op(), self.act[name]
+            o, z = B.Op(), self.act[name][:self.N]
             o.kind, o.flags = B.OP_DEQUANTIZE, B.OPF_IN_U8 if name in self.unsigned else 0
             o.x, o.n, o.q_x = B._ptr(z, torch.int8), z.numel(), self.q[name]
             out_slots.append((2, add(post, o), name, 0))
@@ -851,7 +851,7 @@ class Engine:
         the batch is large enough for that to pay; ``serial`` issues the launches of every
         part one pipeline after the other on the caller's stream."""
         for name, out in (dequant or {}).items():
-            if out is not None and out.numel() < self.act[name].numel():
+            if out is not None and out.numel() < self.act[name][:self.N].numel():
                 raise ValueError(f"run_step: the buffer of {name} is shorter than the tensor")
         if not serial and self._plannable(x, dequant or {}):
             self._run_planned(x, dequant or {})

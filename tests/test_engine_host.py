@@ -140,3 +140,16 @@ def test_planned_step_refuses_what_the_layer_calls_refuse(recorded):
         eng.act[out] = other
         with pytest.raises(AssertionError):
             step()
+
+
+def test_planned_step_takes_buffers_longer_than_the_batch(recorded):
+    net = wl.bottleneck_block()
+    out = net.outputs[0]
+    eng, step = recorded(net, 2)
+    n = eng.act[out].numel()
+    eng.act[out] = torch.cat([eng.act[out]] * 2)
+    r = torch.empty(eng.act[out][:2].shape)
+    deq = [o for o in step(None, {out: r}) if o.kind == B.OP_DEQUANTIZE]
+    assert [o.n for o in deq] == [n] * len(deq)
+    with pytest.raises(ValueError):
+        step(None, {out: r[:1]})
