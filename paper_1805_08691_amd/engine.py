@@ -620,7 +620,7 @@ class Engine:
         o.kind, o.d = B.OP_CONV, self.conv_desc(op, n)
         o.x, o.y = self._codes(op.src, lo, n), self._codes(op.dst, lo, n)
         o.w, o.bias = B._ptr(packed, torch.int8), B._ptr(bias, torch.int32)
-        o.q_x, o.q_out = self.q[op.src], self.q[op.dst]
+        o.q_x, o.q_out = self.q[op.src], 1.0 if op.dst in self.real else self.q[op.dst]
         o.q_w = 1.0 if self.per_channel else self.qw[op.name]
         if op.res:
             o.residual, o.q_res = self._codes(op.res, lo, n), self.q[op.res]

@@ -153,3 +153,13 @@ def test_planned_step_takes_buffers_longer_than_the_batch(recorded):
     assert [o.n for o in deq] == [n] * len(deq)
     with pytest.raises(ValueError):
         step(None, {out: r[:1]})
+
+
+def test_planned_step_needs_no_factor_of_a_real_valued_output(recorded):
+    net = wl.bottleneck_block()
+    out = net.outputs[0]
+    eng, step = recorded(net, 2, real_outputs=True)
+    assert eng.real == {out}
+    del eng.q[out]
+    o = step()[-1]
+    assert o.flags == B.OPF_REAL and o.y_f32
