@@ -702,7 +702,7 @@ class Engine:
             us.append(B.conv_estimate_us(self.conv_desc(op, n)) if op.kind == "conv" else 3.0)
             work = n * d.H * d.W * (op.K if op.kind == "conv" else d.C)
             share.append(min(1.0, work / 65536.0))     # tiles of 16 x 16 against 256 CUs
-        depth = max(early) + 1
+        depth = max(early, default=-1) + 1
         members = [[] for _ in range(depth)]
         cost = lambda m: (max([us[i] for i in m] + [2.7 + sum((us[i] - 2.7) * share[i] for i in m)])
                           if m else 0.0)

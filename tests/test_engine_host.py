@@ -163,3 +163,12 @@ def test_planned_step_needs_no_factor_of_a_real_valued_output(recorded):
     del eng.q[out]
     o = step()[-1]
     assert o.flags == B.OPF_REAL and o.y_f32
+
+
+def test_step_without_layers(recorded):
+    net = wl.Network("nothing", "x")
+    net.tensor("x", 5, 7, 16)
+    net.outputs = ["x"]
+    eng, step = recorded(net, 2)
+    ops = step(torch.zeros((2, 5, 7, 16)), {"x": torch.zeros((2, 5, 7, 16))})
+    assert [o.kind for o in ops] == [B.OP_QUANTIZE, B.OP_DEQUANTIZE]
