@@ -591,7 +591,7 @@ int conv_fill_op(const q8_op* o, ConvParams& p, bool* empty) {
     y = nullptr;
   }
   if (f & Q8_OPF_DEQUANT) {
-    Q8_REQUIRE(o->y_f32 != nullptr, Q8_EINVAL);
+    Q8_REQUIRE(o->y_f32 != nullptr || o->d.N == 0, Q8_EINVAL);
     u.y_deq = o->y_f32;
   }
   return conv_fill(&o->d, u, static_cast<const int8_t*>(o->x), o->w,

@@ -288,3 +288,16 @@ def test_chain_plan_splits_the_batch_over_eight_queues():
         per_image = [i // w if w else 0 for i, w in zip(n_items, want)]
         assert [bool(i) for i in n_items] == [bool(w) for w in want]
         assert len({p for p, w in zip(per_image, want) if w == want[0]}) == 1
+
+
+def test_run_ops_takes_empty_batches_as_the_single_calls_do():
+    d = B.ConvDesc(0, 9, 9, 64, 64, 1, 1)
+    fake, L = C.c_void_p(0x1000), B.lib
+    assert L.q8_conv_int8_dequantized(C.byref(d), None, fake, None, 0.5, 0.5, 0.5, None, 0.0, None, None, None) == 0
+    ops = (B.Op * 1)()
+    o = ops[0]
+    o.kind, o.flags, o.d, o.w, o.q_x, o.q_w, o.q_out = B.OP_CONV, B.OPF_DEQUANT, d, 0x1000, 0.5, 0.5, 0.5
+    streams = (C.c_void_p * 1)(None)
+    assert L.q8_run_ops(ops, 1, streams, 1) == 0
+    o.d.N = 1                                  # not empty: the output is needed
+    assert L.q8_run_ops(ops, 1, streams, 1) == -1
