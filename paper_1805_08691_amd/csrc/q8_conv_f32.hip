@@ -129,10 +129,17 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
         // behind the end of a filter stands the next one, whose values must not meet this one's
         // sums, not even times zero (an infinity there)
         const int left = MODE == 2 ? 4 : p.rsc - (st * NC + c) * 16 - quarter * 4;
-        af[BUF][c][i] = __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                     rsrc_w, ((st < n_st) & (left > 0) ? a_off[i] : kOob) + c * 64, st * NC * 64, 0));
-        if constexpr (MODE == 0) {
+        const bool in = (st < n_st) & (left > 0);
+        if constexpr (MODE != 0) {
+          af[BUF][c][i] = __builtin_bit_cast(
+              v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, (in ? a_off[i] : kOob) + c * 64,
+                                                         st * NC * 64, 0));
+        } else {
+          // the 16 bytes may end behind the last filter: the whole offset in the vector operand,
+          // which is what the range check compares with the descriptor's size, dword by dword
+          af[BUF][c][i] = __builtin_bit_cast(
+              v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                       rsrc_w, in ? a_off[i] + (st * NC + c) * 64 : kOob, 0, 0));
 #pragma unroll
           for (int e = 1; e < 4; ++e) af[BUF][c][i][e] = e < left ? af[BUF][c][i][e] : 0.0f;
         }

@@ -1554,6 +1554,22 @@ def test_conv_f32_tiles(B, geom, res, slice_):
         assert np.array_equal(host(ref), got)                 # the same sums without the maxima
 
 
+@pytest.mark.parametrize("C, R, K", [(1, 1, 1), (3, 1, 1), (7, 1, 2), (5, 3, 33), (3, 7, 64)])
+def test_conv_f32_filters_end_their_tensor(B, C, R, K):
+    """The filters are the last values of their allocation and their reduction ends inside a 16-byte
+    chunk: the same sums as with zeros behind them."""
+    rng = np.random.default_rng(C)
+    n = K * R * R * C
+    size = -(-n // 128) * 128                 # (allocations are multiples of 512 bytes)
+    d = B.ConvDesc(N=1, H=5, W=9, C=C, K=K, R=R, S=R, pad_h=R // 2, pad_w=R // 2)
+    x = dev(rng.standard_normal((1, 5, 9, C)).astype(np.float32))
+    last = torch.from_numpy(rng.standard_normal(size).astype(np.float32)).cuda()[size - n:]
+    padded = torch.zeros(n + 64, device="cuda")
+    padded[:n] = last
+    got = [host(B.conv_f32_ref(d, x, w.view(K, R, R, C))) for w in (last, padded[:n])]
+    assert np.array_equal(got[0], got[1]) and np.isfinite(got[0]).all() and got[0].any()
+
+
 @pytest.mark.parametrize("C, R, K", [(3, 7, 8), (20, 1, 50), (5, 1, 33), (24, 3, 40)])
 def test_conv_f32_keeps_filters_apart(B, C, R, K):
     """An infinity in one filter stays in its own channel, where the reduction ends inside a stage."""
