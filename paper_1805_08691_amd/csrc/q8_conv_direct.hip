@@ -3,8 +3,17 @@
 
 namespace q8 {
 
-// The residual codes are read as words through a descriptor.
+namespace {
+// Bytes of the start values: the bias, or the table with a row per rectangle of taps.
+long start_bytes(const ConvParams& p) {
+  const long rows = p.tap_sums ? (long)(p.R + 1) * (p.R + 1) * (p.S + 1) * (p.S + 1) : p.bias ? 1 : 0;
+  return rows * p.K * 4;
+}
+}  // namespace
+
+// The start values and the residual codes (as words) are read through descriptors.
 bool direct_applicable(const ConvParams& p) {
+  if (start_bytes(p) > 0x7fffffffL) return false;
   return !p.res || (p.res_bytes > 0 && p.res_cs % 4 == 0 && p.res_off % 4 == 0 && q8_aligned(p.res, 4));
 }
 
@@ -25,7 +34,7 @@ DirectParams direct_params(const ConvParams& p) {
   d.vec4 = p.vec4; d.f32_vec4 = p.f32_vec4; d.in_u8 = p.in_u8; d.out_u8 = p.out_u8; d.res_u8 = p.res_u8;
   d.tap_sums = p.tap_sums; d.m_vec = p.m_vec; d.y_f32 = p.y_f32; d.y_deq = p.y_deq; d.q_deq = p.q_deq;
   d.acc_dump = p.acc_dump;
-  d.start_bytes = (p.tap_sums ? (p.R + 1) * (p.R + 1) * (p.S + 1) * (p.S + 1) : p.bias ? 1 : 0) * p.K * 4;
+  d.start_bytes = (int)start_bytes(p);
   d.res_bytes = p.res ? p.res_bytes : 0;
   d.mode = p.C % 64 != 0 ? 0 : p.R * p.S == 1 && (p.pad_h | p.pad_w) == 0 ? 2 : 1;
   return d;

@@ -1607,6 +1607,25 @@ def test_conv_latency_family(B, idx):
                        seed=31 * v + idx, variant=v)
 
 
+def test_unsigned_codes_with_a_start_table_beyond_4_gib(B):
+    """A layer the latency family would take, whose table of start values (a row per rectangle of
+    taps) a 32-bit offset cannot reach into."""
+    d = B.ConvDesc(1, 5, 6, 16, 620000, 5, 6, pad_w=1, relu=1)
+    assert (6 * 6 * 7 * 7) * d.K * 4 > 2**32 and "direct" in B.conv_variant(d)
+    rng = np.random.default_rng(4)
+    w = torch.from_numpy(rng.integers(-128, 128, d.K * 480).astype(np.int8)).cuda().view(d.K, 5, 6, 16)
+    b = dev(rng.integers(-20000, 20000, d.K).astype(np.int32))
+    x = rng.integers(0, 256, (1, 5, 6, 16)).astype(np.uint8)
+    taps, bias = B.u8_prepare(d, w, b)
+    scale = float(np.float32(1e-4))
+    got = B.conv_u8(d, 1, 1, 0, dev(_stored(x)), B.pack_weights(d, w), bias, taps, 1.0, scale, 1.0)
+    frame = torch.zeros((5, 8, 16), device="cuda")
+    frame[:, 1:7] = dev(x)[0].float()
+    for wo in range(3):                  # sums below 2^24: exact in fp32 in any order
+        acc = (w.float() * frame[:, wo:wo + 6]).sum((1, 2, 3)) + b
+        assert torch.equal(got[0, 0, wo].int() + 128, (acc * scale).round().clamp(0, 255).int())
+
+
 def test_run_ops_groups_equal_single_calls(B):
     """Independent layers of one group (joined into one launch) and a list of tensors to dequantise
     give the bits of the calls one by one."""
