@@ -292,17 +292,28 @@ class Engine:
             if op.kind == "conv" and op.res is not None:
                 last_use[op.res] = i
         last_write = {op.dst: i for i, op in enumerate(net.ops)}
-        pooled = {op.dst for op in net.ops if op.kind == "pool"
-                  and net.tensors[op.dst].C != net.tensors[op.src].C}
+        # tensors of slices that are measured once complete: a pooling takes no maximum, and of
+        # slices that are written over only the last values count
+        slices, late = {}, set()
+        for op in net.ops:
+            width = op.K if op.kind == "conv" else net.tensors[op.src].C
+            if net.tensors[op.dst].C != width:
+                lo, hi = op.dst_c_off, op.dst_c_off + width
+                if op.kind == "pool" or any(a < hi and lo < b for a, b in slices.get(op.dst, ())):
+                    late.add(op.dst)
+                slices.setdefault(op.dst, []).append((lo, hi))
         for i, op in enumerate(net.ops):
             d = net.tensors[op.dst]
             width = op.K if op.kind == "conv" else net.tensors[op.src].C
+            observed = slot[op.dst]
             if d.C == width:        # written whole
                 out = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
             else:                   # a slice: the channels that no op writes are zeros
                 out = t.get(op.dst)
                 if out is None:
                     out = torch.zeros((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
+                if op.dst in late:
+                    observed = None
             if op.kind == "pool":
                 B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H, d.W, out=out,
                            out_c_off=op.dst_c_off)
@@ -312,12 +323,12 @@ class Engine:
                 desc.in_c_stride = desc.res_c_stride = 0
                 desc.out_c_stride = d.C
                 B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
-                                    slot[op.name + ":branch"] if op.res else None, slot[op.dst])
-            if op.dst in pooled and last_write[op.dst] == i:
+                                    slot[op.name + ":branch"] if op.res else None, observed)
+            if op.dst in late and last_write[op.dst] == i:
                 B.calibrate_maxabs(out, slot[op.dst])
             t[op.dst] = out
             for name in {op.src, getattr(op, "res", None)}:
-                if name is not None and last_use.get(name) == i:
+                if name is not None and last_use.get(name) == i and last_write.get(name, i) <= i:
                     del t[name]
 
     def calibrate(self, batches):

@@ -1511,6 +1511,34 @@ def test_gpu_calibration_of_partly_written_tensors(B):
         assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
 
 
+@pytest.mark.parametrize("scale", [100.0, 0.01])
+def test_gpu_calibration_of_slices_written_over(B, scale):
+    """Of a tensor's slices that one layer writes, another reads and a third writes over, the final
+    values are measured, those of a pooling among them, also where nothing reads them."""
+    from paper_1805_08691_amd.engine import Engine
+    net = wl.Network("written_over", "x")
+    net.tensor("x", 9, 11, 16)
+    net.tensor("cat", 9, 11, 48)
+    wl._conv(net, "a", "x", 24, 1, 1, dst="cat", dst_c_off=0)
+    wl._pool(net, "p", "x", 3, 1, 1, dst="cat", dst_c_off=24)
+    net.outputs = [wl._conv(net, "c", "cat", 32, 3, 3, relu=False), "cat"]
+    wl._conv(net, "e", "x", 20, 1, 1, dst="cat", dst_c_off=4)
+    params = {op.name: wl.conv_params(2, i, op) for i, op in enumerate(net.convs())}
+    for k in ("W", "b", "beta", "mu"):             # (channels 4 and up are written over by e)
+        params["a"][k][4 if scale > 1 else 0:] *= np.float32(scale)
+        params["e"][k] *= np.float32(0.01)
+    rng = np.random.default_rng(3)
+    xs = [rng.standard_normal((4, 9, 11, 16)).astype(np.float32) for _ in range(2)]
+    q_o = onet.calibrate(net, onet.fold_all(net, params), xs)
+    eng = Engine(net, 4)
+    eng.load_params(params)
+    eng.fold()
+    q_g = eng.calibrate([dev(x) for x in xs])
+    assert set(q_g) == set(q_o)
+    for k in q_o:
+        assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
+
+
 # the fp32 forward of calibration: every tile build (128 x 128, 64 x 64 and 32 x 32 shared by four
 # wavefront groups), every chunk mode (C % 32, C % 16, C % 4, other), tails in pixels, channels
 # and reduction, stride, dilation, a channel slice
