@@ -235,55 +235,16 @@ class Engine:
                                              p["var"], p["eps"])
 
     def forward_f32(self, x, observe=None):
-        """fp32 forward of the folded network; ``observe(key, tensor)`` sees every activation."""
-        t = {self.net.input: x}
-        N = x.shape[0]
-        for op in self.net.ops:
-            d = self.net.tensors[op.dst]
-            if op.kind == "pool":
-                if d.C == self.net.tensors[op.src].C:
-                    t[op.dst] = B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H,
-                                           d.W)
-                else:
-                    if op.dst not in t:
-                        t[op.dst] = torch.zeros((N, d.H, d.W, d.C), dtype=torch.float32,
-                                                device=self.dev)
-                    B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H, d.W,
-                               out=t[op.dst], out_c_off=op.dst_c_off)
-            else:
-                Wf, bf = self.folded[op.name]
-                desc = self._desc(op, N, framed=False)
-                desc.in_c_stride = desc.out_c_stride = desc.res_c_stride = 0
-                if op.res is not None and observe:
-                    desc.relu = 0                  # the branch's own output, before the sum
-                    observe(op.name + ":branch", B.conv_f32_ref(desc, t[op.src], Wf, bf))
-                desc.relu = int(op.relu)
-                y = B.conv_f32_ref(desc, t[op.src], Wf, bf, t[op.res] if op.res else None)
-                if d.C == op.K:
-                    t[op.dst] = y
-                else:
-                    if op.dst not in t:
-                        t[op.dst] = torch.zeros((N, d.H, d.W, d.C), dtype=torch.float32,
-                                                device=self.dev)
-                    t[op.dst][..., op.dst_c_off:op.dst_c_off + op.K] = y
-            width = op.K if op.kind == "conv" else self.net.tensors[op.src].C
-            if observe and d.C == width:
-                observe(op.dst, t[op.dst])
-        if observe:
-            seen = set()
-            for op in self.net.ops:             # concat targets: observe once complete
-                d = self.net.tensors[op.dst]
-                width = op.K if op.kind == "conv" else self.net.tensors[op.src].C
-                if d.C != width and op.dst not in seen:
-                    seen.add(op.dst)
-                    observe(op.dst, t[op.dst])
-        return t
+        """fp32 forward of the folded network: its tensors by name.  ``observe(key, tensor)`` sees
+        every activation (tensors written in slices once they are complete) and every value in
+        front of a fused sum."""
+        return self._forward_f32(x, None, observe)
 
-    def _observed_forward(self, x, slot):
-        """fp32 forward of the folded network that leaves the running max-abs of every tensor in
-        ``slot`` (one-element device tensors by key).  A convolution takes the maxima of its own
-        output and of its value before a fused sum while it holds them; a stand-alone pooling
-        keeps its input's factor and is not measured."""
+    def _forward_f32(self, x, slot, observe=None):
+        """The fp32 forward.  With ``slot`` (one-element device tensors by key) it leaves the running
+        max-abs of every tensor there and keeps no tensor longer than it is read: a convolution
+        takes the maxima of its own output and of its value before a fused sum while it holds
+        them; a stand-alone pooling keeps its input's factor and is not measured."""
         net, N = self.net, x.shape[0]
         t = {net.input: x}
         last_use = {}
@@ -305,7 +266,7 @@ class Engine:
         for i, op in enumerate(net.ops):
             d = net.tensors[op.dst]
             width = op.K if op.kind == "conv" else net.tensors[op.src].C
-            observed = slot[op.dst]
+            observed = slot[op.dst] if slot else None
             if d.C == width:        # written whole
                 out = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
             else:                   # a slice: the channels that no op writes are zeros
@@ -322,14 +283,25 @@ class Engine:
                 desc = self._desc(op, N, framed=False)
                 desc.in_c_stride = desc.res_c_stride = 0
                 desc.out_c_stride = d.C
+                branch = op.name + ":branch"       # the value before the sum
+                if op.res and observe:
+                    desc.relu = 0
+                    observe(branch, B.conv_f32_ref(desc, t[op.src], Wf, bf))
+                    desc.relu = int(op.relu)
                 B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
-                                    slot[op.name + ":branch"] if op.res else None, observed)
-            if op.dst in late and last_write[op.dst] == i:
+                                    slot[branch] if op.res and slot else None, observed)
+            if slot and op.dst in late and last_write[op.dst] == i:
                 B.calibrate_maxabs(out, slot[op.dst])
             t[op.dst] = out
+            if observe and d.C == width:
+                observe(op.dst, out)
             for name in {op.src, getattr(op, "res", None)}:
-                if name is not None and last_use.get(name) == i and last_write.get(name, i) <= i:
+                if slot and name is not None and last_use.get(name) == i and last_write.get(name, i) <= i:
                     del t[name]
+        if observe:
+            for name in slices:
+                observe(name, t[name])
+        return t
 
     def calibrate(self, batches):
         """Running max-abs over fp32 forwards of ``batches`` (device fp32 NHWC tensors, at least
@@ -345,7 +317,7 @@ class Engine:
         n_batches = 0
         for x in batches:
             B.calibrate_maxabs(x.contiguous(), slot[self.net.input])
-            self._observed_forward(x.contiguous(), slot)
+            self._forward_f32(x.contiguous(), slot)
             n_batches += 1
         if not n_batches:
             raise ValueError("calibrate: no batches")     # every factor would be 1

@@ -1539,15 +1539,62 @@ def test_gpu_calibration_of_slices_written_over(B, scale):
         assert abs(q_g[k] - float(q_o[k])) <= 1e-5 * float(q_o[k]), k
 
 
-# the fp32 forward of calibration: every tile build (128 x 128, 64 x 64 and 32 x 32 shared by four
-# wavefront groups), every chunk mode (C % 32, C % 16, C % 4, other), tails in pixels, channels
-# and reduction, stride, dilation, a channel slice
-@pytest.mark.parametrize("geom,res,slice_", [
-    ((1, 5, 7, 3, 20, 3, 3, 1, 1), False, (0, 0)), ((2, 17, 15, 7, 33, 5, 5, 2, 1), True, (0, 0)),
-    ((1, 7, 7, 12, 64, 1, 1, 1, 1), True, (0, 0)), ((3, 9, 11, 20, 70, 3, 3, 1, 2), False, (90, 12)),
-    ((1, 1, 1, 2048, 50, 1, 1, 1, 1), False, (0, 0)), ((2, 28, 28, 48, 192, 3, 3, 1, 1), True, (0, 0)),
-    ((4, 57, 55, 32, 65, 3, 3, 2, 1), True, (0, 0)), ((8, 64, 66, 16, 130, 1, 7, 1, 1), False, (133, 1))])
-def test_conv_f32_tiles(B, geom, res, slice_):
+@pytest.mark.parametrize("make", [wl.bottleneck_block, _padded_concat_net])
+def test_gpu_forward_f32_shows_what_calibration_measures(B, make):
+    from paper_1805_08691_amd.engine import Engine
+    net = make()
+    t_in = net.tensors[net.input]
+    eng = Engine(net, 2, own_sum_factor=True)
+    eng.load_params({op.name: wl.conv_params(2, i, op) for i, op in enumerate(net.convs())})
+    eng.fold()
+    x = np.random.default_rng(3).standard_normal((2, t_in.H, t_in.W, t_in.C)).astype(np.float32)
+    seen = {}
+    t = eng.forward_f32(dev(x), lambda key, v: seen.update({key: v}))
+    assert set(t) == set(net.tensors)
+    q = eng.calibrate([dev(x)])
+    assert set(seen) == set(q) - {net.input}
+    for key, v in seen.items():
+        assert q[key] == B.qfactor(float(v.abs().max()), 7), key
+        assert key not in t or t[key] is v
+    want, branches = onet.forward_f32(net, {k: (host(w), host(b)) for k, (w, b) in eng.folded.items()}, x)
+    for key, v in {**want, **{k + ":branch": v for k, v in branches.items()}}.items():
+        got = host(seen.get(key, t.get(key)))
+        # three layers of at most 576 products and sums each in another order: 3 * 578 * 2^-24 of what
+        # is summed
+        assert np.abs(got - v).max() <= 1.1e-4 * np.abs(v).max(), key
+
+
+# the fp32 forward of calibration: every tile build (256 x 64, 128 x 128, 64 x 64 and 32 x 32 shared by
+# four wavefront groups) in every chunk mode (a stage in one tap, 16 bytes in one tap, single values),
+# tails in pixels, channels and reduction, stride, dilation, a channel slice, residuals that are read
+# as vectors and one by one
+F32_256, F32_128, F32_64, F32_32 = "4,1,4,4,1,1,3", "2,2,4,4,1,1,3", "1,1,4,4,4,1,3", "1,1,2,2,4,2,3"
+
+
+@pytest.mark.parametrize("build,geom,res,slice_", [
+    (F32_32 + ",0", (1, 5, 7, 3, 20, 3, 3, 1, 1), False, (0, 0)),
+    (F32_32 + ",0", (2, 17, 15, 7, 33, 5, 5, 2, 1), True, (0, 0)),
+    (F32_32 + ",1", (1, 7, 7, 12, 64, 1, 1, 1, 1), True, (0, 0)),
+    (F32_32 + ",1", (3, 9, 11, 20, 70, 3, 3, 1, 2), False, (90, 12)),
+    (F32_32 + ",2", (1, 1, 1, 2048, 50, 1, 1, 1, 1), False, (0, 0)),
+    (F32_32 + ",1", (2, 28, 28, 48, 192, 3, 3, 1, 1), True, (0, 0)),
+    (F32_32 + ",2", (4, 57, 55, 32, 65, 3, 3, 2, 1), True, (0, 0)),
+    (F32_128 + ",2", (8, 64, 66, 16, 130, 1, 7, 1, 1), False, (133, 1)),
+    (F32_128 + ",0", (5, 57, 59, 7, 132, 3, 3, 1, 1), True, (0, 0)),
+    (F32_128 + ",1", (5, 57, 59, 20, 130, 3, 3, 1, 1), True, (0, 0)),
+    (F32_128 + ",2", (5, 57, 59, 48, 140, 1, 1, 1, 1), True, (0, 0)),
+    (F32_64 + ",0", (5, 57, 59, 7, 40, 3, 3, 1, 2), True, (0, 0)),
+    (F32_64 + ",0", (5, 113, 117, 3, 45, 7, 7, 2, 1), False, (0, 0)),
+    (F32_64 + ",1", (5, 31, 33, 20, 140, 3, 3, 1, 1), True, (0, 0)),
+    (F32_64 + ",1", (5, 57, 59, 12, 33, 1, 3, 1, 1), False, (41, 5)),
+    (F32_64 + ",2", (5, 57, 59, 80, 50, 1, 1, 1, 1), True, (0, 0)),
+    (F32_64 + ",2", (5, 31, 33, 48, 160, 3, 3, 1, 1), False, (0, 0)),
+    (F32_256 + ",0", (3, 149, 151, 3, 50, 3, 3, 1, 1), False, (0, 0)),
+    (F32_256 + ",0", (3, 149, 151, 5, 64, 1, 1, 1, 1), True, (0, 0)),
+    (F32_256 + ",1", (3, 149, 151, 12, 36, 3, 3, 1, 1), True, (0, 0)),
+    (F32_256 + ",2", (3, 149, 151, 16, 33, 3, 3, 1, 1), True, (0, 0)),
+    (F32_256 + ",2", (3, 149, 151, 80, 60, 1, 1, 1, 1), False, (64, 4))])
+def test_conv_f32_tiles(B, build, geom, res, slice_):
     import torch
     N, H, W, Cc, K, R, S, st, dil = geom
     rng = np.random.default_rng(11)
