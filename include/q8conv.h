@@ -451,6 +451,9 @@ int q8_conv_f32_observed(const q8_conv_desc *d, const float *x_dev, const float 
                          const float *b_dev, const float *res_dev, float *y_dev,
                          float *maxabs_sum_dev, float *maxabs_out_dev, void *stream);
 
+/* Name of the kernel build these two take for this geometry, as q8_conv_variant.          */
+const char *q8_conv_f32_variant(const q8_conv_desc *d);
+
 /* int8 max-pool over an R x S window; taps outside the image are ignored.         */
 int q8_maxpool_i8(const int8_t *x_dev, int N, int H, int W, int C, int R, int S,
                   int stride, int pad, int Ho, int Wo, int8_t *y_dev, void *stream);

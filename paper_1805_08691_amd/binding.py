@@ -34,7 +34,7 @@ EXPORTS = [
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8", "q8_run_ops", "q8_conv_estimate_us",
-    "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
+    "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
 
@@ -155,6 +155,8 @@ lib.q8_sum_factor.restype = _f
 lib.q8_sum_factor.argtypes = [_f, _f]
 lib.q8_probe_mfma_i8.argtypes = [_i, _i, _vp, _vp]
 lib.q8_conv_f32_ref.argtypes = [_dp, _vp, _vp, _vp, _vp, _vp, _vp]
+lib.q8_conv_f32_variant.restype = C.c_char_p
+lib.q8_conv_f32_variant.argtypes = [_dp]
 lib.q8_conv_f32_observed.argtypes = [_dp] + [_vp] * 8
 lib.q8_maxpool_i8.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
 lib.q8_maxpool_f32.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
@@ -537,6 +539,10 @@ def conv_f32_ref(desc, x, w, b=None, res=None, out=None):
                                _ptr(b, torch.float32), _ptr(res, torch.float32),
                                _ptr(out, torch.float32), _stream()))
     return out
+
+
+def conv_f32_variant(desc):
+    return lib.q8_conv_f32_variant(C.byref(desc)).decode()
 
 
 def conv_f32_observed(desc, x, w, b, res, out, maxabs_sum, maxabs_out):

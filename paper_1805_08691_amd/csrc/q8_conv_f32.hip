@@ -378,11 +378,59 @@ int launch_f32(F32Params& p, hipStream_t stream) {
   return q8_launch_status();
 }
 
+// The builds of the tiled kernel; MODE follows from the channel count.
+struct F32Build {
+  int (*launch)(F32Params&, hipStream_t);
+  int nc;
+  const char* name[3];
+};
+#define Q8_F32_NAME(WP, WC, TP, TC, KW, NC, NB, MODE) \
+  "conv_f32_mfma_kernel<" #WP "," #WC "," #TP "," #TC "," #KW "," #NC "," #NB "," #MODE ">"
+#define Q8_F32_ROW(WP, WC, TP, TC, KW, NC, NB) \
+  { &launch_f32<WP, WC, TP, TC, KW, NC, NB>, NC, \
+    { Q8_F32_NAME(WP, WC, TP, TC, KW, NC, NB, 0), Q8_F32_NAME(WP, WC, TP, TC, KW, NC, NB, 1), \
+      Q8_F32_NAME(WP, WC, TP, TC, KW, NC, NB, 2) } },
+const F32Build kF32Builds[] = {
+    Q8_F32_ROW(4, 1, 4, 4, 1, 1, 3)   // 0: 256 pixels x 64 channels
+    Q8_F32_ROW(2, 2, 4, 4, 1, 1, 3)   // 1: 128 x 128
+    Q8_F32_ROW(1, 1, 4, 4, 4, 1, 3)   // 2: 64 x 64, its reduction shared by four wavefronts
+    Q8_F32_ROW(1, 1, 2, 2, 4, 2, 3)   // 3: 32 x 32, the same
+};
+#undef Q8_F32_ROW
+#undef Q8_F32_NAME
+
+// The largest tile that still gives every CU one; below that the tile is shared by four
+// groups of wavefronts (their SIMDs), first 64 x 64, then 32 x 32 where those leave CUs idle.
+// (Short reductions shared by two groups of a 128 x 64 tile, or by none of a 64 x 64 tile of four
+// wavefronts, are slower: 128 -> 512 on 28 x 28 x 8 48 and 50 us against 38.)
+// Up to 64 channels and many tiles: no sharing, whose exchange of accumulators then costs more
+// than it hides (7x7 on 224 x 224 x 8, 1568 tiles of 64 x 64: 64 -> 46 us).
+int pick_f32(long M, int K) {
+  auto tiles = [&](long t) { return (M + t - 1) / t * ((K + t - 1) / t); };
+  if (K <= 64 && K > 32 && tiles(64) >= 1024) return 0;
+  if (K > 64 && tiles(128) >= 256) return 1;
+  return K > 32 && tiles(64) >= 192 ? 2 : 3;
+}
+
+bool f32_desc_sane(const q8_conv_desc* d) {
+  return d && d->N >= 0 && d->H >= 1 && d->W >= 1 && d->C >= 1 && d->K >= 1 && d->R >= 1 &&
+         d->S >= 1 && d->stride_h >= 1 && d->stride_w >= 1 && d->pad_h >= 0 &&
+         d->pad_w >= 0 && d->dil_h >= 1 && d->dil_w >= 1;
+}
+
+// Whether the tiled kernel's 32-bit offsets reach everything it addresses.
+bool f32_tiled(const q8_conv_desc* d, long M, long per_img) {
+  const long rsc = (long)d->R * d->S * d->C, img = (long)d->H * d->W * d->C * 4;
+  // what one tile of at most 256 pixels can reach: its images and the padding around them
+  const long reach = (255 / per_img + 2) * img +
+                     ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + (long)d->S * d->dil_w) * d->C * 4;
+  return !(M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || reach > 0x7fffffffL || d->H > (1 << 28) ||
+           (long)d->R * d->dil_h > (1 << 28));
+}
+
 int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float* b, const float* res,
              float* y, int out_cs, int out_off, float* obs_sum, float* obs_out, hipStream_t stream) {
-  Q8_REQUIRE(d && d->N >= 0 && d->H >= 1 && d->W >= 1 && d->C >= 1 && d->K >= 1 && d->R >= 1 &&
-                 d->S >= 1 && d->stride_h >= 1 && d->stride_w >= 1 && d->pad_h >= 0 &&
-                 d->pad_w >= 0 && d->dil_h >= 1 && d->dil_w >= 1, Q8_EINVAL);
+  Q8_REQUIRE(f32_desc_sane(d), Q8_EINVAL);
   F32Params p{};
   p.Ho = q8_conv_out_h(d); p.Wo = q8_conv_out_w(d);
   const long M = (long)d->N * p.Ho * p.Wo;
@@ -397,33 +445,18 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.vec_y = (out_cs % 4 == 0 && out_off % 4 == 0 && q8_aligned(y, 16) &&
              (!res || (d->K % 4 == 0 && q8_aligned(res, 16)))) ? 1 : 0;
   p.vec_b = q8_aligned(b, 16) ? 1 : 0;
-  const long rsc = (long)d->R * d->S * d->C, img = (long)d->H * d->W * d->C * 4;
   const long per_img = (long)p.Ho * p.Wo;
-  // what one tile of at most 256 pixels can reach: its images and the padding around them
-  const long reach = (255 / per_img + 2) * img +
-                     ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + d->S * d->dil_w) * d->C * 4;
-  if (M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || reach > 0x7fffffffL || d->H > (1 << 28) ||
-      (long)d->R * d->dil_h > (1 << 28)) {
+  if (!f32_tiled(d, M, per_img)) {
     const size_t total = (size_t)M * d->K;
     const size_t blocks = (total + kThreads - 1) / kThreads;
     hipLaunchKernelGGL(conv_f32_any_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)),
                        dim3(kThreads), 0, stream, p);
     return q8_launch_status();
   }
-  p.M = (int)M; p.rsc = (int)rsc;
+  p.M = (int)M; p.rsc = d->R * d->S * d->C;
   p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
   p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
-  // The largest tile that still gives every CU one; below that the tile is shared by four
-  // groups of wavefronts (their SIMDs), first 64 x 64, then 32 x 32 where those leave CUs idle.
-  auto tiles = [&](long t) { return (M + t - 1) / t * ((d->K + t - 1) / t); };
-  // (Short reductions shared by two groups of a 128 x 64 tile, or by none of a 64 x 64 tile of four
-  // wavefronts, are slower: 128 -> 512 on 28 x 28 x 8 48 and 50 us against 38.)
-  // Up to 64 channels and many tiles: no sharing, whose exchange of accumulators then costs more
-  // than it hides (7x7 on 224 x 224 x 8, 1568 tiles of 64 x 64: 64 -> 46 us).
-  if (d->K <= 64 && d->K > 32 && tiles(64) >= 1024) return launch_f32<4, 1, 4, 4, 1, 1, 3>(p, stream);
-  if (d->K > 64 && tiles(128) >= 256) return launch_f32<2, 2, 4, 4, 1, 1, 3>(p, stream);
-  if (d->K > 32 && tiles(64) >= 192) return launch_f32<1, 1, 4, 4, 4, 1, 3>(p, stream);
-  return launch_f32<1, 1, 2, 2, 4, 2, 3>(p, stream);
+  return kF32Builds[pick_f32(M, d->K)].launch(p, stream);
 }
 
 }  // namespace
@@ -444,6 +477,14 @@ int q8_conv_f32_observed(const q8_conv_desc* d, const float* x_dev, const float*
   return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev,
                       d && d->out_c_stride ? d->out_c_stride : (d ? d->K : 0), d ? d->out_c_off : 0,
                       maxabs_sum_dev, maxabs_out_dev, (hipStream_t)stream);
+}
+
+const char* q8_conv_f32_variant(const q8_conv_desc* d) {
+  if (!q8::f32_desc_sane(d)) return "unsupported";
+  const long per_img = (long)q8_conv_out_h(d) * q8_conv_out_w(d), M = d->N * per_img;
+  if (M > 0 && !q8::f32_tiled(d, M, per_img)) return "conv_f32_any_kernel";
+  const q8::F32Build& b = q8::kF32Builds[q8::pick_f32(M, d->K)];
+  return b.name[d->C % (16 * b.nc) == 0 ? 2 : d->C % 4 == 0 ? 1 : 0];
 }
 
 }  // extern "C"

@@ -1601,6 +1601,7 @@ def test_conv_f32_tiles(B, build, geom, res, slice_):
     ph, pw = dil * (R - 1) // 2, dil * (S - 1) // 2
     desc = B.ConvDesc(N, H, W, Cc, K, R, S, st, st, ph, pw, dil, dil, relu=1, out_c_stride=slice_[0],
                       out_c_off=slice_[1])
+    assert B.conv_f32_variant(desc) == f"conv_f32_mfma_kernel<{build}>"
     x = rng.standard_normal((N, H, W, Cc)).astype(np.float32)
     w = rng.standard_normal((K, R, S, Cc)).astype(np.float32)
     b = rng.standard_normal(K).astype(np.float32)
@@ -1627,6 +1628,41 @@ def test_conv_f32_tiles(B, build, geom, res, slice_):
     if slice_ == (0, 0):
         ref = B.conv_f32_ref(desc, dev(x), dev(w), dev(b), dev(r) if res else None)
         assert np.array_equal(host(ref), got)                 # the same sums without the maxima
+
+
+# tensors that the tiled builds' 32-bit offsets cannot reach into, by a dilation that leaves one row of
+# taps inside the image, and one as tall as the dilation with all three rows in use
+@pytest.mark.parametrize("H,W,C,K,S,slice_", [(9, 7, 24, 21, 3, (30, 4)), (2**20 + 37, 1, 64, 4, 1, (0, 0))])
+def test_conv_f32_of_any_size(B, H, W, C, K, S, slice_):
+    dil = 2**20
+    d = B.ConvDesc(1, H, W, C, K, 3, S, pad_h=dil, pad_w=S // 2, dil_h=dil, relu=1, out_c_stride=slice_[0],
+                   out_c_off=slice_[1])
+    assert B.conv_f32_variant(d) == "conv_f32_any_kernel" and (d.Ho, d.Wo) == (H, W)
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def rand(*shape):
+        return torch.randn(shape, device="cuda", generator=g)
+    x, w, b, r = rand(1, H, W, C), rand(K, 3, S, C), rand(K), rand(1, H, W, K)
+    out, m = torch.full((1, H, W, slice_[0] or K), -7.0, device="cuda"), torch.zeros(2, device="cuda")
+    B.conv_f32_observed(d, x, w, b, r, out, m[:1], m[1:])
+
+    def fp64(x, w, b):
+        y = torch.zeros((H, W, K), dtype=torch.float64, device="cuda") + b.double()
+        for row in range(3):
+            lo, hi = max(0, (1 - row) * dil), min(H, H - (row - 1) * dil)
+            for s in range(S):
+                w0, w1 = max(0, S // 2 - s), min(W, W - (s - S // 2))
+                if lo < hi:
+                    part = x[0, lo + (row - 1) * dil:hi + (row - 1) * dil, w0 + s - S // 2:w1 + s - S // 2]
+                    y[lo:hi, w0:w1] += part.double() @ w[:, row, s].double().t()
+        return y
+    pre = fp64(x, w, b)
+    bound = (3 * S * C + 4) * 2.0 ** -24 * (fp64(x.abs(), w.abs(), b.abs()) + r[0].abs())
+    lo = slice_[1]
+    got = out[0, :, :, lo:lo + K]
+    assert bool(((got - (pre + r[0]).clamp(min=0)).abs() <= bound).all())
+    assert bool((out[..., :lo] == -7).all()) and bool((out[..., lo + K:] == -7).all())
+    assert float(m[1]) == float(got.max()) and abs(float(m[0]) - float(pre.abs().max())) <= float(bound.max())
 
 
 @pytest.mark.parametrize("C, R, K", [(1, 1, 1), (3, 1, 1), (7, 1, 2), (5, 3, 33), (3, 7, 64)])
