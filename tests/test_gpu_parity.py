@@ -588,6 +588,47 @@ def test_quantize_dequantize_u8(B):
     assert np.array_equal(back, orc.D_u8(want, q))
 
 
+@pytest.mark.parametrize("q", [0.0371, 1.0, 3.3e-5, 1e-37])   # (of the last no reciprocal is taken)
+@pytest.mark.parametrize("unsigned", [True, False])
+def test_quantize_alignments_and_ties(B, q, unsigned):
+    """Eq. Q where the vector body does not start at the first value, does not fit both buffers or
+    is empty, on values on and within three ulps of every tie, and outside the code range."""
+    q = np.float32(q)
+    call = B.quantize_u8 if unsigned else lambda r, q, out: B.quantize(r, q, 7, out)
+    ties = ((np.arange(-131, 260) + 0.5) * np.float64(q)).astype(np.float32)
+    vals = [ties]
+    for direction in (np.float32(-np.inf), np.float32(np.inf)):
+        v = ties
+        for _ in range(3):
+            v = np.nextafter(v, direction, dtype=np.float32)
+            vals.append(v)
+    vals = np.concatenate(vals + [np.array([0, np.inf, -np.inf, 1e30, -1e30], np.float32)])
+    want = _stored(orc.Q_u8(np.maximum(vals, 0), q)) if unsigned else orc.Q(vals, q, 7)
+    n_max = vals.size
+    r_buf, z_buf = torch.zeros(n_max + 4, device="cuda"), torch.empty(n_max + 8, dtype=torch.int8, device="cuda")
+    for r_off in range(4):
+        r_buf[r_off:r_off + n_max] = dev(vals)
+        for z_off in range(4):
+            for n in (*range(1, 34), 64, n_max):
+                z_buf.fill_(55)
+                call(r_buf[r_off:r_off + n], float(q), z_buf[z_off:z_off + n])
+                got = host(z_buf)
+                assert np.array_equal(got[z_off:z_off + n], want[:n]), (r_off, z_off, n)
+                assert np.all(got[:z_off] == 55) and np.all(got[z_off + n:] == 55)
+
+
+@pytest.mark.parametrize("z_off, r_off", [(0, 0), (4, 0), (1, 0), (0, 1), (3, 2)])
+def test_dequantize_u8_alignments(B, z_off, r_off):
+    z = np.random.default_rng(2).integers(-128, 128, 9000 + z_off).astype(np.int8)
+    zd, r = dev(z), torch.empty(9000 + r_off, device="cuda")
+    for n in (1, 2, 3, 4, 5, 63, 4095, 4096, 4097, 9000):
+        r.fill_(-7)
+        B.dequantize_u8(zd[z_off:z_off + n], 0.0123, r[r_off:r_off + n])
+        want = orc.D_u8((z[z_off:z_off + n].astype(np.int16) + 128).astype(np.uint8), np.float32(0.0123))
+        got = host(r)
+        assert np.array_equal(got[r_off:r_off + n], want) and np.all(got[r_off + n:] == -7)
+
+
 U8_CASES = [
     # geometry, in_u8, out_u8, res ("u8", "s8" or None), relu
     (dict(N=2, H=14, W=14, C=64, K=160, R=3, S=3, pad_h=1, pad_w=1), 1, 1, "u8", 1),
@@ -1090,9 +1131,13 @@ def test_run_step_one_and_two_pipelines_and_serial(B):
     net, params, x, folded, q, qparams, z_in, acts, accs = _oracle_pipeline(cfg_id, batch, True)
     o = net.outputs[0]
     want = orc.D(acts[o], q[o])
-    for n_streams, serial, fuse_deq in ((1, False, False), (2, False, False), (2, True, False),
-                                        (3, False, False), (2, False, True), (1, False, True)):
+    # (left to itself a step this short runs as one pipeline)
+    for n_streams, forced, serial, fuse_deq in (
+            (1, False, False, False), (2, False, False, False), (2, True, False, False), (2, True, True, False),
+            (3, True, False, False), (2, True, False, True), (3, True, False, True), (1, False, False, True)):
         eng = Engine(net, batch, n_streams=n_streams, fuse_dequant=fuse_deq)
+        if forced:
+            eng._pipelines_pay = lambda ops: True
         eng.load_params(params)
         eng.fold()
         eng.set_factors(q)
@@ -1102,6 +1147,7 @@ def test_run_step_one_and_two_pipelines_and_serial(B):
             assert eng.parts == [(0, 4), (4, 3)]
         if n_streams == 3:
             assert eng.parts == [(0, 3), (3, 2), (5, 2)]
+        assert eng._plan(True, (o,))[3] == (n_streams if forced else 1)
         out = torch.full(eng.act[o].shape, -1.0, dtype=torch.float32, device="cuda")
         eng.run_step(dev(x), {o: out}, serial=serial)
         torch.cuda.synchronize()
@@ -1788,6 +1834,15 @@ def _run_ops(B, ops):
     return rc
 
 
+def test_run_ops_dequantises_a_long_list(B):
+    """More tensors than one launch takes, unaligned and empty ones among them."""
+    lengths = [4096 * (i % 3) + 5 * i for i in range(40)]
+    ops, zs, outs, factors = _dequantize_ops(B, 40, lengths, offset_of=(3, 17, 39))
+    assert lengths[0] == 0 and _run_ops(B, ops) == 0
+    for i in range(40):
+        assert torch.equal(outs[i], factors[i] * (zs[i].float() + 128 * (i % 3 == 1))), i
+
+
 def test_run_ops_dequantises_what_stands_in_front_of_a_refused_op(B):
     lengths = [5000, 64, 1, 300, 77]
     ops, zs, outs, factors = _dequantize_ops(B, 5, lengths)
@@ -1825,27 +1880,41 @@ def test_run_ops_group_with_a_refused_op(B, refused):
         assert torch.equal(out, (pool if i % 2 else conv) if ran else torch.full_like(out, 55)), i
 
 
-# one layer per tiled family with a build for unsigned codes and per-channel scales: 3x3 tiles of
-# each split, the persistent 3x3 and 1x1 kernels, the ring of K = 128 rows, the image rows; channel counts that
-# end inside a tile and images that end inside one
+# one layer per tiled build for unsigned codes and per-channel scales: 3x3 tiles of each split, the
+# persistent 3x3 and 1x1 kernels (the latter also with a residual), the rings of K = 128 rows and of
+# eight wavefronts on 256 pixels, the image rows at both vertical strides; channel counts that end inside
+# a tile and images that end inside one
 EXT_CASES = [
-    dict(N=16, H=28, W=28, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1), dict(N=5, H=29, W=23, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
-    dict(N=8, H=28, W=28, C=128, K=192, R=3, S=3, pad_h=1, pad_w=1), dict(N=8, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
-    dict(N=2, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1), dict(N=16, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1),
-    dict(N=16, H=55, W=57, C=128, K=144, R=3, S=3, pad_h=1, pad_w=1), dict(N=12, H=55, W=57, C=64, K=64, R=3, S=3, pad_h=1, pad_w=1),
-    dict(N=24, H=55, W=57, C=64, K=64, R=1, S=1), dict(N=24, H=37, W=35, C=128, K=128, R=1, S=1, stride_h=2, stride_w=2),
-    dict(N=16, H=37, W=35, C=512, K=80, R=1, S=1), dict(N=8, H=117, W=117, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)]
+    ("halo3_kernel<2,2,1,1,2,1,9>", dict(N=16, H=28, W=28, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,1,1,2,2,9>", dict(N=5, H=29, W=23, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,1,2,2,2>", dict(N=8, H=28, W=28, C=128, K=192, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,2,1,4>", dict(N=8, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,2,1,8>", dict(N=2, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,2,2,4>", dict(N=16, H=55, W=57, C=128, K=80, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<4,2,2,2,4>", dict(N=16, H=55, W=57, C=128, K=144, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<4,2,2,2,8>", dict(N=4, H=89, W=131, C=128, K=144, R=3, S=3, pad_h=1, pad_w=1)),
+    ("p3b_kernel", dict(N=12, H=55, W=57, C=64, K=64, R=3, S=3, pad_h=1, pad_w=1)),
+    ("pw_kernel<1,1>", dict(N=24, H=55, W=57, C=64, K=64, R=1, S=1)),
+    ("pw_kernel<1,1> + residual", dict(N=24, H=55, W=57, C=64, K=80, R=1, S=1)),
+    ("ring_kernel<2,2,1,1,128,4>", dict(N=24, H=37, W=35, C=128, K=128, R=1, S=1, stride_h=2, stride_w=2)),
+    ("ring_kernel<2,4,2,1,64,4>", dict(N=16, H=37, W=35, C=512, K=80, R=1, S=1)),
+    ("ring_kernel<4,2,2,2,64,3>", dict(N=34, H=37, W=35, C=320, K=272, R=1, S=1)),
+    ("ring_kernel<2,2,2,1,64,2>", dict(N=8, H=117, W=117, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)),
+    ("stem_kernel", dict(N=8, H=135, W=137, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)),
+    ("stem_kernel", dict(N=12, H=37, W=97, C=3, K=48, R=5, S=5, in_c_stride=4))]
 
 
 @pytest.mark.parametrize("idx", range(len(EXT_CASES)))
 def test_conv_extended_builds(B, idx):
-    d = B.ConvDesc(relu=1, **EXT_CASES[idx])
+    kernel, geom = EXT_CASES[idx]
+    d = B.ConvDesc(relu=1, **geom)
+    assert B.conv_variant(d) == "conv_i8_" + kernel.split()[0]
     image = d.C == 3
     rng = np.random.default_rng(900 + idx)
     w = rng.integers(-128, 128, (d.K, d.R, d.S, d.C)).astype(np.int8)
     b = rng.integers(-20000, 20000, d.K).astype(np.int32)
     x = rng.integers(0, 128 if image else 256, (d.N, d.H, d.W, d.in_c_stride or d.C)).astype(np.uint8)
-    res = None if idx in (7, 8, 11) else rng.integers(0, 256, (d.N, d.Ho, d.Wo, d.K)).astype(np.uint8)
+    res = None if image or kernel in ("p3b_kernel", "pw_kernel<1,1>") else rng.integers(0, 256, (d.N, d.Ho, d.Wo, d.K)).astype(np.uint8)
 
     def accumulate(codes):            # whole numbers below 2^53: exact in fp64
         acc = torch.nn.functional.conv2d(
