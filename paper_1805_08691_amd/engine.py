@@ -790,11 +790,16 @@ class Engine:
         # factors, switch, filters and buffers are attributes a program may set between steps, and a
         # tensor's storage may be another than it was: the plan holds for the same names, the same
         # objects (whose types and strides were checked) and the addresses that they have now
-        tensors = [t for t in itertools.chain(*self.wq.values(), self.act.values(), self.act_f32.values(),
-                                              self.m_vec.values(), self.taps.values()) if t is not None]
+        tensors = [*itertools.chain.from_iterable(self.wq.values()), *self.act.values(),
+                   *self.act_f32.values(), *self.m_vec.values(), *self.taps.values()]
+        try:
+            addresses = [*map(torch.Tensor.data_ptr, tensors)]
+        except TypeError:                    # a layer without a bias
+            tensors = [t for t in tensors if t is not None]
+            addresses = [t.data_ptr() for t in tensors]
         q_w = () if self.per_channel else self.qw.values()
-        given = (self.fuse_dequant, *self.q, *self.q.values(), *self.wq, *self.act, *self.taps, *self.m_vec, *q_w,
-                 *map(torch.Tensor.data_ptr, tensors))
+        given = (self.fuse_dequant, *self.q, *self.q.values(), *self.wq, *self.act, *self.taps, *self.m_vec,
+                 *q_w, *addresses)
         plan, planned_for, planned_with = self._plans.get(key, (None, None, None))
         if planned_for != given or not all(map(operator.is_, planned_with, tensors)):
             plan = self._plan(*key)
