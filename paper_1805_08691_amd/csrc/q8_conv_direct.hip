@@ -75,8 +75,8 @@ int launch_direct(const ConvParams& p, hipStream_t stream) {
 // us of a launch = base + per_wg * (workgroups beyond 256) / 100
 //                 + per_byte * (operand bytes of one tile / 100 KB) * (tiles the busiest CU gets),
 // fitted to launches behind one another with operands from the last-level cache: the layers of
-// the three benchmark networks at batch 1 to 16 (mean error 0.9 us over 2.7 ... 60 us).  The
-// operand term is 14 bytes per clock and CU, what gathered register loads reach here.
+// the three benchmark networks at batch 1 to 16 (over the 165 of them that the choice gives to this
+// family, 2.4 ... 17 us: mean error 0.5 us, largest 1.8).  The operand term is 14 bytes per clock and CU, what gathered register loads reach here.
 struct DirectVariant {
   const char* name;
   int (*launch)(const ConvParams&, hipStream_t);

@@ -3,9 +3,12 @@
 // A helper around the quantised path, not part of it.
 //
 // What bounds it: on large layers the fp32 matrix rate (122 of the 153 TF a library product of
-// 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at batch 64); on the layers of a calibration batch
-// of eight (200 - 400 tiles) the operand loads, 15 - 20 bytes per clock and CU from L2.  16
-// reduction bytes per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments
+// 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at batch 64).  On the layers of a calibration batch
+// of eight: 3x3 layers (14 x 14 x 256, 392 tiles of 590 KB, 34 us) by the operand loads, 11 bytes
+// per clock and CU; 1x1 layers, of two to eight stages a tile, by the tile's chain of latencies
+// (128 -> 512 on 28 x 28, 784 tiles of 64 KB: 24 us, 3 bytes per clock and CU) and in the first
+// batch by the maxima, whose atomics then come from every wavefront at once (the same layer with
+// its slots at zero: 34 us, with a residual 45).  16 reduction bytes per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments
 // straight into the MFMA's register layout (16 rows x 64 bytes a load), two stages ahead of the
 // one it computes: no LDS and no barrier inside the loop.  ResNet-50 calibration on 8 images:
 // 13.9 -> 1.8 ms, with the max-abs taken here instead of in a pass over every tensor and the value
@@ -402,7 +405,8 @@ const F32Build kF32Builds[] = {
 // The largest tile that still gives every CU one; below that the tile is shared by four
 // groups of wavefronts (their SIMDs), first 64 x 64, then 32 x 32 where those leave CUs idle.
 // (Short reductions shared by two groups of a 128 x 64 tile, or by none of a 64 x 64 tile of four
-// wavefronts, are slower: 128 -> 512 on 28 x 28 x 8 48 and 50 us against 38.)
+// wavefronts, are slower: 128 -> 512 on 28 x 28 x 8 48 and 50 us against 38, the maxima's slots at
+// zero.)
 // Up to 64 channels and many tiles: no sharing, whose exchange of accumulators then costs more
 // than it hides (7x7 on 224 x 224 x 8, 1568 tiles of 64 x 64: 64 -> 46 us).
 int pick_f32(long M, int K) {
