@@ -179,7 +179,10 @@ __device__ __forceinline__ void conv_tile_ring(const ConvParams& p, const int pt
     const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
     a_off[j] = ch < p.K ? ch * p.red_len + lchunk * 16 : kOobOffset;
   }
-  const bool pointwise = p.R * p.S == 1 && p.stride_h * p.stride_w == 1 && (p.pad_h | p.pad_w) == 0;
+  // (a one-row filter over a 4-channel image has one tap too, of overlapping pixels: fewer outputs
+  // a row than pixels)
+  const bool pointwise = p.R * p.S == 1 && p.stride_h * p.stride_w == 1 && (p.pad_h | p.pad_w) == 0 &&
+                         p.Wo == p.W;
   int b_off[B_LOADS];                  // offset of tap (0,0), channel 0 (+ chunk if UNIFORM)
   unsigned b_mask[B_LOADS];            // bit t: tap t of this pixel lies inside the image
 #pragma unroll

@@ -530,6 +530,36 @@ def test_quantize_image_next_to_ties(B, q):
     assert not got[..., 3].any()
 
 
+# (the last two as the kernel that holds whole image rows)
+@pytest.mark.parametrize("N, H, W, K, S, stride", [
+    (2, 28, 36, 128, 7, 1), (3, 9, 11, 40, 4, 1), (1, 5, 33, 70, 13, 1), (2, 9, 20, 64, 1, 1), (2, 9, 21, 64, 5, 2),
+    (2, 6, 9, 16, 2, 1), (8, 70, 76, 64, 7, 1), (8, 131, 139, 48, 7, 2)])
+def test_conv_image_filters_of_one_row(B, N, H, W, K, S, stride):
+    """A 1 x S filter over an unpadded image of three channels, in every precision."""
+    d = B.ConvDesc(N, H, W, 3, K, 1, S, stride, stride, in_c_stride=4, relu=1)
+    rng = np.random.default_rng(S)
+    x = rng.integers(-128, 128, (N, H, W, 4)).astype(np.int8)
+    w, b = rng.integers(-128, 128, (K, 1, S, 3)).astype(np.int8), rng.integers(-20000, 20000, K).astype(np.int32)
+    acc = torch.nn.functional.conv2d(torch.from_numpy(x[..., :3].astype(np.float64)).permute(0, 3, 1, 2),
+                                     torch.from_numpy(w.astype(np.float64)).permute(0, 3, 1, 2),
+                                     torch.from_numpy(b.astype(np.float64)), stride)
+    acc = acc.permute(0, 2, 3, 1).contiguous().numpy().astype(np.int32)
+    scale = np.float32(60.0 / (74.0 * 74.0 * np.sqrt(3 * S)))
+    packed, dump = B.pack_weights(d, dev(w)), torch.zeros(acc.shape, dtype=torch.int32, device="cuda")
+    got = B.conv_int8(d, dev(x), packed, dev(b), 1.0, float(scale), 1.0, acc_dump=dump)
+    want = orc.requant(acc, orc.requant_scale(1.0, scale, 1.0), True)
+    assert np.array_equal(host(dump), acc) and np.array_equal(host(got), want)
+    got = B.conv_int8(d, dev(x), packed, dev(b), 1.0, float(scale), 1.0)
+    assert np.array_equal(host(got), want) and len(np.unique(want)) > 16
+    if K > 32:
+        m = (scale * rng.uniform(0.3, 3.0, K)).astype(np.float32)
+        got = B.conv_int8_per_channel(d, dev(x), packed, dev(b), dev(m), 1.0)
+        assert np.array_equal(host(got), orc.requant_pc(acc, m, True, None, np.float32(0)))
+        got = B.conv_u8(d, 0, 1, 0, dev(x), packed, dev(b), None, 1.0, float(scale), 1.0)
+        assert np.array_equal(host(got), _stored(orc.requant_mixed(
+            acc, orc.requant_scale(1.0, scale, 1.0), True, None, np.float32(0), out_unsigned=True)))
+
+
 @pytest.mark.parametrize("geom", [
     dict(N=2, H=37, W=41, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, pad_h=3, pad_w=3),
     dict(N=1, H=39, W=39, C=3, K=64, R=3, S=3, stride_h=2, stride_w=2),
