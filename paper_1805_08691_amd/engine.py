@@ -253,27 +253,22 @@ class Engine:
             if op.kind == "conv" and op.res is not None:
                 last_use[op.res] = i
         last_write = {op.dst: i for i, op in enumerate(net.ops)}
-        # tensors of slices that are measured once complete: a pooling takes no maximum, and of
-        # slices that are written over only the last values count
-        slices, late = {}, set()
-        for op in net.ops:
-            width = op.K if op.kind == "conv" else net.tensors[op.src].C
-            if net.tensors[op.dst].C != width:
-                lo, hi = op.dst_c_off, op.dst_c_off + width
-                if op.kind == "pool" or any(a < hi and lo < b for a, b in slices.get(op.dst, ())):
-                    late.add(op.dst)
-                slices.setdefault(op.dst, []).append((lo, hi))
+        slices = {}             # tensors written in slices: see _slices
         for i, op in enumerate(net.ops):
             d = net.tensors[op.dst]
             width = op.K if op.kind == "conv" else net.tensors[op.src].C
             observed = slot[op.dst] if slot else None
             if d.C == width:        # written whole
                 out = torch.empty((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
-            else:                   # a slice: the channels that no op writes are zeros
+            else:                   # a slice: channels that are read unwritten are zeros
+                if op.dst not in slices:
+                    slices[op.dst] = self._slices(op.dst)
+                late, covered = slices[op.dst]
                 out = t.get(op.dst)
                 if out is None:
-                    out = torch.zeros((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
-                if op.dst in late:
+                    make = torch.empty if covered else torch.zeros
+                    out = make((N, d.H, d.W, d.C), dtype=torch.float32, device=self.dev)
+                if late:
                     observed = None
             if op.kind == "pool":
                 B.pool_f32(t[op.src], op.mode, op.R, op.S, op.stride, op.pad, d.H, d.W, out=out,
@@ -290,7 +285,7 @@ class Engine:
                     desc.relu = int(op.relu)
                 B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
                                     slot[branch] if op.res and slot else None, observed)
-            if slot and op.dst in late and last_write[op.dst] == i:
+            if slot and last_write[op.dst] == i and slices.get(op.dst, (False,))[0]:
                 B.calibrate_maxabs(out, slot[op.dst])
             t[op.dst] = out
             if observe and d.C == width:
@@ -302,6 +297,29 @@ class Engine:
             for name in slices:
                 observe(name, t[name])
         return t
+
+    def _slices(self, name):
+        """Of a tensor written in slices: whether it is measured once complete (a pooling takes no
+        maximum, and of slices that are written over only the last values count), and whether
+        all of its channels are written before any is read."""
+        written, before, late, read = [], [], False, False
+        for op in self.net.ops:
+            read = read or name in (op.src, getattr(op, "res", None))
+            if op.dst != name:
+                continue
+            lo = op.dst_c_off
+            hi = lo + (op.K if op.kind == "conv" else self.net.tensors[op.src].C)
+            if hi - lo == self.net.tensors[name].C:
+                continue
+            late = late or op.kind == "pool" or any(a < hi and lo < b for a, b in written)
+            written.append((lo, hi))
+            if not read:
+                before.append((lo, hi))
+        end = 0
+        for lo, hi in sorted(before):
+            if lo <= end:
+                end = max(end, hi)
+        return late, end == self.net.tensors[name].C
 
     def calibrate(self, batches):
         """Running max-abs over fp32 forwards of ``batches`` (device fp32 NHWC tensors, at least

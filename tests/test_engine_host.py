@@ -172,3 +172,24 @@ def test_step_without_layers(recorded):
     eng, step = recorded(net, 2)
     ops = step(torch.zeros((2, 5, 7, 16)), {"x": torch.zeros((2, 5, 7, 16))})
     assert [o.kind for o in ops] == [B.OP_QUANTIZE, B.OP_DEQUANTIZE]
+
+
+@pytest.mark.parametrize("layers, late, covered", [
+    ([("a", 0, 16), ("b", 16, 32)], False, True), ([("b", 16, 32), ("a", 0, 16)], False, True),
+    ([("a", 0, 16), ("b", 16, 16)], False, False), ([("a", 0, 16), ("b", 32, 16)], False, False),
+    ([("b", 16, 32)], False, False), ([("a", 0, 32), ("b", 16, 32)], True, True),
+    ([("a", 0, 32), ("pool", 32, 16)], True, True), ([("a", 0, 16), ("read",), ("b", 16, 32)], False, False),
+    ([("a", 0, 32), ("b", 32, 16), ("read",), ("c", 8, 16)], True, True)])
+def test_slices_of_a_tensor(layers, late, covered):
+    """What the calibration forward measures once complete and what it has to clear."""
+    net = wl.Network("slices", "x")
+    net.tensor("x", 5, 7, 16)
+    net.tensor("cat", 5, 7, 48)
+    for name, *at in layers:
+        if name == "read":
+            wl._conv(net, "read", "cat", 16, 1, 1)
+        elif name == "pool":
+            wl._pool(net, "pool", "x", 3, 1, 1, dst="cat", dst_c_off=at[0])
+        else:
+            wl._conv(net, name, "x", at[1], 1, 1, dst="cat", dst_c_off=at[0])
+    assert Engine(net, 1, device="cpu")._slices("cat") == (late, covered)
