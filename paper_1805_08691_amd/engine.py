@@ -761,7 +761,8 @@ class Engine:
                 deq = fused.get(op.dst) is op
                 i = add(body, self._op_conv(op, lo, n, deq), k, group)
                 if deq:
-                    out_slots.append((1, i, op.dst, 4 * lo * self.act[op.dst].shape[1:].numel()))
+                    values = self.act[op.dst].shape[1:].numel()
+                    out_slots.append((1, i, op.dst, 4 * lo * values, self.N * values))
         if len(parts) == 1:
             pooled_head = with_x and self.head and self.head[1]
             dst_of = lambda o: self.head[1].dst if pooled_head and o is self.head[0] else o.dst
@@ -781,7 +782,7 @@ class Engine:
             o, z = B.Op(), self.act[name][:self.N]
             o.kind, o.flags = B.OP_DEQUANTIZE, B.OPF_IN_U8 if name in self.unsigned else 0
             o.x, o.n, o.q_x = B._ptr(z, torch.int8), z.numel(), self.q[name]
-            out_slots.append((2, add(post, o), name, 0))
+            out_slots.append((2, add(post, o), name, 0, z.numel()))
         segments = [(B.Op * len(s))(*s) for s in (pre, body, post)]
         return segments, x_slots, out_slots, len(parts)
 
@@ -808,27 +809,28 @@ class Engine:
         # factors, switch, filters and buffers are attributes a program may set between steps, and a
         # tensor's storage may be another than it was: the plan holds for the same names, the same
         # objects (whose types and strides were checked) and the addresses that they have now
-        tensors = [*itertools.chain.from_iterable(self.wq.values()), *self.act.values(),
-                   *self.act_f32.values(), *self.m_vec.values(), *self.taps.values()]
-        try:
-            addresses = [*map(torch.Tensor.data_ptr, tensors)]
-        except TypeError:                    # a layer without a bias
-            tensors = [t for t in tensors if t is not None]
-            addresses = [t.data_ptr() for t in tensors]
-        q_w = () if self.per_channel else self.qw.values()
-        given = (self.fuse_dequant, *self.q, *self.q.values(), *self.wq, *self.act, *self.taps, *self.m_vec,
-                 *q_w, *addresses)
-        plan, planned_for, planned_with = self._plans.get(key, (None, None, None))
-        if planned_for != given or not all(map(operator.is_, planned_with, tensors)):
+        given = [self.fuse_dequant, *self.q, *self.q.values(), *self.wq, *self.act, *self.taps, *self.m_vec]
+        if not self.per_channel:
+            given += self.qw.values()
+        objects = itertools.chain(itertools.chain.from_iterable(self.wq.values()), self.act.values(),
+                                  self.act_f32.values(), self.m_vec.values(), self.taps.values())
+        plan, planned_for, planned_with, tensors, addresses = self._plans.get(key, (None,) * 5)
+        if (planned_for != given or not all(map(operator.is_, planned_with, objects))
+                or addresses != [*map(torch.Tensor.data_ptr, tensors)]):
             plan = self._plan(*key)
-            self._plans[key] = plan, given, tensors
+            objects = [*itertools.chain(*self.wq.values(), self.act.values(), self.act_f32.values(),
+                                        self.m_vec.values(), self.taps.values())]
+            tensors = [t for t in objects if t is not None]          # (a layer may have no bias)
+            self._plans[key] = plan, given, objects, tensors, [t.data_ptr() for t in tensors]
         segments, x_slots, out_slots, n_parts = plan
         if x is not None:
             base = B._ptr(x, torch.float32)
             for s, i, off in x_slots:
                 segments[s][i].x = base + off
-        for s, i, name, off in out_slots:
-            segments[s][i].y_f32 = B._ptr(dequant[name], torch.float32) + off
+        for s, i, name, off, length in out_slots:
+            out = dequant[name]
+            self._check_length(name, out, length)
+            segments[s][i].y_f32 = B._ptr(out, torch.float32) + off
         run = B.lib.q8_run_ops
         streams = (ctypes.c_void_p * n_parts)(B._stream(),
                                               *(s.cuda_stream for s in self.side[:n_parts - 1]))
@@ -849,6 +851,11 @@ class Engine:
         if len(post):
             B._check(run(post, len(post), streams, 1))
 
+    @staticmethod
+    def _check_length(name, out, length):
+        if out.numel() < length:
+            raise ValueError(f"run_step: the buffer of {name} is shorter than the tensor")
+
     def run_step(self, x=None, dequant=None, serial=False):
         """One pass over the batch: Eq. Q on ``x`` (if given), every layer, Eq. D on the
         tensors named in ``dequant`` ({name: fp32 output buffer, of the batch or longer}).  With two streams the
@@ -856,15 +863,15 @@ class Engine:
         quantise and dequantise launches -- splitting those two as well was slower -- where
         the batch is large enough for that to pay; ``serial`` issues the launches of every
         part one pipeline after the other on the caller's stream."""
-        for name, out in (dequant or {}).items():
-            if out is not None and out.numel() < self.act[name][:self.N].numel():
-                raise ValueError(f"run_step: the buffer of {name} is shorter than the tensor")
         if not serial and self._plannable(x, dequant or {}):
             self._run_planned(x, dequant or {})
             for name, out in (dequant or {}).items():
                 if out is None:
                     self.dequantize(name)
             return
+        for name, out in (dequant or {}).items():
+            if out is not None:
+                self._check_length(name, out, self.act[name][:self.N].numel())
         self._x = None
         if x is not None:
             self.set_input(x)
