@@ -368,6 +368,11 @@ typedef struct q8_op {
 } q8_op;
 int q8_run_ops(const q8_op *ops, int n_ops, void *const *streams, int n_streams);
 
+/* Name of the joint launch that q8_run_ops would give the convolutions of ONE group (at most
+ * eight ops; the larger of two, where they fall into two); "single launches" if each would go by itself,
+ * "unsupported" if an op would be refused.  For tests and measurement code.               */
+const char *q8_group_variant(const q8_op *ops, int n_ops);
+
 /* Estimated duration in us of one launch of this layer on an otherwise idle chip (host
  * arithmetic; what the library chooses kernels by): for programs that order independent
  * layers.  0 if the layer is unsupported.                                               */

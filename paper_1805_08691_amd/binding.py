@@ -33,7 +33,7 @@ EXPORTS = [
     "q8_conv_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
-    "q8_probe_mfma_i8", "q8_run_ops", "q8_conv_estimate_us",
+    "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant", "q8_conv_estimate_us",
     "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
@@ -149,6 +149,8 @@ lib.q8_conv_int8_dequantized.argtypes = [_dp, _vp, _vp, _vp, _f, _f, _f, _vp, _f
 lib.q8_conv_image_f32_supported.argtypes = [_dp, _i, _i, _i, _i, _i, _i]
 lib.q8_conv_image_f32_int8.argtypes = [_dp, _vp, _i, _i, _i, _i, _i, _f, _i, _vp, _vp, _f, _f, _i, _vp, _vp]
 lib.q8_run_ops.argtypes = [_vp, _i, _vp, _i]
+lib.q8_group_variant.restype = C.c_char_p
+lib.q8_group_variant.argtypes = [_vp, _i]
 lib.q8_conv_estimate_us.restype = _f
 lib.q8_conv_estimate_us.argtypes = [_dp]
 lib.q8_sum_factor.restype = _f

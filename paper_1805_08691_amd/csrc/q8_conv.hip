@@ -605,6 +605,20 @@ int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
   const int v = pick_variant(d, is_extended(p), -1, us);
   return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d) : v;
 }
+// Whether a layer may join a group launch of the main kernel (plain codes only).  1: its tiled choice
+// is one of that kernel's small tiles; 2: it is the 3x3 family's smallest, 64 x 64 (a layer with a
+// tile or two per CU: 448 -> 384 on 8 x 8 x 32 images 20 us beside a launch of 11 us for the rest of
+// its module, 20 us together; the larger tiles fill the chip and stay by themselves); 0: no (the
+// other families, tiles of 256 pixels).
+int ring_group_takes(const q8_conv_desc* d, const ConvParams& p) {
+  if (is_extended(p) || conv_mode(d) != 0) return 0;
+  const int v = pick_tiled(d);
+  if (v < num_ring_variants()) return v != 3 && v != 13 ? 1 : 0;
+  if (v >= first_pw_variant()) return 0;
+  int bp = 0, bc = 0;
+  halo_variant_tile(v - num_ring_variants(), &bp, &bc);
+  return bp * bc == 64 * 64 ? 2 : 0;
+}
 int conv_launch_chosen(int variant, ConvParams& p, hipStream_t s) {
   p.n_split = 1;
   p.ws_counters = nullptr;

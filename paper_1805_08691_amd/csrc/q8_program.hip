@@ -12,6 +12,11 @@ int num_direct_variants();
 bool direct_applicable(const ConvParams& p);
 int pick_direct_group(const ConvParams* const* p, int n, float* us);
 int launch_direct_group_variant(int variant, const ConvParams* const* p, int n, hipStream_t stream);
+int ring_group_takes(const q8_conv_desc* d, const ConvParams& p);
+int pick_ring_group(const ConvParams** p, int n, float* us);
+int launch_ring_group_variant(int build, const ConvParams* const* p, int n, hipStream_t stream);
+const char* direct_variant_name(int variant);
+const char* ring_group_variant_name(int build);
 int dequantize_list(const q8_op* ops, int n, hipStream_t stream);   // q8_elementwise.hip
 
 namespace {
@@ -54,23 +59,73 @@ int run_one(const q8_op& o, void* stream) {
   }
 }
 
-// A run of independent ops on one stream.  The convolutions that would be launched as the latency
-// family anyway go together, or all of them do, or none: whatever is estimated shortest.  Ops in
-// front of a refused one are enqueued, those behind it are not: the convolutions, whose arguments
-// are checked without a launch, therefore go behind the others.
-int run_group(const q8_op* ops, int n, void* stream) {
+// How the convolutions of a run of independent ops are launched: in part or in whole together, as
+// the latency family or as the main kernel's group builds, or each by itself, whatever is estimated
+// shortest.
+struct GroupPlan {
+  // Who may go where: every layer the latency family takes (all of them or none); those that it
+  // would be launched as anyway (small); those whose tiled choice is the main kernel, the same with
+  // the 3x3 family's, and of the former the ones that are not small.
+  enum { kAllDirect, kSmallDirect, kTiled, kTiled3x3, kLargeTiled, kSets };
   ConvParams p[kMaxGroup];
-  const ConvParams *small[kMaxGroup], *all[kMaxGroup];
-  int variant[kMaxGroup], n_small = 0, n_all = 0, n_conv = 0, refused = Q8_OK;
-  bool is_small[kMaxGroup] = {}, waiting[kMaxGroup] = {};
-  float us_each[kMaxGroup], us_small = 0.0f, us_all = 0.0f;
-  const int first = first_direct_variant(), last = first + num_direct_variants();
+  bool waiting[kMaxGroup] = {};        // convolutions that still have to be launched
+  int variant[kMaxGroup];              // what each would be launched as on its own
+  const ConvParams* set[kSets][kMaxGroup];
+  int count[kSets] = {}, build[kSets], member[kMaxGroup] = {};
+  int chosen[2] = {-1, -1};            // sets to launch together
+
+  void choose(const q8_op* ops, int n) {
+    const int first = first_direct_variant(), last = first + num_direct_variants();
+    float alone[kSets] = {}, saved[kSets];
+    int n_conv = 0;
+    for (int i = 0; i < n; ++i) {
+      if (!waiting[i]) continue;
+      ++n_conv;
+      float us = 0.0f;
+      variant[i] = conv_choose(&ops[i].d, p[i], &us);
+      const bool small = variant[i] >= first && variant[i] < last;
+      const int tiled = ring_group_takes(&ops[i].d, p[i]);
+      const bool in[kSets] = {direct_applicable(p[i]) && p[i].S4 == 0, small, tiled == 1, tiled != 0,
+                              tiled == 1 && !small};
+      for (int s = 0; s < kSets; ++s) {
+        if (!in[s]) continue;
+        member[i] |= 1 << s;
+        set[s][count[s]++] = &p[i];
+        alone[s] += us;
+      }
+    }
+    for (int s = 0; s < kSets; ++s) {
+      saved[s] = 0.0f;
+      if (count[s] < 2 || (s == kAllDirect && count[s] != n_conv)) continue;
+      float us = 0.0f;
+      build[s] = s <= kSmallDirect ? pick_direct_group(set[s], count[s], &us)
+                                   : pick_ring_group(set[s], count[s], &us);
+      if (build[s] >= 0 && us < alone[s]) saved[s] = alone[s] - us;
+    }
+    int best = kAllDirect;
+    for (int s : {kTiled, kTiled3x3})
+      if (saved[s] > saved[best]) best = s;
+    if (saved[best] > 0.0f && saved[best] >= saved[kSmallDirect] + saved[kLargeTiled]) {
+      chosen[0] = best;
+    } else {
+      if (saved[kLargeTiled] > 0.0f) chosen[0] = kLargeTiled;
+      if (saved[kSmallDirect] > 0.0f) chosen[1] = kSmallDirect;
+    }
+  }
+};
+
+// A run of independent ops on one stream.  Ops in front of a refused one are enqueued, those behind
+// it are not: the convolutions, whose arguments are checked without a launch, therefore go behind
+// the others.
+int run_group(const q8_op* ops, int n, void* stream) {
+  GroupPlan g;
+  int refused = Q8_OK;
   for (int i = 0; i < n && refused == Q8_OK; ++i) {
     if (ops[i].kind != Q8_OP_CONV) continue;
     bool empty = false;
-    refused = conv_fill_op(&ops[i], p[i], &empty);
+    refused = conv_fill_op(&ops[i], g.p[i], &empty);
     if (refused != Q8_OK) n = i;
-    else waiting[i] = !empty;
+    else g.waiting[i] = !empty;
   }
   for (int i = 0; i < n; ++i) {
     if (ops[i].kind == Q8_OP_CONV) continue;
@@ -80,34 +135,17 @@ int run_group(const q8_op* ops, int n, void* stream) {
       n = i;
     }
   }
-  for (int i = 0; i < n; ++i) {
-    if (!waiting[i]) continue;
-    ++n_conv;
-    variant[i] = conv_choose(&ops[i].d, p[i], &us_each[i]);
-    us_all += us_each[i];
-    if (direct_applicable(p[i]) && p[i].S4 == 0) all[n_all++] = &p[i];
-    if (variant[i] >= first && variant[i] < last) {
-      is_small[i] = true;
-      us_small += us_each[i];
-      small[n_small++] = &p[i];
-    }
-  }
-  float us_g = 0.0f, us_a = 0.0f;
-  const int vs = n_small >= 2 ? pick_direct_group(small, n_small, &us_g) : -1;
-  const int va = n_all >= 2 && n_all == n_conv ? pick_direct_group(all, n_all, &us_a) : -1;
-  const float saved_small = vs >= 0 ? us_small - us_g : 0.0f, saved_all = va >= 0 ? us_all - us_a : 0.0f;
-  if (saved_all > 0.0f && saved_all >= saved_small) {
-    const int rc = launch_direct_group_variant(va, all, n_all, (hipStream_t)stream);
-    return rc != Q8_OK ? rc : refused;
-  }
-  if (saved_small > 0.0f) {
-    const int rc = launch_direct_group_variant(vs, small, n_small, (hipStream_t)stream);
+  g.choose(ops, n);
+  for (int s : g.chosen) {
+    if (s < 0) continue;
+    const int rc = (s <= GroupPlan::kSmallDirect ? launch_direct_group_variant : launch_ring_group_variant)(
+        g.build[s], g.set[s], g.count[s], (hipStream_t)stream);
     if (rc != Q8_OK) return rc;
-    for (int i = 0; i < n; ++i) waiting[i] = waiting[i] && !is_small[i];
+    for (int i = 0; i < n; ++i) g.waiting[i] = g.waiting[i] && !(g.member[i] >> s & 1);
   }
   for (int i = 0; i < n; ++i) {
-    if (!waiting[i]) continue;
-    const int rc = conv_launch_chosen(variant[i], p[i], (hipStream_t)stream);
+    if (!g.waiting[i]) continue;
+    const int rc = conv_launch_chosen(g.variant[i], g.p[i], (hipStream_t)stream);
     if (rc != Q8_OK) return rc;
   }
   return refused;
@@ -138,4 +176,20 @@ extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int
     i = j;
   }
   return Q8_OK;
+}
+
+extern "C" const char* q8_group_variant(const q8_op* ops, int n_ops) {
+  if (!ops || n_ops < 1 || n_ops > q8::kMaxGroup) return "unsupported";
+  q8::GroupPlan g;
+  for (int i = 0; i < n_ops; ++i) {
+    bool empty = false;
+    if (ops[i].kind != Q8_OP_CONV) continue;
+    if (q8::conv_fill_op(&ops[i], g.p[i], &empty) != Q8_OK) return "unsupported";
+    g.waiting[i] = !empty;
+  }
+  g.choose(ops, n_ops);
+  const int s = g.chosen[0] >= 0 ? g.chosen[0] : g.chosen[1];
+  if (s < 0) return "single launches";
+  return s <= q8::GroupPlan::kSmallDirect ? q8::direct_variant_name(g.build[s])
+                                          : q8::ring_group_variant_name(g.build[s]);
 }

@@ -763,19 +763,15 @@ class Engine:
                 if deq:
                     values = self.act[op.dst].shape[1:].numel()
                     out_slots.append((1, i, op.dst, 4 * lo * values, self.N * values))
-        if len(parts) == 1:
-            pooled_head = with_x and self.head and self.head[1]
-            dst_of = lambda o: self.head[1].dst if pooled_head and o is self.head[0] else o.dst
-            for level, members in enumerate(self._levels(ops, self.N, dst_of)):
+        pooled_head = with_x and self.head and self.head[1]
+        dst_of = lambda o: self.head[1].dst if pooled_head and o is self.head[0] else o.dst
+        # level by level, alternating between the pipelines: a captured graph hands its nodes to
+        # the GPU in the order they were recorded, and a pipeline recorded whole before the next
+        # one starts that much earlier and runs alone meanwhile
+        for level, members in enumerate(self._levels(ops, parts[0][1], dst_of)):
+            for k in list(range(1, len(parts))) + [0]:
                 for i in sorted(members):
-                    emit(ops[i], 0, level + 1)
-        else:
-            # layer by layer, alternating between the pipelines: a captured graph hands its nodes
-            # to the GPU in the order they were recorded, and a pipeline recorded whole before
-            # the next one starts that much earlier and runs alone meanwhile
-            for op in ops:
-                for k in list(range(1, len(parts))) + [0]:
-                    emit(op, k, 0)
+                    emit(ops[i], k, level + 1)
         for name in names:
             if name in fused:
                 continue
@@ -789,9 +785,22 @@ class Engine:
     def _pipelines_pay(self, ops):
         """Concurrent pipelines hide one launch's latency and tail behind the other's work, and cost
         a second set of launches (in a recorded graph also a dependency per launch): worth it
-        where the average launch on the whole batch is well above its latency."""
-        us = sum(B.conv_estimate_us(self.conv_desc(o, self.N)) for o in ops if o.kind == "conv")
-        return us > 8.5 * len(ops)
+        where the layers' time on the whole batch is well above the latencies of the layers and of the
+        levels they form (at least a launch each).  Measured (us with one and with two): ResNet-50 16 images
+        360 / 421, 20: 402 / 392, 24: 495 / 461; Inception-v3 16 images 550 / 559, 18: 625 / 563; the
+        detector 2 images 289 / 293, 5: 442 / 375; with unsigned codes ResNet-50 20 images 420 / 432,
+        28: 578 / 533."""
+        if self.N < 4:           # (unequal parts: the detector 3 images 291 / 330 us at 286 pixels)
+            return False
+        us, depth = 0.0, {}
+        for o in ops:
+            us += B.conv_estimate_us(self.conv_desc(o, self.N)) if o.kind == "conv" else 0.0
+            depth[o.dst] = max(depth.get(o.dst, 0), 1 + max(depth.get(o.src, 0),
+                                                            depth.get(getattr(o, "res", None), 0)))
+        levels = max(depth.values(), default=0)
+        if len(ops) < 16:        # (the fork and the join count: a bottleneck block 32 images 52 / 85 us)
+            return us > 8.5 * len(ops)
+        return us > (8.0 * len(ops) if self.unsigned else 5.8 * len(ops) + 1.75 * levels)
 
     def _plannable(self, x, dequant):
         """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and

@@ -1840,6 +1840,75 @@ def test_run_ops_groups_equal_single_calls(B):
         assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
 
 
+# layers whose reduction steps cross filter taps: several taps a step (C below the step's bytes), at
+# most one further (C above), the most taps that the kernel takes, as one row and as one column
+TAP_CASES = [
+    dict(N=1, H=9, W=11, C=16, K=40, R=5, S=5, pad_h=2, pad_w=2),
+    dict(N=2, H=12, W=13, C=32, K=64, R=3, S=3, stride_h=2, stride_w=2, pad_h=1, pad_w=1),
+    dict(N=1, H=10, W=14, C=48, K=65, R=5, S=5, pad_h=2, pad_w=2),
+    dict(N=1, H=13, W=12, C=80, K=48, R=3, S=3, pad_h=2, pad_w=2, dil_h=2, dil_w=2),
+    dict(N=3, H=5, W=7, C=112, K=96, R=1, S=3, pad_w=1),
+    dict(N=1, H=11, W=6, C=144, K=33, R=7, S=1, pad_h=3),
+    dict(N=1, H=2, W=40, C=16, K=34, R=1, S=32, pad_w=4),
+    dict(N=1, H=40, W=2, C=16, K=34, R=32, S=1, pad_h=4),
+]
+
+
+@pytest.mark.parametrize("idx", range(len(TAP_CASES)))
+def test_conv_steps_across_taps(B, idx):
+    names = [B.lib.q8_conv_variant_name(v).decode() for v in range(B.conv_num_variants())]
+    for v, name in enumerate(names):
+        if "ring_kernel" in name:
+            _run_conv_case(B, TAP_CASES[idx], relu=bool(v % 2), with_res=bool((v + idx) % 2), with_bias=True,
+                           seed=900 * idx + v, variant=v)
+
+
+# a module's branches as one launch of the main kernel, in both group builds: 1x1 layers, steps in one
+# tap, across taps (C below and above a step), a layer of the 3x3 family, stride and dilation, tails in
+# pixels and channels, a residual, slices of one tensor
+GROUP_LAYERS = [dict(C=320, K=72, R=1, S=1), dict(C=160, K=64, R=1, S=7, pad_w=3),
+                dict(C=48, K=50, R=5, S=5, pad_h=2, pad_w=2), dict(C=192, K=130, R=3, S=3, pad_h=1, pad_w=1),
+                dict(C=112, K=65, R=3, S=3, stride_h=2, stride_w=2, pad_h=1, pad_w=1),
+                dict(C=128, K=64, R=3, S=3, pad_h=3, pad_w=3, dil_h=3, dil_w=3), dict(C=256, K=33, R=1, S=1)]
+
+
+@pytest.mark.parametrize("N,H,W,build", [(9, 17, 17, "2,2,1,1,128,4"), (5, 17, 19, "2,2,1,1,128,4"),
+                                         (16, 21, 23, "2,2,2,1,64,4")])
+def test_run_ops_tiled_groups_equal_the_oracle(B, N, H, W, build):
+    rng = np.random.default_rng(N)
+    n = len(GROUP_LAYERS)
+    ops, keep, want = (B.Op * n)(), [], []
+    q_x, q_w = np.float32(0.02), np.float32(0.002)
+    cat_c = sum(g["K"] for g in GROUP_LAYERS if "stride_h" not in g)
+    cat, off = torch.full((N, H, W, cat_c), 77, dtype=torch.int8, device="cuda"), 0
+    for i, layer in enumerate(GROUP_LAYERS):
+        g = orc.ConvGeom(N=N, H=H, W=W, **layer)
+        sliced = "stride_h" not in layer
+        x = rng.integers(-128, 128, (N, H, W, g.C)).astype(np.int8)
+        w = rng.integers(-128, 128, (g.K, g.R, g.S, g.C)).astype(np.int8)
+        b = rng.integers(-20000, 20000, g.K).astype(np.int32)
+        res = rng.integers(-128, 128, (N, g.Ho, g.Wo, g.K)).astype(np.int8) if i % 3 == 0 else None
+        q_out = np.float32(q_x * q_w * 5476.0 * np.sqrt(g.R * g.S * g.C) / 40.0)
+        q_res = np.float32(0.3) * q_out
+        codes = orc.requant(orc.conv_i8(g, x, w, b), orc.requant_scale(q_x, q_w, q_out), bool(i % 2), res,
+                            orc.residual_scale(q_res, q_out) if res is not None else 0.0)
+        d = B.ConvDesc(N, H, W, g.C, g.K, g.R, g.S, g.stride_h, g.stride_w, g.pad_h, g.pad_w, g.dil_h, g.dil_w,
+                       relu=i % 2, out_c_stride=cat_c if sliced else 0, out_c_off=off if sliced else 0)
+        y = cat if sliced else torch.zeros(codes.shape, dtype=torch.int8, device="cuda")
+        t = [dev(x), B.pack_weights(d, dev(w)), dev(b), y, dev(res) if res is not None else None]
+        o = ops[i]
+        o.kind, o.group, o.d, o.q_x, o.q_w, o.q_out, o.q_res = B.OP_CONV, 1, d, q_x, q_w, q_out, q_res
+        o.x, o.w, o.bias, o.y = (v.data_ptr() for v in t[:4])
+        o.residual = t[4].data_ptr() if res is not None else None
+        keep.append(t)
+        want.append((codes, slice(off, off + g.K) if sliced else slice(0, g.K)))
+        off += g.K if sliced else 0
+    assert B.lib.q8_group_variant(ops, n).decode() == f"conv_i8_ring_group_kernel<{build}>"
+    _run_ops(B, ops)
+    for i, (codes, part) in enumerate(want):
+        assert np.array_equal(host(keep[i][3])[..., part], codes), GROUP_LAYERS[i]
+
+
 def _dequantize_ops(B, n, lengths, offset_of=()):
     """A list of Q8_OP_DEQUANTIZE ops over int8 tensors of ``lengths``, those in ``offset_of`` one
     value behind an aligned address; (ops, tensors, outputs, factors)."""
