@@ -456,7 +456,17 @@ int q8_conv_f32_observed(const q8_conv_desc *d, const float *x_dev, const float 
                          const float *b_dev, const float *res_dev, float *y_dev,
                          float *maxabs_sum_dev, float *maxabs_out_dev, void *stream);
 
-/* Name of the kernel build these two take for this geometry, as q8_conv_variant.          */
+/* The same with n_slots copies of each maximum, 32 values apart: a workgroup raises one of them, so
+ * that the atomics of a launch do not queue on one address.  A maximum is the largest of its
+ * copies: q8_calibrate_fold writes out_dev[k] = max over j of spread_dev[(k n_slots + j) 32] for
+ * n_keys of them (all values non-negative, as the maxima of an array that was zero are).       */
+int q8_conv_f32_observed_spread(const q8_conv_desc *d, const float *x_dev, const float *w_dev,
+                                const float *b_dev, const float *res_dev, float *y_dev,
+                                float *maxabs_sum_dev, float *maxabs_out_dev, int n_slots,
+                                void *stream);
+int q8_calibrate_fold(const float *spread_dev, int n_keys, int n_slots, float *out_dev, void *stream);
+
+/* Name of the kernel build these take for this geometry, as q8_conv_variant.              */
 const char *q8_conv_f32_variant(const q8_conv_desc *d);
 
 /* int8 max-pool over an R x S window; taps outside the image are ignored.         */

@@ -34,7 +34,7 @@ EXPORTS = [
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant", "q8_conv_estimate_us",
-    "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
+    "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_observed_spread", "q8_calibrate_fold", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
 
@@ -160,6 +160,8 @@ lib.q8_conv_f32_ref.argtypes = [_dp, _vp, _vp, _vp, _vp, _vp, _vp]
 lib.q8_conv_f32_variant.restype = C.c_char_p
 lib.q8_conv_f32_variant.argtypes = [_dp]
 lib.q8_conv_f32_observed.argtypes = [_dp] + [_vp] * 8
+lib.q8_conv_f32_observed_spread.argtypes = [_dp] + [_vp] * 7 + [_i, _vp]
+lib.q8_calibrate_fold.argtypes = [_vp, _i, _i, _vp, _vp]
 lib.q8_maxpool_i8.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
 lib.q8_maxpool_f32.argtypes = [_vp] + [_i] * 10 + [_vp, _vp]
 
@@ -547,13 +549,28 @@ def conv_f32_variant(desc):
     return lib.q8_conv_f32_variant(C.byref(desc)).decode()
 
 
+SLOT_STRIDE = 32         # values between the copies of a spread maximum (a cache line)
+
+
 def conv_f32_observed(desc, x, w, b, res, out, maxabs_sum, maxabs_out):
     """conv_f32_ref into a channel slice of ``out``, with the running max-abs of the value before
-    the residual sum and of the output (1-element fp32 device tensors, or None)."""
-    _check(lib.q8_conv_f32_observed(C.byref(desc), _ptr(x, torch.float32), _ptr(w, torch.float32),
-                                    _ptr(b, torch.float32), _ptr(res, torch.float32),
-                                    _ptr(out, torch.float32), _ptr(maxabs_sum, torch.float32),
-                                    _ptr(maxabs_out, torch.float32), _stream()))
+    the residual sum and of the output (fp32 device tensors or None: of one value, or of n *
+    SLOT_STRIDE values that hold n copies, see calibrate_fold)."""
+    sizes = {(m.numel() + SLOT_STRIDE - 1) // SLOT_STRIDE for m in (maxabs_sum, maxabs_out) if m is not None}
+    assert len(sizes) <= 1, "as many copies of one maximum as of the other"
+    _check(lib.q8_conv_f32_observed_spread(
+        C.byref(desc), _ptr(x, torch.float32), _ptr(w, torch.float32), _ptr(b, torch.float32),
+        _ptr(res, torch.float32), _ptr(out, torch.float32), _ptr(maxabs_sum, torch.float32),
+        _ptr(maxabs_out, torch.float32), max(sizes, default=1), _stream()))
+    return out
+
+
+def calibrate_fold(spread, out):
+    """out[k] = the largest of the copies spread[k, ::SLOT_STRIDE]."""
+    n_keys, n = spread.shape
+    assert n % SLOT_STRIDE == 0 and out.numel() == n_keys
+    _check(lib.q8_calibrate_fold(_ptr(spread, torch.float32), n_keys, n // SLOT_STRIDE,
+                                 _ptr(out, torch.float32), _stream()))
     return out
 
 

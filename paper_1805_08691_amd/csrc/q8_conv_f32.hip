@@ -2,52 +2,21 @@
 // activations calibration measures, with the max-abs of what it computes taken on the way.
 // A helper around the quantised path, not part of it.
 //
-// What bounds it: on large layers the fp32 matrix rate (122 of the 153 TF a library product of
-// 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at batch 64).  On the layers of a calibration batch
-// of eight: 3x3 layers (14 x 14 x 256, 392 tiles of 590 KB, 34 us) by the operand loads, 11 bytes
-// per clock and CU; 1x1 layers, of two to eight stages a tile, by the tile's chain of latencies
-// (128 -> 512 on 28 x 28, 784 tiles of 64 KB: 24 us, 3 bytes per clock and CU) and in the first
-// batch by the maxima, whose atomics then come from every wavefront at once (the same layer with
-// its slots at zero: 34 us, with a residual 45).  16 reduction bytes per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments
-// straight into the MFMA's register layout (16 rows x 64 bytes a load), two stages ahead of the
-// one it computes: no LDS and no barrier inside the loop.  ResNet-50 calibration on 8 images:
-// 13.9 -> 1.8 ms, with the max-abs taken here instead of in a pass over every tensor and the value
-// in front of a fused sum measured on the way instead of in a second convolution.
+// This file: the register-fed builds, for channel counts and alignments that those on LDS
+// (q8_conv_f32_lds.hip) do not take, and the host side.  What bounds them: on large layers the fp32
+// matrix rate (122 of the 153 TF a library product of 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at
+// batch 64); on small maps the operand loads, 11 to 14 bytes per clock and CU.  16 reduction bytes
+// per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments straight into the MFMA's
+// register layout (16 rows x 64 bytes a load), two stages ahead of the one it computes: no LDS and no
+// barrier inside the loop.  ResNet-50 calibration on 8 images: 13.9 ms with the max-abs as passes over
+// every tensor, 1.78 ms with these builds alone and an atomic per wavefront, 1.07 ms now.
 //
 // Small maps have few tiles (7 x 7 at batch 8: 392 pixels): KW groups of wavefronts then share
 // the stages of one tile and add their accumulators through LDS in a fixed order.
-#include "q8_common.h"
-#include "q8_conv_common.h"
+#include "q8_conv_f32.h"
 
 namespace q8 {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-struct F32Params {
-  const float* __restrict__ x;
-  const float* __restrict__ w;
-  const float* __restrict__ b;
-  const float* __restrict__ res;
-  float* __restrict__ y;
-  unsigned* __restrict__ obs_sum;      // max |conv + bias| before the residual sum, or null
-  unsigned* __restrict__ obs_out;      // max |y|, or null
-  int N, H, W, C, K, R, S, sh, sw, ph, pw, dh, dw, Ho, Wo, M, rsc, out_cs, out_off, relu;
-  int vec_y, vec_b;                    // output / residual rows, the bias take 16-byte accesses
-  FastDiv by_img, by_row, by_c, by_s;
-  int n_ptiles, n_ctiles;
-};
-
-[[maybe_unused]] constexpr int kOob = (int)0x80000000;   // beyond any descriptor (they span at most 2^31 - 1 bytes)
-
-__device__ __forceinline__ void observe(unsigned* slot, float m) {
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) {
-    const unsigned bits = __float_as_uint(m);
-    if (bits > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(slot, bits);
-  }
-}
 
 // WP x WC wavefronts, each TP x TC MFMA tiles of 16 pixels x 16 channels; NC chunks of 64 bytes per
 // row and stage, NB stages in registers.
@@ -329,8 +298,8 @@ __global__ __launch_bounds__(WP * WC * KW * 64, 2) void conv_f32_mfma_kernel(con
         if (e < nvalid) y[e] = v[e];
     }
   }
-  if (p.obs_sum) observe(p.obs_sum, m_sum);
-  if (p.obs_out) observe(p.obs_out, m_out);
+  __shared__ float mx[2 * NW * KW];
+  observe_block<NW * KW>(p, m_sum, m_out, mx);
 #endif
 }
 
@@ -364,8 +333,8 @@ __global__ __launch_bounds__(kThreads) void conv_f32_any_kernel(const F32Params 
     m_out = fmaxf(m_out, fabsf(v));
     p.y[pix * p.out_cs + p.out_off + k] = v;
   }
-  if (p.obs_sum) observe(p.obs_sum, m_sum);
-  if (p.obs_out) observe(p.obs_out, m_out);
+  __shared__ float mx[2 * kThreads / 64];
+  observe_block<kThreads / 64>(p, m_sum, m_out, mx);
 }
 
 template <int WP, int WC, int TP, int TC, int KW, int NC, int NB>
@@ -379,6 +348,16 @@ int launch_f32(F32Params& p, hipStream_t stream) {
                                : conv_f32_mfma_kernel<WP, WC, TP, TC, KW, NC, NB, 0>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(WP * WC * KW * 64), 0, stream, p);
   return q8_launch_status();
+}
+
+// One wavefront per maximum: the largest of its copies.
+__global__ __launch_bounds__(64) void fold_slots_kernel(const float* __restrict__ spread, int n_slots,
+                                                        float* __restrict__ out) {
+  float m = 0.0f;
+  for (int j = threadIdx.x; j < n_slots; j += 64)
+    m = fmaxf(m, spread[((size_t)blockIdx.x * n_slots + j) * kSlotStride]);
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if (threadIdx.x == 0) out[blockIdx.x] = m;
 }
 
 // The builds of the tiled kernel; MODE follows from the channel count.
@@ -432,8 +411,14 @@ bool f32_tiled(const q8_conv_desc* d, long M, long per_img) {
            (long)d->R * d->dil_h > (1 << 28));
 }
 
+// Whether the builds on LDS take the layer: whole 128-byte pieces of a tap, whole groups of a lane's
+// channels, output (residual, bias) rows of 16-byte accesses.
+bool f32_lds_takes(const q8_conv_desc* d, int out_cs, int out_off) {
+  return d->C % 32 == 0 && d->K % 16 == 0 && out_cs % 4 == 0 && out_off % 4 == 0;
+}
+
 int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float* b, const float* res,
-             float* y, int out_cs, int out_off, float* obs_sum, float* obs_out, hipStream_t stream) {
+             float* y, int out_cs, int out_off, float* obs_sum, float* obs_out, int n_slots, hipStream_t stream) {
   Q8_REQUIRE(f32_desc_sane(d), Q8_EINVAL);
   F32Params p{};
   p.Ho = q8_conv_out_h(d); p.Wo = q8_conv_out_w(d);
@@ -442,6 +427,7 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   Q8_REQUIRE(x && w && y && out_off >= 0 && out_cs >= out_off + d->K, Q8_EINVAL);
   p.x = x; p.w = w; p.b = b; p.res = res; p.y = y;
   p.obs_sum = reinterpret_cast<unsigned*>(obs_sum); p.obs_out = reinterpret_cast<unsigned*>(obs_out);
+  p.n_slots = n_slots;
   p.N = d->N; p.H = d->H; p.W = d->W; p.C = d->C; p.K = d->K; p.R = d->R; p.S = d->S;
   p.sh = d->stride_h; p.sw = d->stride_w; p.ph = d->pad_h; p.pw = d->pad_w;
   p.dh = d->dil_h; p.dw = d->dil_w;
@@ -460,6 +446,8 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.M = (int)M; p.rsc = d->R * d->S * d->C;
   p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
   p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
+  if (f32_lds_takes(d, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16))
+    return launch_f32_lds(pick_f32_lds(M, d->K, p.rsc), p, stream);
   return kF32Builds[pick_f32(M, d->K)].launch(p, stream);
 }
 
@@ -471,7 +459,7 @@ extern "C" {
 int q8_conv_f32_ref(const q8_conv_desc* d, const float* x_dev, const float* w_dev,
                     const float* b_dev, const float* res_dev, float* y_dev, void* stream) {
   return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev, d ? d->K : 0, 0, nullptr, nullptr,
-                      (hipStream_t)stream);
+                      1, (hipStream_t)stream);
 }
 
 int q8_conv_f32_observed(const q8_conv_desc* d, const float* x_dev, const float* w_dev,
@@ -480,13 +468,34 @@ int q8_conv_f32_observed(const q8_conv_desc* d, const float* x_dev, const float*
   Q8_REQUIRE(q8_aligned(maxabs_sum_dev, 4) && q8_aligned(maxabs_out_dev, 4), Q8_EALIGN);
   return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev,
                       d && d->out_c_stride ? d->out_c_stride : (d ? d->K : 0), d ? d->out_c_off : 0,
-                      maxabs_sum_dev, maxabs_out_dev, (hipStream_t)stream);
+                      maxabs_sum_dev, maxabs_out_dev, 1, (hipStream_t)stream);
+}
+
+int q8_conv_f32_observed_spread(const q8_conv_desc* d, const float* x_dev, const float* w_dev,
+                                const float* b_dev, const float* res_dev, float* y_dev,
+                                float* maxabs_sum_dev, float* maxabs_out_dev, int n_slots, void* stream) {
+  Q8_REQUIRE(n_slots >= 1, Q8_EINVAL);
+  Q8_REQUIRE(q8_aligned(maxabs_sum_dev, 4) && q8_aligned(maxabs_out_dev, 4), Q8_EALIGN);
+  return q8::conv_f32(d, x_dev, w_dev, b_dev, res_dev, y_dev,
+                      d && d->out_c_stride ? d->out_c_stride : (d ? d->K : 0), d ? d->out_c_off : 0,
+                      maxabs_sum_dev, maxabs_out_dev, n_slots, (hipStream_t)stream);
+}
+
+int q8_calibrate_fold(const float* spread_dev, int n_keys, int n_slots, float* out_dev, void* stream) {
+  Q8_REQUIRE(n_keys >= 0 && n_slots >= 1 && (n_keys == 0 || (spread_dev && out_dev)), Q8_EINVAL);
+  Q8_REQUIRE(q8_aligned(spread_dev, 4) && q8_aligned(out_dev, 4), Q8_EALIGN);
+  if (n_keys == 0) return Q8_OK;
+  hipLaunchKernelGGL(q8::fold_slots_kernel, dim3(n_keys), dim3(64), 0, (hipStream_t)stream, spread_dev, n_slots,
+                     out_dev);
+  return q8_launch_status();
 }
 
 const char* q8_conv_f32_variant(const q8_conv_desc* d) {
   if (!q8::f32_desc_sane(d)) return "unsupported";
   const long per_img = (long)q8_conv_out_h(d) * q8_conv_out_w(d), M = d->N * per_img;
   if (M > 0 && !q8::f32_tiled(d, M, per_img)) return "conv_f32_any_kernel";
+  if (M > 0 && q8::f32_lds_takes(d, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off))
+    return q8::f32_lds_name(q8::pick_f32_lds(M, d->K, d->R * d->S * d->C));
   const q8::F32Build& b = q8::kF32Builds[q8::pick_f32(M, d->K)];
   return b.name[d->C % (16 * b.nc) == 0 ? 2 : d->C % 4 == 0 ? 1 : 0];
 }

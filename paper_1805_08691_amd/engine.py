@@ -241,7 +241,7 @@ class Engine:
         return self._forward_f32(x, None, observe)
 
     def _forward_f32(self, x, slot, observe=None):
-        """The fp32 forward.  With ``slot`` (one-element device tensors by key) it leaves the running
+        """The fp32 forward.  With ``slot`` (device tensors by key, see conv_f32_observed) it leaves the running
         max-abs of every tensor there and keeps no tensor longer than it is read: a convolution
         takes the maxima of its own output and of its value before a fused sum while it holds
         them; a stand-alone pooling keeps its input's factor and is not measured."""
@@ -286,7 +286,7 @@ class Engine:
                 B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
                                     slot[branch] if op.res and slot else None, observed)
             if slot and last_write[op.dst] == i and slices.get(op.dst, (False,))[0]:
-                B.calibrate_maxabs(out, slot[op.dst])
+                B.calibrate_maxabs(out, slot[op.dst][:1])
             t[op.dst] = out
             if observe and d.C == width:
                 observe(op.dst, out)
@@ -330,16 +330,17 @@ class Engine:
                 keys.append(op.name + ":branch")
             if op.dst not in keys:
                 keys.append(op.dst)
-        slots = torch.zeros(len(keys), dtype=torch.float32, device=self.dev)
-        slot = dict(zip(keys, slots.split(1)))
+        # sixteen copies of every maximum, so that a launch's atomics do not queue on one address
+        spread = torch.zeros((len(keys), 16 * B.SLOT_STRIDE), dtype=torch.float32, device=self.dev)
+        slot = dict(zip(keys, spread))
         n_batches = 0
         for x in batches:
-            B.calibrate_maxabs(x.contiguous(), slot[self.net.input])
+            B.calibrate_maxabs(x.contiguous(), slot[self.net.input][:1])
             self._forward_f32(x.contiguous(), slot)
             n_batches += 1
         if not n_batches:
             raise ValueError("calibrate: no batches")     # every factor would be 1
-        vals = slots.cpu().numpy()
+        vals = B.calibrate_fold(spread, torch.empty(len(keys), device=self.dev)).cpu().numpy()
         q = {k: B.qfactor(float(v), 8 if k in self.unsigned else P_ACT)
              for k, v in zip(keys, vals)}
         for op in self.net.ops:

@@ -1706,6 +1706,67 @@ def test_conv_f32_tiles(B, build, geom, res, slice_):
         assert np.array_equal(host(ref), got)                 # the same sums without the maxima
 
 
+# the builds on LDS: fewer steps than groups and than the ring holds, steps that do not divide, tails in
+# pixels and channels, stride, dilation, row and column filters, slices, residuals, several images a tile
+@pytest.mark.parametrize("build,geom,res,slice_", [
+    ("1,1,4,4", (1, 5, 7, 32, 16, 1, 1, 1, 1), True, (0, 0)),
+    ("1,1,4,4", (9, 3, 3, 96, 48, 3, 3, 1, 1), False, (56, 4)),
+    ("1,1,4,4", (3, 13, 11, 64, 80, 3, 3, 2, 1), True, (0, 0)),
+    ("1,1,4,4", (2, 19, 19, 64, 144, 3, 3, 1, 6), True, (0, 0)),
+    ("1,1,4,4", (4, 29, 31, 160, 176, 1, 7, 1, 1), False, (0, 0)),
+    ("1,2,2,4", (8, 28, 28, 32, 48, 5, 5, 1, 1), True, (0, 0)),
+    ("2,1,2,4", (8, 64, 66, 32, 32, 1, 7, 1, 1), False, (40, 8)),
+    ("2,1,2,4", (8, 65, 67, 64, 16, 3, 3, 2, 1), True, (0, 0)),
+    ("2,2,1,4", (5, 57, 59, 32, 64, 1, 1, 1, 1), False, (0, 0)),
+    ("2,2,1,4", (7, 35, 37, 32, 272, 1, 1, 1, 1), True, (0, 0))])
+def test_conv_f32_lds_builds(B, build, geom, res, slice_):
+    N, H, W, Cc, K, R, S, st, dil = geom
+    rng = np.random.default_rng(12)
+    ph, pw = dil * (R - 1) // 2, dil * (S - 1) // 2
+    desc = B.ConvDesc(N, H, W, Cc, K, R, S, st, st, ph, pw, dil, dil, relu=int(not res), out_c_stride=slice_[0],
+                      out_c_off=slice_[1])
+    assert B.conv_f32_variant(desc) == f"conv_f32_lds_kernel<{build}>"
+    x = rng.standard_normal((N, H, W, Cc)).astype(np.float32)
+    w = rng.standard_normal((K, R, S, Cc)).astype(np.float32)
+    b = rng.standard_normal(K).astype(np.float32)
+    r = rng.standard_normal((N, desc.Ho, desc.Wo, K)).astype(np.float32) if res else None
+
+    def fp64(x, w, b):
+        y = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2),
+                                       torch.from_numpy(w).double().permute(0, 3, 1, 2),
+                                       torch.from_numpy(b).double(), st, (ph, pw), dil)
+        return y.permute(0, 2, 3, 1).numpy()
+    pre = fp64(x, w, b)
+    want = pre + r if res else np.maximum(pre, 0.0)
+    # any order of n fp32 products and sums: |error| <= (n + 2) 2^-24 sum |x||w| (+ |b| + |r|)
+    bound = (R * S * Cc + 4) * 2.0 ** -24 * (fp64(abs(x), abs(w), abs(b)) + (abs(r) if res else 0))
+    spread = torch.zeros((2, 3 * B.SLOT_STRIDE), device="cuda")
+    out = torch.full((N, desc.Ho, desc.Wo, slice_[0] or K), -7.0, device="cuda")
+    B.conv_f32_observed(desc, dev(x), dev(w), dev(b), dev(r) if res else None, out, spread[0], spread[1])
+    got, lo = host(out), slice_[1]
+    assert np.all(abs(got[..., lo:lo + K] - want) <= bound)
+    assert np.all(got[..., :lo] == -7) and np.all(got[..., lo + K:] == -7)
+    m = host(B.calibrate_fold(spread, torch.empty(2, device="cuda")))
+    assert m[1] == abs(got[..., lo:lo + K]).max() and abs(m[0] - abs(pre).max()) <= bound.max()
+    one = torch.zeros(2, device="cuda")                       # one copy: the same maxima
+    B.conv_f32_observed(desc, dev(x), dev(w), dev(b), dev(r) if res else None, out, one[:1], one[1:])
+    assert np.array_equal(host(one), m)
+    # addresses the builds cannot read: the register-fed ones give as good a sum
+    moved = torch.empty(w.size + 1, device="cuda")[1:]
+    moved.copy_(dev(w).view(-1))
+    ref = host(B.conv_f32_ref(desc, dev(x), moved.view(w.shape), dev(b), dev(r) if res else None)) \
+        if slice_ == (0, 0) else want
+    assert np.all(abs(ref - want) <= bound)
+
+
+@pytest.mark.parametrize("n_keys,n_slots", [(1, 1), (3, 16), (130, 70)])
+def test_calibrate_fold(B, n_keys, n_slots):
+    spread = torch.rand((n_keys, n_slots * B.SLOT_STRIDE), device="cuda")
+    out = torch.full((n_keys,), -1.0, device="cuda")
+    B.calibrate_fold(spread, out)
+    assert torch.equal(out, spread.view(n_keys, n_slots, B.SLOT_STRIDE)[..., 0].amax(1))
+
+
 # tensors that the tiled builds' 32-bit offsets cannot reach into, by a dilation that leaves one row of
 # taps inside the image, and one as tall as the dilation with all three rows in use
 @pytest.mark.parametrize("H,W,C,K,S,slice_", [(9, 7, 24, 21, 3, (30, 4)), (2**20 + 37, 1, 64, 4, 1, (0, 0))])
