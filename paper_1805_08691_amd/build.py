@@ -1,4 +1,5 @@
-"""Compiles the HIP sources in csrc/ for gfx950 into libq8conv.so next to this file.
+"""Compiles the HIP sources in csrc/ for gfx950 into libq8conv.so next to this file, and the binding's
+extension module (host code) into _q8call.so.
 
 Run as ``python -m paper_1805_08691_amd.build``.  Flags: no fused multiply-add
 (-ffp-contract=off, the epilogue's op order is part of the result), packed-fp32
@@ -7,6 +8,7 @@ instructions disabled, correctly rounded fp32 division and square root (hipcc de
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,10 +40,24 @@ def _compile(src):
     return obj
 
 
+def _compile_call():
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    include = [*include_paths(), sysconfig.get_paths()["include"]]
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           *(a for p in include for a in ("-isystem", p)), os.path.join(CSRC, "q8_call.cpp"),
+                           "-o", os.path.join(HERE, "_q8call.so"),
+                           "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-ltorch_cpu",
+                           "-ltorch_python"])
+
+
 def build(verbose=True):
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        call = ex.submit(_compile_call)
         objs = list(ex.map(_compile, SOURCES))
+        call.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     if verbose:
         print("built", LIB)

@@ -301,3 +301,27 @@ def test_run_ops_takes_empty_batches_as_the_single_calls_do():
     assert L.q8_run_ops(ops, 1, streams, 1) == 0
     o.d.N = 1                                  # not empty: the output is needed
     assert L.q8_run_ops(ops, 1, streams, 1) == -1
+
+
+def test_layer_calls_check_their_arguments():
+    """The extension module's checks are the binding's: device tensors, a descriptor, real factors."""
+    import torch
+    d = B.ConvDesc(1, 4, 4, 16, 16, 1, 1)
+    x = torch.zeros((1, 4, 4, 16), dtype=torch.int8)
+    calls = [lambda t, desc=d, q=1.0: B.conv_int8(desc, t, t, t, q, 1.0, 1.0, out=x),
+             lambda t, desc=d, q=1.0: B.conv_u8(desc, 1, 1, 0, t, t, t, None, q, 1.0, 1.0, out=x),
+             lambda t, desc=d, q=1.0: B.conv_int8_per_channel(desc, t, t, t, t, q, out=x),
+             lambda t, desc=d, q=1.0: B.conv_int8_real_output(desc, t, t, t, q, 1.0, out=x)]
+    for call in calls:
+        for t in (x, torch.nn.Parameter(x, requires_grad=False)):
+            with pytest.raises(AssertionError):
+                call(t)                                   # not on the device
+        with pytest.raises(TypeError):
+            call(None, desc="no descriptor")
+        with pytest.raises(TypeError):
+            call(None, q="no factor")
+    with pytest.raises(AssertionError):
+        B.conv_f32_observed(d, x.float(), None, None, None, None, None, None)
+    for f in (B._q8call.conv_int8, B._q8call.conv_u8, B._q8call.conv_per_channel, B._q8call.conv_real, B._q8call.conv_f32):
+        with pytest.raises(TypeError):
+            f(d)

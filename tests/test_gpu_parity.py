@@ -1767,6 +1767,38 @@ def test_calibrate_fold(B, n_keys, n_slots):
     assert torch.equal(out, spread.view(n_keys, n_slots, B.SLOT_STRIDE)[..., 0].amax(1))
 
 
+def test_layer_calls_take_what_they_took(B):
+    """Layer calls with tensors of a subclass, factors that are numpy numbers, a second stream; what is
+    not contiguous, of another type or refused by the library raises."""
+    rng = np.random.default_rng(3)
+    d = B.ConvDesc(2, 9, 9, 64, 48, 3, 3, pad_h=1, pad_w=1, relu=1)
+    x = dev(rng.integers(-128, 128, (2, 9, 9, 64)).astype(np.int8))
+    w = B.pack_weights(d, dev(rng.integers(-128, 128, (48, 3, 3, 64)).astype(np.int8)))
+    b = dev(rng.integers(-2000, 2000, 48).astype(np.int32))
+    want = B.conv_int8(d, x, w, b, 0.01, 0.01, 0.5)
+    as_param = lambda t: torch.nn.Parameter(t, requires_grad=False)
+    f = np.float32
+    assert torch.equal(B.conv_int8(d, as_param(x), as_param(w), as_param(b), f(0.01), f(0.01), f(0.5)), want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        got = B.conv_int8(d, x, w, b, 0.01, 0.01, 0.5)
+    side.synchronize()
+    assert torch.equal(got, want)
+    assert B.conv_int8_real_output(d, x, w.view(torch.uint8), b, 0.01, 0.01).dtype is torch.float32
+    for bad in (lambda: B.conv_int8(d, x.transpose(1, 2), w, b, 0.01, 0.01, 0.5),
+                lambda: B.conv_int8(d, x, w, b.float(), 0.01, 0.01, 0.5),
+                lambda: B.conv_int8(d, x, w, b, 0.01, 0.01, 0.5, out=want.cpu())):
+        with pytest.raises(AssertionError):
+            bad()
+    with pytest.raises(B.Q8Error):
+        B.conv_int8(d, x, w, b, 0.0, 0.01, 0.5)
+    with pytest.raises(B.Q8Error):
+        B.conv_int8(d, None, w, b, 0.01, 0.01, 0.5, out=want)
+    empty = B.ConvDesc(0, 9, 9, 64, 48, 3, 3, pad_h=1, pad_w=1)
+    assert B.conv_int8(empty, x[:0], w, None, 0.01, 0.01, 0.5).shape == (0, 9, 9, 48)
+
+
 # tensors that the tiled builds' 32-bit offsets cannot reach into, by a dilation that leaves one row of
 # taps inside the image, and one as tall as the dilation with all three rows in use
 @pytest.mark.parametrize("H,W,C,K,S,slice_", [(9, 7, 24, 21, 3, (30, 4)), (2**20 + 37, 1, 64, 4, 1, (0, 0))])
