@@ -133,7 +133,10 @@ int pick_halo3(const q8_conv_desc* d) {
     if (d->W > s.max_w || (s.bc == 128 && d->K <= 64)) continue;
     const long tiles = ((M + s.bp - 1) / s.bp) * ((d->K + s.bc - 1) / s.bc);
     // (the 64 x 64 tile inside a network, its filters coming from HBM: a ring of nine slabs)
-    if (tiles >= 360) return s.index == 6 ? 11 : s.index;
+    // Between 256 and 360 of those tiles no two-group workgroups either (below): one fills a CU's LDS,
+    // and the tiles beyond 256 are a second round (28 x 28 x 128 at batch 13, 320 tiles: 8.9 us by two
+    // groups, 6.4 by one; ResNet-50 13 images 364 -> 354 us, unsigned 394 -> 384, 48 images 624 -> 603).
+    if (tiles >= 360 || (s.index == 6 && tiles > 256)) return s.index == 6 ? 11 : s.index;
     smallest = s.index;
   }
   // Down at the 64 x 64 tile there are at most a tile or two per CU and a tile's time is its
