@@ -133,19 +133,19 @@ int pick_halo3(const q8_conv_desc* d) {
     if (d->W > s.max_w || (s.bc == 128 && d->K <= 64)) continue;
     const long tiles = ((M + s.bp - 1) / s.bp) * ((d->K + s.bc - 1) / s.bc);
     // (the 64 x 64 tile inside a network, its filters coming from HBM: a ring of nine slabs)
-    // Between 256 and 360 of those tiles no two-group workgroups either (below): one fills a CU's LDS,
-    // and the tiles beyond 256 are a second round (28 x 28 x 128 at batch 13, 320 tiles: 8.9 us by two
-    // groups, 6.4 by one; ResNet-50 13 images 364 -> 354 us, unsigned 394 -> 384, 48 images 624 -> 603).
-    if (tiles >= 360 || (s.index == 6 && tiles > 256)) return s.index == 6 ? 11 : s.index;
+    if (tiles >= 360) return s.index == 6 ? 11 : s.index;
     smallest = s.index;
   }
   // Down at the 64 x 64 tile there are at most a tile or two per CU and a tile's time is its
   // chain of reduction steps: with an even number of 64-channel chunks two groups of
   // wavefronts share the chain (builds 8 and 9 of the family's table), on 64 x 128 tiles
-  // where those still give most CUs one.
+  // where those still give most CUs one.  More than 256 tiles of 64 x 64 stay with one group: a
+  // two-group workgroup fills a CU's LDS, and the tiles beyond 256 would be a second round (28 x 28 x
+  // 128 at batch 13, 320 tiles: 8.9 us by two groups, 6.4 by one; ResNet-50 13 images 364 -> 354 us,
+  // unsigned 394 -> 384, 48 images 624 -> 603).
   if (smallest == 6 && d->C % 128 == 0) {
-    const long tiles_wide = ((M + 63) / 64) * ((d->K + 127) / 128);
-    return d->K > 64 && tiles_wide >= 192 ? 9 : 12;
+    const long tiles = ((M + 63) / 64) * ((d->K + 63) / 64), tiles_wide = ((M + 63) / 64) * ((d->K + 127) / 128);
+    return d->K > 64 && tiles_wide >= 192 ? 9 : tiles > 256 ? 11 : 12;
   }
   return smallest;
 }
