@@ -168,11 +168,11 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1) {
       return q8::first_stem_variant();
     return d->K <= 64 ? 8 : 4;   // short reduction: small tiles, many per CU
   }
-  // 3x3 / stride 1 / padding 1 on 64 channels with K <= 64 and many pixel tiles: persistent
-  // workgroups with every filter resident, on 8 x 16 blocks of the map (any width; also a
-  // little faster than the build on runs of 128 pixels where that one fits)
-  if (d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 &&
-      d->pad_w == 1 && d->dil_h == 1 && d->dil_w == 1 && d->C == 64 && d->K <= 64 &&
+  // 3x3 / stride 1 / padding 0 or 1 on 64 or 32 channels with K <= 64 and many pixel tiles: persistent
+  // workgroups with every filter in registers, on blocks of the map (any width; also a little faster
+  // than the build on runs of 128 pixels where that one fits)
+  if (d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == d->pad_w &&
+      d->pad_h <= 1 && d->dil_h == 1 && d->dil_w == 1 && (d->C == 64 || d->C == 32) && d->K <= 64 &&
       (d->K & 15) == 0 && (long)d->N * d->H * d->W >= 128L * 256)
     return q8::first_p3_variant() + 2;
   const int halo = pick_halo3(d);

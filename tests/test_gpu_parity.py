@@ -2129,3 +2129,40 @@ def test_conv_extended_builds(B, idx):
     got = B.conv_int8_per_channel(d, dev(x_s), packed, dev(b), dev(m), 1.0, None if res is None else dev(res_s), 0.4)
     acc = accumulate(x_s) if not image else acc
     assert np.array_equal(host(got), orc.requant_pc(acc, m, True, res_s, np.float32(0.4)))
+
+
+# the block-tiled 3x3 kernel: blocks that end inside the map in both directions, one row and one column,
+# padding 0 and 1, 32 and 64 channels in, 16 to 64 out (blocks of 16 x 16 up to 32), images of several
+# tiles and tiles beyond one per workgroup, slices; unsigned codes at the border
+P3B_CASES = [dict(N=1, H=1, W=1, C=32, K=16, pad_h=1, pad_w=1), dict(N=3, H=17, W=16, C=32, K=32, pad_h=1, pad_w=1),
+             dict(N=2, H=19, W=35, C=32, K=32, pad_h=0, pad_w=0), dict(N=2, H=9, W=33, C=32, K=48, pad_h=1, pad_w=1),
+             dict(N=2, H=10, W=18, C=32, K=64, pad_h=0, pad_w=0), dict(N=1, H=1, W=40, C=64, K=64, pad_h=1, pad_w=1),
+             dict(N=2, H=23, W=17, C=64, K=16, pad_h=0, pad_w=0), dict(N=61, H=50, W=49, C=32, K=32, pad_h=1, pad_w=1),
+             dict(N=40, H=47, W=50, C=32, K=64, pad_h=1, pad_w=1)]
+
+
+@pytest.mark.parametrize("idx", range(len(P3B_CASES)))
+def test_conv_block_tiles(B, idx):
+    geom = dict(P3B_CASES[idx], R=3, S=3)
+    names = [B.lib.q8_conv_variant_name(v).decode() for v in range(B.conv_num_variants())]
+    v = names.index("conv_i8_p3b_kernel")
+    _run_conv_case(B, geom, relu=bool(idx % 2), with_res=False, with_bias=idx % 3 != 0, seed=70 + idx, variant=v,
+                   out_pad=16 * (idx % 3), out_off=16 * (idx % 3 == 2), dump_acc=False)
+    d = B.ConvDesc(relu=1, **geom)
+    if d.N * d.H * d.W < 32768 or d.K <= 32:
+        return
+    assert B.conv_variant(d) == "conv_i8_p3b_kernel"
+    rng = np.random.default_rng(idx)
+    x = rng.integers(0, 256, (d.N, d.H, d.W, d.C)).astype(np.uint8)
+    w = rng.integers(-128, 128, (d.K, 3, 3, d.C)).astype(np.int8)
+    b = rng.integers(-20000, 20000, d.K).astype(np.int32)
+    taps, bias = B.u8_prepare(d, dev(w), dev(b))
+    got = host(B.conv_u8(d, 1, 1, 0, dev(_stored(x)), B.pack_weights(d, dev(w)), bias, taps, 1.0, 1e-4, 1.0))
+    xs = torch.nn.functional.pad(dev(x).float().permute(0, 3, 1, 2), (1, 1, 1, 1))
+    acc = torch.zeros((d.N, d.H, d.W, d.K), dtype=torch.float64, device="cuda") + dev(b).double()
+    for r in range(3):                 # sums of 288 products of at most 255 * 128: exact in fp64
+        for s in range(3):
+            part = xs[:, :, r:r + d.H, s:s + d.W].permute(0, 2, 3, 1).reshape(-1, d.C).double()
+            acc += (part @ dev(w)[:, r, s].double().t().contiguous()).view(acc.shape)
+    want = (acc.float() * torch.tensor(np.float32(np.float32(1.0) * np.float32(1e-4))).cuda()).round().clamp(0, 255)
+    assert np.array_equal(got.astype(int) + 128, host(want.int()))
