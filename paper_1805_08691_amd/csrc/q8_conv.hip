@@ -150,6 +150,25 @@ int pick_halo3(const q8_conv_desc* d) {
   return smallest;
 }
 
+// Pointwise layers on few channels: persistent workgroups (q8_conv_pw_kernel.h) with the filters of a
+// channel tile in LDS, as soon as there are tiles of 128 pixels x 64 channels for more than one per CU
+// (us, the ring build that came before -> this family): 64 -> 64 on 40768 pixels 4.7 -> 4.0, 64 -> 512
+// 11.0 -> 8.6, 128 -> 128 5.8 -> 5.1, 128 -> 512 12.0 -> 9.6; with 196 tiles 3.9 -> 4.0.  Tiles of 128
+// channels read the pixels half as often and leave one workgroup per CU: from 2400 tiles on (128 -> 512 on
+// 200704 pixels 32.6 and 29.7, on 25088 8.0 and 8.4).  256 channels leave little LDS for anything else:
+// only the largest layers (256 -> 512 on 94080 pixels 32.9 -> 26.9, with a residual 37.5 -> 35.3; 256 ->
+// 256 with a residual 20.1 and 21.1).  A layer the build cannot take -- odd strides, a dump of the
+// accumulators, real outputs -- goes on to the general kernel.  -1: not one of these.
+int pick_pointwise(const q8_conv_desc* d) {
+  if (d->R * d->S != 1 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != 0 || d->pad_w != 0 ||
+      (d->K & 15) != 0)
+    return -1;
+  const long tiles = (((long)d->N * d->H * d->W + 127) / 128) * ((d->K + 63) / 64);
+  if (d->C == 256) return d->K >= 256 && tiles >= 4000 ? 5 : -1;
+  if ((d->C != 64 && d->C != 128) || tiles < 320) return -1;
+  return d->C == 64 ? 0 : d->K >= 256 && tiles >= 2400 ? 3 : 2;
+}
+
 // Among the tiled kernels.  `forced`: -1, or a variant of the main kernel to use where that kernel
 // is applicable.
 int pick_tiled(const q8_conv_desc* d, int forced = -1) {
@@ -178,11 +197,8 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1) {
   const int halo = pick_halo3(d);
   if (halo >= 0) return q8::num_ring_variants() + halo;
   const int red = d->R * d->S * d->C;
-  // pointwise layers on 64 channels with many pixel tiles: persistent workgroups (a layer the
-  // build cannot take -- odd strides, a dump of the accumulators -- goes to the generic kernel)
-  if (d->R * d->S == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0 &&
-      d->C == 64 && (d->K & 15) == 0 && (long)d->N * d->H * d->W >= 128L * 512)
-    return q8::first_pw_variant();
+  const int pw = pick_pointwise(d);
+  if (pw >= 0) return q8::first_pw_variant() + pw;
   const int nk = (red + 63) / 64;     // reduction steps of 64 bytes
   const long M = (long)d->N * out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h) *
                  out_extent(d->W, d->pad_w, d->dil_w, d->S, d->stride_w);
@@ -238,6 +254,9 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
   int bp = 0, bc = 0;
   float tiled_us = 0.0f;
   if (est_us) *est_us = 3.0f + (float)M * (float)d->K * (float)red_len * 1.1e-9f;   // ~ 1.8 POP/s
+  // (the pointwise family: its bytes at 5.3 TB/s, or 1.1 POP/s)
+  if (est_us && tiled >= first_pw && tiled < q8::first_split_variant())
+    *est_us = 3.2f + (float)M * fmaxf((float)(d->C + d->K) * 1.9e-7f, (float)d->K * (float)red_len * 1.75e-9f);
   if (tiled >= first_pw) return tiled;
   if (tiled >= first_halo) {
     q8::halo_variant_tile(tiled - first_halo, &bp, &bc);

@@ -18,6 +18,11 @@ int halo_ext(ConvParams& p, hipStream_t stream) {
   return Q8_EUNSUPPORTED;
 }
 
+template <int TC, int KS>
+int pw_ext(ConvParams& p, hipStream_t stream) {
+  return pw_applicable<TC, KS>(p) ? launch_pw<TC, KS, 1>(p, stream) : Q8_EUNSUPPORTED;
+}
+
 }  // namespace
 
 // `family`: the variant's number inside its family.  Q8_EUNSUPPORTED, with nothing launched: there
@@ -40,7 +45,13 @@ int launch_p3_ext(int family, ConvParams& p, hipStream_t stream) {
   return family == 2 && p3b_applicable(p) ? launch_p3b<1>(p, stream) : Q8_EUNSUPPORTED;
 }
 int launch_pw_ext(int family, ConvParams& p, hipStream_t stream) {
-  return family == 0 && pw_applicable<1, 1>(p) ? launch_pw<1, 1, 1>(p, stream) : Q8_EUNSUPPORTED;
+  switch (family) {     // the order of q8_conv_pw.hip's table
+    case 0: return pw_ext<1, 1>(p, stream);
+    case 2: return pw_ext<1, 2>(p, stream);
+    case 3: return pw_ext<2, 2>(p, stream);
+    case 5: return pw_ext<2, 4>(p, stream);
+    default: return Q8_EUNSUPPORTED;
+  }
 }
 
 }  // namespace q8

@@ -8,7 +8,7 @@ namespace {
 template <int TC, int KS>
 int launch_pw_or_generic(ConvParams& p, hipStream_t stream) {
   if (pw_applicable<TC, KS>(p)) return launch_pw<TC, KS, 0>(p, stream);
-  return launch_ring<2, 2, 2, 2, 64, 3, 0>(p, stream);
+  return launch_ring<2, 2, 2, 1, 64, 2, 0>(p, stream);
 }
 
 struct PwVariant {

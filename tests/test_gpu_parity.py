@@ -2166,3 +2166,36 @@ def test_conv_block_tiles(B, idx):
             acc += (part @ dev(w)[:, r, s].double().t().contiguous()).view(acc.shape)
     want = (acc.float() * torch.tensor(np.float32(np.float32(1.0) * np.float32(1e-4))).cuda()).round().clamp(0, 255)
     assert np.array_equal(got.astype(int) + 128, host(want.int()))
+
+
+# the pointwise family by its rule, plain and extended: from the first size at which it is taken (320 tiles),
+# at both tiles of 128 channels in, a last tile of one pixel, channel counts that end inside a tile
+PW_RULE_CASES = [("<1,1>", (1, 1, 40833, 64, 64)), ("<1,2>", (2, 91, 113, 128, 80)), ("<2,2>", (1, 1, 61441, 128, 272)),
+                 ("<2,4>", (1, 1, 128129, 256, 256))]
+
+
+@pytest.mark.parametrize("build,size", PW_RULE_CASES)
+@pytest.mark.parametrize("with_res", [False, True])
+def test_conv_pointwise_rule(B, build, size, with_res):
+    n, h, w_, c, k = size
+    d = B.ConvDesc(N=n, H=h, W=w_, C=c, K=k, R=1, S=1, relu=1)
+    assert B.conv_variant(d) == "conv_i8_pw_kernel" + build
+    if build == "<1,1>":
+        assert "pw" not in B.conv_variant(B.ConvDesc(N=1, H=1, W=319 * 128, C=c, K=k, R=1, S=1))
+    rng = np.random.default_rng(c + k + with_res)
+    x = rng.integers(-128, 128, (n, h, w_, c)).astype(np.int8)
+    w = rng.integers(-128, 128, (k, 1, 1, c)).astype(np.int8)
+    b = rng.integers(-20000, 20000, k).astype(np.int32)
+    r = rng.integers(-128, 128, (n, h, w_, k)).astype(np.int8) if with_res else None
+    # whole numbers below 2^24: exact in fp32
+    acc = (x.reshape(-1, c).astype(np.float32) @ w.reshape(k, c).T.astype(np.float32)).astype(np.int32) + b
+    acc = acc.reshape(n, h, w_, k)
+    m = (np.float32(60.0 / (74.0 * 74.0 * np.sqrt(c))) * rng.uniform(0.3, 3.0, k)).astype(np.float32)
+    got = B.conv_int8_per_channel(d, dev(x), B.pack_weights(d, dev(w)), dev(b), dev(m), 1.0,
+                                  None if r is None else dev(r), 0.4)
+    assert np.array_equal(host(got), orc.requant_pc(acc, m, True, r, np.float32(0.4)))
+    got = B.conv_int8(d, dev(x), B.pack_weights(d, dev(w)), dev(b), 0.01, 0.01, 0.5,
+                      None if r is None else dev(r), 0.2 if with_res else 0.0)
+    one = np.full(k, orc.requant_scale(np.float32(0.01), np.float32(0.01), np.float32(0.5)), np.float32)
+    m_r = orc.residual_scale(np.float32(0.2), np.float32(0.5))
+    assert np.array_equal(host(got), orc.requant_pc(acc, one, True, r, m_r))
