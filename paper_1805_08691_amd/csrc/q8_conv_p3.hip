@@ -13,9 +13,11 @@ int launch_p3_or_generic(ConvParams& p, hipStream_t stream) {
   return launch_ring<2, 2, 2, 2, 64, 3, 0>(p, stream);
 }
 
+// (a residual, real outputs, rows that are not aligned: the general kernel's choice for K <= 64; with a
+// residual 32 -> 64 on 147 x 147 x 16 takes 22.4 us on 128 x 64 tiles and 31.5 on 128 x 128)
 int launch_p3b_or_generic(ConvParams& p, hipStream_t stream) {
   if (p3b_applicable(p)) return launch_p3b<0>(p, stream);
-  return launch_ring<2, 2, 2, 2, 64, 3, 0>(p, stream);
+  return launch_ring<2, 2, 2, 1, 64, 2, 0>(p, stream);
 }
 
 struct P3Variant {

@@ -96,7 +96,10 @@ int launch_stream_variant(int variant, ConvParams& p, hipStream_t stream) {
     int rc = Q8_EUNSUPPORTED;
     if (variant >= first_stem_variant())
       rc = launch_stem_variant(variant - first_stem_variant(), p, stream);
-    else if (variant >= first_p3_variant()) rc = launch_p3_ext(variant - first_p3_variant(), p, stream);
+    else if (variant >= first_p3_variant()) {
+      rc = launch_p3_ext(variant - first_p3_variant(), p, stream);
+      variant = 8;                                 // (what such layers have without this family)
+    }
     else if (variant >= first_split_variant()) {}
     else if (variant >= first_pw_variant()) {
       rc = launch_pw_ext(variant - first_pw_variant(), p, stream);

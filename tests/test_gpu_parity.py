@@ -2199,3 +2199,27 @@ def test_conv_pointwise_rule(B, build, size, with_res):
     one = np.full(k, orc.requant_scale(np.float32(0.01), np.float32(0.01), np.float32(0.5)), np.float32)
     m_r = orc.residual_scale(np.float32(0.2), np.float32(0.5))
     assert np.array_equal(host(got), orc.requant_pc(acc, one, True, r, m_r))
+
+
+@pytest.mark.parametrize("C,pad", [(32, 1), (64, 0)])
+def test_conv_block_tiles_with_a_residual(B, C, pad):
+    """A layer that the block-tiled kernel is chosen for by its sizes but cannot take: the general kernel,
+    plain and with per-channel scales."""
+    d = B.ConvDesc(N=3, H=131, W=97, C=C, K=48, R=3, S=3, pad_h=pad, pad_w=pad, relu=1)
+    assert B.conv_variant(d) == "conv_i8_p3b_kernel"
+    rng = np.random.default_rng(C + pad)
+    x = rng.integers(-128, 128, (d.N, d.H, d.W, C)).astype(np.int8)
+    w = rng.integers(-128, 128, (d.K, 3, 3, C)).astype(np.int8)
+    b = rng.integers(-20000, 20000, d.K).astype(np.int32)
+    r = rng.integers(-128, 128, (d.N, d.Ho, d.Wo, d.K)).astype(np.int8)
+    acc = torch.nn.functional.conv2d(          # whole numbers below 2^24: exact in fp32
+        torch.from_numpy(x.astype(np.float32)).permute(0, 3, 1, 2),
+        torch.from_numpy(w.astype(np.float32)).permute(0, 3, 1, 2), padding=pad)
+    acc = acc.permute(0, 2, 3, 1).contiguous().numpy().astype(np.int32) + b
+    packed = B.pack_weights(d, dev(w))
+    m = (np.float32(60.0 / (74.0 * 74.0 * np.sqrt(9 * C))) * rng.uniform(0.3, 3.0, d.K)).astype(np.float32)
+    got = B.conv_int8_per_channel(d, dev(x), packed, dev(b), dev(m), 1.0, dev(r), 0.4)
+    assert np.array_equal(host(got), orc.requant_pc(acc, m, True, r, np.float32(0.4)))
+    got = B.conv_int8(d, dev(x), packed, dev(b), 0.01, 0.01, 0.5, dev(r), 0.2)
+    one = np.full(d.K, orc.requant_scale(0.01, 0.01, 0.5), np.float32)
+    assert np.array_equal(host(got), orc.requant_pc(acc, one, True, r, orc.residual_scale(0.2, 0.5)))
