@@ -401,20 +401,27 @@ bool f32_desc_sane(const q8_conv_desc* d) {
          d->pad_w >= 0 && d->dil_h >= 1 && d->dil_w >= 1;
 }
 
+// Bytes that one tile of at most 256 pixels can reach: its images and the padding rows around them.
+long f32_reach(const q8_conv_desc* d, long per_img) {
+  return (255 / per_img + 2) * ((long)d->H * d->W * d->C * 4) +
+         ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + (long)d->S * d->dil_w) * d->C * 4;
+}
+
 // Whether the tiled kernel's 32-bit offsets reach everything it addresses.
 bool f32_tiled(const q8_conv_desc* d, long M, long per_img) {
-  const long rsc = (long)d->R * d->S * d->C, img = (long)d->H * d->W * d->C * 4;
-  // what one tile of at most 256 pixels can reach: its images and the padding around them
-  const long reach = (255 / per_img + 2) * img +
-                     ((long)d->R * d->dil_h + d->pad_h + 1) * ((long)d->W + (long)d->S * d->dil_w) * d->C * 4;
-  return !(M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || reach > 0x7fffffffL || d->H > (1 << 28) ||
-           (long)d->R * d->dil_h > (1 << 28));
+  const long rsc = (long)d->R * d->S * d->C;
+  return !(M > 0x7fffff00L || rsc * d->K * 4 > 0x7fffffffL || f32_reach(d, per_img) > 0x7fffffffL ||
+           d->H > (1 << 28) || (long)d->R * d->dil_h > (1 << 28));
 }
 
 // Whether the builds on LDS take the layer: whole 128-byte pieces of a tap, whole groups of a lane's
-// channels, output (residual, bias) rows of 16-byte accesses.
-bool f32_lds_takes(const q8_conv_desc* d, int out_cs, int out_off) {
-  return d->C % 32 == 0 && d->K % 16 == 0 && out_cs % 4 == 0 && out_off % 4 == 0;
+// channels, output (residual, bias) rows of 16-byte accesses.  Their descriptor starts at the image's
+// first tap, pad_h rows and pad_w pixels in front of it, so the padding has to fit the 32-bit offsets
+// on both sides of the map, its columns too, which the other builds do not count (in a descriptor of
+// more than 2^31 - 1 bytes the out-of-range offset would lie inside).
+bool f32_lds_takes(const q8_conv_desc* d, long per_img, int out_cs, int out_off) {
+  return d->C % 32 == 0 && d->K % 16 == 0 && out_cs % 4 == 0 && out_off % 4 == 0 &&
+         f32_reach(d, per_img) + ((long)d->pad_h * d->W + 2L * d->pad_w) * d->C * 4 <= 0x7fffffffL;
 }
 
 int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float* b, const float* res,
@@ -446,7 +453,7 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.M = (int)M; p.rsc = d->R * d->S * d->C;
   p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
   p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
-  if (f32_lds_takes(d, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16))
+  if (f32_lds_takes(d, per_img, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16))
     return launch_f32_lds(pick_f32_lds(M, d->K, p.rsc), p, stream);
   return kF32Builds[pick_f32(M, d->K)].launch(p, stream);
 }
@@ -494,7 +501,7 @@ const char* q8_conv_f32_variant(const q8_conv_desc* d) {
   if (!q8::f32_desc_sane(d)) return "unsupported";
   const long per_img = (long)q8_conv_out_h(d) * q8_conv_out_w(d), M = d->N * per_img;
   if (M > 0 && !q8::f32_tiled(d, M, per_img)) return "conv_f32_any_kernel";
-  if (M > 0 && q8::f32_lds_takes(d, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off))
+  if (M > 0 && q8::f32_lds_takes(d, per_img, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off))
     return q8::f32_lds_name(q8::pick_f32_lds(M, d->K, d->R * d->S * d->C));
   const q8::F32Build& b = q8::kF32Builds[q8::pick_f32(M, d->K)];
   return b.name[d->C % (16 * b.nc) == 0 ? 2 : d->C % 4 == 0 ? 1 : 0];

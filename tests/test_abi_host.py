@@ -325,3 +325,17 @@ def test_layer_calls_check_their_arguments():
     for f in (B._q8call.conv_int8, B._q8call.conv_u8, B._q8call.conv_per_channel, B._q8call.conv_real, B._q8call.conv_f32):
         with pytest.raises(TypeError):
             f(d)
+
+
+def test_fp32_builds_on_lds_leave_wide_paddings_alone():
+    """Their descriptor starts pad_h rows and pad_w pixels in front of the image: a padding that 32 bits
+    do not hold goes to the register-fed builds, by the columns as by the rows."""
+    name = lambda **kw: B.conv_f32_variant(B.ConvDesc(1, 1, 8, 1024, 16, 1, 1, **kw))
+    assert name().startswith("conv_f32_lds_kernel")
+    assert name(pad_w=1000).startswith("conv_f32_lds_kernel")
+    span = 2 * 8 * 4096 + 2 * 9 * 4096      # two images, and two rows of the map and a tap
+    fits = (2**31 - 1 - span) // (2 * 4096)
+    assert name(pad_w=fits).startswith("conv_f32_lds_kernel")
+    for pad in (fits + 1, 2**19 - 1, 2**19, 600000, 2**20):      # 2^19 pixels of 4 KB: the shift's sign
+        assert name(pad_w=pad).startswith("conv_f32_mfma_kernel"), pad
+    assert name(pad_h=2**15).startswith(("conv_f32_mfma_kernel", "conv_f32_any_kernel"))
