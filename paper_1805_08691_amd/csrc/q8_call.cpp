@@ -48,12 +48,18 @@ struct Args {
     if (!ok || a[i] == Py_None) return nullptr;
     if (Py_TYPE(a[i]) == (PyTypeObject*)THPVariableClass) {
       const at::Tensor& t = THPVariable_Unpack(a[i]);
-      if (t.is_cuda() && t.is_contiguous() && (type == at::ScalarType::Undefined || t.scalar_type() == type)) {
-        if (elements) *elements = t.numel();
-        return static_cast<T*>(t.mutable_data_ptr());
+      try {
+        if (t.is_cuda() && t.has_storage() && t.is_contiguous() &&
+            (type == at::ScalarType::Undefined || t.scalar_type() == type)) {
+          T* const p = static_cast<T*>(t.mutable_data_ptr());
+          if (elements) *elements = t.numel();
+          return p;
+        }
+      } catch (...) {        // (none may leave through the interpreter's frames)
       }
     }
-    // (the binding's own checks, and their exceptions)
+    // The binding's own checks, and their exceptions: also for tensors of that type without storage,
+    // as a function under vmap, grad or functionalize sees them.
     PyObject* address = PyObject_CallFunctionObjArgs(g_ptr, a[i], dtype, nullptr);
     void* p = address ? PyLong_AsVoidPtr(address) : nullptr;
     Py_XDECREF(address);

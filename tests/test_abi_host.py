@@ -327,6 +327,32 @@ def test_layer_calls_check_their_arguments():
             f(d)
 
 
+def test_layer_calls_raise_for_tensors_without_storage():
+    """Under vmap a tensor is of exactly torch.Tensor's type, on the device and contiguous, and has no
+    address: an exception, as from the binding's own check, and the process goes on."""
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    d = B.ConvDesc(1, 4, 4, 16, 16, 1, 1)
+    calls = [lambda t: B.conv_int8(d, t, t, None, 1.0, 1.0, 1.0),
+             lambda t: B.conv_u8(d, 1, 1, 0, t, t, None, None, 1.0, 1.0, 1.0),
+             lambda t: B.conv_int8_per_channel(d, t, t, None, None, 1.0),
+             lambda t: B.conv_int8_real_output(d, t, t, None, 1.0, 1.0),
+             lambda t: B.conv_f32_observed(d, t.float(), None, None, None, None, None, None)]
+    seen = []
+
+    def body(t, call):
+        assert type(t) is torch.Tensor and t.is_cuda and t.is_contiguous()
+        with pytest.raises(RuntimeError, match="storage"):
+            call(t)
+        seen.append(call)
+        return t
+    with FakeTensorMode():                      # (device tensors without a device)
+        batch = torch.empty((3, 1, 4, 4, 16), dtype=torch.int8, device="cuda")
+        for call in calls:
+            torch.vmap(lambda t: body(t, call))(batch)
+    assert len(seen) == 5
+
+
 def test_fp32_builds_on_lds_leave_wide_paddings_alone():
     """Their descriptor starts pad_h rows and pad_w pixels in front of the image: a padding that 32 bits
     do not hold goes to the register-fed builds, by the columns as by the rows."""
