@@ -82,8 +82,10 @@ struct Args {
   }
   int flag(int i) {
     if (!ok) return 0;
-    const int v = PyObject_IsTrue(a[i]);
-    if (v < 0) ok = false;
+    PyObject* n = PyNumber_Long(a[i]);      // as int() takes it
+    const int v = n ? (int)PyLong_AsUnsignedLongMask(n) : 0;
+    Py_XDECREF(n);
+    if (PyErr_Occurred()) ok = false;
     return v;
   }
   void* stream() {

@@ -353,6 +353,13 @@ def test_layer_calls_raise_for_tensors_without_storage():
     assert len(seen) == 5
 
 
+def test_layer_calls_take_flags_as_int_does():
+    d = B.ConvDesc(1, 4, 4, 16, 16, 1, 1)
+    for bad in (None, "no number", []):
+        with pytest.raises((TypeError, ValueError)):
+            B._q8call.conv_u8(d, bad, 0, 0, *[None] * 4, 1.0, 1.0, 1.0, None, 0.0, None, None)
+
+
 def test_fp32_builds_on_lds_leave_wide_paddings_alone():
     """Their descriptor starts pad_h rows and pad_w pixels in front of the image: a padding that 32 bits
     do not hold goes to the register-fed builds, by the columns as by the rows."""
