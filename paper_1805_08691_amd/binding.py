@@ -549,13 +549,13 @@ def conv_f32_variant(desc):
 SLOT_STRIDE = 32         # values between the copies of a spread maximum (a cache line)
 
 
-def conv_f32_observed(desc, x, w, b, res, out, maxabs_sum, maxabs_out):
+def conv_f32_observed(desc, x, w, b, res, out, maxabs_sum, maxabs_out, copies=1):
     """conv_f32_ref into a channel slice of ``out``, with the running max-abs of the value before
-    the residual sum and of the output (fp32 device tensors or None: of one value, or of n *
-    SLOT_STRIDE values that hold n copies, see calibrate_fold)."""
-    sizes = {(m.numel() + SLOT_STRIDE - 1) // SLOT_STRIDE for m in (maxabs_sum, maxabs_out) if m is not None}
-    assert len(sizes) <= 1, "as many copies of one maximum as of the other"
-    _check(_q8call.conv_f32(desc, x, w, b, res, out, maxabs_sum, maxabs_out, max(sizes, default=1)))
+    the residual sum and of the output (fp32 device tensors or None): their first value, or
+    ``copies`` of them SLOT_STRIDE values apart, of which the largest counts (see calibrate_fold)."""
+    for m in (maxabs_sum, maxabs_out) if copies > 1 else ():
+        assert m is None or m.numel() > (copies - 1) * SLOT_STRIDE, "room for every copy"
+    _check(_q8call.conv_f32(desc, x, w, b, res, out, maxabs_sum, maxabs_out, copies))
     return out
 
 

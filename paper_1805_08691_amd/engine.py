@@ -21,6 +21,7 @@ from . import binding as B
 
 P_ACT = 7
 P_W = 7
+MAX_COPIES = 16       # copies of a maximum of calibration: a launch's atomics do not queue on one address
 
 
 def _pad_c(c):
@@ -241,8 +242,9 @@ class Engine:
         return self._forward_f32(x, None, observe)
 
     def _forward_f32(self, x, slot, observe=None):
-        """The fp32 forward.  With ``slot`` (device tensors by key, see conv_f32_observed) it leaves the running
-        max-abs of every tensor there and keeps no tensor longer than it is read: a convolution
+        """The fp32 forward.  With ``slot`` (device tensors of MAX_COPIES copies by key, see
+        conv_f32_observed) it leaves the running max-abs of every tensor there and keeps no tensor longer
+        than it is read: a convolution
         takes the maxima of its own output and of its value before a fused sum while it holds
         them; a stand-alone pooling keeps its input's factor and is not measured."""
         net, N = self.net, x.shape[0]
@@ -284,7 +286,8 @@ class Engine:
                     observe(branch, B.conv_f32_ref(desc, t[op.src], Wf, bf))
                     desc.relu = int(op.relu)
                 B.conv_f32_observed(desc, t[op.src], Wf, bf, t[op.res] if op.res else None, out,
-                                    slot[branch] if op.res and slot else None, observed)
+                                    slot[branch] if op.res and slot else None, observed,
+                                    MAX_COPIES if slot else 1)
             if slot and last_write[op.dst] == i and slices.get(op.dst, (False,))[0]:
                 B.calibrate_maxabs(out, slot[op.dst][:1])
             t[op.dst] = out
@@ -330,8 +333,7 @@ class Engine:
                 keys.append(op.name + ":branch")
             if op.dst not in keys:
                 keys.append(op.dst)
-        # sixteen copies of every maximum, so that a launch's atomics do not queue on one address
-        spread = torch.zeros((len(keys), 16 * B.SLOT_STRIDE), dtype=torch.float32, device=self.dev)
+        spread = torch.zeros((len(keys), MAX_COPIES * B.SLOT_STRIDE), dtype=torch.float32, device=self.dev)
         slot = dict(zip(keys, spread))
         n_batches = 0
         for x in batches:

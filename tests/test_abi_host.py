@@ -360,6 +360,20 @@ def test_layer_calls_take_flags_as_int_does():
             B._q8call.conv_u8(d, bad, 0, 0, *[None] * 4, 1.0, 1.0, 1.0, None, 0.0, None, None)
 
 
+def test_a_long_slot_is_one_maximum_unless_copies_are_asked_for(monkeypatch):
+    import torch
+    seen = []
+    monkeypatch.setattr(B._q8call, "conv_f32", lambda *a: seen.append(a[-1]) or 0)
+    slot = lambda n: torch.empty(n, device="meta")
+    for a, b in ((1, 1), (33, 1), (None, 512), (40, 40), (0, 1)):
+        B.conv_f32_observed(*[None] * 6, *(None if n is None else slot(n) for n in (a, b)))
+    assert seen == [1] * 5
+    B.conv_f32_observed(*[None] * 6, slot(33), slot(64), 2)
+    assert seen[5:] == [2]
+    with pytest.raises(AssertionError):
+        B.conv_f32_observed(*[None] * 6, slot(33), slot(32), 2)
+
+
 def test_fp32_builds_on_lds_leave_wide_paddings_alone():
     """Their descriptor starts pad_h rows and pad_w pixels in front of the image: a padding that 32 bits
     do not hold goes to the register-fed builds, by the columns as by the rows."""

@@ -1742,7 +1742,7 @@ def test_conv_f32_lds_builds(B, build, geom, res, slice_):
     bound = (R * S * Cc + 4) * 2.0 ** -24 * (fp64(abs(x), abs(w), abs(b)) + (abs(r) if res else 0))
     spread = torch.zeros((2, 3 * B.SLOT_STRIDE), device="cuda")
     out = torch.full((N, desc.Ho, desc.Wo, slice_[0] or K), -7.0, device="cuda")
-    B.conv_f32_observed(desc, dev(x), dev(w), dev(b), dev(r) if res else None, out, spread[0], spread[1])
+    B.conv_f32_observed(desc, dev(x), dev(w), dev(b), dev(r) if res else None, out, spread[0], spread[1], 3)
     got, lo = host(out), slice_[1]
     assert np.all(abs(got[..., lo:lo + K] - want) <= bound)
     assert np.all(got[..., :lo] == -7) and np.all(got[..., lo + K:] == -7)
@@ -1757,6 +1757,23 @@ def test_conv_f32_lds_builds(B, build, geom, res, slice_):
     ref = host(B.conv_f32_ref(desc, dev(x), moved.view(w.shape), dev(b), dev(r) if res else None)) \
         if slice_ == (0, 0) else want
     assert np.all(abs(ref - want) <= bound)
+
+
+@pytest.mark.parametrize("channels", [(64, 64), (12, 8)])       # a build on LDS, a register-fed one
+def test_conv_f32_observed_raises_the_first_value_of_a_slot(B, channels):
+    """A slot of any length holds one maximum, in its first value, unless copies are asked for."""
+    c, k = channels
+    desc = B.ConvDesc(3, 19, 17, c, k, 3, 3, pad_h=1, pad_w=1)
+    x, w = torch.randn(3, 19, 17, c, device="cuda"), torch.randn(k, 3, 3, c, device="cuda")
+    out = torch.empty(3, 19, 17, k, device="cuda")
+    slots = [torch.zeros(n, device="cuda") for n in (1, 33, 40, 512)]
+    for a, b in zip(slots, slots[1:] + slots[:1]):            # of two lengths
+        a.zero_(), b.zero_()
+        B.conv_f32_observed(desc, x, w, None, None, out, a, b)
+        for m in (a, b):
+            assert float(m[0]) == float(out.abs().max()) and not m[1:].any()
+    with pytest.raises(AssertionError):
+        B.conv_f32_observed(desc, x, w, None, None, out, slots[1], None, 3)     # 33 values: two copies
 
 
 @pytest.mark.parametrize("n_keys,n_slots", [(1, 1), (3, 16), (130, 70)])
