@@ -29,6 +29,8 @@ void ring_variant_tile(int variant, int* bp, int* bc);
 void halo_variant_tile(int variant, int* bp, int* bc);
 int pick_direct(long M, int K, int red_len, float* us);
 bool direct_applicable(const ConvParams& p);
+bool p3_variant_takes(int variant, const ConvParams& p);
+bool pw_variant_takes(int variant, const ConvParams& p);
 int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us);
 int launch_stem_image(ConvParams& p, const StemImage& im, int pool, bool dry_run, hipStream_t stream);
 int first_split_variant();
@@ -157,8 +159,7 @@ int pick_halo3(const q8_conv_desc* d) {
 // channels read the pixels half as often and leave one workgroup per CU: from 2400 tiles on (128 -> 512 on
 // 200704 pixels 32.6 and 29.7, on 25088 8.0 and 8.4).  256 channels leave little LDS for anything else:
 // only the largest layers (256 -> 512 on 94080 pixels 32.9 -> 26.9, with a residual 37.5 -> 35.3; 256 ->
-// 256 with a residual 20.1 and 21.1).  A layer the build cannot take -- odd strides, a dump of the
-// accumulators, real outputs -- goes on to the general kernel.  -1: not one of these.
+// 256 with a residual 20.1 and 21.1).  -1: not one of these.
 int pick_pointwise(const q8_conv_desc* d) {
   if (d->R * d->S != 1 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != 0 || d->pad_w != 0 ||
       (d->K & 15) != 0)
@@ -170,8 +171,8 @@ int pick_pointwise(const q8_conv_desc* d) {
 }
 
 // Among the tiled kernels.  `forced`: -1, or a variant of the main kernel to use where that kernel
-// is applicable.
-int pick_tiled(const q8_conv_desc* d, int forced = -1) {
+// is applicable; `persistent`: with the families of persistent workgroups (3x3 blocks, pointwise).
+int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
   const int mode = conv_mode(d);
   const int tile = d->K > 64 ? 0 : d->K > 32 ? 1 : 2;      // 128x128, 256x64, 256x32
   if (!stream_capable(d)) return kRegBase + 3 * mode + tile;
@@ -190,14 +191,14 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1) {
   // 3x3 / stride 1 / padding 0 or 1 on 64 or 32 channels with K <= 64 and many pixel tiles: persistent
   // workgroups with every filter in registers, on blocks of the map (any width; also a little faster
   // than the build on runs of 128 pixels where that one fits)
-  if (d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == d->pad_w &&
+  if (persistent && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == d->pad_w &&
       d->pad_h <= 1 && d->dil_h == 1 && d->dil_w == 1 && (d->C == 64 || d->C == 32) && d->K <= 64 &&
       (d->K & 15) == 0 && (long)d->N * d->H * d->W >= 128L * 256)
     return q8::first_p3_variant() + 2;
   const int halo = pick_halo3(d);
   if (halo >= 0) return q8::num_ring_variants() + halo;
   const int red = d->R * d->S * d->C;
-  const int pw = pick_pointwise(d);
+  const int pw = persistent ? pick_pointwise(d) : -1;
   if (pw >= 0) return q8::first_pw_variant() + pw;
   const int nk = (red + 63) / 64;     // reduction steps of 64 bytes
   const long M = (long)d->N * out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h) *
@@ -241,8 +242,9 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1) {
 // steps fed at 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail; the 3x3 family
 // by its 64-channel chunks.  The persistent families are only chosen for sizes far above this.
 // ext: unsigned codes or per-channel scales (the extended builds).
-int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float* est_us = nullptr) {
-  const int tiled = pick_tiled(d, forced);
+int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float* est_us = nullptr,
+                 bool persistent = true) {
+  const int tiled = pick_tiled(d, forced, persistent);
   if (est_us)
     *est_us = 4.0f + (float)d->N * (float)d->H * (float)d->W * (float)d->K * (float)(d->R * d->S * d->C) * 2e-9f;
   if (forced >= 0 || tiled >= kRegBase || conv_mode(d) != 0) return tiled;
@@ -621,11 +623,22 @@ int conv_fill_op(const q8_op* o, ConvParams& p, bool* empty) {
                    static_cast<const int8_t*>(o->residual), o->q_res, y, nullptr, p, empty);
 }
 
+// Whether the layer can have what the sizes alone choose from the families of persistent workgroups.
+// They take no odd strides, no dump of the accumulators and no real outputs, the 3x3 blocks no
+// residual: such a layer is chosen for as if there were no such families (3x3, 32 -> 16 on 28 x 28 x 43
+// with a residual: 6.0 us on the one general build that the family fell back to, 4.3 in the latency
+// family; 32 -> 32 on 56 x 56 x 11 without padding 5.1 and 4.1).
+bool persistent_takes(const q8_conv_desc* d, const ConvParams& p) {
+  const int v = pick_tiled(d);
+  if (v >= first_p3_variant() && v < first_stem_variant()) return p3_variant_takes(v - first_p3_variant(), p);
+  return v < first_pw_variant() || v >= first_split_variant() || pw_variant_takes(v - first_pw_variant(), p);
+}
 // What one layer would be launched as on its own, and the estimate; launches it.
 int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
   *us = 0.0f;
-  const int v = pick_variant(d, is_extended(p), -1, us);
-  return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d) : v;
+  const bool persistent = persistent_takes(d, p);
+  const int v = pick_variant(d, is_extended(p), -1, us, persistent);
+  return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d, -1, persistent) : v;
 }
 // Whether a layer may join a group launch of the main kernel (plain codes only).  1: its tiled choice
 // is one of that kernel's small tiles; 2: it is the 3x3 family's smallest, 64 x 64 (a layer with a
@@ -634,7 +647,7 @@ int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
 // other families, tiles of 256 pixels).
 int ring_group_takes(const q8_conv_desc* d, const ConvParams& p) {
   if (is_extended(p) || conv_mode(d) != 0) return 0;
-  const int v = pick_tiled(d);
+  const int v = pick_tiled(d, -1, persistent_takes(d, p));
   if (v < num_ring_variants()) return v != 3 && v != 13 ? 1 : 0;
   if (v >= first_pw_variant()) return 0;
   int bp = 0, bc = 0;

@@ -13,8 +13,6 @@ int launch_p3_or_generic(ConvParams& p, hipStream_t stream) {
   return launch_ring<2, 2, 2, 2, 64, 3, 0>(p, stream);
 }
 
-// (a residual, real outputs, rows that are not aligned: the general kernel's choice for K <= 64; with a
-// residual 32 -> 64 on 147 x 147 x 16 takes 22.4 us on 128 x 64 tiles and 31.5 on 128 x 128)
 int launch_p3b_or_generic(ConvParams& p, hipStream_t stream) {
   if (p3b_applicable(p)) return launch_p3b<0>(p, stream);
   return launch_ring<2, 2, 2, 1, 64, 2, 0>(p, stream);
@@ -37,6 +35,9 @@ int num_p3_variants() { return kNumP3Variants; }
 int launch_p3_variant(int variant, ConvParams& p, hipStream_t stream) {
   if (variant < 0 || variant >= kNumP3Variants) return Q8_EINVAL;
   return kP3Variants[variant].launch(p, stream);
+}
+bool p3_variant_takes(int variant, const ConvParams& p) {
+  return variant == 0 ? p3_applicable<4>(p) : variant == 1 ? p3_applicable<6>(p) : p3b_applicable(p);
 }
 const char* p3_variant_name(int variant) {
   return variant >= 0 && variant < kNumP3Variants ? kP3Variants[variant].name : "unsupported";

@@ -14,8 +14,9 @@ int launch_pw_or_generic(ConvParams& p, hipStream_t stream) {
 struct PwVariant {
   const char* name;
   int (*launch)(ConvParams&, hipStream_t);
+  bool (*takes)(const ConvParams&);
 };
-#define Q8_PW_ROW(TC, KS) { "conv_i8_pw_kernel<" #TC "," #KS ">", &launch_pw_or_generic<TC, KS> },
+#define Q8_PW_ROW(TC, KS) { "conv_i8_pw_kernel<" #TC "," #KS ">", &launch_pw_or_generic<TC, KS>, &pw_applicable<TC, KS> },
 const PwVariant kPwVariants[] = {
     Q8_PW_ROW(1, 1)    // 0: 128 pixels x 64 channels, C = 64
     Q8_PW_ROW(2, 1)    // 1: 128 x 128, C = 64
@@ -34,6 +35,7 @@ int launch_pw_variant(int variant, ConvParams& p, hipStream_t stream) {
   if (variant < 0 || variant >= kNumPwVariants) return Q8_EINVAL;
   return kPwVariants[variant].launch(p, stream);
 }
+bool pw_variant_takes(int variant, const ConvParams& p) { return kPwVariants[variant].takes(p); }
 const char* pw_variant_name(int variant) {
   return variant >= 0 && variant < kNumPwVariants ? kPwVariants[variant].name : "unsupported";
 }

@@ -92,19 +92,14 @@ int launch_stream_variant(int variant, ConvParams& p, hipStream_t stream) {
     else return launch_direct_variant(variant - first_direct_variant(), p, stream);
   }
   if (is_extended(p)) {
-    // the other families' extended builds; variants without one fall back to the 128 x 128 ring of 3
+    // the other families' extended builds; variants without one, and layers that a build does not
+    // take, fall back to a ring (ext_variant)
     int rc = Q8_EUNSUPPORTED;
     if (variant >= first_stem_variant())
       rc = launch_stem_variant(variant - first_stem_variant(), p, stream);
-    else if (variant >= first_p3_variant()) {
-      rc = launch_p3_ext(variant - first_p3_variant(), p, stream);
-      variant = 8;                                 // (what such layers have without this family)
-    }
+    else if (variant >= first_p3_variant()) rc = launch_p3_ext(variant - first_p3_variant(), p, stream);
     else if (variant >= first_split_variant()) {}
-    else if (variant >= first_pw_variant()) {
-      rc = launch_pw_ext(variant - first_pw_variant(), p, stream);
-      variant = 8;                                 // (what such layers have without this family)
-    }
+    else if (variant >= first_pw_variant()) rc = launch_pw_ext(variant - first_pw_variant(), p, stream);
     else if (variant >= kNumRingVariants) rc = launch_halo_ext(variant - kNumRingVariants, p, stream);
     if (rc != Q8_EUNSUPPORTED) return rc;
     return launch_ring_ext_variant(ext_variant(variant), p, stream);

@@ -386,3 +386,25 @@ def test_fp32_builds_on_lds_leave_wide_paddings_alone():
     for pad in (fits + 1, 2**19 - 1, 2**19, 600000, 2**20):      # 2^19 pixels of 4 KB: the shift's sign
         assert name(pad_w=pad).startswith("conv_f32_mfma_kernel"), pad
     assert name(pad_h=2**15).startswith(("conv_f32_mfma_kernel", "conv_f32_any_kernel"))
+
+
+def _group_variant(d, n=2, flags=0, residual=False, out_cs=0):
+    """Name of the launch that n such layers of a group get (addresses stand in, nothing is launched)."""
+    ops = (B.Op * n)()
+    for i, o in enumerate(ops):
+        o.kind, o.group, o.d, o.flags, o.q_x, o.q_w, o.q_out, o.q_res = B.OP_CONV, 1, d, flags, 1.0, 1.0, 1.0, 1.0
+        o.d.out_c_stride = out_cs
+        o.x, o.w, o.y, o.y_f32 = (1 << 20) * (4 * i + 1), (1 << 20) * (4 * i + 2), (1 << 20) * (4 * i + 3), 1 << 30
+        o.residual = (1 << 20) * (4 * i + 4) if residual else None
+    return B.lib.q8_group_variant(ops, n).decode()
+
+
+@pytest.mark.parametrize("C_, K, pad", [(32, 16, 1), (32, 32, 0), (64, 16, 0)])
+def test_layers_that_the_3x3_blocks_do_not_take_keep_the_latency_family(C_, K, pad):
+    """The sizes choose the block-tiled kernel, the residual, the real output or the odd output stride does
+    not go there: such a layer gets what it would get if there were no such kernel."""
+    d = B.ConvDesc(43, 28, 28, C_, K, 3, 3, pad_h=pad, pad_w=pad)
+    assert B.conv_variant(d) == "conv_i8_p3b_kernel"
+    assert _group_variant(d) == "single launches"
+    for kw in (dict(residual=True), dict(flags=B.OPF_REAL), dict(flags=B.OPF_DEQUANT), dict(out_cs=K + 4)):
+        assert _group_variant(d, **kw).startswith("conv_i8_direct_kernel"), kw
