@@ -170,6 +170,30 @@ int pick_pointwise(const q8_conv_desc* d) {
   return d->C == 64 ? 0 : d->K >= 256 && tiles >= 2400 ? 3 : 2;
 }
 
+// us of a layer on tiles of bp pixels x bc channels of the main kernel: a chain of reduction steps fed at
+// 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail.  A fit to single launches.
+float ring_tiles_us(const q8_conv_desc* d, long M, int bp, int bc) {
+  const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
+  const float bytes = (float)((long)(bp + bc) * (d->R * d->S * d->C)) * 1e-5f * fmaxf(1.0f, wg / 256.0f);
+  return d->C % 64 == 0 ? 3.64f + 1.47f * bytes + 0.312f * wg * 0.01f : 4.22f + 2.05f * bytes + 0.164f * wg * 0.01f;
+}
+
+// us of the block-tiled 3x3 kernel (q8_conv_p3b_kernel.h); 0: not one of its layers (3x3, stride 1,
+// padding 0 or 1, 64 or 32 channels, K <= 64, many pixels).  What its tiles take is the same however
+// much of them lies on the map, so it is rounds of 512 of them, two per CU: 64 channels 5.3 us up to 512 tiles,
+// 7.4 up to 1000, 13.4 at 1710 and 25 at 4940; 32 channels 4.2, 6.4 at 1000 and 17 at 4940.
+float block_tiles_us(const q8_conv_desc* d) {
+  if (d->R != 3 || d->S != 3 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != d->pad_w || d->pad_h > 1 ||
+      d->dil_h != 1 || d->dil_w != 1 || (d->C != 64 && d->C != 32) || d->K > 64 || (d->K & 15) != 0 ||
+      (long)d->N * d->H * d->W < 128L * 256)
+    return 0.0f;
+  const int rows = d->C == 32 && d->K <= 32 ? 16 : 8;
+  const long tiles = (long)d->N * ((out_extent(d->H, d->pad_h, 1, 3, 1) + rows - 1) / rows) *
+                     ((out_extent(d->W, d->pad_w, 1, 3, 1) + 15) / 16);
+  const float rounds = (float)((tiles + 511) / 512);
+  return d->C == 64 ? 3.0f + 2.25f * rounds : 2.75f + 1.47f * rounds;
+}
+
 // Among the tiled kernels.  `forced`: -1, or a variant of the main kernel to use where that kernel
 // is applicable; `persistent`: with the families of persistent workgroups (3x3 blocks, pointwise).
 int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
@@ -188,21 +212,23 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
       return q8::first_stem_variant();
     return d->K <= 64 ? 8 : 4;   // short reduction: small tiles, many per CU
   }
-  // 3x3 / stride 1 / padding 0 or 1 on 64 or 32 channels with K <= 64 and many pixel tiles: persistent
-  // workgroups with every filter in registers, on blocks of the map (any width; also a little faster
-  // than the build on runs of 128 pixels where that one fits)
-  if (persistent && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == d->pad_w &&
-      d->pad_h <= 1 && d->dil_h == 1 && d->dil_w == 1 && (d->C == 64 || d->C == 32) && d->K <= 64 &&
-      (d->K & 15) == 0 && (long)d->N * d->H * d->W >= 128L * 256)
-    return q8::first_p3_variant() + 2;
+  const long M = (long)d->N * out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h) *
+                 out_extent(d->W, d->pad_w, d->dil_w, d->S, d->stride_w);
+  // 3x3 on few channels with many pixels: persistent workgroups with every filter in registers, on
+  // blocks of the map (any width; also a little faster than the build on runs of 128 pixels where
+  // that one fits), unless the maps leave its blocks so empty that the general kernel is faster (us on blocks
+  // and there, without padding: 64 -> 64 on 5 x 5 x 8000 34.9 and 7.9, 9 x 9 x 2470 14.5 and 10.3, 28 x 28 x 256
+  // 13.5 and 14.8; 32 -> 64 on 13 x 13 x 1184 11.5 and 9.3, 17 x 17 x 693 8.1 and 9.5).  With 0.9 of its estimate
+  // the choice is 1 % from the better one over 880 layers of 7 to 150 rows and 33 to 200 thousand pixels,
+  // 23 % at worst; always the blocks: 9 %, 127 % at worst.
+  const float block_us = persistent ? block_tiles_us(d) : 0.0f;
+  if (block_us > 0.0f && block_us <= 0.9f * ring_tiles_us(d, M, 128, 64)) return q8::first_p3_variant() + 2;
   const int halo = pick_halo3(d);
   if (halo >= 0) return q8::num_ring_variants() + halo;
   const int red = d->R * d->S * d->C;
   const int pw = persistent ? pick_pointwise(d) : -1;
   if (pw >= 0) return q8::first_pw_variant() + pw;
   const int nk = (red + 63) / 64;     // reduction steps of 64 bytes
-  const long M = (long)d->N * out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h) *
-                 out_extent(d->W, d->pad_w, d->dil_w, d->S, d->stride_w);
   const long tiles128 = ((M + 127) / 128) * ((d->K + 127) / 128);
   // Variant numbers: see kRingVariants.  Rules fitted to a sweep of every variant over the
   // ResNet-50 shapes at batch 64 (56x56 ... 7x7 maps, 64 ... 2048 channels):
@@ -240,7 +266,8 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
 // Layers with few tiles: the latency family (q8_conv_direct_kernel.h) where its estimate is below
 // that of the tiled build.  The tiled estimates are fits to the same launches: a chain of reduction
 // steps fed at 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail; the 3x3 family
-// by its 64-channel chunks.  The persistent families are only chosen for sizes far above this.
+// by its 64-channel chunks, the 3x3 blocks by their rounds (block_tiles_us).  The pointwise family is only
+// chosen for sizes far above this.
 // ext: unsigned codes or per-channel scales (the extended builds).
 int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float* est_us = nullptr,
                  bool persistent = true) {
@@ -259,18 +286,18 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
   // (the pointwise family: its bytes at 5.3 TB/s, or 1.1 POP/s)
   if (est_us && tiled >= first_pw && tiled < q8::first_split_variant())
     *est_us = 3.2f + (float)M * fmaxf((float)(d->C + d->K) * 1.9e-7f, (float)d->K * (float)red_len * 1.75e-9f);
-  if (tiled >= first_pw) return tiled;
-  if (tiled >= first_halo) {
+  const bool blocks = tiled >= q8::first_p3_variant() && tiled < q8::first_stem_variant();
+  if (tiled >= first_pw && !blocks) return tiled;
+  if (blocks) {
+    tiled_us = block_tiles_us(d);
+  } else if (tiled >= first_halo) {
     q8::halo_variant_tile(tiled - first_halo, &bp, &bc);
     const bool two_groups = tiled - first_halo == 12 || tiled - first_halo == 9;
     const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
     tiled_us = 4.34f + (two_groups ? 0.668f : 1.58f) * (float)(d->C / 64) * fmaxf(1.0f, wg / 256.0f);
   } else {
     q8::ring_variant_tile(ext ? q8::ext_variant(tiled) : tiled, &bp, &bc);
-    const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
-    const float bytes = (float)((long)(bp + bc) * red_len) * 1e-5f * fmaxf(1.0f, wg / 256.0f);
-    tiled_us = d->C % 64 == 0 ? 3.64f + 1.47f * bytes + 0.312f * wg * 0.01f
-                              : 4.22f + 2.05f * bytes + 0.164f * wg * 0.01f;
+    tiled_us = ring_tiles_us(d, M, bp, bc);
   }
   float us = 0.0f;
   const int direct = q8::pick_direct(M, d->K, red_len, &us);

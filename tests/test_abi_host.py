@@ -405,6 +405,18 @@ def test_layers_that_the_3x3_blocks_do_not_take_keep_the_latency_family(C_, K, p
     not go there: such a layer gets what it would get if there were no such kernel."""
     d = B.ConvDesc(43, 28, 28, C_, K, 3, 3, pad_h=pad, pad_w=pad)
     assert B.conv_variant(d) == "conv_i8_p3b_kernel"
-    assert _group_variant(d) == "single launches"
     for kw in (dict(residual=True), dict(flags=B.OPF_REAL), dict(flags=B.OPF_DEQUANT), dict(out_cs=K + 4)):
         assert _group_variant(d, **kw).startswith("conv_i8_direct_kernel"), kw
+
+
+@pytest.mark.parametrize("N, H, W, C_, K, pad, blocks", [
+    # maps that leave the blocks empty: the general kernel or the latency family
+    (8000, 5, 5, 64, 64, 0, False), (1320, 5, 5, 32, 16, 0, False), (4082, 7, 7, 32, 32, 0, False),
+    (2470, 9, 9, 64, 64, 0, False), (2470, 9, 9, 64, 48, 1, False), (1184, 13, 13, 32, 64, 0, False),
+    (8, 5000, 1, 32, 64, 1, False),
+    # maps that fill them (1 row of 16 columns more than a block, too), and below the first size
+    (693, 17, 17, 32, 64, 0, True), (1184, 13, 13, 32, 32, 1, True), (256, 28, 28, 64, 64, 1, True),
+    (9, 150, 150, 64, 64, 0, True), (2, 8192, 16, 64, 64, 1, True), (32767, 1, 1, 64, 64, 1, False)])
+def test_3x3_blocks_are_chosen_by_how_full_they_are(N, H, W, C_, K, pad, blocks):
+    d = B.ConvDesc(N, H, W, C_, K, 3, 3, pad_h=pad, pad_w=pad)
+    assert (B.conv_variant(d) == "conv_i8_p3b_kernel") == blocks
