@@ -153,21 +153,42 @@ int pick_halo3(const q8_conv_desc* d) {
 }
 
 // Pointwise layers on few channels: persistent workgroups (q8_conv_pw_kernel.h) with the filters of a
-// channel tile in LDS, as soon as there are tiles of 128 pixels x 64 channels for more than one per CU
-// (us, the ring build that came before -> this family): 64 -> 64 on 40768 pixels 4.7 -> 4.0, 64 -> 512
-// 11.0 -> 8.6, 128 -> 128 5.8 -> 5.1, 128 -> 512 12.0 -> 9.6; with 196 tiles 3.9 -> 4.0.  Tiles of 128
-// channels read the pixels half as often and leave one workgroup per CU: from 2400 tiles on (128 -> 512 on
-// 200704 pixels 32.6 and 29.7, on 25088 8.0 and 8.4).  256 channels leave little LDS for anything else:
-// only the largest layers (256 -> 512 on 94080 pixels 32.9 -> 26.9, with a residual 37.5 -> 35.3; 256 ->
-// 256 with a residual 20.1 and 21.1).  -1: not one of these.
-int pick_pointwise(const q8_conv_desc* d) {
+// channel tile in LDS, as soon as there are tiles of 128 pixels x 64 channels for more than one per CU (us, the
+// general kernel and this family: 64 -> 64 on 40960 pixels 3.8 and 3.6, 64 -> 512 10.6 and 8.4, 128 -> 128 5.1 and
+// 4.8, 128 -> 512 11.7 and 9.3; with 196 tiles 3.9 and 4.0).  Tiles of 128 channels read the pixels half as often:
+// from 2400 tiles on (128 -> 512 on 200704 pixels 32.6 and 29.7, on 25088 8.0 and 8.4).  256 channels leave
+// little LDS for anything else: only the largest layers (256 -> 512 on 94080 pixels 32.9 -> 26.9, with a
+// residual 37.5 -> 35.3; 256 -> 256 with a residual 20.1 and 21.1).
+//
+// Workgroups come in whole sets, one per channel tile on each of the eight XCDs, so what a layer takes is
+// rounds of sets x tiles per workgroup: channel tiles that leave places free, or pixel tiles that eight XCDs
+// share unevenly, cost as much as full ones.  The estimate (a fit to 635 layers of 2 to 1025 pixel tiles, its
+// error 3 to 10 %) is held against one for the general kernel (2 to 7 %).  us, there and here: 128 -> 16384 on 196
+// pixels 5.3 and 11.1, 256 -> 2304 on 40900 54 and 77, 128 -> 2304 on 3140 6.7 and 7.4, on 1988 6.2 and 5.1.
+// -1: not one of these; *us: the estimate.
+int pick_pointwise(const q8_conv_desc* d, float* us) {
   if (d->R * d->S != 1 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != 0 || d->pad_w != 0 ||
       (d->K & 15) != 0)
     return -1;
-  const long tiles = (((long)d->N * d->H * d->W + 127) / 128) * ((d->K + 63) / 64);
-  if (d->C == 256) return d->K >= 256 && tiles >= 4000 ? 5 : -1;
-  if ((d->C != 64 && d->C != 128) || tiles < 320) return -1;
-  return d->C == 64 ? 0 : d->K >= 256 && tiles >= 2400 ? 3 : 2;
+  const long pixels = (long)d->N * d->H * d->W, ptiles = (pixels + 127) / 128, tiles = ptiles * ((d->K + 63) / 64);
+  struct Build { int index, bc, places; float base, set, tile, ring_base, ring_tile; };
+  static const Build builds[] = {{0, 64, 512, 2.33f, 0.61f, 0.81f, 3.85f, 0.00274f},
+                                 {2, 64, 512, 1.72f, 0.98f, 1.23f, 3.8f, 0.0034f},
+                                 {3, 128, 512, 3.47f, 0.82f, 2.07f, 3.8f, 0.0034f},
+                                 {5, 128, 256, 3.5f, 2.1f, 1.8f, 5.6f, 0.00415f}};
+  const Build* b = nullptr;
+  if (d->C == 64 && tiles >= 320) b = &builds[0];
+  if (d->C == 128 && tiles >= 320) b = &builds[d->K >= 256 && tiles >= 2400 ? 2 : 1];
+  if (d->C == 256 && d->K >= 256 && tiles >= 4000) b = &builds[3];
+  if (!b) return -1;
+  const long set = 8L * ((d->K + b->bc - 1) / b->bc);
+  const long fit = b->places / set, need = (ptiles + 7) / 8, sets = fit < 1 ? 1 : fit < need ? fit : need;
+  const float rounds = (float)((sets * set + b->places - 1) / b->places);
+  const float est = b->base + rounds * (b->set + b->tile * (float)((need + sets - 1) / sets));
+  if (est > b->ring_base + b->ring_tile * (float)(tiles > 256 ? tiles : 256)) return -1;
+  // (in front of other layers' work, its bytes come from memory: 5.3 TB/s)
+  *us = fmaxf(est, 3.2f + (float)pixels * (float)(d->C + d->K) * 1.9e-7f);
+  return b->index;
 }
 
 // us of a layer on tiles of bp pixels x bc channels of the main kernel: a chain of reduction steps fed at
@@ -226,7 +247,8 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
   const int halo = pick_halo3(d);
   if (halo >= 0) return q8::num_ring_variants() + halo;
   const int red = d->R * d->S * d->C;
-  const int pw = persistent ? pick_pointwise(d) : -1;
+  float pw_us = 0.0f;
+  const int pw = persistent ? pick_pointwise(d, &pw_us) : -1;
   if (pw >= 0) return q8::first_pw_variant() + pw;
   const int nk = (red + 63) / 64;     // reduction steps of 64 bytes
   const long tiles128 = ((M + 127) / 128) * ((d->K + 127) / 128);
@@ -283,9 +305,7 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
   int bp = 0, bc = 0;
   float tiled_us = 0.0f;
   if (est_us) *est_us = 3.0f + (float)M * (float)d->K * (float)red_len * 1.1e-9f;   // ~ 1.8 POP/s
-  // (the pointwise family: its bytes at 5.3 TB/s, or 1.1 POP/s)
-  if (est_us && tiled >= first_pw && tiled < q8::first_split_variant())
-    *est_us = 3.2f + (float)M * fmaxf((float)(d->C + d->K) * 1.9e-7f, (float)d->K * (float)red_len * 1.75e-9f);
+  if (est_us && tiled >= first_pw && tiled < q8::first_split_variant()) pick_pointwise(d, est_us);
   const bool blocks = tiled >= q8::first_p3_variant() && tiled < q8::first_stem_variant();
   if (tiled >= first_pw && !blocks) return tiled;
   if (blocks) {

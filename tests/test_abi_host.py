@@ -420,3 +420,16 @@ def test_layers_that_the_3x3_blocks_do_not_take_keep_the_latency_family(C_, K, p
 def test_3x3_blocks_are_chosen_by_how_full_they_are(N, H, W, C_, K, pad, blocks):
     d = B.ConvDesc(N, H, W, C_, K, 3, 3, pad_h=pad, pad_w=pad)
     assert (B.conv_variant(d) == "conv_i8_p3b_kernel") == blocks
+
+
+@pytest.mark.parametrize("pixels, C_, K, persistent", [
+    # more channel tiles than places, and few pixel tiles to share: the general kernel
+    (196, 128, 16384, False), (196, 64, 16384, False), (640, 128, 8192, False), (1140, 64, 16384, False),
+    # channel tiles that leave a quarter or more of the places free
+    (40900, 256, 2304, False), (40900, 256, 5120, False), (3140, 128, 2304, False),
+    # full sets, at the first sizes and the largest
+    (40833, 64, 64, True), (2560, 128, 1024, True), (1988, 128, 2304, True), (16324, 128, 16384, True),
+    (61441, 128, 272, True), (128129, 256, 256, True), (40900, 256, 4096, True), (200704, 64, 256, True)])
+def test_pointwise_family_is_chosen_by_its_places(pixels, C_, K, persistent):
+    name = B.conv_variant(B.ConvDesc(1, 1, pixels, C_, K, 1, 1))
+    assert name.startswith("conv_i8_pw_kernel") == persistent, name
