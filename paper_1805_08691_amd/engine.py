@@ -791,8 +791,10 @@ class Engine:
         where the layers' time on the whole batch is well above the latencies of the layers and of the
         levels they form (at least a launch each).  Measured (us with one and with two): ResNet-50 16 images
         360 / 421, 20: 402 / 392, 24: 495 / 461; Inception-v3 16 images 550 / 559, 18: 625 / 563; the
-        detector 2 images 289 / 293, 5: 442 / 375; with unsigned codes ResNet-50 20 images 420 / 432,
-        28: 578 / 533."""
+        detector 2 images 289 / 293, 5: 442 / 375.  Layers with unsigned codes or per-channel scales cannot
+        share a launch, so a level counts as its layers: ResNet-50 20 images 424 / 432 and 430 / 434, 21: 463 /
+        466 and 478 / 462, 22: 492 / 470 and 500 / 482; at 160 pixels 40 images 423 / 451 and 438 / 452, 48:
+        517 / 494 and 518 / 502."""
         if self.N < 4:           # (unequal parts: the detector 3 images 291 / 330 us at 286 pixels)
             return False
         us, depth = 0.0, {}
@@ -803,7 +805,9 @@ class Engine:
         levels = max(depth.values(), default=0)
         if len(ops) < 16:        # (the fork and the join count: a bottleneck block 32 images 52 / 85 us)
             return us > 8.5 * len(ops)
-        return us > (8.0 * len(ops) if self.unsigned else 5.8 * len(ops) + 1.75 * levels)
+        if self.unsigned or self.per_channel:
+            return us > 7.7 * len(ops)
+        return us > 5.8 * len(ops) + 1.75 * levels
 
     def _plannable(self, x, dequant):
         """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and

@@ -193,3 +193,25 @@ def test_slices_of_a_tensor(layers, late, covered):
         else:
             wl._conv(net, name, "x", at[1], 1, 1, dst="cat", dst_c_off=at[0])
     assert Engine(net, 1, device="cpu")._slices("cat") == (late, covered)
+
+
+def _two_pipelines(net, batch, **kw):
+    eng = Engine(net, batch, device="cpu", **kw)
+    return eng._pipelines_pay([o for o in net.ops if not eng.head or o is not eng.head[1]])
+
+
+@pytest.mark.parametrize("image, batch, two", [(224, 16, False), (224, 20, False), (224, 22, True), (224, 24, True),
+                                               (160, 40, False), (160, 48, True)])
+def test_pipelines_of_layers_that_cannot_share_a_launch(image, batch, two):
+    """Unsigned codes and per-channel scales have the same rule, for the same reason; the batches are
+    those around the measured crossing."""
+    net = wl.resnet50(image=image)
+    assert _two_pipelines(net, batch, unsigned_activations=True) == two
+    assert _two_pipelines(net, batch, per_channel_weights=True) == two
+
+
+def test_pipelines_of_per_channel_layers_follow_the_unsigned_rule():
+    net = wl.resnet50()
+    for batch in range(4, 40):
+        assert _two_pipelines(net, batch, unsigned_activations=True) == \
+            _two_pipelines(net, batch, per_channel_weights=True), batch
