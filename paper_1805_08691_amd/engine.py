@@ -790,8 +790,9 @@ class Engine:
         a second set of launches (in a recorded graph also a dependency per launch): worth it
         where the layers' time on the whole batch is well above the latencies of the layers and of the
         levels they form (at least a launch each).  Measured (us with one and with two): ResNet-50 16 images
-        360 / 421, 20: 402 / 392, 24: 495 / 461; Inception-v3 16 images 550 / 559, 18: 625 / 563; the
-        detector 2 images 289 / 293, 5: 442 / 375.  Layers with unsigned codes or per-channel scales cannot
+        357 / 374, 19: 392 / 387, 20: 390 / 395, 24: 468 / 437; Inception-v3 17 images 553 / 574, 18: 610 /
+        545, at 235 pixels 30 images 570 / 579, 32: 597 / 559; the detector 2 images 286 / 288, 4: 359 /
+        350, 5: 392 / 401, 6: 484 / 442.  Layers with unsigned codes or per-channel scales cannot
         share a launch, so a level counts as its layers: ResNet-50 20 images 424 / 432 and 430 / 434, 21: 463 /
         466 and 478 / 462, 22: 492 / 470 and 500 / 482; at 160 pixels 40 images 423 / 451 and 438 / 452, 48:
         517 / 494 and 518 / 502."""
@@ -807,7 +808,7 @@ class Engine:
             return us > 8.5 * len(ops)
         if self.unsigned or self.per_channel:
             return us > 7.7 * len(ops)
-        return us > 5.8 * len(ops) + 1.75 * levels
+        return us > 5.38 * len(ops) + 2.2 * levels
 
     def _plannable(self, x, dequant):
         """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and

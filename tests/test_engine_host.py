@@ -215,3 +215,13 @@ def test_pipelines_of_per_channel_layers_follow_the_unsigned_rule():
     for batch in range(4, 40):
         assert _two_pipelines(net, batch, unsigned_activations=True) == \
             _two_pipelines(net, batch, per_channel_weights=True), batch
+
+
+@pytest.mark.parametrize("net, image, batch, two", [
+    (wl.resnet50, 224, 16, False), (wl.resnet50, 224, 21, True), (wl.resnet50, 160, 32, False),
+    (wl.resnet50, 160, 48, True), (wl.inception_v3, 299, 17, False), (wl.inception_v3, 299, 18, True),
+    (wl.inception_v3, 235, 28, False), (wl.inception_v3, 235, 32, True), (wl.ssd300_vgg16, 300, 2, False),
+    (wl.ssd300_vgg16, 300, 4, True), (wl.ssd300_vgg16, 270, 3, False)])
+def test_pipelines_of_layers_that_share_launches(net, image, batch, two):
+    """The batches around the measured crossings (the fused head as a deployed model has it)."""
+    assert _two_pipelines(net(image=image), batch, fuse_head=True) == two
