@@ -2019,6 +2019,58 @@ def test_run_ops_tiled_groups_equal_the_oracle(B, N, H, W, build):
         assert np.array_equal(host(keep[i][3])[..., part], codes), GROUP_LAYERS[i]
 
 
+# outputs that leave the codes, in one launch with layers that do not: real values with and without a
+# residual, Eq. D beside the codes, slices, channel counts that end inside a group of four; steps in one tap and
+# across taps.  (All of a size's layers have one kernel by themselves, so that all of them are in the launch.)
+GROUP_OUTPUTS = [("codes", dict(C=320, K=72, R=1, S=1)), ("real", dict(C=160, K=84, R=1, S=7, pad_w=3)),
+                 ("deq", dict(C=48, K=50, R=5, S=5, pad_h=2, pad_w=2)), ("real", dict(C=64, K=65, R=3, S=3, pad_h=1, pad_w=1)),
+                 ("deq", dict(C=128, K=64, R=3, S=3, stride_h=2, stride_w=2, pad_h=1, pad_w=1))]
+
+
+@pytest.mark.parametrize("N,H,W,build", [(1, 17, 17, "direct"), (11, 17, 19, "ring_group_kernel<2,2,1,1,128,4>"),
+                                         (27, 23, 25, "ring_group_kernel<2,2,2,1,64,4>")])
+def test_run_ops_groups_with_real_valued_outputs(B, N, H, W, build):
+    rng = np.random.default_rng(40 + N)
+    n = len(GROUP_OUTPUTS)
+    ops, keep, want = (B.Op * n)(), [], []
+    q_x, q_w = np.float32(0.021), np.float32(0.0017)
+    for i, (kind, layer) in enumerate(GROUP_OUTPUTS):
+        g = orc.ConvGeom(N=N, H=H, W=W, **layer)
+        x = rng.integers(-128, 128, (N, H, W, g.C)).astype(np.int8)
+        w = rng.integers(-128, 128, (g.K, g.R, g.S, g.C)).astype(np.int8)
+        b = rng.integers(-20000, 20000, g.K).astype(np.int32)
+        relu, with_res, pad = i % 2, i % 3 == 1, 4 * (i % 3)     # (slices behind 4 or 8 channels)
+        res = rng.integers(-128, 128, (N, g.Ho, g.Wo, g.K)).astype(np.int8) if with_res else None
+        q_out = np.float32(q_x * q_w * 5476.0 * np.sqrt(g.R * g.S * g.C) / 40.0)
+        q_res = np.float32(0.3) * q_out
+        ocs = g.K + pad
+        codes, values = np.full((N, g.Ho, g.Wo, ocs), 77, np.int8), np.full((N, g.Ho, g.Wo, ocs), np.float32(-7.5))
+        acc = orc.conv_i8(g, x, w, b)
+        if kind == "real":
+            orc.real_output(acc, q_x, q_w, relu, res, q_res, out=values, out_c_stride=ocs, out_c_off=pad)
+        else:
+            orc.requant(acc, orc.requant_scale(q_x, q_w, q_out), bool(relu), res,
+                        orc.residual_scale(q_res, q_out) if with_res else 0.0, out=codes, out_c_stride=ocs, out_c_off=pad)
+        if kind == "deq":
+            values[..., pad:] = orc.D(codes[..., pad:], q_out)
+        d = B.ConvDesc(N, H, W, g.C, g.K, g.R, g.S, g.stride_h, g.stride_w, g.pad_h, g.pad_w, relu=relu,
+                       out_c_stride=ocs, out_c_off=pad)
+        t = [dev(x), B.pack_weights(d, dev(w)), dev(b), torch.full(codes.shape, 77, dtype=torch.int8, device="cuda"),
+             torch.full(values.shape, -7.5, device="cuda"), dev(res) if with_res else None]
+        o = ops[i]
+        o.kind, o.group, o.d, o.q_x, o.q_w, o.q_out, o.q_res = B.OP_CONV, 1, d, q_x, q_w, q_out, q_res
+        o.flags = {"codes": 0, "real": B.OPF_REAL, "deq": B.OPF_DEQUANT}[kind]
+        o.x, o.w, o.bias, o.y, o.y_f32 = (v.data_ptr() for v in t[:5])
+        o.residual = t[5].data_ptr() if with_res else None
+        keep.append(t)
+        want.append((codes, values))
+    assert B.lib.q8_group_variant(ops, n).decode().startswith("conv_i8_" + build)
+    assert _run_ops(B, ops) == 0
+    for i, (codes, values) in enumerate(want):
+        assert np.array_equal(host(keep[i][3]), codes), GROUP_OUTPUTS[i]
+        assert np.array_equal(host(keep[i][4]), values), GROUP_OUTPUTS[i]
+
+
 def _dequantize_ops(B, n, lengths, offset_of=()):
     """A list of Q8_OP_DEQUANTIZE ops over int8 tensors of ``lengths``, those in ``offset_of`` one
     value behind an aligned address; (ops, tensors, outputs, factors)."""
@@ -2090,7 +2142,7 @@ def test_run_ops_group_with_a_refused_op(B, refused):
 
 
 # one layer per tiled build for unsigned codes and per-channel scales: 3x3 tiles of each split, the
-# persistent 3x3 and 1x1 kernels (the latter also with a residual), the rings of K = 128 rows and of
+# persistent 3x3 (32 and 64 channels, padding 0 and 1) and 1x1 kernels (the latter also with a residual), the rings of K = 128 rows and of
 # eight wavefronts on 256 pixels, the image rows at both vertical strides; channel counts that end inside
 # a tile and images that end inside one
 EXT_CASES = [
@@ -2110,7 +2162,13 @@ EXT_CASES = [
     ("ring_kernel<4,2,2,2,64,3>", dict(N=34, H=37, W=35, C=320, K=272, R=1, S=1)),
     ("ring_kernel<2,2,2,1,64,2>", dict(N=8, H=117, W=117, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)),
     ("stem_kernel", dict(N=8, H=135, W=137, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, in_c_stride=4)),
-    ("stem_kernel", dict(N=12, H=37, W=97, C=3, K=48, R=5, S=5, in_c_stride=4))]
+    ("stem_kernel", dict(N=12, H=37, W=97, C=3, K=48, R=5, S=5, in_c_stride=4)),
+    ("p3b_kernel", dict(N=12, H=57, W=59, C=64, K=64, R=3, S=3)),
+    ("p3b_kernel", dict(N=12, H=57, W=59, C=32, K=48, R=3, S=3)),
+    ("p3b_kernel", dict(N=12, H=55, W=57, C=32, K=64, R=3, S=3, pad_h=1, pad_w=1)),
+    ("pw_kernel<1,2> + residual", dict(N=2, H=91, W=113, C=128, K=80, R=1, S=1)),
+    ("pw_kernel<2,2> + residual", dict(N=1, H=1, W=61441, C=128, K=272, R=1, S=1)),
+    ("pw_kernel<2,4> + residual", dict(N=1, H=1, W=128129, C=256, K=368, R=1, S=1))]
 
 
 @pytest.mark.parametrize("idx", range(len(EXT_CASES)))
