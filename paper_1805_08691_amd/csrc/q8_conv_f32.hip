@@ -9,7 +9,7 @@
 // per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments straight into the MFMA's
 // register layout (16 rows x 64 bytes a load), two stages ahead of the one it computes: no LDS and no
 // barrier inside the loop.  ResNet-50 calibration on 8 images: 13.9 ms with the max-abs as passes over
-// every tensor, 1.78 ms with these builds alone and an atomic per wavefront, 1.07 ms now.
+// every tensor, 1.78 ms with these builds alone and an atomic per wavefront, 1.11 ms now.
 //
 // Small maps have few tiles (7 x 7 at batch 8: 392 pixels): KW groups of wavefronts then share
 // the stages of one tile and add their accumulators through LDS in a fixed order.

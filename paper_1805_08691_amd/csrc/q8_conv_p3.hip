@@ -1,6 +1,5 @@
 // The builds of the persistent 3x3 tile family (see q8_conv_p3_kernel.h, q8_conv_p3b_kernel.h)
-// and their table.  A
-// build asked for a layer it cannot take hands the layer to the generic kernel.
+// and their table.  A build asked for a layer it cannot take hands the layer to the generic kernel.
 #include "q8_conv_p3_kernel.h"
 #include "q8_conv_p3b_kernel.h"
 
@@ -25,7 +24,7 @@ struct P3Variant {
 const P3Variant kP3Variants[] = {
     {"conv_i8_p3_kernel<4>", &launch_p3_or_generic<4>},     // maps up to 63 pixels wide
     {"conv_i8_p3_kernel<6>", &launch_p3_or_generic<6>},     // up to 127
-    {"conv_i8_p3b_kernel", &launch_p3b_or_generic},         // 8 x 16 blocks: maps of any width
+    {"conv_i8_p3b_kernel", &launch_p3b_or_generic},         // 8 x 16 blocks (16 x 16 for K <= 32): any width
 };
 constexpr int kNumP3Variants = sizeof(kP3Variants) / sizeof(kP3Variants[0]);
 

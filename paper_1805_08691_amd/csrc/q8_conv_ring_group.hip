@@ -27,7 +27,7 @@ constexpr int kNumRingGroups = sizeof(kRingGroups) / sizeof(kRingGroups[0]);
 // us of a group as tiles of bp x bc: the chain of the longest tile or the operand bytes of all tiles
 // at the rate of the chip (28 bytes per clock and CU, a sixth less where a step is not in one tap),
 // 0.3 us per hundred workgroups, behind a launch; the rates are those of a single layer's estimate
-// (pick_variant), the base is fitted to Inception-v3 against the latency family's groups (us at 3 / 4 /
+// (ring_tiles_us), the base is fitted to Inception-v3 against the latency family's groups (us at 3 / 4 /
 // 6 / 8 images: 322 / 353 / 425 / 487 with those alone, 320 / 355 / 405 / 437 with this choice).
 // Measured on that network, a module's branches as launches of their own and together: 8 images
 // 487 -> 437 us, 16: 727 -> 541, 32: 1043 -> 708, 64: 1285 -> 1046 (with the second pipeline from 18

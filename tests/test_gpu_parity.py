@@ -2208,7 +2208,8 @@ def test_conv_extended_builds(B, idx):
 
 # the block-tiled 3x3 kernel: blocks that end inside the map in both directions, one row and one column,
 # padding 0 and 1, 32 and 64 channels in, 16 to 64 out (blocks of 16 x 16 up to 32), images of several
-# tiles and tiles beyond one per workgroup, slices; unsigned codes at the border
+# tiles and tiles beyond one per workgroup, slices; the last one with unsigned codes at the border, too (those
+# without padding and on 64 channels: EXT_CASES)
 P3B_CASES = [dict(N=1, H=1, W=1, C=32, K=16, pad_h=1, pad_w=1), dict(N=3, H=17, W=16, C=32, K=32, pad_h=1, pad_w=1),
              dict(N=2, H=19, W=35, C=32, K=32, pad_h=0, pad_w=0), dict(N=2, H=9, W=33, C=32, K=48, pad_h=1, pad_w=1),
              dict(N=2, H=10, W=18, C=32, K=64, pad_h=0, pad_w=0), dict(N=1, H=1, W=40, C=64, K=64, pad_h=1, pad_w=1),
