@@ -333,25 +333,56 @@ __device__ __forceinline__ void finish16(const ConvParams& p, int pix, int ch, c
   }
 }
 
+// The 16 codes of values whose lower bound is zero (a ReLU layer's, or unsigned codes), packed four to a
+// word: v_cvt_pk_u8_f32 rounds half to even, saturates at 0 and 255 and puts the byte in its place, in one
+// instruction an element where adding 1.5 * 2^23 and byte permutes take 1.75 (tests hold it against the oracle;
+// checked once over all floats).  clamp: the upper bound hi is below 255.
+__device__ __forceinline__ v4i pack16_nonneg(const float (&t)[16], bool clamp, float hi) {
+  v4i out;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    unsigned w = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const float u = clamp ? __builtin_amdgcn_fmed3f(t[4 * a + b], 0.0f, hi) : t[4 * a + b];
+      w = __builtin_amdgcn_cvt_pk_u8_f32(u, b, w);
+    }
+    out[a] = (int)w;
+  }
+  return out;
+}
+// The same for any sign: Round by adding 1.5 * 2^23 -- for |t| <= 128 the fp32 sum is the
+// round-half-to-even integer and its low byte is the two's-complement int8 code -- then byte permutes.
+__device__ __forceinline__ v4i pack16_signed(const float (&t)[16]) {
+  v4i out;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    unsigned r[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      r[b] = __float_as_uint(__builtin_amdgcn_fmed3f(t[4 * a + b], -128.0f, 127.0f) + 12582912.0f);
+    const unsigned w01 = __builtin_amdgcn_perm(r[1], r[0], 0x0c0c0400u);
+    const unsigned w23 = __builtin_amdgcn_perm(r[3], r[2], 0x0c0c0400u);
+    out[a] = (int)__builtin_amdgcn_perm(w23, w01, 0x05040100u);
+  }
+  return out;
+}
+
 // The same tail for a COMPLETE group (all 16 channels valid, 16-byte aligned addresses, no
-// accumulator dump), branch-free and with as few vector instructions per element as the
-// fixed arithmetic allows: convert, scale, (residual: convert, scale, add), one median for
-// ReLU + clamp, and Round by adding 1.5 * 2^23 -- for |t| <= 128 the fp32 sum is the
-// round-half-to-even integer and its low byte is the two's-complement int8 code -- then
-// byte permutes to pack four codes per word.  Bit-identical to finish16.
-// U8: the output may be unsigned codes stored minus 128 (run-time flag: a different clamp
-// and one XOR per packed word); RES_U8: the residual holds such codes.
-// PC: one scale per output channel (mv) instead of p.m.
-template <bool HAS_RES, bool U8 = false, bool RES_U8 = false, bool PC = false>
-__device__ __forceinline__ v4i codes16_fast(const ConvParams& p, const int (&v)[16],
+// accumulator dump), with as few vector instructions per element as the fixed arithmetic allows: convert,
+// scale, (residual: convert, scale, add), one median for ReLU + clamp (none for unsigned codes), Round
+// and pack.  Bit-identical to finish16.  Instructions an element, beside 4.75 and 7.75 with a residual as long as
+// every output was packed as a signed one: 4 and 7 behind a ReLU, 3 and 6 for unsigned codes.
+// U8: the output may be unsigned codes stored minus 128 (run-time flag: no clamp and one XOR per packed
+// word); RES_U8: the residual holds such codes.
+// PC: one scale per output channel (mv) instead of p.m.  RELU: 1 or 0 where the caller knows p.relu.
+template <bool HAS_RES, bool U8 = false, bool RES_U8 = false, bool PC = false, int RELU = -1, class P>
+__device__ __forceinline__ v4i codes16_fast(const P& p, const int (&v)[16],
                                             const int (&rw)[4], const float (&mv)[16]) {
-  const bool out_u8 = U8 && p.out_u8;
-  const float lo = (p.relu || out_u8) ? 0.0f : -128.0f;   // ReLU folded into the lower bound
-  const float hi = out_u8 ? 255.0f : 127.0f;
-  unsigned r[16];
+  float t[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    float t = (float)v[e] * (PC ? mv[e] : p.m);
+    t[e] = (float)v[e] * (PC ? mv[e] : p.m);
     if (HAS_RES) {
       float code;
       if (RES_U8)      // stored byte ^ 0x80 = the unsigned code: one unsigned byte convert
@@ -359,34 +390,30 @@ __device__ __forceinline__ v4i codes16_fast(const ConvParams& p, const int (&v)[
       else
         code = (float)(int8_t)((rw[e >> 2] >> (8 * (e & 3))) & 0xff);
       const float u = code * p.m_r;
-      t = t + u;
+      t[e] = t[e] + u;
     }
-    t = __builtin_amdgcn_fmed3f(t, lo, hi);
-    r[e] = __float_as_uint(t + 12582912.0f);      // low byte = the code (0..255 or int8)
   }
-  const unsigned flip = out_u8 ? 0x80808080u : 0u;   // code - 128 = code ^ 0x80 in a byte
-  v4i out;
+  if (U8 && p.out_u8) {                          // code - 128 = code ^ 0x80 in a byte
+    v4i out = pack16_nonneg(t, false, 255.0f);
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const unsigned w01 = __builtin_amdgcn_perm(r[4 * a + 1], r[4 * a], 0x0c0c0400u);
-    const unsigned w23 = __builtin_amdgcn_perm(r[4 * a + 3], r[4 * a + 2], 0x0c0c0400u);
-    out[a] = (int)(__builtin_amdgcn_perm(w23, w01, 0x05040100u) ^ flip);
+    for (int a = 0; a < 4; ++a) out[a] ^= 0x80808080;
+    return out;
   }
-  return out;
+  return (RELU < 0 ? p.relu : RELU) ? pack16_nonneg(t, true, 127.0f) : pack16_signed(t);
 }
 
-template <bool HAS_RES, bool U8 = false, bool RES_U8 = false, bool PC = false>
+template <bool HAS_RES, bool U8 = false, bool RES_U8 = false, bool PC = false, int RELU = -1>
 __device__ __forceinline__ void finish16_fast(const ConvParams& p, int pix, int ch,
                                               const int (&v)[16], const int (&rw)[4],
                                               const float (&mv)[16]) {
   *reinterpret_cast<v4i*>(p.y + (size_t)pix * p.out_cs + p.out_off + ch) =
-      codes16_fast<HAS_RES, U8, RES_U8, PC>(p, v, rw, mv);
+      codes16_fast<HAS_RES, U8, RES_U8, PC, RELU>(p, v, rw, mv);
 }
 
 // The codes of a complete group in a build that is plain (EXT = 0) or takes unsigned codes and
 // per-channel scales by run-time flags (EXT = 1).
-template <int EXT>
-__device__ __forceinline__ v4i codes16_build(const ConvParams& p, const int (&v)[16],
+template <int EXT, class P>
+__device__ __forceinline__ v4i codes16_build(const P& p, const int (&v)[16],
                                              const int (&rw)[4], const float (&mv)[16], bool has_res) {
   if constexpr (EXT) {
     if (p.m_vec)

@@ -71,14 +71,14 @@ __device__ __forceinline__ void finish_tile(const ConvParams& p, const v16i (&ac
   auto finish_all = [&](auto mode_c) __attribute__((always_inline)) {
     // 0 general; 1 fast; 2 fast + residual; 3, 4, 5: fast with unsigned codes (no
     // residual, signed residual, unsigned residual); 6, 7: fast with per-channel scales
-    // (no residual, residual)
+    // (no residual, residual); 8, 9: 1 and 2 behind a ReLU
     constexpr int MODE = decltype(mode_c)::value;
 #pragma unroll
     for (int i = 0; i < TC; ++i) {
       const int ch = ch0 + (wave_c * TC + i) * 32 + 16 * (lane >> 5);
       if (ch >= p.K) continue;
       float mv[16] = {};
-      if constexpr (MODE >= 6) load_scale16(p, ch, mv);
+      if constexpr (MODE == 6 || MODE == 7) load_scale16(p, ch, mv);
 #pragma unroll
       for (int j = 0; j < TP; ++j) {
         const int pix = pix0 + (wave_p * TP + j) * 32 + (lane & 31);
@@ -87,7 +87,8 @@ __device__ __forceinline__ void finish_tile(const ConvParams& p, const v16i (&ac
 #pragma unroll
         for (int e = 0; e < 16; ++e) v[e] = acc[i][j][e];
         if constexpr (MODE == 0) finish16(p, pix, ch, v, res_w[i][j]);
-        else if constexpr (MODE <= 2) finish16_fast<MODE == 2>(p, pix, ch, v, res_w[i][j], mv);
+        else if constexpr (MODE <= 2) finish16_fast<MODE == 2, false, false, false, 0>(p, pix, ch, v, res_w[i][j], mv);
+        else if constexpr (MODE >= 8) finish16_fast<MODE == 9, false, false, false, 1>(p, pix, ch, v, res_w[i][j], mv);
         else if constexpr (MODE <= 5)
           finish16_fast<MODE >= 4, true, MODE == 5>(p, pix, ch, v, res_w[i][j], mv);
         else finish16_fast<MODE == 7, false, false, true>(p, pix, ch, v, res_w[i][j], mv);
@@ -98,6 +99,9 @@ __device__ __forceinline__ void finish_tile(const ConvParams& p, const v16i (&ac
   else if (U8 && p.m_vec) {
     if (p.res) finish_all(std::integral_constant<int, 7>{});
     else finish_all(std::integral_constant<int, 6>{});
+  } else if (!U8 && p.relu) {
+    if (p.res) finish_all(std::integral_constant<int, 9>{});
+    else finish_all(std::integral_constant<int, 8>{});
   } else if (!p.res) finish_all(std::integral_constant<int, U8 ? 3 : 1>{});
   else if (U8 && p.res_u8) finish_all(std::integral_constant<int, 5>{});
   else finish_all(std::integral_constant<int, U8 ? 4 : 2>{});

@@ -195,9 +195,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int tc = 0; tc < 2; ++tc) load_scale16(p, tc * 32 + 16 * (lane >> 5), scales[tc]);
   }
-  const float code_lo = p.relu ? 0.0f : -128.0f;          // ReLU folded into the lower bound
-  constexpr float kMagic = 12582912.0f;                   // 1.5 * 2^23: t + kMagic rounds t to an
-                                                          // integer, held in the low mantissa bits
   // POOL: running maximum of the ACCUMULATORS over the output rows of the open pooling window.
   // The layer's tail (scale by m > 0, clamp, Round) never decreases when the accumulator
   // grows, so the maximum of the codes is the code of the maximum: the tail runs once per
@@ -287,26 +284,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       }
     }
     // ---- the layer's tail (the fixed fp32 sequence: convert, scale, clamp with ReLU as the
-    // lower bound, Round by adding 1.5 * 2^23, low byte = code) into the staging tile
+    // lower bound, Round) into the staging tile
     if (emit) {
       const int row = wave * 32 + frag_row;
 #pragma unroll
       for (int tc = 0; tc < 2; ++tc) {
         const int slot = tc * 2 + frag_half;
-        unsigned t[16];
+        float t[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          t[e] = __float_as_uint(
-              __builtin_amdgcn_fmed3f((float)acc[tc][e] * (EXT && p.m_vec ? scales[tc][e] : p.m),
-                                      EXT && p.out_u8 ? 0.0f : code_lo,
-                                      EXT && p.out_u8 ? 255.0f : 127.0f) + kMagic);
+        for (int e = 0; e < 16; ++e) t[e] = (float)acc[tc][e] * (EXT && p.m_vec ? scales[tc][e] : p.m);
         v4i out;
+        if (EXT && p.out_u8) {
+          out = pack16_nonneg(t, false, 255.0f);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const unsigned w01 = __builtin_amdgcn_perm(t[4 * a + 1], t[4 * a], 0x0c0c0400u);
-          const unsigned w23 = __builtin_amdgcn_perm(t[4 * a + 3], t[4 * a + 2], 0x0c0c0400u);
-          out[a] = (int)(__builtin_amdgcn_perm(w23, w01, 0x05040100u) ^
-                         (EXT && p.out_u8 ? 0x80808080u : 0u));       // unsigned codes minus 128
+          for (int a = 0; a < 4; ++a) out[a] ^= 0x80808080;       // unsigned codes minus 128
+        } else {
+          out = p.relu ? pack16_nonneg(t, true, 127.0f) : pack16_signed(t);
         }
         *reinterpret_cast<v4i*>(stage + row * BC + ((slot ^ swz_out<SLOTS>(row)) << 4)) = out;
       }

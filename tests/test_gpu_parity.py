@@ -1950,6 +1950,32 @@ def test_run_ops_groups_equal_single_calls(B):
         assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
 
 
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("C,N", [(64, 1), (64, 13), (256, 13)])
+def test_tails_on_ties_and_bounds(B, C, N, relu):
+    """Every tail on values at, beside and far beyond its ties and bounds: zero activations, so that the
+    accumulators are the biases, -768 ... 767 and the ends of their range, at a scale of one half; one call
+    in each family (few pixels: the latency family; many: persistent or general), every tile variant
+    of the main kernel, and unsigned codes."""
+    K, H = 1536, 28 if N > 1 else 3
+    bias = np.arange(-768, 768, dtype=np.int32)
+    bias[[5, 900, 1300]] = [-2**31 + 1, 2**30, 2**31 - 1]
+    d = B.ConvDesc(N, H, H, C, K, 1, 1, relu=relu)
+    x, w, b = (torch.zeros(s, dtype=torch.int8, device="cuda") for s in ((N, H, H, C), (K, 1, 1, C), 1))
+    w, b = B.pack_weights(d, w), dev(bias)
+    acc = np.broadcast_to(bias, (1, 1, 1, K))
+    want = orc.requant(acc, 0.5, relu)
+    assert len(np.unique(want)) == (128 if relu else 256)
+    variants = [-1] + ([v for v in range(B.conv_num_variants())] if N == 13 else [])
+    for v in variants:
+        got = host(B.conv_int8(d, x, w, b, 0.5, 1.0, 1.0, variant=v))
+        assert np.array_equal(got, np.broadcast_to(want, got.shape)), v
+    if relu:
+        got = host(B.conv_u8(d, False, True, False, x, w, b, None, 0.5, 1.0, 1.0))
+        want = orc.requant_mixed(acc, 0.5, 1, out_unsigned=True)
+        assert np.array_equal(got.view(np.uint8) ^ 0x80, np.broadcast_to(want, got.shape))
+
+
 # layers whose reduction steps cross filter taps: several taps a step (C below the step's bytes), at
 # most one further (C above), the most taps that the kernel takes, as one row and as one column
 TAP_CASES = [
