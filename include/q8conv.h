@@ -346,7 +346,11 @@ int q8_conv_chain_static_status(int32_t *status_host);
  *   Q8_OP_DEQUANTIZE  q8_dequantize (or _u8 with Q8_OPF_IN_U8): x, n, q_x, y_f32
  * `stream` is an index into `streams`.  Ops are enqueued in order.  Neighbours with the same
  * nonzero `group` (and stream) must not depend on each other; the library may then run several
- * of them as one launch.  Neighbouring Q8_OP_DEQUANTIZE ops never depend on each other.
+ * of them as one launch.  Q8_OPF_BLOCK on the first of three neighbouring Q8_OP_CONV ops of one stream
+ * and no group says that they may run as one launch too: a bottleneck block, i.e. a 1x1 layer, the 3x3
+ * layer (stride 1, padding 1) that reads its output and the 1x1 layer that reads that one's (with any
+ * fused sum), all three tensors written as by single calls.  Where they are no such block, or the
+ * estimates are against it, they are launched one after the other.  Neighbouring Q8_OP_DEQUANTIZE ops never depend on each other.
  * Returns the first error; ops behind it are not enqueued.                               */
 enum {
   Q8_OP_CONV = 0, Q8_OP_HEAD, Q8_OP_POOL, Q8_OP_MAXPOOL, Q8_OP_QUANTIZE, Q8_OP_QUANTIZE_PAD,
@@ -354,7 +358,7 @@ enum {
 };
 enum {
   Q8_OPF_IN_U8 = 1, Q8_OPF_OUT_U8 = 2, Q8_OPF_RES_U8 = 4, Q8_OPF_PER_CHANNEL = 8, Q8_OPF_REAL = 16,
-  Q8_OPF_DEQUANT = 32, Q8_OPF_POOL = 64
+  Q8_OPF_DEQUANT = 32, Q8_OPF_POOL = 64, Q8_OPF_BLOCK = 128
 };
 typedef struct q8_op {
   int32_t kind, flags, group, stream;
@@ -372,6 +376,17 @@ int q8_run_ops(const q8_op *ops, int n_ops, void *const *streams, int n_streams)
  * eight ops; the larger of two, where they fall into two); "single launches" if each would go by itself,
  * "unsupported" if an op would be refused.  For tests and measurement code.               */
 const char *q8_group_variant(const q8_op *ops, int n_ops);
+
+/* Name of the build that q8_run_ops would give three ops marked with Q8_OPF_BLOCK; "single launches"
+ * if they would go one after the other.                                                   */
+const char *q8_block_variant(const q8_op *ops);
+
+/* Tests and tuning only: three Q8_OP_CONV ops that form a bottleneck block (see q8_run_ops) as one launch of
+ * the given build (0 .. q8_num_bottleneck_builds() - 1).  Q8_EUNSUPPORTED if the ops are no such
+ * block or the build does not take its sizes.                                             */
+int q8_num_bottleneck_builds(void);
+const char *q8_bottleneck_build_name(int build);
+int q8_run_bottleneck(const q8_op *ops, int build, void *stream);
 
 /* Estimated duration in us of one launch of this layer on an otherwise idle chip (host
  * arithmetic; what the library chooses kernels by): for programs that order independent

@@ -35,7 +35,8 @@ EXPORTS = [
     "q8_conv_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
-    "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant", "q8_conv_estimate_us",
+    "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant",
+    "q8_block_variant", "q8_num_bottleneck_builds", "q8_bottleneck_build_name", "q8_run_bottleneck", "q8_conv_estimate_us",
     "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_observed_spread", "q8_calibrate_fold", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
@@ -90,7 +91,7 @@ class Op(C.Structure):
 (OP_CONV, OP_HEAD, OP_POOL, OP_MAXPOOL, OP_QUANTIZE, OP_QUANTIZE_PAD, OP_QUANTIZE_IMAGE,
  OP_DEQUANTIZE) = range(8)
 (OPF_IN_U8, OPF_OUT_U8, OPF_RES_U8, OPF_PER_CHANNEL, OPF_REAL, OPF_DEQUANT,
- OPF_POOL) = (1 << i for i in range(7))
+ OPF_POOL, OPF_BLOCK) = (1 << i for i in range(8))
 
 _vp, _sz, _f, _i = C.c_void_p, C.c_size_t, C.c_float, C.c_int
 _dp = C.POINTER(ConvDesc)
@@ -152,6 +153,12 @@ lib.q8_conv_image_f32_int8.argtypes = [_dp, _vp, _i, _i, _i, _i, _i, _f, _i, _vp
 lib.q8_run_ops.argtypes = [_vp, _i, _vp, _i]
 lib.q8_group_variant.restype = C.c_char_p
 lib.q8_group_variant.argtypes = [_vp, _i]
+lib.q8_block_variant.restype = C.c_char_p
+lib.q8_block_variant.argtypes = [_vp]
+lib.q8_num_bottleneck_builds.argtypes = []
+lib.q8_bottleneck_build_name.restype = C.c_char_p
+lib.q8_bottleneck_build_name.argtypes = [_i]
+lib.q8_run_bottleneck.argtypes = [_vp, _i, _vp]
 lib.q8_conv_estimate_us.restype = _f
 lib.q8_conv_estimate_us.argtypes = [_dp]
 lib.q8_sum_factor.restype = _f

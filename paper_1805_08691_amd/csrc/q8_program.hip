@@ -17,6 +17,12 @@ int pick_ring_group(const ConvParams** p, int n, float* us);
 int launch_ring_group_variant(int build, const ConvParams* const* p, int n, hipStream_t stream);
 const char* direct_variant_name(int variant);
 const char* ring_group_variant_name(int build);
+int num_bneck_builds();
+const char* bneck_build_name(int build);
+bool bneck_applicable(const ConvParams& a, const ConvParams& b, const ConvParams& c);
+bool bneck_build_takes(int build, const ConvParams& a, const ConvParams& b, const ConvParams& c);
+int pick_bneck(const ConvParams& a, const ConvParams& b, const ConvParams& c, float* us);
+int launch_bneck(int build, const ConvParams& a, const ConvParams& b, const ConvParams& c, hipStream_t stream);
 int dequantize_list(const q8_op* ops, int n, hipStream_t stream);   // q8_elementwise.hip
 
 namespace {
@@ -57,6 +63,28 @@ int run_one(const q8_op& o, void* stream) {
     default:
       return Q8_EINVAL;
   }
+}
+
+// The build for a block of three layers, -1: three launches.  The estimates of single launches miss what
+// three dependent ones take in a row by a factor that goes with the map (measured / estimated at 1 to 32 images:
+// 14 x 14 pixels 1.03 ... 0.8, 28 x 28 1.02 ... 1.09, 56 x 56 0.9 ... 1.24), so each kind of block has its own.
+int block_choose(const q8_op* ops, const ConvParams* p) {
+  float us = 0.0f, single = 0.0f;
+  const int build = bneck_applicable(p[0], p[1], p[2]) ? pick_bneck(p[0], p[1], p[2], &us) : -1;
+  if (build < 0) return -1;
+  for (int i = 0; i < 3; ++i) {
+    float t = 0.0f;
+    conv_choose(&ops[i].d, p[i], &t);
+    single += t;
+  }
+  return us < (p[0].K == 64 ? 1.15f : 0.95f) * single ? build : -1;
+}
+int block_fill(const q8_op* ops, ConvParams* p) {
+  for (int i = 0; i < 3; ++i) {
+    bool empty = false;
+    if (ops[i].kind != Q8_OP_CONV || conv_fill_op(&ops[i], p[i], &empty) != Q8_OK || empty) return -1;
+  }
+  return block_choose(ops, p);
 }
 
 // How the convolutions of a run of independent ops are launched: in part or in whole together, as
@@ -151,6 +179,18 @@ int run_group(const q8_op* ops, int n, void* stream) {
   return refused;
 }
 
+// A bottleneck block: one launch where there is a build for it that is estimated shorter than three.
+int run_block(const q8_op* ops, void* stream) {
+  ConvParams p[3];
+  const int build = block_fill(ops, p);
+  if (build >= 0) return launch_bneck(build, p[0], p[1], p[2], (hipStream_t)stream);
+  for (int i = 0; i < 3; ++i) {
+    const int rc = run_one(ops[i], stream);
+    if (rc != Q8_OK) return rc;
+  }
+  return Q8_OK;
+}
+
 }  // namespace
 }  // namespace q8
 
@@ -164,6 +204,10 @@ extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int
     if (o.kind == Q8_OP_DEQUANTIZE) {
       while (j < n_ops && ops[j].kind == Q8_OP_DEQUANTIZE && ops[j].stream == o.stream) ++j;
       rc = q8::dequantize_list(ops + i, j - i, (hipStream_t)streams[o.stream]);
+    } else if (o.kind == Q8_OP_CONV && (o.flags & Q8_OPF_BLOCK) && !o.group && i + 2 < n_ops &&
+               ops[i + 1].stream == o.stream && ops[i + 2].stream == o.stream) {
+      j = i + 3;
+      rc = q8::run_block(ops + i, streams[o.stream]);
     } else if (o.group) {
       while (j < n_ops && j - i < q8::kMaxGroup && ops[j].group == o.group && ops[j].stream == o.stream &&
              ops[j].kind != Q8_OP_DEQUANTIZE)
@@ -192,4 +236,30 @@ extern "C" const char* q8_group_variant(const q8_op* ops, int n_ops) {
   if (s < 0) return "single launches";
   return s <= q8::GroupPlan::kSmallDirect ? q8::direct_variant_name(g.build[s])
                                           : q8::ring_group_variant_name(g.build[s]);
+}
+
+extern "C" const char* q8_block_variant(const q8_op* ops) {
+  q8::ConvParams p[3];
+  const int build = ops ? q8::block_fill(ops, p) : -1;
+  return build >= 0 ? q8::bneck_build_name(build) : "single launches";
+}
+
+extern "C" int q8_num_bottleneck_builds(void) { return q8::num_bneck_builds(); }
+
+extern "C" const char* q8_bottleneck_build_name(int build) {
+  return build >= 0 && build < q8::num_bneck_builds() ? q8::bneck_build_name(build) : "unsupported";
+}
+
+extern "C" int q8_run_bottleneck(const q8_op* ops, int build, void* stream) {
+  Q8_REQUIRE(ops && build >= 0 && build < q8::num_bneck_builds(), Q8_EINVAL);
+  q8::ConvParams p[3];
+  for (int i = 0; i < 3; ++i) {
+    bool empty = false;
+    Q8_REQUIRE(ops[i].kind == Q8_OP_CONV, Q8_EINVAL);
+    const int rc = q8::conv_fill_op(&ops[i], p[i], &empty);
+    if (rc != Q8_OK) return rc;
+    Q8_REQUIRE(!empty, Q8_EUNSUPPORTED);
+  }
+  Q8_REQUIRE(q8::bneck_applicable(p[0], p[1], p[2]) && q8::bneck_build_takes(build, p[0], p[1], p[2]), Q8_EUNSUPPORTED);
+  return q8::launch_bneck(build, p[0], p[1], p[2], (hipStream_t)stream);
 }

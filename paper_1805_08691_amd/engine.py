@@ -771,10 +771,18 @@ class Engine:
         # level by level, alternating between the pipelines: a captured graph hands its nodes to
         # the GPU in the order they were recorded, and a pipeline recorded whole before the next
         # one starts that much earlier and runs alone meanwhile
+        blocks = self._blocks(ops, fused, parts[0][1])
+        inside = {i for pair in blocks.values() for i in pair}
         for level, members in enumerate(self._levels(ops, parts[0][1], dst_of)):
             for k in list(range(1, len(parts))) + [0]:
                 for i in sorted(members):
-                    emit(ops[i], k, level + 1)
+                    if i in blocks:                  # the whole block, where its last layer has its place
+                        first = len(body)
+                        for j in (*blocks[i], i):
+                            emit(ops[j], k, 0)
+                        body[first].flags |= B.OPF_BLOCK
+                    elif i not in inside:
+                        emit(ops[i], k, level + 1)
         for name in names:
             if name in fused:
                 continue
@@ -784,6 +792,36 @@ class Engine:
             out_slots.append((2, add(post, o), name, 0, z.numel()))
         segments = [(B.Op * len(s))(*s) for s in (pre, body, post)]
         return segments, x_slots, out_slots, len(parts)
+
+    def _blocks(self, ops, fused, n):
+        """Bottleneck blocks that the library would run as one launch on ``n`` images: {index of the last
+        layer: (1x1, 3x3)}.  Only the block itself reads its inner tensors, and nothing behind its first
+        layer writes over what it reads or writes: it can then run where its last layer has its place."""
+        at = {o.dst: i for i, o in enumerate(ops)}
+        found = {}
+        for i, c in enumerate(ops):
+            if c.kind != "conv" or (c.R, c.S, c.stride, c.pad_h, c.pad_w) != (1, 1, 1, 0, 0):
+                continue
+            ib = at.get(c.src, i)
+            b = ops[ib]
+            if ib >= i or b.kind != "conv" or b.res or \
+                    (b.R, b.S, b.stride, b.pad_h, b.pad_w, b.dil) != (3, 3, 1, 1, 1, 1):
+                continue
+            ia = at.get(b.src, ib)
+            a = ops[ia]
+            if ia >= ib or a.kind != "conv" or a.res or (a.R, a.S, a.pad_h, a.pad_w) != (1, 1, 0, 0) or \
+                    c.dst in self.real or c.dst in fused or (self.head and a is self.head[0]):
+                continue
+            touched = {a.src, c.res, a.dst, b.dst, c.dst}
+            others = [o for j, o in enumerate(ops) if j not in (ia, ib, i)]
+            if (any({a.dst, b.dst} & {o.src, getattr(o, "res", None)} for o in others) or
+                    any(o.dst in touched for o in ops[ia + 1:] if o is not b and o is not c) or
+                    any(o.dst in (a.dst, b.dst, c.dst) for o in others)):
+                continue
+            three = (B.Op * 3)(*(self._op_conv(o, 0, n, False) for o in (a, b, c)))
+            if B.lib.q8_block_variant(three) != b"single launches":
+                found[i] = (ia, ib)
+        return found
 
     def _pipelines_pay(self, ops):
         """Concurrent pipelines hide one launch's latency and tail behind the other's work, and cost

@@ -433,3 +433,39 @@ def test_3x3_blocks_are_chosen_by_how_full_they_are(N, H, W, C_, K, pad, blocks)
 def test_pointwise_family_is_chosen_by_its_places(pixels, C_, K, persistent):
     name = B.conv_variant(B.ConvDesc(1, 1, pixels, C_, K, 1, 1))
     assert name.startswith("conv_i8_pw_kernel") == persistent, name
+
+
+def _block(mid=64, C=256, H=56, N=4, K2=256, **change):
+    """Three ops of a bottleneck block at made-up addresses (nothing is launched)."""
+    d = [B.ConvDesc(N, H, H, C, mid, 1, 1, relu=1), B.ConvDesc(N, H, H, mid, mid, 3, 3, 1, 1, 1, 1, relu=1),
+         B.ConvDesc(N, H, H, mid, K2, 1, 1, relu=1)]
+    at, ops = 1 << 40, (B.Op * 3)()
+    for i, o in enumerate(ops):
+        o.kind, o.d, o.q_x, o.q_w, o.q_out = B.OP_CONV, d[i], 0.1, 0.1, 0.1
+        o.x = ops[i - 1].y if i else at
+        o.w, o.bias, o.y = at + (1 << 33) * (i + 1), at + (1 << 33) * (i + 4), at + (1 << 33) * (i + 8)
+    ops[2].residual, ops[2].q_res = at, 0.1
+    for name, value in change.items():
+        i, field = int(name[1]), name[3:]
+        setattr(ops[i].d if hasattr(ops[i].d, field) else ops[i], field, value)
+    return ops
+
+
+def test_bottleneck_blocks_that_one_launch_takes():
+    name = lambda ops: B.lib.q8_block_variant(ops).decode()
+    taken = _block()
+    assert name(taken).startswith("conv_i8_bneck_kernel<64,")
+    assert name(_block(mid=128, C=512, H=28, K2=512)).startswith("conv_i8_bneck_kernel<128,")
+    assert name(_block(mid=256, C=1024, H=14, N=32, K2=1024)).startswith("conv_i8_bneck_kernel<256,")
+    assert name(_block(o2_residual=None)) == name(taken)
+    single = [dict(o1_x=taken[0].x), dict(o2_x=taken[0].y), dict(o2_y=taken[0].x),           # other tensors, in place
+              dict(o1_y=taken[0].y), dict(o2_y=taken[1].y + 64), dict(o0_y=taken[0].w), dict(o2_residual=taken[0].y),
+              dict(o1_dil_h=2, o1_pad_h=2), dict(o1_pad_w=0), dict(o1_stride_h=2), dict(o2_pad_h=1), dict(o0_R=3, o0_pad_h=1),
+              dict(o0_residual=taken[0].x, o0_q_res=0.1), dict(o2_out_c_stride=260), dict(o2_out_c_stride=264, o2_out_c_off=8),
+              dict(o2_flags=B.OPF_DEQUANT, o2_y_f32=None), dict(o0_flags=B.OPF_OUT_U8), dict(o1_kind=B.OP_POOL),
+              dict(mid=32, C=64, K2=64), dict(mid=64, K2=96), dict(C=48), dict(H=86), dict(mid=256, C=1024, H=14, N=1, K2=1024)]
+    for change in single:
+        assert name(_block(**change)) == "single launches", change
+    assert B.lib.q8_run_bottleneck(_block(o2_y=taken[0].x), 4, None) == -2
+    assert B.lib.q8_run_bottleneck(taken, 0, None) == -2 and B.lib.q8_run_bottleneck(taken, 99, None) == -1
+    assert B.lib.q8_run_bottleneck(None, 0, None) == -1 and name(None) == "single launches"

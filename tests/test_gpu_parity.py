@@ -1976,6 +1976,92 @@ def test_tails_on_ties_and_bounds(B, C, N, relu):
         assert np.array_equal(got.view(np.uint8) ^ 0x80, np.broadcast_to(want, got.shape))
 
 
+# bottleneck blocks: mid channels, input channels, output rows and columns, images, output channels,
+# stride of the first layer: one pixel, one row, the widest maps, ragged last strips, one to four rounds
+BLOCKS = [(64, 64, 1, 1, 3, 64, 1), (64, 192, 7, 9, 2, 192, 1), (64, 256, 5, 56, 1, 256, 2), (64, 64, 3, 85, 1, 128, 1),
+          (128, 128, 13, 28, 1, 384, 1), (128, 256, 9, 17, 2, 512, 2), (128, 512, 3, 64, 1, 128, 1),
+          (256, 128, 14, 14, 1, 256, 1), (256, 512, 10, 13, 3, 1024, 1), (256, 256, 3, 32, 1, 512, 2), (256, 1024, 1, 7, 2, 768, 1)]
+
+
+@pytest.mark.parametrize("option", ["plain", "bare", "unsigned", "per_channel"])
+@pytest.mark.parametrize("idx", range(len(BLOCKS)))
+def test_bottleneck_builds(B, idx, option):
+    """Every build that takes the block gives the three tensors of three calls (plain: of the oracle),
+    and writes nothing beside them; bare: no biases, no residual, the first two layers without ReLU."""
+    import ctypes
+    mid, C, H, W, N, K2, stride = BLOCKS[idx]
+    rng = np.random.default_rng(40 + idx)
+    Hi, Wi = (H - 1) * stride + 1, (W - 1) * stride + 1
+    relu = [0, 0, 1] if option == "bare" else [1, 1, 1]
+    slices = [(mid + 48, 32), (mid, 0), (K2 + 16, 16)] if idx % 2 else [(mid, 0), (mid, 0), (K2, 0)]
+    shapes = [(Hi, Wi, C, mid, 1, 0, stride), (H, W, mid, mid, 3, 1, 1), (H, W, mid, K2, 1, 0, 1)]
+    x = dev(rng.integers(-128, 128, (N, Hi, Wi, C)).astype(np.int8))
+    res = None if option == "bare" else dev(rng.integers(-128, 128, (N, H, W, K2)).astype(np.int8))
+    q = [0.02, 0.013, 0.017, 0.011]
+    q_w, q_res = [0.01 / np.sqrt(s[2] * s[4] ** 2) * 1.2 for s in shapes], 0.009
+    ops, keep, want = (B.Op * 3)(), [], []
+    src, chain, oracle_src = x, x, host(x)     # what the launch reads, what single calls read
+    for i, (h, w_, c, k, R, pad, st) in enumerate(shapes):
+        z_w = rng.integers(-128, 128, (k, R, R, c)).astype(np.int8)
+        bias = rng.integers(-2000, 2000, k).astype(np.int32)
+        cs, off = slices[i]
+        d = B.ConvDesc(N, h, w_, c, k, R, R, st, st, pad, pad, 1, 1, relu=relu[i], out_c_stride=cs, out_c_off=off,
+                       in_c_stride=slices[i - 1][0] if i else 0)
+        wp, b = B.pack_weights(d, dev(z_w)), None if option == "bare" else dev(bias)
+        out = torch.full((N, H, W, cs), 77, dtype=torch.int8, device="cuda")
+        r, qr = (res, q_res) if i == 2 and res is not None else (None, 0.0)
+        o = ops[i]
+        o.kind, o.d, o.w, o.bias = B.OP_CONV, d, wp.data_ptr(), b.data_ptr() if b is not None else None
+        o.x = src.data_ptr() + (slices[i - 1][1] if i else 0)
+        o.q_x, o.q_w, o.q_out = q[i], q_w[i], q[i + 1]
+        if r is not None:
+            o.residual, o.q_res = r.data_ptr(), qr
+        xin = chain if not i else chain.flatten()[slices[i - 1][1]:]
+        if option == "unsigned":
+            o.flags = B.OPF_OUT_U8 | B.OPF_IN_U8 | (B.OPF_RES_U8 if i == 2 and idx % 2 else 0)
+            taps, b = B.u8_prepare(d, dev(z_w), b)
+            o.bias, o.aux = b.data_ptr(), taps.data_ptr()
+            B.conv_u8(d, True, True, bool(o.flags & B.OPF_RES_U8), xin, wp, b, taps, q[i], q_w[i], q[i + 1], r, qr, out=out)
+            keep.append(taps)
+        elif option == "per_channel":
+            m = dev((q[i] * q_w[i] / q[i + 1] * rng.uniform(0.5, 2.0, k)).astype(np.float32))
+            o.flags, o.aux = B.OPF_PER_CHANNEL, m.data_ptr()
+            B.conv_int8_per_channel(d, xin, wp, b, m, q[i + 1], r, qr, out=out)
+            keep.append(m)
+        else:
+            B.conv_int8(d, xin, wp, b, q[i], q_w[i], q[i + 1], r, qr, out=out)
+            g = orc.ConvGeom(N=N, H=h, W=w_, C=c, K=k, R=R, S=R, stride_h=st, stride_w=st, pad_h=pad, pad_w=pad)
+            oracle_src = orc.conv_layer_i8(g, oracle_src, q[i], z_w, q_w[i], None if b is None else bias, q[i + 1],
+                                           relu[i], host(r) if r is not None else None, qr or None)[0]
+            assert np.array_equal(host(out)[..., off:off + k], oracle_src)
+        want.append(host(out))
+        assert len(np.unique(want[-1])) > (32 if out.numel() > 2000 else 8)
+        keep += [wp, b, out]
+        chain, src = out, torch.full_like(out, 77)
+        o.y = src.data_ptr()
+        keep.append(src)
+    outs = [next(t for t in keep if t is not None and t.data_ptr() == ops[i].y) for i in range(3)]
+    taken = 0
+    for build in range(B.lib.q8_num_bottleneck_builds()):
+        for t in outs:
+            t.fill_(77)
+        code = B.lib.q8_run_bottleneck(ops, build, torch.cuda.current_stream().cuda_stream)
+        assert code in (0, -2)
+        if code == 0:
+            taken += 1
+            for t, w_ in zip(outs, want):
+                assert np.array_equal(host(t), w_), B.lib.q8_bottleneck_build_name(build)
+    assert taken == (2 if 3 * W <= {64: 192, 128: 128, 256: 64}[mid] else 1)
+    # as a marked triple, whatever the library makes of it
+    for t in outs:
+        t.fill_(77)
+    ops[0].flags |= B.OPF_BLOCK
+    streams = (ctypes.c_void_p * 1)(torch.cuda.current_stream().cuda_stream)
+    assert B.lib.q8_run_ops(ops, 3, streams, 1) == 0
+    for t, w_ in zip(outs, want):
+        assert np.array_equal(host(t), w_)
+
+
 # layers whose reduction steps cross filter taps: several taps a step (C below the step's bytes), at
 # most one further (C above), the most taps that the kernel takes, as one row and as one column
 TAP_CASES = [
