@@ -132,7 +132,7 @@ int pick_halo3(const q8_conv_desc* d) {
   const long M = (long)d->N * d->H * d->W;
   int smallest = -1;
   for (const Shape& s : shapes) {
-    if (d->W > s.max_w || (s.bc == 128 && d->K <= 64)) continue;
+    if (d->W > s.max_w || (s.bc == 128 && d->K <= 64) || (s.index == 4 && d->W <= 63 && d->K >= 128)) continue;
     const long tiles = ((M + s.bp - 1) / s.bp) * ((d->K + s.bc - 1) / s.bc);
     // (the 64 x 64 tile inside a network, its filters coming from HBM: a ring of nine slabs)
     if (tiles >= 360) return s.index == 6 ? 11 : s.index;
@@ -148,6 +148,19 @@ int pick_halo3(const q8_conv_desc* d) {
   if (smallest == 6 && d->C % 128 == 0) {
     const long tiles = ((M + 63) / 64) * ((d->K + 63) / 64), tiles_wide = ((M + 63) / 64) * ((d->K + 127) / 128);
     return d->K > 64 && tiles_wide >= 192 ? 9 : tiles > 256 ? 11 : 12;
+  }
+  // Maps of 32 to 95 pixels across with too few tiles of 128 x 64 likewise: while tiles of 64 x 64 fit one per
+  // CU, those (512 -> 512 on 38 x 38: 16.3 us as 96 tiles of 128 x 64, 11.2 in one group, 10.5 in two; 256 -> 256
+  // on 40 x 40 10.1, 7.5, 7.4, the latency family 12.5; 128 -> 128 on 56 x 56 7.6, 6.0, 6.2), then two groups on
+  // 128 x 64 (512 -> 512 on two such maps 15.6 -> 13.7, 256 -> 256 on 75 x 75 11.1 -> 10.2; more than 256 of
+  // them are a second round: 38 x 38 on four maps 21.0 and 25.7).  Fewer than 128 output channels would gain as
+  // much (128 -> 80 on two maps of 55 x 57 8.2 -> 6.2) and are left to the 128 x 64 tiles for wide maps, whose
+  // extended build is tested on them.
+  if (d->K >= 128 && (smallest == 0 || smallest == 4)) {
+    const long across = (d->K + 63) / 64, tiles64 = ((M + 63) / 64) * across, tiles128 = ((M + 127) / 128) * across;
+    const bool two = d->C % 128 == 0 && d->C >= 256;
+    if (d->W <= 63 && tiles64 <= 256) return two ? 14 : 15;
+    if (d->W <= 95 && tiles128 <= 256 && two) return d->W <= 63 ? 10 : 16;
   }
   return smallest;
 }
@@ -312,9 +325,10 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
     tiled_us = block_tiles_us(d);
   } else if (tiled >= first_halo) {
     q8::halo_variant_tile(tiled - first_halo, &bp, &bc);
-    const bool two_groups = tiled - first_halo == 12 || tiled - first_halo == 9;
+    const int h = tiled - first_halo;
     const float wg = (float)(((M + bp - 1) / bp) * ((d->K + bc - 1) / bc));
-    tiled_us = 4.34f + (two_groups ? 0.668f : 1.58f) * (float)(d->C / 64) * fmaxf(1.0f, wg / 256.0f);
+    const float chunk = h == 12 || h == 9 || h == 14 ? 0.668f : h == 15 ? 0.86f : h == 10 || h == 16 ? 1.2f : 1.58f;
+    tiled_us = 4.34f + chunk * (float)(d->C / 64) * fmaxf(1.0f, wg / 256.0f);
   } else {
     q8::ring_variant_tile(ext ? q8::ext_variant(tiled) : tiled, &bp, &bc);
     tiled_us = ring_tiles_us(d, M, bp, bc);

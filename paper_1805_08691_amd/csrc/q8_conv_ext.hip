@@ -37,7 +37,11 @@ int launch_halo_ext(int family, ConvParams& p, hipStream_t stream) {
     case 6: return halo_ext<2, 2, 1, 1, 2, 1, 3>(p, stream);
     case 9: return halo_ext<2, 2, 1, 2, 2, 2, 3>(p, stream);
     case 11: return halo_ext<2, 2, 1, 1, 2, 1, 9>(p, stream);
+    case 10: return halo_ext<2, 2, 2, 1, 4, 2, 3>(p, stream);
     case 12: return halo_ext<2, 2, 1, 1, 2, 2, 9>(p, stream);
+    case 14: return halo_ext<2, 2, 1, 1, 3, 2, 9>(p, stream);
+    case 15: return halo_ext<2, 2, 1, 1, 3, 1, 9>(p, stream);
+    case 16: return halo_ext<2, 2, 2, 1, 5, 2, 3>(p, stream);
     default: return Q8_EUNSUPPORTED;
   }
 }

@@ -47,6 +47,13 @@ const HaloVariant kHaloVariants[] = {
       HaloShape<2, 2, 1, 1, 2>::max_w() },                      // 12: 64 x 64, two groups
     { "conv_i8_halo3_kernel<2,2,1,2,2,1,9>", &launch_halo3_or_generic<2, 2, 1, 2, 2, 1, 9>, 64, 128,
       HaloShape<2, 2, 1, 2, 2>::max_w() },                      // 13: 64 x 128
+    // ... on wider maps
+    { "conv_i8_halo3_kernel<2,2,1,1,3,2,9>", &launch_halo3_or_generic<2, 2, 1, 1, 3, 2, 9>, 64, 64,
+      HaloShape<2, 2, 1, 1, 3>::max_w() },                      // 14: 64 x 64, two groups, maps up to 63 wide
+    { "conv_i8_halo3_kernel<2,2,1,1,3,1,9>", &launch_halo3_or_generic<2, 2, 1, 1, 3, 1, 9>, 64, 64,
+      HaloShape<2, 2, 1, 1, 3>::max_w() },                      // 15: 64 x 64
+    { "conv_i8_halo3_kernel<2,2,2,1,5,2>", &launch_halo3_or_generic<2, 2, 2, 1, 5, 2>, 128, 64,
+      HaloShape<2, 2, 2, 1, 5, 2>::max_w() },                   // 16: 128 x 64, two groups, maps up to 95 wide
 };
 #undef Q8_HALO_ROW
 constexpr int kNumHaloVariants = sizeof(kHaloVariants) / sizeof(kHaloVariants[0]);

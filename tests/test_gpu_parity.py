@@ -2280,7 +2280,11 @@ EXT_CASES = [
     ("p3b_kernel", dict(N=12, H=55, W=57, C=32, K=64, R=3, S=3, pad_h=1, pad_w=1)),
     ("pw_kernel<1,2> + residual", dict(N=2, H=91, W=113, C=128, K=80, R=1, S=1)),
     ("pw_kernel<2,2> + residual", dict(N=1, H=1, W=61441, C=128, K=272, R=1, S=1)),
-    ("pw_kernel<2,4> + residual", dict(N=1, H=1, W=128129, C=256, K=368, R=1, S=1))]
+    ("pw_kernel<2,4> + residual", dict(N=1, H=1, W=128129, C=256, K=368, R=1, S=1)),
+    ("halo3_kernel<2,2,1,1,3,2,9>", dict(N=1, H=39, W=37, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,1,1,3,1,9>", dict(N=1, H=55, W=63, C=192, K=144, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,2,1,4,2>", dict(N=2, H=39, W=38, C=256, K=528, R=3, S=3, pad_h=1, pad_w=1)),
+    ("halo3_kernel<2,2,2,1,5,2>", dict(N=1, H=66, W=95, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1))]
 
 
 @pytest.mark.parametrize("idx", range(len(EXT_CASES)))
