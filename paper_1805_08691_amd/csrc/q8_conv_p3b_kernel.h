@@ -76,13 +76,16 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p)
   auto slot_of = [](int rho, int chunk) {
     return CHUNKS == 4 ? chunk ^ ((rho >> 2) & 3) : chunk ^ ((rho >> 3) & 1);
   };
+  // (by the column alone for 64 channels: an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and 24-27
+  // together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next)
+  auto patch_slot = [&](int rho, int x, int chunk) { return CHUNKS == 4 ? chunk ^ ((x >> 2) & 3) : slot_of(rho, chunk); };
   int pr_y[PL], pr_x[PL], pr_off[PL];          // ... and its offset from the block's
 #pragma unroll
   for (int j = 0; j < PL; ++j) {
     const int rho = (wave + NW * j) * Sh::RPW + lane / CHUNKS;
     pr_y[j] = rho < Sh::PATCH_PIX ? rho / PW : -4096;            // beyond the patch: never inside
     pr_x[j] = rho % PW;
-    pr_off[j] = (pr_y[j] * W + pr_x[j]) * p.in_cs + slot_of(rho, lane % CHUNKS) * 16;
+    pr_off[j] = (pr_y[j] * W + pr_x[j]) * p.in_cs + patch_slot(rho, pr_x[j], lane % CHUNKS) * 16;
   }
   // tile number -> image and block origin
   auto tile_origin = [&](int tile, int& n, int& h0, int& w0) {
@@ -142,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p)
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
         const int rho = (wave_p * TP * 2 + q + (frag_row >> 4)) * PW + (frag_row & 15) + s;
-        b_foff[s][q][h] = rho * CB + slot_of(rho, 2 * h + frag_half) * 16;
+        b_foff[s][q][h] = rho * CB + patch_slot(rho, (frag_row & 15) + s, 2 * h + frag_half) * 16;
       }
 
   int st_off[STORES];
