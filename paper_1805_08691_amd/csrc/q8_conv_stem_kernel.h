@@ -410,7 +410,11 @@ int launch_stem(ConvParams& p, const StemImage& im, hipStream_t stream) {
   // 0.700 ms per step with 5 instead of 3 pooled rows per strip) -- between four and six rows
   // each (POOL: three to six pooled rows, i.e. 7 .. 13 output rows of which one is computed
   // twice).
-  const int rows = POOL ? im.Hp : p.Ho, least = POOL ? 3 : 4, most = 6;
+  // Few images: shorter strips, down to one row, as long as each still gets a CU of its own (a workgroup's
+  // start and its rows one after the other are what takes the time).
+  const int rows = POOL ? im.Hp : p.Ho, most = 6;
+  int least = 1;
+  while (least < (POOL ? 3 : 4) && (long)p.N * ((rows + least - 1) / least) > 256) ++least;
   int strips = (resident / 2 + p.N - 1) / p.N;
   if (strips < 1) strips = 1;
   int rows_per_strip = (rows + strips - 1) / strips;
