@@ -1,4 +1,5 @@
 // The builds of the latency family (see q8_conv_direct_kernel.h) and their table.
+#include <utility>
 #include "q8_conv_direct_kernel.h"
 
 namespace q8 {
@@ -117,8 +118,11 @@ int pick_direct(long M, int K, int red_len, float* us) {
   return best;
 }
 // The same for several independent layers in one launch: the busiest CU has the largest tile, or
-// its share of all of them.
-int pick_direct_group(const ConvParams* const* p, int n, float* us) {
+// its share of all of them.  Puts the layers with the longest tiles first, so that the launch does not
+// end with them.
+int pick_direct_group(const ConvParams** p, int n, float* us) {
+  for (int i = 1; i < n; ++i)
+    for (int j = i; j > 0 && p[j]->red_len > p[j - 1]->red_len; --j) std::swap(p[j], p[j - 1]);
   int best = -1;
   for (int v = 0; v < kNumDirectVariants; ++v) {
     const DirectVariant& d = kDirectVariants[v];

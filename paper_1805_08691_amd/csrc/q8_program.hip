@@ -10,7 +10,7 @@ int conv_launch_chosen(int variant, ConvParams& p, hipStream_t s);
 int first_direct_variant();
 int num_direct_variants();
 bool direct_applicable(const ConvParams& p);
-int pick_direct_group(const ConvParams* const* p, int n, float* us);
+int pick_direct_group(const ConvParams** p, int n, float* us);
 int launch_direct_group_variant(int variant, const ConvParams* const* p, int n, hipStream_t stream);
 int ring_group_takes(const q8_conv_desc* d, const ConvParams& p);
 int pick_ring_group(const ConvParams** p, int n, float* us);
