@@ -1072,6 +1072,37 @@ def test_pool_i8(B, mode, shape, win, m, slice_):
     assert np.array_equal(host(got), want)
 
 
+@pytest.mark.parametrize("m", [1.0, 0.37])
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("shape,win,extra", [
+    ((1, 1, 1, 16), (3, 1, 1), 0), ((2, 2, 1, 48), (3, 1, 2), 0), ((1, 5, 6, 16), (3, 1, 0), 0),
+    ((3, 7, 4, 32), (3, 1, 1), 16), ((1, 3, 3, 16), (3, 2, 2), 0), ((2, 6, 9, 48), (3, 2, 1), 0),
+    ((2, 9, 8, 16), (2, 2, 0), 16), ((1, 5, 7, 32), (2, 2, 0), 1), ((1, 5, 5, 16), (3, 3, 0), 0),
+])
+def test_pool_i8_strips(B, shape, win, extra, mode, m):
+    """Windows at every edge of the image, odd rests of a strip, a slice of a wider tensor, and one output row
+    and column beyond the last whole window (extra = 1); codes at their bounds among them."""
+    rng = np.random.default_rng(sum(shape) + 10 * win[0] + win[1])
+    x = rng.integers(-128, 128, size=shape, dtype=np.int8)
+    x[rng.random(shape) < 0.3] = -128
+    x[rng.random(shape) < 0.2] = 127
+    R, stride, pad = win
+    Ho = (shape[1] + 2 * pad - R) // stride + 1 + extra % 2
+    Wo = (shape[2] + 2 * pad - R) // stride + 1 + extra % 2
+    off = extra & ~1
+    base = rng.integers(-128, 128, size=(shape[0], Ho, Wo, shape[3] + off), dtype=np.int8)
+    q_out = np.float32(0.013)
+    q_in = np.float32(m) * q_out
+    want = orc.pool_i8(x, mode, R, R, stride, pad, Ho, Wo, orc.residual_scale(q_in, q_out), out=base.copy(),
+                       out_c_off=off)
+    got = B.pool_i8(dev(x), mode, R, R, stride, pad, Ho, Wo, float(q_in), float(q_out), out=dev(base),
+                    out_c_off=off)
+    assert np.array_equal(host(got), want)
+    if mode == "max" and m == 1.0:
+        got = host(B.maxpool_i8(dev(x), R, R, stride, pad, Ho, Wo))
+        assert np.array_equal(got, orc.maxpool_i8(x, R, R, stride, pad, Ho, Wo))
+
+
 def test_pool_f32(B):
     import torch
     rng = np.random.default_rng(7)
