@@ -20,6 +20,12 @@
 // waits for a tile's stores.  64 -> 64 on 300 x 300 x 32 images 160 -> 133 us, on 56 x 56 x 32 9.2 -> 8.9;
 // 32 -> 64 on 147 x 147 x 32 34.5 us in the general kernel (half a step per tap), 20.5 here, 32 -> 32 29.2 and
 // 15.6 (48 MB: 9.3 us of a copy).
+//
+// POOL: the 2x2 maximum with stride 2 behind the layer in the same launch.  Blocks begin on even rows and columns,
+// so every window lies in one staging tile: two rows of it in the lane that stores them, the other two in a lane
+// of the same sixteen.  The pass that reads the layer's whole output again is gone, and so is its launch: two
+// launches / one, us: 64 -> 64 on 300 x 300, 32 images 151 / 142, one 12.4 / 8.8; on 56 x 56 x 64 19.1 / 14.7;
+// 32 -> 64 on 147 x 147 x 32 32.0 / 25.2.
 #pragma once
 #include "q8_conv_ring_kernel.h"
 
@@ -41,16 +47,22 @@ struct P3bShape {
   static constexpr int LDS_BYTES = PATCH_BYTES + (PATCH_BYTES + S_BYTES > A_BYTES ? PATCH_BYTES + S_BYTES : A_BYTES);
 };
 
+// The maximum's output for POOL: pooled rows and columns, address as of pooled pixel (0, 0, 0).
+struct P3bPool {
+  int8_t* y;
+  int bytes, Hp, Wp, cs;
+};
+
 // p.n_ptiles = tiles in all (N * tiles_h * tiles_w); div_img and div_row divide a tile's number by the
 // tiles of an image and of a row of them, n_ctiles (set by launch_p3b).
-template <int CB, int WC, int EXT>
-__global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p) {
+template <int CB, int WC, int EXT, bool POOL = false>
+__global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p, const P3bPool pool) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = P3bShape<CB, WC>;
   constexpr int NW = Sh::NW, WP = Sh::WP, TP = Sh::TP, BP = Sh::BP, BC = Sh::BC, CHUNKS = Sh::CHUNKS;
   constexpr int TH = Sh::TH, TW = Sh::TW, PW = Sh::PW, PL = Sh::PL;
   constexpr int SLOTS = BC / 16, NH = CB / 32, NQ = 2 * TP + 1;
-  constexpr int STORES = BP * SLOTS / (NW * 64);
+  constexpr int STORES = BP * SLOTS / (NW * 64), ALL_STORES = STORES + POOL;
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int8_t* const patch = lds;
   int8_t* const stage = lds + 2 * Sh::PATCH_BYTES;
@@ -148,12 +160,12 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p)
         b_foff[s][q][h] = rho * CB + patch_slot(rho, (frag_row & 15) + s, 2 * h + frag_half) * 16;
       }
 
-  int st_off[STORES];
-#pragma unroll
-  for (int k = 0; k < STORES; ++k) {
-    const int row = (tid + k * NW * 64) / SLOTS;
-    st_off[k] = (row / TW * Wo + row % TW) * p.out_cs + (tid + k * NW * 64) % SLOTS * 16;
-  }
+  // Copy-out: a lane's two groups, half a block apart; for POOL in rows below one another (without it that order
+  // costs 64 -> 64 on 300 x 300 x 32 images 115 -> 120 us).
+  constexpr int LPR = TW * SLOTS;                 // lanes of a block row
+  static_assert(STORES == 2 && NW * 64 / LPR * 2 == TH, "a lane stores two rows of a block");
+  constexpr int DOWN = POOL ? 1 : TH / 2;
+  const int out_y = tid / LPR * (POOL ? 2 : 1), out_x = tid % LPR / SLOTS, out_g = tid % SLOTS;
   // Bare barriers behind this wave's own LDS accesses: a fence would also wait for the patch in flight
   // and for the stores.
   auto meet = [&]() __attribute__((always_inline)) {
@@ -182,10 +194,10 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p)
     // lanes outside the map out of range) and the next patch: nobody waits for the stores.
     if (next < p.n_ptiles) {
       issue_patch(next, buf ^ 1);
-      if (it) wait_vmcnt<PL + STORES>();
+      if (it) wait_vmcnt<PL + ALL_STORES>();
       else wait_vmcnt<PL>();
     } else {
-      if (it) wait_vmcnt<STORES>();
+      if (it) wait_vmcnt<ALL_STORES>();
       else wait_vmcnt<0>();
     }
     meet();
@@ -242,16 +254,43 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p)
       int n, h0, w0;
       tile_origin(tile, n, h0, w0);
       const int origin = ((n * Ho + h0) * Wo + w0) * p.out_cs + p.out_off;
+      const bool in = (w0 + out_x < Wo) & (out_g * 16 < p.K);
+      v4i codes[STORES];
 #pragma unroll
       for (int k = 0; k < STORES; ++k) {
-        const int c = tid + k * NW * 64;
-        const int row = c / SLOTS, g = c % SLOTS;             // pixel of the block, channel group
-        const v4i codes =
-            *reinterpret_cast<const v4i*>(stage + row * BC + ((g ^ swz_out<SLOTS>(row)) << 4));
-        int off = origin + st_off[k];
+        const int y = out_y + k * DOWN, row = y * TW + out_x;
+        codes[k] = *reinterpret_cast<const v4i*>(stage + row * BC + ((out_g ^ swz_out<SLOTS>(row)) << 4));
+        int off = origin + (y * Wo + out_x) * p.out_cs + out_g * 16;
         asm volatile("" : "+v"(off));
-        off = (h0 + row / TW < Ho) & (w0 + row % TW < Wo) & (g * 16 < p.K) ? off : kOobOffset;
-        __builtin_amdgcn_raw_buffer_store_b128(codes, rsrc_y, off, 0, 0);
+        off = in & (h0 + y < Ho) ? off : kOobOffset;
+        __builtin_amdgcn_raw_buffer_store_b128(codes[k], rsrc_y, off, 0, 0);
+      }
+      if constexpr (POOL) {
+        const __amdgpu_buffer_rsrc_t rsrc_p =
+            __builtin_amdgcn_make_buffer_rsrc((void*)pool.y, 0, pool.bytes, 0x00020000);
+        const bool below = h0 + out_y + 1 < Ho, beside = w0 + out_x + 1 < Wo;     // else the same pixel again
+        v4i most;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {             // 16-bit lanes: odd bytes in place, even ones shifted
+          auto larger = [](int u, int v) __attribute__((always_inline)) {
+            typedef short v2s __attribute__((ext_vector_type(2)));
+            return __builtin_bit_cast(int, __builtin_elementwise_max(__builtin_bit_cast(v2s, u), __builtin_bit_cast(v2s, v)));
+          };
+          // the pixel to the right is SLOTS lanes on, in the same row of 16 lanes for every even one
+          auto right = [](int u) __attribute__((always_inline)) {
+            return __builtin_amdgcn_update_dpp(u, u, 0x100 + SLOTS, 0xf, 0xf, false);
+          };
+          const int w = codes[0][q], w1 = below ? codes[1][q] : w;
+          const int odd = larger(w, w1), even = larger(w << 8, w1 << 8);
+          const int odd1 = right(odd), even1 = right(even);
+          most[q] = (int)__builtin_amdgcn_perm((unsigned)larger(odd, beside ? odd1 : odd),
+                                               (unsigned)larger(even, beside ? even1 : even), 0x07030501u);
+        }
+        const int hp = (h0 + out_y) / 2, wp = (w0 + out_x) / 2;
+        int off = ((n * pool.Hp + hp) * pool.Wp + wp) * pool.cs + out_g * 16;
+        asm volatile("" : "+v"(off));
+        off = in & (out_x % 2 == 0) & (hp < pool.Hp) & (wp < pool.Wp) ? off : kOobOffset;
+        __builtin_amdgcn_raw_buffer_store_b128(most, rsrc_p, off, 0, 0);
       }
     }
     // every wave has read this tile's patch and the staging tile before the next pass
@@ -269,8 +308,8 @@ inline bool p3b_applicable(const ConvParams& p) {
          (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
-template <int CB, int WC, int EXT>
-int launch_p3b_build(ConvParams& p, hipStream_t stream) {
+template <int CB, int WC, int EXT, bool POOL = false>
+int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}) {
   using Sh = P3bShape<CB, WC>;
   const long tiles_w = (p.Wo + Sh::TW - 1) / Sh::TW, tiles_h = (p.Ho + Sh::TH - 1) / Sh::TH;
   const long tiles = (long)p.N * tiles_h * tiles_w;
@@ -280,7 +319,7 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream) {
   const FastDiv img = make_fast_div((unsigned)(tiles_h * tiles_w)), row = make_fast_div((unsigned)tiles_w);
   p.div_img_m = img.m; p.div_img_s = img.s;
   p.div_row_m = row.m; p.div_row_s = row.s;
-  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT>;
+  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT, POOL>;
   static const int resident = [&]() {
     int per_cu = 0, dev = 0, cus = 256;
     hipDeviceProp_t prop;
@@ -294,7 +333,7 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream) {
   // as many workgroups as stay resident, every one with the same number of tiles (+- 1)
   const int passes = (p.n_ptiles + resident - 1) / resident;
   const int grid = (p.n_ptiles + passes - 1) / passes;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), Sh::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), Sh::LDS_BYTES, stream, p, pool);
   return q8_launch_status();
 }
 

@@ -17,6 +17,8 @@ int pick_ring_group(const ConvParams** p, int n, float* us);
 int launch_ring_group_variant(int build, const ConvParams* const* p, int n, hipStream_t stream);
 const char* direct_variant_name(int variant);
 const char* ring_group_variant_name(int build);
+int first_p3_variant();
+int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, long bytes, hipStream_t stream);
 int num_bneck_builds();
 const char* bneck_build_name(int build);
 bool bneck_applicable(const ConvParams& a, const ConvParams& b, const ConvParams& c);
@@ -194,16 +196,84 @@ int run_block(const q8_op* ops, void* stream) {
   return Q8_OK;
 }
 
+// Whether pool is the 2x2 maximum with stride 2 over conv's output and nothing else: no change of factor, no
+// window without a pixel, every address in reach, and an output apart from all that the convolution reads and
+// writes (a program may reuse the convolution's input there).
+bool pool_behind(const q8_op& pool, const q8_op& conv, const ConvParams& p) {
+  const bool to_slice = pool.kind == Q8_OP_POOL;
+  if (!(to_slice ? pool.mode == 0 && pool.q_x == pool.q_out && q8_finite_pos(pool.q_x) : pool.kind == Q8_OP_MAXPOOL))
+    return false;
+  const int cs = to_slice ? pool.d.out_c_stride : pool.C, c_off = to_slice ? pool.d.out_c_off : 0;
+  if (pool.x != conv.y || pool.d.N != p.N || pool.H != p.Ho || pool.W != p.Wo || pool.C != p.K || p.out_cs != p.K ||
+      p.out_off != 0 || pool.R != 2 || pool.S != 2 || pool.stride != 2 || pool.pad != 0 || pool.Ho < 1 || pool.Wo < 1 ||
+      pool.Ho > (p.Ho + 1) / 2 || pool.Wo > (p.Wo + 1) / 2 || !pool.y || c_off < 0 || cs < c_off + pool.C ||
+      (cs | c_off) % 16 || !q8_aligned(pool.y, 16))
+    return false;
+  const size_t bytes = (size_t)p.N * pool.Ho * pool.Wo * cs, table = (size_t)p.K * sizeof(int32_t);
+  auto apart = [&](const void* b, size_t n) {
+    const char *const a = (const char*)pool.y, *const c = (const char*)b;
+    return !b || c + n <= a || a + bytes <= c;
+  };
+  return apart(p.x, p.x_bytes) && apart(p.w, p.w_bytes) && apart(p.bias, table) &&
+         apart(p.y, (size_t)p.M * p.out_cs);
+}
+
+// A convolution, and the op behind it on the same stream in the same launch (*both) where the block-tiled 3x3
+// kernel takes the layer and that op is the maximum over its output.
+int run_conv_and_next(const q8_op& conv, const q8_op& next, bool* both, void* stream) {
+  ConvParams p;
+  bool empty = false;
+  int rc = conv_fill_op(&conv, p, &empty);
+  if (rc != Q8_OK || empty) return rc;
+  float us = 0.0f;
+  const int variant = conv_choose(&conv.d, p, &us);
+  if (variant == first_p3_variant() + 2 && pool_behind(next, conv, p)) {
+    const bool to_slice = next.kind == Q8_OP_POOL;
+    const int cs = to_slice ? next.d.out_c_stride : next.C, c_off = to_slice ? next.d.out_c_off : 0;
+    rc = launch_p3b_pooled(p, (int8_t*)next.y + c_off, next.Ho, next.Wo, cs,
+                           (long)p.N * next.Ho * next.Wo * cs - c_off, (hipStream_t)stream);
+    *both = rc == Q8_OK;
+    if (rc != Q8_EUNSUPPORTED) return rc;
+  }
+  return conv_launch_chosen(variant, p, (hipStream_t)stream);
+}
+
 }  // namespace
 }  // namespace q8
 
 extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int n_streams) {
   Q8_REQUIRE(n_ops >= 0 && (n_ops == 0 || (ops && streams && n_streams >= 1)), Q8_EINVAL);
   for (int i = 0; i < n_ops; ++i) Q8_REQUIRE(ops[i].stream >= 0 && ops[i].stream < n_streams, Q8_EINVAL);
+  // Ops that went in front of their place, with the convolution whose output they read: each the next op of
+  // its stream behind that one (streams wait for each other outside of a list only).
+  constexpr int kAhead = 8;
+  int done[kAhead], n_done = 0;
+  auto run_single = [&](int i) {
+    const q8_op& o = ops[i];
+    int next = i + 1;
+    while (next < n_ops && next - i < kAhead && ops[next].stream != o.stream) ++next;
+    if (o.kind != Q8_OP_CONV || next >= n_ops || ops[next].stream != o.stream || n_done == kAhead ||
+        (ops[next].kind != Q8_OP_POOL && ops[next].kind != Q8_OP_MAXPOOL))
+      return q8::run_one(o, streams[o.stream]);
+    bool both = false;
+    const int rc = q8::run_conv_and_next(o, ops[next], &both, streams[o.stream]);
+    if (both) done[n_done++] = next;
+    return rc;
+  };
   for (int i = 0; i < n_ops;) {
     const q8_op& o = ops[i];
     int j = i + 1;
     int rc;
+    bool skip = false;
+    for (int k = 0; k < n_done; ++k)
+      if (done[k] == i) {
+        skip = true;
+        done[k] = done[--n_done];
+      }
+    if (skip) {
+      ++i;
+      continue;
+    }
     if (o.kind == Q8_OP_DEQUANTIZE) {
       while (j < n_ops && ops[j].kind == Q8_OP_DEQUANTIZE && ops[j].stream == o.stream) ++j;
       rc = q8::dequantize_list(ops + i, j - i, (hipStream_t)streams[o.stream]);
@@ -215,9 +285,9 @@ extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int
       while (j < n_ops && j - i < q8::kMaxGroup && ops[j].group == o.group && ops[j].stream == o.stream &&
              ops[j].kind != Q8_OP_DEQUANTIZE)
         ++j;
-      rc = j - i == 1 ? q8::run_one(o, streams[o.stream]) : q8::run_group(ops + i, j - i, streams[o.stream]);
+      rc = j - i == 1 ? run_single(i) : q8::run_group(ops + i, j - i, streams[o.stream]);
     } else {
-      rc = q8::run_one(o, streams[o.stream]);
+      rc = run_single(i);
     }
     if (rc != Q8_OK) return rc;
     i = j;

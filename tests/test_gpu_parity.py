@@ -1072,6 +1072,58 @@ def test_pool_i8(B, mode, shape, win, m, slice_):
     assert np.array_equal(host(got), want)
 
 
+@pytest.mark.parametrize("shape,C,K,pad,ceil,slice_", [
+    ((1, 299, 301), 64, 64, 1, False, (64, 0)),    # odd maps, rests of blocks in both directions
+    ((1, 299, 301), 64, 48, 1, True, (80, 16)),    # the last windows hold one row and column; into a slice
+    ((5, 149, 163), 32, 64, 1, True, (64, 0)),
+    ((2, 149, 151), 32, 32, 0, False, (32, 0)),    # 16 x 16 blocks
+])
+def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
+    """The block-tiled 3x3 kernel with the 2x2 maximum in its launch: both tensors as by two calls, nothing
+    beside them; a maximum that writes over the layer's input goes behind it."""
+    import ctypes
+    N, H, W = shape
+    rng = np.random.default_rng(H * W + C + K)
+    Ho, Wo = H + 2 * pad - 2, W + 2 * pad - 2
+    Hp, Wp = (Ho + ceil) // 2, (Wo + ceil) // 2
+    cs, off = slice_
+    x = rng.integers(-128, 128, (N, H, W, C)).astype(np.int8)
+    z_w = rng.integers(-128, 128, (K, 3, 3, C)).astype(np.int8)
+    bias = rng.integers(-2000, 2000, K).astype(np.int32)
+    g = orc.ConvGeom(N=N, H=H, W=W, C=C, K=K, R=3, S=3, pad_h=pad, pad_w=pad)
+    q_x, q_w, q_out = 0.02, 0.01 / np.sqrt(9.0 * C), 0.011
+    d = B.ConvDesc(N, H, W, C, K, 3, 3, 1, 1, pad, pad, 1, 1)
+    assert B.conv_variant(d) == "conv_i8_p3b_kernel"
+    want = orc.conv_layer_i8(g, x, q_x, z_w, q_w, bias, q_out, 0)[0]
+    pooled = np.full((N, Hp, Wp, cs), 77, np.int8)
+    pooled = orc.pool_i8(want, "max", 2, 2, 2, 0, Hp, Wp, np.float32(1), out=pooled, out_c_off=off)
+    wp, b = B.pack_weights(d, dev(z_w)), dev(bias)
+    streams = (ctypes.c_void_p * 1)(torch.cuda.current_stream().cuda_stream)
+    for apart in (True, False):
+        xd = dev(x)
+        if not apart and xd.numel() < pooled.size:
+            continue
+        y = torch.full((N, Ho, Wo, K), 77, dtype=torch.int8, device="cuda")
+        z = torch.full(pooled.shape, 77, dtype=torch.int8, device="cuda")
+        ops = (B.Op * 2)()
+        o = ops[0]
+        o.kind, o.d, o.x, o.w, o.bias, o.y = B.OP_CONV, d, xd.data_ptr(), wp.data_ptr(), b.data_ptr(), y.data_ptr()
+        o.q_x, o.q_w, o.q_out, o.group = q_x, q_w, q_out, 1
+        o = ops[1]
+        o.kind = B.OP_POOL
+        o.x, o.y = y.data_ptr(), (z if apart else xd).data_ptr()
+        o.d.N, o.H, o.W, o.C = N, Ho, Wo, K
+        o.R = o.S = o.stride = 2
+        o.Ho, o.Wo, o.q_x, o.q_out, o.group = Hp, Wp, q_out, q_out, 2
+        o.d.out_c_stride, o.d.out_c_off = cs, off
+        assert B.lib.q8_run_ops(ops, 2, streams, 1) == 0
+        assert np.array_equal(host(y), want)
+        got = host(z if apart else xd.flatten()[:pooled.size].view(pooled.shape))
+        assert np.array_equal(got[..., off:off + K], pooled[..., off:off + K])
+        if apart:
+            assert np.array_equal(got, pooled)
+
+
 @pytest.mark.parametrize("m", [1.0, 0.37])
 @pytest.mark.parametrize("mode", ["max", "avg"])
 @pytest.mark.parametrize("shape,win,extra", [
