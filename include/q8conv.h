@@ -352,7 +352,8 @@ int q8_conv_chain_static_status(int32_t *status_host);
  * fused sum), all three tensors written as by single calls.  Where they are no such block, or the
  * estimates are against it, they are launched one after the other.  Neighbouring Q8_OP_DEQUANTIZE ops never depend on each other.
  * A 2x2 maximum with stride 2 over the output of the convolution in front of it on its stream may run in that
- * one's launch, both tensors written; a maximum that writes over what the convolution reads runs behind it.
+ * one's launch, both tensors written (so in front of ops of other streams that stand between the two); a maximum that
+ * writes over what the convolution reads runs behind it.
  * Returns the first error; ops behind it are not enqueued.                               */
 enum {
   Q8_OP_CONV = 0, Q8_OP_HEAD, Q8_OP_POOL, Q8_OP_MAXPOOL, Q8_OP_QUANTIZE, Q8_OP_QUANTIZE_PAD,
