@@ -70,13 +70,14 @@ int run_one(const q8_op& o, void* stream) {
 // The build for a block of three layers, -1: three launches.  The estimates of single launches miss what
 // three dependent ones take in a row by a factor that goes with the map (measured / estimated at 1 to 32 images:
 // 14 x 14 pixels 1.03 ... 0.8, 28 x 28 1.02 ... 1.09, 56 x 56 0.9 ... 1.24), so each kind of block has its own.
-// One image's unsigned or per-channel blocks stay three launches: 9.7 us and 8.5 by themselves, but inside
-// ResNet-50 209.0 and 211.9 with three of them (plain codes 203.0 and 200.9).
+// Unsigned or per-channel blocks of one or two images stay three launches: 9.7 us and 8.5 by themselves, but inside
+// ResNet-50 209.0 and 211.9 with three of them (plain codes 203.0 and 200.9); two images unsigned 247.1 with three
+// launches and 249.0, per channel 247.3 and 247.2; three per channel 303.6 and 275.6.
 int block_choose(const q8_op* ops, const ConvParams* p) {
   float us = 0.0f, single = 0.0f;
   const int build = bneck_applicable(p[0], p[1], p[2]) ? pick_bneck(p[0], p[1], p[2], &us) : -1;
   if (build < 0) return -1;
-  if (p[0].N == 1 && (is_extended(p[0]) || is_extended(p[1]) || is_extended(p[2]))) return -1;
+  if (p[0].N <= 2 && (is_extended(p[0]) || is_extended(p[1]) || is_extended(p[2]))) return -1;
   for (int i = 0; i < 3; ++i) {
     float t = 0.0f;
     conv_choose(&ops[i].d, p[i], &t);
