@@ -120,12 +120,13 @@ void conv_i8_bneck_kernel(const BneckParams q) {
   constexpr int PB = Sh::param_bytes(MID);               // biases: layer A, B, C; then the scales
   const int scales_off = 2 * PB + Sh::param_bytes(K2);
 
-  // ---- biases and scales into LDS, a wave-wide load at a time
+  // ---- biases and scales into LDS, a wave-wide load at a time (the whole offset in the vector operand: that
+  // is what the range check compares with the table's bytes, whichever way it counts a scalar offset)
   {
     auto copy = [&](const void* from, int k, int8_t* to, int first) __attribute__((always_inline)) {
       const int loads = Sh::param_bytes(k) >> 10;
       for (int i = (wave + NW - first) % NW; i < loads; i += NW)
-        load_lds(rsrc_of(from, from ? k * 4 : 0), to + i * 1024, lane * 16, i * 1024);
+        load_lds(rsrc_of(from, from ? k * 4 : 0), to + i * 1024, i * 1024 + lane * 16, 0);
     };
     copy(q.bias_a, MID, params, 0);
     copy(q.bias_b, MID, params + PB, 1);
@@ -170,9 +171,10 @@ void conv_i8_bneck_kernel(const BneckParams q) {
         for (int j = 0; j < FL; ++j) f_off[j] = f_ch[j] * MID + f_chunk[j];
         f_soff = (f_segment - 2) * (MID * MID);
         f_left = MID / G;
-      } else {                             // behind the last: zeros, nothing is read
+      } else {          // behind the last, each time: no bytes and no scalar offset, so nothing is read
         f_rsrc = rsrc_of(q.wc, 0);
-        f_left = 0x7fffffff;
+        f_soff = 0;
+        f_left = 1;
       }
     }
   };

@@ -2145,6 +2145,49 @@ def test_bottleneck_builds(B, idx, option):
         assert np.array_equal(host(t), w_)
 
 
+@pytest.mark.parametrize("mid,K2", [(64, 320), (128, 384)])
+def test_bottleneck_tables_end_in_a_part_of_a_load(B, mid, K2):
+    """Biases and scales are copied 256 values at a time and the last copy is a part of one; the filters are
+    requested on behind their last piece.  What lies behind the three tensors changes nothing."""
+    N, H, W, C = 2, 6, 11, 128
+    shapes = [(C, mid, 1), (mid, mid, 3), (mid, K2, 1)]
+    stream = torch.cuda.current_stream().cuda_stream
+    x = torch.randint(-128, 128, (N, H, W, C), dtype=torch.int8, device="cuda")
+    z = [torch.randint(-128, 128, (k, R, R, c), dtype=torch.int8, device="cuda") for c, k, R in shapes]
+    bias = [torch.randint(-2000, 2000, (k,), dtype=torch.int32, device="cuda") for _, k, _ in shapes]
+    scale = [torch.rand(k, device="cuda") * 2e-3 + 1e-4 for _, k, _ in shapes]
+
+    def ends(t, behind):                       # t as the last values of a buffer in front of others
+        buffer = torch.full((t.numel() + 4096,), behind, dtype=t.dtype, device="cuda")
+        buffer[:t.numel()] = t.flatten()
+        return buffer
+    taken = 0
+    for per_channel in (False, True):
+        got = {}
+        for behind in (0, 99):
+            ops, keep, src = (B.Op * 3)(), [], x
+            for i, (c, k, R) in enumerate(shapes):
+                o, d = ops[i], B.ConvDesc(N, H, W, c, k, R, R, 1, 1, R // 2, R // 2, relu=1)
+                y = torch.zeros((N, H, W, k), dtype=torch.int8, device="cuda")
+                keep += [ends(B.pack_weights(d, z[i]), behind), ends(bias[i], behind), ends(scale[i], behind), y]
+                o.kind, o.d, o.x, o.y = B.OP_CONV, d, src.data_ptr(), y.data_ptr()
+                o.w, o.bias = keep[-4].data_ptr(), keep[-3].data_ptr()
+                o.q_x, o.q_w, o.q_out = 0.02, 1.0 if per_channel else 0.0005, 0.011
+                if per_channel:
+                    o.flags, o.aux = B.OPF_PER_CHANNEL, keep[-2].data_ptr()
+                src = y
+            for build in range(B.lib.q8_num_bottleneck_builds()):
+                code = B.lib.q8_run_bottleneck(ops, build, stream)
+                assert code in (0, -2)
+                if code == 0:
+                    taken += 1
+                    got.setdefault(build, []).append([host(t) for t in keep[3::4]])
+        for first, second in got.values():
+            for a, b in zip(first, second):
+                assert np.array_equal(a, b) and len(np.unique(a)) > 32
+    assert taken >= 8
+
+
 # layers whose reduction steps cross filter taps: several taps a step (C below the step's bytes), at
 # most one further (C above), the most taps that the kernel takes, as one row and as one column
 TAP_CASES = [
