@@ -352,8 +352,9 @@ int q8_conv_chain_static_status(int32_t *status_host);
  * fused sum), all three tensors written as by single calls.  Where they are no such block, or the
  * estimates are against it, they are launched one after the other.  Neighbouring Q8_OP_DEQUANTIZE ops never depend on each other.
  * A 2x2 maximum with stride 2 over the output of the convolution in front of it on its stream may run in that
- * one's launch, both tensors written (so in front of ops of other streams that stand between the two); a maximum that
- * writes over what the convolution reads runs behind it.
+ * one's launch, both tensors written: the launch stands where the maximum does, behind ops of other streams
+ * between the two, none of them ordered with that stream (the same one at another index, the legacy default
+ * stream).  A maximum that writes over what the convolution reads runs behind it.
  * Returns the first error; ops behind it are not enqueued.                               */
 enum {
   Q8_OP_CONV = 0, Q8_OP_HEAD, Q8_OP_POOL, Q8_OP_MAXPOOL, Q8_OP_QUANTIZE, Q8_OP_QUANTIZE_PAD,
@@ -390,6 +391,10 @@ const char *q8_block_variant(const q8_op *ops);
 int q8_num_bottleneck_builds(void);
 const char *q8_bottleneck_build_name(int build);
 int q8_run_bottleneck(const q8_op *ops, int build, void *stream);
+
+/* Index of the maximum that q8_run_ops would put into the launch of the convolution ops[i] (one that is in no
+ * group with others and no marked block); -1: none.  For tests and measurement code.                       */
+int q8_joined_op(const q8_op *ops, int n_ops, void *const *streams, int n_streams, int i);
 
 /* Estimated duration in us of one launch of this layer on an otherwise idle chip (host
  * arithmetic; what the library chooses kernels by): for programs that order independent

@@ -38,11 +38,13 @@ int launch_p3_variant(int variant, ConvParams& p, hipStream_t stream) {
 bool p3_variant_takes(int variant, const ConvParams& p) {
   return variant == 0 ? p3_applicable<4>(p) : variant == 1 ? p3_applicable<6>(p) : p3b_applicable(p);
 }
-// The block-tiled build with a 2x2 maximum of stride 2 behind it (Hp x Wp pooled pixels, cs bytes from one
-// to the next, y 16-byte aligned).  Q8_EUNSUPPORTED where it does not take the layer.
-int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, long bytes, hipStream_t stream) {
-  if (!p3b_applicable(p) || is_extended(p) || bytes >= 0x7fffffffL) return Q8_EUNSUPPORTED;
-  const P3bPool pool{y, (int)bytes, Hp, Wp, cs};
+// The block-tiled build with a 2x2 maximum of stride 2 behind it, and whether it takes the layer and that many
+// bytes of pooled pixels (Hp x Wp of them, cs bytes from one to the next, y 16-byte aligned).
+bool p3b_pooled_takes(const ConvParams& p, size_t bytes) {
+  return p3b_applicable(p) && !is_extended(p) && bytes < 0x7fffffffUL;
+}
+int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, int bytes, hipStream_t stream) {
+  const P3bPool pool{y, bytes, Hp, Wp, cs};
   if (p.C == 64) return launch_p3b_build<64, 2, 0, true>(p, stream, pool);
   if (p.K <= 32) return launch_p3b_build<32, 1, 0, true>(p, stream, pool);
   return launch_p3b_build<32, 2, 0, true>(p, stream, pool);

@@ -18,7 +18,8 @@ int launch_ring_group_variant(int build, const ConvParams* const* p, int n, hipS
 const char* direct_variant_name(int variant);
 const char* ring_group_variant_name(int build);
 int first_p3_variant();
-int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, long bytes, hipStream_t stream);
+bool p3b_pooled_takes(const ConvParams& p, size_t bytes);
+int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, int bytes, hipStream_t stream);
 int num_bneck_builds();
 const char* bneck_build_name(int build);
 bool bneck_applicable(const ConvParams& a, const ConvParams& b, const ConvParams& c);
@@ -197,10 +198,17 @@ int run_block(const q8_op* ops, void* stream) {
   return Q8_OK;
 }
 
-// Whether pool is the 2x2 maximum with stride 2 over conv's output and nothing else: no change of factor, no
+// The 2x2 maximum with stride 2 as the kernel writes it: address of pooled pixel (0, 0), bytes from there on, bytes
+// from one pixel to the next.
+struct Pooled {
+  int8_t* y;
+  int bytes, cs;
+};
+
+// Whether pool is that maximum over conv's output and nothing else: no change of factor, no
 // window without a pixel, every address in reach, and an output apart from all that the convolution reads and
 // writes (a program may reuse the convolution's input there).
-bool pool_behind(const q8_op& pool, const q8_op& conv, const ConvParams& p) {
+bool pool_behind(const q8_op& pool, const q8_op& conv, const ConvParams& p, Pooled* out) {
   const bool to_slice = pool.kind == Q8_OP_POOL;
   if (!(to_slice ? pool.mode == 0 && pool.q_x == pool.q_out && q8_finite_pos(pool.q_x) : pool.kind == Q8_OP_MAXPOOL))
     return false;
@@ -215,29 +223,84 @@ bool pool_behind(const q8_op& pool, const q8_op& conv, const ConvParams& p) {
     const char *const a = (const char*)pool.y, *const c = (const char*)b;
     return !b || c + n <= a || a + bytes <= c;
   };
-  return apart(p.x, p.x_bytes) && apart(p.w, p.w_bytes) && apart(p.bias, table) &&
-         apart(p.y, (size_t)p.M * p.out_cs);
+  if (!p3b_pooled_takes(p, bytes) || !apart(p.x, p.x_bytes) || !apart(p.w, p.w_bytes) || !apart(p.bias, table) ||
+      !apart(p.y, (size_t)p.M * p.out_cs))
+    return false;
+  *out = {(int8_t*)pool.y + c_off, (int)(bytes - c_off), cs};
+  return true;
 }
 
-// A convolution, and the op behind it on the same stream in the same launch (*both) where the block-tiled 3x3
-// kernel takes the layer and that op is the maximum over its output.
-int run_conv_and_next(const q8_op& conv, const q8_op& next, bool* both, void* stream) {
-  ConvParams p;
-  bool empty = false;
-  int rc = conv_fill_op(&conv, p, &empty);
-  if (rc != Q8_OK || empty) return rc;
-  float us = 0.0f;
-  const int variant = conv_choose(&conv.d, p, &us);
-  if (variant == first_p3_variant() + 2 && pool_behind(next, conv, p)) {
-    const bool to_slice = next.kind == Q8_OP_POOL;
-    const int cs = to_slice ? next.d.out_c_stride : next.C, c_off = to_slice ? next.d.out_c_off : 0;
-    rc = launch_p3b_pooled(p, (int8_t*)next.y + c_off, next.Ho, next.Wo, cs,
-                           (long)p.N * next.Ho * next.Wo * cs - c_off, (hipStream_t)stream);
-    *both = rc == Q8_OK;
-    if (rc != Q8_EUNSUPPORTED) return rc;
-  }
-  return conv_launch_chosen(variant, p, (hipStream_t)stream);
+// Whether work on one of two different handles waits for work enqueued on the other: the legacy default stream
+// and streams that were not created to ignore it.
+bool streams_wait(void* a, void* b) {
+  auto legacy = [](void* s) { return s == nullptr || s == (void*)1; };             // (1: hipStreamLegacy)
+  if (legacy(a) == legacy(b)) return legacy(a);
+  unsigned flags = 0;
+  return hipStreamGetFlags((hipStream_t)(legacy(a) ? b : a), &flags) != hipSuccess || !(flags & hipStreamNonBlocking);
 }
+
+// A list's convolutions that wait for the maximum behind them, to go into one launch with it at its place.
+// A convolution goes behind ops of other streams only (streams wait for each other outside of a list only), and is
+// enqueued by itself where one of those is refused: what stands in front of a refused op runs, what stands
+// behind it does not.
+struct Waiting {
+  static constexpr int kAhead = 8;         // ops from a convolution to its maximum; convolutions that wait
+  struct Entry {
+    int conv, pool, variant;
+    ConvParams p;
+    Pooled pooled;
+  };
+  Entry entry[kAhead];
+  int n = 0;
+
+  // Op i, a convolution: the index of the op that goes into its launch, -1: none.
+  static int behind(const q8_op* ops, int n_ops, void* const* streams, int i, const ConvParams& p, int variant,
+                    Pooled* pooled) {
+    if (variant != first_p3_variant() + 2) return -1;
+    void* const own = streams[ops[i].stream];
+    for (int j = i + 1; j < n_ops && j - i < kAhead; ++j) {
+      void* const other = streams[ops[j].stream];
+      if (other == own) return pool_behind(ops[j], ops[i], p, pooled) ? j : -1;
+      if (streams_wait(own, other)) return -1;
+    }
+    return -1;
+  }
+  int run(const q8_op* ops, int n_ops, void* const* streams, int i) {
+    const q8_op& o = ops[i];
+    void* const stream = streams[o.stream];
+    if (o.kind != Q8_OP_CONV || n == kAhead) return run_one(o, stream);
+    bool empty = false;
+    Entry& e = entry[n];
+    const int rc = conv_fill_op(&o, e.p, &empty);
+    if (rc != Q8_OK || empty) return rc;
+    float us = 0.0f;
+    e.variant = conv_choose(&o.d, e.p, &us);
+    e.pool = behind(ops, n_ops, streams, i, e.p, e.variant, &e.pooled);
+    if (e.pool < 0) return conv_launch_chosen(e.variant, e.p, (hipStream_t)stream);
+    e.conv = i;
+    ++n;
+    return Q8_OK;
+  }
+  // Op i, if it is one of those maxima: both run.
+  bool take(const q8_op* ops, void* const* streams, int i, int* rc) {
+    for (int k = 0; k < n; ++k) {
+      if (entry[k].pool != i) continue;
+      Entry& e = entry[k];
+      *rc = launch_p3b_pooled(e.p, e.pooled.y, ops[i].Ho, ops[i].Wo, e.pooled.cs, e.pooled.bytes,
+                              (hipStream_t)streams[ops[i].stream]);
+      for (--n; k < n; ++k) entry[k] = entry[k + 1];
+      return true;
+    }
+    return false;
+  }
+  int refused(const q8_op* ops, void* const* streams, int code) {
+    for (int k = 0; k < n; ++k) {
+      const int rc = conv_launch_chosen(entry[k].variant, entry[k].p, (hipStream_t)streams[ops[entry[k].conv].stream]);
+      if (rc != Q8_OK) return rc;
+    }
+    return code;
+  }
+};
 
 }  // namespace
 }  // namespace q8
@@ -245,37 +308,14 @@ int run_conv_and_next(const q8_op& conv, const q8_op& next, bool* both, void* st
 extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int n_streams) {
   Q8_REQUIRE(n_ops >= 0 && (n_ops == 0 || (ops && streams && n_streams >= 1)), Q8_EINVAL);
   for (int i = 0; i < n_ops; ++i) Q8_REQUIRE(ops[i].stream >= 0 && ops[i].stream < n_streams, Q8_EINVAL);
-  // Ops that went in front of their place, with the convolution whose output they read: each the next op of
-  // its stream behind that one (streams wait for each other outside of a list only).
-  constexpr int kAhead = 8;
-  int done[kAhead], n_done = 0;
-  auto run_single = [&](int i) {
-    const q8_op& o = ops[i];
-    int next = i + 1;
-    while (next < n_ops && next - i < kAhead && ops[next].stream != o.stream) ++next;
-    if (o.kind != Q8_OP_CONV || next >= n_ops || ops[next].stream != o.stream || n_done == kAhead ||
-        (ops[next].kind != Q8_OP_POOL && ops[next].kind != Q8_OP_MAXPOOL))
-      return q8::run_one(o, streams[o.stream]);
-    bool both = false;
-    const int rc = q8::run_conv_and_next(o, ops[next], &both, streams[o.stream]);
-    if (both) done[n_done++] = next;
-    return rc;
-  };
+  q8::Waiting waiting;
   for (int i = 0; i < n_ops;) {
     const q8_op& o = ops[i];
     int j = i + 1;
     int rc;
-    bool skip = false;
-    for (int k = 0; k < n_done; ++k)
-      if (done[k] == i) {
-        skip = true;
-        done[k] = done[--n_done];
-      }
-    if (skip) {
-      ++i;
-      continue;
-    }
-    if (o.kind == Q8_OP_DEQUANTIZE) {
+    if (waiting.take(ops, streams, i, &rc)) {
+      // (its convolution ran with it)
+    } else if (o.kind == Q8_OP_DEQUANTIZE) {
       while (j < n_ops && ops[j].kind == Q8_OP_DEQUANTIZE && ops[j].stream == o.stream) ++j;
       rc = q8::dequantize_list(ops + i, j - i, (hipStream_t)streams[o.stream]);
     } else if (o.kind == Q8_OP_CONV && (o.flags & Q8_OPF_BLOCK) && !o.group && i + 2 < n_ops &&
@@ -286,11 +326,11 @@ extern "C" int q8_run_ops(const q8_op* ops, int n_ops, void* const* streams, int
       while (j < n_ops && j - i < q8::kMaxGroup && ops[j].group == o.group && ops[j].stream == o.stream &&
              ops[j].kind != Q8_OP_DEQUANTIZE)
         ++j;
-      rc = j - i == 1 ? run_single(i) : q8::run_group(ops + i, j - i, streams[o.stream]);
+      rc = j - i == 1 ? waiting.run(ops, n_ops, streams, i) : q8::run_group(ops + i, j - i, streams[o.stream]);
     } else {
-      rc = run_single(i);
+      rc = waiting.run(ops, n_ops, streams, i);
     }
-    if (rc != Q8_OK) return rc;
+    if (rc != Q8_OK) return waiting.refused(ops, streams, rc);
     i = j;
   }
   return Q8_OK;
@@ -336,4 +376,16 @@ extern "C" int q8_run_bottleneck(const q8_op* ops, int build, void* stream) {
   }
   Q8_REQUIRE(q8::bneck_applicable(p[0], p[1], p[2]) && q8::bneck_build_takes(build, p[0], p[1], p[2]), Q8_EUNSUPPORTED);
   return q8::launch_bneck(build, p[0], p[1], p[2], (hipStream_t)stream);
+}
+
+extern "C" int q8_joined_op(const q8_op* ops, int n_ops, void* const* streams, int n_streams, int i) {
+  if (!ops || !streams || i < 0 || i >= n_ops || ops[i].kind != Q8_OP_CONV) return -1;
+  for (int k = i; k < n_ops; ++k)
+    if (ops[k].stream < 0 || ops[k].stream >= n_streams) return -1;
+  q8::ConvParams p;
+  q8::Pooled pooled;
+  bool empty = false;
+  float us = 0.0f;
+  if (q8::conv_fill_op(&ops[i], p, &empty) != Q8_OK || empty) return -1;
+  return q8::Waiting::behind(ops, n_ops, streams, i, p, q8::conv_choose(&ops[i].d, p, &us), &pooled);
 }

@@ -469,3 +469,46 @@ def test_bottleneck_blocks_that_one_launch_takes():
     assert B.lib.q8_run_bottleneck(_block(o2_y=taken[0].x), 4, None) == -2
     assert B.lib.q8_run_bottleneck(taken, 0, None) == -2 and B.lib.q8_run_bottleneck(taken, 99, None) == -1
     assert B.lib.q8_run_bottleneck(None, 0, None) == -1 and name(None) == "single launches"
+
+
+def _layer_and_maximum(n=1, kind=B.OP_MAXPOOL, **change):
+    """n layers of the block-tiled 3x3 kernel, then the 2x2 maxima over their outputs, the last one's first, each pair
+    on a stream index of its own, at made-up addresses (nothing is launched)."""
+    ops, at = (B.Op * (2 * n))(), 1 << 40
+    for i in range(n):
+        o, m = ops[i], ops[2 * n - 1 - i]
+        o.kind, o.d, o.stream, o.q_x, o.q_w, o.q_out = B.OP_CONV, B.ConvDesc(2, 149, 163, 64, 64, 3, 3, 1, 1, 1, 1, relu=1), i, 0.1, 0.1, 0.1
+        o.x, o.w, o.bias, o.y = (at + (1 << 33) * (5 * i + j) for j in range(4))
+        m.kind, m.stream, m.x, m.y, m.q_x, m.q_out = kind, i, o.y, at + (1 << 33) * (5 * i + 4), 0.1, 0.1
+        m.d.N, m.H, m.W, m.C, m.R, m.S, m.stride, m.Ho, m.Wo, m.d.out_c_stride = 2, 149, 163, 64, 2, 2, 2, 75, 82, 64
+    for name, value in change.items():
+        o, field = ops[int(name[1])], name[3:]
+        setattr(o if hasattr(o, field) else o.d, field, value)
+    return ops
+
+
+def test_maxima_that_join_their_layer():
+    def joined(ops, *handles, first=0):
+        return B.lib.q8_joined_op(ops, len(ops), (C.c_void_p * len(handles))(*handles), len(handles), first)
+    assert B.conv_variant(_layer_and_maximum()[0].d) == "conv_i8_p3b_kernel"
+    for kind in (B.OP_MAXPOOL, B.OP_POOL):
+        assert joined(_layer_and_maximum(kind=kind), 64) == 1
+        assert joined(_layer_and_maximum(kind=kind, o1_Ho=74, o1_Wo=81), 64) == 1
+        for change in (dict(o1_R=3), dict(o1_S=1), dict(o1_stride=1), dict(o1_pad=1), dict(o1_Ho=76), dict(o1_C=48), dict(o1_H=148),
+                       dict(o1_x=1 << 40), dict(o1_y=1 << 40), dict(o1_y=(1 << 40) + (1 << 33)), dict(o1_y=None),
+                       dict(o1_y=(1 << 40) + (3 << 33) + 1024), dict(o1_y=(1 << 45) + 8), dict(o0_out_c_stride=128),
+                       dict(o0_out_c_stride=128, o0_out_c_off=64), dict(o0_flags=B.OPF_OUT_U8), dict(o0_flags=B.OPF_DEQUANT),
+                       dict(o0_q_out=-1.0), dict(o1_kind=B.OP_QUANTIZE)):
+            assert joined(_layer_and_maximum(kind=kind, **change), 64) == -1, change
+    for change in (dict(o1_mode=1), dict(o1_q_x=0.2), dict(o1_q_x=float("nan"), o1_q_out=float("nan")),
+                   dict(o1_out_c_stride=72), dict(o1_out_c_stride=80, o1_out_c_off=8), dict(o1_out_c_stride=48)):
+        assert joined(_layer_and_maximum(kind=B.OP_POOL, **change), 64) == -1, change
+    assert joined(_layer_and_maximum(kind=B.OP_POOL, o1_out_c_stride=96, o1_out_c_off=32), 64) == 1
+    # ops of other streams between the two: up to seven places on, each pair on its own
+    two = _layer_and_maximum(2)
+    assert joined(two, 64, 128) == 3 and joined(two, 64, 128, first=1) == 2 and joined(two, 64, 128, first=2) == -1
+    assert joined(_layer_and_maximum(4), 64, 128, 192, 256) == 7
+    assert joined(_layer_and_maximum(5), *range(64, 69)) == -1 and joined(_layer_and_maximum(5), *range(64, 69), first=1) == 8
+    # ... unless they are ordered with it: the same stream under another index, the legacy default stream's two names
+    assert joined(two, 64, 64) == -1 and joined(two, 64, 64, first=1) == 2 and joined(two, None, 1) == -1
+    assert joined(two, 64) == -1 and joined(two, 64, 128, first=4) == -1

@@ -1124,6 +1124,67 @@ def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
             assert np.array_equal(got, pooled)
 
 
+@pytest.mark.parametrize("case", ["one stream, two indices", "default stream", "refused", "two streams"])
+def test_maximum_and_ops_of_other_streams(B, case):
+    """Layers and the maxima over their outputs with ops of other streams between the two: what the list's order
+    says where that binds the streams, nothing behind a refused op, and every tensor as by single calls."""
+    import ctypes
+    N, H, W, C, pairs = 2, 149, 163, 64, 10 if case == "two streams" else 1
+    d = B.ConvDesc(N, H, W, C, C, 3, 3, 1, 1, 1, 1, relu=1)
+    assert B.conv_variant(d) == "conv_i8_p3b_kernel"
+    def codes(*shape):
+        return torch.randint(-128, 128, shape, dtype=torch.int8, device="cuda")
+    w = B.pack_weights(d, codes(C, 3, 3, C))
+    x = [codes(N, H, W, C) for _ in range(pairs)]
+    other = codes(N, H, W, C)
+    y = [torch.full((N, H, W, C), 77, dtype=torch.int8, device="cuda") for _ in x]
+    z = [torch.full((N, H // 2, W // 2, C), 77, dtype=torch.int8, device="cuda") for _ in x]
+    want = [B.conv_int8(d, t, w, None, 0.02, 0.0004, 0.011) for t in x]
+
+    def conv(i, stream):
+        o = B.Op()
+        o.kind, o.d, o.stream, o.x, o.w, o.y = B.OP_CONV, d, stream, x[i].data_ptr(), w.data_ptr(), y[i].data_ptr()
+        o.q_x, o.q_w, o.q_out = 0.02, 0.0004, 0.011
+        return o
+
+    def maximum(src, dst, win, stream):
+        o = B.Op()
+        o.kind, o.stream, o.x, o.y = B.OP_MAXPOOL, stream, src.data_ptr(), dst.data_ptr()
+        o.d.N, o.H, o.W, o.C, o.R, o.S, o.stride, o.Ho, o.Wo = N, H, W, C, win, win, win, H // max(win, 1), W // max(win, 1)
+        return o
+    torch.cuda.synchronize()
+    if case == "two streams":
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        handles, ops = [s.cuda_stream for s in streams], []
+        for i in range(pairs):             # conv 0, conv 1, maximum 1, maximum 0, conv 3, ...
+            ops += [conv(i, 0)] if i % 2 == 0 else [conv(i, 1), maximum(y[i], z[i], 2, 1), maximum(y[i - 1], z[i - 1], 2, 0)]
+        joined = 3
+    elif case == "refused":
+        handles = [torch.cuda.Stream().cuda_stream, torch.cuda.Stream().cuda_stream]
+        ops, joined = [conv(0, 0), maximum(other, other, 0, 1), maximum(y[0], z[0], 2, 0)], 2
+    else:                                  # a copy over the layer's output between the layer and its maximum
+        handles = [torch.cuda.Stream().cuda_stream] * 2
+        if case == "default stream":       # ordered with every stream that does not say otherwise
+            hip, made = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+            assert hip.hipStreamCreate(ctypes.byref(made)) == 0
+            handles = [made.value, None]
+        ops, joined = [conv(0, 0), maximum(other, y[0], 1, 1), maximum(y[0], z[0], 2, 0)], -1
+    array, streams = (B.Op * len(ops))(*ops), (ctypes.c_void_p * 2)(*handles)
+    code = B.lib.q8_run_ops(array, len(ops), streams, 2)
+    torch.cuda.synchronize()
+    if case == "refused":
+        assert code == -1 and np.array_equal(host(y[0]), host(want[0])) and (host(z[0]) == 77).all()
+    elif case == "two streams":
+        assert code == 0
+        for a, b, c in zip(y, want, z):
+            assert np.array_equal(host(a), host(b))
+            assert np.array_equal(host(c), host(B.maxpool_i8(b, 2, 2, 2, 0, H // 2, W // 2)))
+    else:
+        assert code == 0 and np.array_equal(host(y[0]), host(other))
+        assert np.array_equal(host(z[0]), host(B.maxpool_i8(other, 2, 2, 2, 0, H // 2, W // 2)))
+    assert B.lib.q8_joined_op(array, len(ops), streams, 2, 0) == joined
+
+
 @pytest.mark.parametrize("m", [1.0, 0.37])
 @pytest.mark.parametrize("mode", ["max", "avg"])
 @pytest.mark.parametrize("shape,win,extra", [
