@@ -796,9 +796,10 @@ class Engine:
     def _blocks(self, ops, fused, n):
         """Bottleneck blocks that the library would run as one launch on ``n`` images: {index of the last
         layer: (1x1, 3x3)}.  Only the block itself reads its inner tensors, and nothing behind its first
-        layer writes over what it reads or writes: it can then run where its last layer has its place."""
+        layer writes over what it reads or writes: it can then run where its last layer has its place.  A
+        layer belongs to one block (the first where one's last layer could begin another)."""
         at = {o.dst: i for i, o in enumerate(ops)}
-        found = {}
+        found, taken = {}, set()
         for i, c in enumerate(ops):
             if c.kind != "conv" or (c.R, c.S, c.stride, c.pad_h, c.pad_w) != (1, 1, 1, 0, 0):
                 continue
@@ -810,7 +811,8 @@ class Engine:
             ia = at.get(b.src, ib)
             a = ops[ia]
             if ia >= ib or a.kind != "conv" or a.res or (a.R, a.S, a.pad_h, a.pad_w) != (1, 1, 0, 0) or \
-                    c.dst in self.real or c.dst in fused or (self.head and a is self.head[0]):
+                    taken & {ia, ib, i} or c.dst in self.real or c.dst in fused or \
+                    (self.head and a is self.head[0]):
                 continue
             touched = {a.src, c.res, a.dst, b.dst, c.dst}
             others = [o for j, o in enumerate(ops) if j not in (ia, ib, i)]
@@ -821,6 +823,7 @@ class Engine:
             three = (B.Op * 3)(*(self._op_conv(o, 0, n, False) for o in (a, b, c)))
             if B.lib.q8_block_variant(three) != b"single launches":
                 found[i] = (ia, ib)
+                taken.update((ia, ib, i))
         return found
 
     def _pipelines_pay(self, ops):

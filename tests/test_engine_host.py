@@ -225,3 +225,55 @@ def test_pipelines_of_per_channel_layers_follow_the_unsigned_rule():
 def test_pipelines_of_layers_that_share_launches(net, image, batch, two):
     """The batches around the measured crossings (the fused head as a deployed model has it)."""
     assert _two_pipelines(net(image=image), batch, fuse_head=True) == two
+
+
+def _two_blocks(*layers, H=56):
+    """Layers (name, source, kernel, residual, tensor written) on 64 channels, tensors made as they come."""
+    net = wl.Network("blocks", "x")
+    net.tensor("x", H, H, 64)
+    for name, src, R, res, dst in layers:
+        if dst not in net.tensors:
+            net.tensor(dst, H, H, 64)
+        wl._conv(net, name, src, 64, R, R, res=res, dst=dst)
+    net.outputs = [layers[-1][4]]
+    return net
+
+
+CHAIN = [("a", "x", 1, None, "ta"), ("b", "ta", 3, None, "tb"), ("c", "tb", 1, None, "tc")]
+
+
+@pytest.mark.parametrize("layers, order, marked", [
+    (CHAIN, "abc", "a"),
+    # a last layer that would also begin the next block belongs to the first one only
+    (CHAIN + [("d", "tc", 3, None, "td"), ("e", "td", 1, None, "te")], "abcde", "a"),
+    (CHAIN + [("d", "tc", 3, None, "td"), ("e", "td", 1, None, "te"), ("f", "te", 3, None, "tf"),
+              ("g", "tf", 1, None, "tg")], "abcdefg", "ae"),
+    # ... where it has a sum, the next block begins with another layer
+    (CHAIN[:2] + [("c", "tb", 1, "x", "tc"), ("d", "tc", 1, None, "td"), ("e", "td", 3, None, "te"),
+                  ("f", "te", 1, "tc", "tf")], "abcdef", "ad"),
+    # an independent layer keeps its place in front of the block's
+    (CHAIN[:2] + [("p", "x", 1, None, "tp"), CHAIN[2]], "pabc", "a"),
+    # another layer reads what lies between, as its input or as its residual
+    (CHAIN + [("d", "ta", 1, None, "td")], None, ""), (CHAIN + [("d", "tc", 1, "tb", "td")], None, ""),
+    # the block's input, a tensor inside it or its output is written over behind its first layer
+    (CHAIN[:1] + [("d", "ta", 1, None, "x")] + CHAIN[1:], None, ""),
+    (CHAIN[:2] + [("p", "x", 1, None, "x"), CHAIN[2]], None, ""),
+    (CHAIN[:2] + [("p", "x", 1, None, "tc"), CHAIN[2]], None, ""),
+    (CHAIN + [("d", "tc", 1, None, "ta")], None, ""),
+    # its residual is written behind the first layer, or in front of it
+    (CHAIN[:2] + [("p", "x", 1, None, "tp"), ("c", "tb", 1, "tp", "tc")], None, ""),
+    ([("p", "x", 1, None, "tp")] + CHAIN[:2] + [("c", "tb", 1, "tp", "tc")], "pabc", "a"),
+    # no block: its layers in another order, or two 3x3 layers
+    ([("a", "x", 3, None, "ta"), ("b", "ta", 1, None, "tb"), ("c", "tb", 1, None, "tc")], "abc", ""),
+    ([("a", "x", 1, None, "ta"), ("b", "ta", 3, None, "tb"), ("c", "tb", 3, None, "tc")], "abc", "")])
+def test_blocks_of_a_planned_step(recorded, layers, order, marked):
+    """Which triples are marked as one launch, in which place, and that every layer runs once."""
+    net = _two_blocks(*layers)
+    eng, step = recorded(net, 4)
+    at = {eng.wq[o.name][0].data_ptr(): o.name for o in net.convs()}
+    ops = step()
+    names = "".join(at[o.w] for o in ops)
+    assert sorted(names) == sorted(o.name for o in net.convs()) and names == (order or names)
+    assert "".join(n for n, o in zip(names, ops) if o.flags & B.OPF_BLOCK) == marked
+    for n, o in zip(names, ops):
+        assert not (o.flags & B.OPF_BLOCK and o.group)
