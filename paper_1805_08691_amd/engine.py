@@ -811,7 +811,7 @@ class Engine:
             ia = at.get(b.src, ib)
             a = ops[ia]
             if ia >= ib or a.kind != "conv" or a.res or (a.R, a.S, a.pad_h, a.pad_w) != (1, 1, 0, 0) or \
-                    taken & {ia, ib, i} or c.dst in self.real or c.dst in fused or \
+                    taken & {ia, ib, i} or c.dst in self.real or {a.dst, b.dst, c.dst} & fused.keys() or \
                     (self.head and a is self.head[0]):
                 continue
             touched = {a.src, c.res, a.dst, b.dst, c.dst}

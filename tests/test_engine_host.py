@@ -277,3 +277,13 @@ def test_blocks_of_a_planned_step(recorded, layers, order, marked):
     assert "".join(n for n, o in zip(names, ops) if o.flags & B.OPF_BLOCK) == marked
     for n, o in zip(names, ops):
         assert not (o.flags & B.OPF_BLOCK and o.group)
+
+
+def test_a_block_whose_inner_values_leave_is_none(recorded):
+    """Eq. D of a tensor inside a block, in the launch that writes it: the block's layers keep their places."""
+    net = _two_blocks(*CHAIN)
+    for name, marked in (("ta", 0), ("tb", 0), ("tc", 0), (None, 1)):
+        eng, step = recorded(net, 4, fuse_dequant=True)
+        ops = step(None, {name: torch.empty(eng.act[name].shape)} if name else None)
+        assert sum(bool(o.flags & B.OPF_BLOCK) for o in ops) == marked
+        assert all(o.group for o in ops) == (not marked)
