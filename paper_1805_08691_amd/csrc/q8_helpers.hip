@@ -65,11 +65,11 @@ __device__ __forceinline__ unsigned xcd_run(unsigned bid, unsigned grid) {
 //  * mean: bytes + 128, two to a word in 16-bit lanes, add up without carries (9 x 255); maximum: a word's
 //    odd bytes are compared in place, whatever the bytes under them, and the even ones shifted up by eight.
 // Before and after, us: 3 x 3 mean, 32 images of 35 x 35 x 288 11.8 / 7.5, 17 x 17 x 768 8.3 / 5.4, 8 x 8 x 2048
-// 5.5 / 4.1 (one image: 2.5 / 2.5, a launch); maximum 3 x 3, 64 images of 19 x 19 x 512 11.3 / 6.5; stride 2, 64
+// 5.5 / 4.1 (one image of 35 x 35 x 288: 2.9 / 2.6); maximum 3 x 3, 64 images of 19 x 19 x 512 11.3 / 6.5; stride 2, 64
 // images of 112 x 112 x 64 11.6 / 11.2 (5.8 TB/s); 2 x 2, 64 images of 300 x 300 x 64 89.7 / 81.9 (5.6 TB/s),
 // one of 75 x 75 x 256 2.65 / 1.90.
 struct PoolParams {
-  int H, W, pad, Ho, Wo, C;                       // C: channels = bytes of a pixel
+  int H, W, stride, pad_h, pad_w, Ho, Wo, C;      // C: channels = bytes of a pixel
   int x_bytes;
   unsigned total;                                 // lanes with work
   q8::FastDiv by_c, by_strip, by_row;             // of C / 16, strips of a row, rows
@@ -79,10 +79,11 @@ struct PoolParams {
   int out_cs, out_off;
 };
 #pragma clang fp contract(off)
-template <int MODE, int WIN, int STRIDE, int NO>
+template <int MODE, int WIN, int NO>
 __global__ __launch_bounds__(kThreads) void pool_strip_kernel(const int8_t* __restrict__ x, const PoolParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  constexpr int COLS = (NO - 1) * STRIDE + WIN;
+  constexpr int COLS = NO - 1 + WIN;
+  const int stride = NO == 1 ? p.stride : 1;
   const unsigned i = xcd_run(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
   if (i >= p.total) return;
   const int t = q8::fast_div((int)i, p.by_c.m, p.by_c.s), c = ((int)i - t * (p.C >> 4)) << 4;
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void pool_strip_kernel(const int8_t* __re
   unsigned row[WIN], col[COLS];
 #pragma unroll
   for (int r = 0; r < WIN; ++r) {
-    const int h = ho * STRIDE - p.pad + r;
+    const int h = ho * stride - p.pad_h + r;
     const int hc = MODE == 0 ? min(max(h, 0), p.H - 1) : h;
     row[r] = (unsigned)((n * p.H + hc) * p.W) * (unsigned)p.C;
     // beyond a mean's buffer of less than 2^30 bytes, and still so with either kind of column offset
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void pool_strip_kernel(const int8_t* __re
   }
 #pragma unroll
   for (int k = 0; k < COLS; ++k) {
-    const int w = wo * STRIDE - p.pad + k;
+    const int w = wo * stride - p.pad_w + k;
     const int wc = MODE == 0 ? min(max(w, 0), p.W - 1) : w;
     col[k] = (unsigned)(wc * p.C + c);
     if (MODE == 1 && (unsigned)w >= (unsigned)p.W) col[k] = 0x80000000u;
@@ -135,12 +136,12 @@ __global__ __launch_bounds__(kThreads) void pool_strip_kernel(const int8_t* __re
     unsigned so[4], se[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      so[q] = odd[k * STRIDE][q];
-      se[q] = even[k * STRIDE][q];
+      so[q] = odd[k][q];
+      se[q] = even[k][q];
 #pragma unroll
       for (int s = 1; s < WIN; ++s) {
-        so[q] = MODE == 0 ? most(so[q], odd[k * STRIDE + s][q]) : so[q] + odd[k * STRIDE + s][q];
-        se[q] = MODE == 0 ? most(se[q], even[k * STRIDE + s][q]) : se[q] + even[k * STRIDE + s][q];
+        so[q] = MODE == 0 ? most(so[q], odd[k + s][q]) : so[q] + odd[k + s][q];
+        se[q] = MODE == 0 ? most(se[q], even[k + s][q]) : se[q] + even[k + s][q];
       }
     }
     if (MODE == 0) {
@@ -235,25 +236,24 @@ __global__ __launch_bounds__(kThreads) void pool_i8_vec_kernel(const int8_t* __r
     int wo = (int)(t % (unsigned)Wo); t /= (unsigned)Wo;
     int ho = (int)(t % (unsigned)Ho);
     int n = (int)(t / (unsigned)Ho);
-    // Two bytes per 32-bit word at a time, as 16-bit lanes: the odd bytes and the even
-    // bytes of a word, each sign-extended by a packed arithmetic shift, take a packed max
-    // or a packed add per tap (a window of at most 128 taps cannot overflow 16 bits).
+    // Two bytes per 32-bit word at a time, as 16-bit lanes.  Maximum: as in the strips.  Mean: the odd bytes
+    // and the even bytes, each sign-extended by a packed arithmetic shift (a window of at most 128 taps cannot
+    // overflow 16 bits).
     v2s acc_odd[4], acc_even[4];
-    const short init = MODE == 0 ? (short)-128 : (short)0;
+    const short init = MODE == 0 ? (short)-32768 : (short)0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc_odd[q] = acc_even[q] = v2s{init, init};
     auto take = [&](const v4i& v) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int w = v[q], w8 = w << 8;
-        const v2s odd = __builtin_bit_cast(v2s, w) >> 8;               // bytes 1 and 3
-        const v2s even = __builtin_bit_cast(v2s, w8) >> 8;             // bytes 0 and 2
+        const v2s odd = __builtin_bit_cast(v2s, w), even = __builtin_bit_cast(v2s, w8);
         if (MODE == 0) {
           acc_odd[q] = __builtin_elementwise_max(acc_odd[q], odd);
           acc_even[q] = __builtin_elementwise_max(acc_even[q], even);
         } else {
-          acc_odd[q] += odd;
-          acc_even[q] += even;
+          acc_odd[q] += odd >> 8;              // bytes 1 and 3
+          acc_even[q] += even >> 8;            // bytes 0 and 2
         }
       }
     };
@@ -266,23 +266,24 @@ __global__ __launch_bounds__(kThreads) void pool_i8_vec_kernel(const int8_t* __r
         take(*reinterpret_cast<const v4i*>(x + ((((size_t)n * H + hi) * W + wi) * C16 + c) * 16));
       }
     }
-    // scale, clamp, Round by adding 1.5 * 2^23 (for |t| <= 128 the fp32 sum is the
-    // round-half-to-even integer, its low byte the int8 code), byte permutes to pack
-    unsigned rr[16];
+    v4i o = {};
+    float f[16];
+    if (MODE == 0) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int val = (e & 1) ? acc_odd[e >> 2][(e >> 1) & 1] : acc_even[e >> 2][(e >> 1) & 1];
-      float f = MODE == 0 ? (float)val : (float)val * inv_count;
-      f = f * m;
-      f = __builtin_amdgcn_fmed3f(f, -128.0f, 127.0f);
-      rr[e] = __float_as_uint(f + 12582912.0f);
+      for (int q = 0; q < 4; ++q) {
+        const v2s odd = acc_odd[q], even = acc_even[q];
+        o[q] = (int)__builtin_amdgcn_perm(__builtin_bit_cast(unsigned, odd), __builtin_bit_cast(unsigned, even),
+                                          0x07030501u);
+      }
     }
-    v4i o;
+    if (MODE == 1 || m != 1.0f) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const unsigned w01 = __builtin_amdgcn_perm(rr[4 * a + 1], rr[4 * a], 0x0c0c0400u);
-      const unsigned w23 = __builtin_amdgcn_perm(rr[4 * a + 3], rr[4 * a + 2], 0x0c0c0400u);
-      o[a] = (int)__builtin_amdgcn_perm(w23, w01, 0x05040100u);
+      for (int e = 0; e < 16; ++e) {
+        const int sum = (e & 1) ? acc_odd[e >> 2][(e >> 1) & 1] : acc_even[e >> 2][(e >> 1) & 1];
+        f[e] = MODE == 0 ? (float)(int8_t)((o[e >> 2] >> (8 * (e & 3))) & 0xff) : (float)sum * inv_count;
+        f[e] = f[e] * m;
+      }
+      o = q8::pack16_signed(f);
     }
     *reinterpret_cast<v4i*>(y + (((size_t)n * Ho + ho) * Wo + wo) * out_cs + out_off + c * 16) = o;
   }
@@ -327,29 +328,42 @@ bool pool_i8_vec_launch(const int8_t* x, int N, int H, int W, int C, int mode, i
       (mode == 1 && R * S > 128) || total / 16 >= 0x7fffffffUL)
     return false;
   const float inv_count = 1.0f / (float)(R * S);
-  // Strips: the windows that networks have.  A tap's offset takes 31 bits, and a mean's buffer ends where
-  // the taps outside the image are sent.  Two outputs a lane where windows share columns, one otherwise: with four,
-  // 64 images of 35 x 35 x 288 take 10.8 us instead of 12.1, 32 images the same, one image 3.1 instead of 2.5
-  // (half the wavefronts, each twice as long); with two at stride 2, 64 of 112 x 112 x 64 12.5 instead of 11.2.
-  const size_t x_bytes = (size_t)N * H * W * C;
-  const bool three = R == 3 && S == 3 && stride <= 2, two = R == 2 && S == 2 && stride == 2 && mode == 0;
-  if ((three || two) && x_bytes < (mode == 0 ? 0x7fffffffUL : 0x40000000UL)) {
-    const int no = three && stride == 1 ? 2 : 1;
-    auto kernel = two ? pool_strip_kernel<0, 2, 2, 1>
-                  : stride == 1 ? (mode == 0 ? pool_strip_kernel<0, 3, 1, 2> : pool_strip_kernel<1, 3, 1, 2>)
-                                : (mode == 0 ? pool_strip_kernel<0, 3, 2, 1> : pool_strip_kernel<1, 3, 2, 1>);
-    PoolParams p;
-    p.H = H; p.W = W; p.pad = pad; p.Ho = Ho; p.Wo = Wo; p.C = C;
-    p.x_bytes = (int)x_bytes;
-    p.strips = (Wo + no - 1) / no;
-    p.total = (unsigned)((size_t)N * Ho * p.strips * (C / 16));
-    p.by_c = q8::make_fast_div((unsigned)(C / 16));
-    p.by_strip = q8::make_fast_div((unsigned)p.strips);
-    p.by_row = q8::make_fast_div((unsigned)Ho);
-    p.m = m; p.inv_count = inv_count;
-    p.y = y; p.out_cs = out_cs; p.out_off = out_off;
-    hipLaunchKernelGGL(kernel, dim3((p.total + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                       (hipStream_t)stream, x, p);
+  // Strips: 3 x 3 windows and the maximum over 2 x 2, with any stride.  A tap's offset takes 31 bits, and a mean's
+  // buffer ends where the taps outside the image are sent, so larger tensors go image by image or in bands of
+  // rows.  (As the kernel for any window: 3 x 3 with stride 3 on one image of 35 x 35 x 288 4.3 us instead of 2.6.)
+  // Two outputs a lane where windows share columns and more than three wavefronts of one output would
+  // stand on a SIMD, one otherwise: one and two, 3 x 3 mean, one image of 35 x 35 x 288 2.64 / 2.96, eight
+  // 3.53 / 3.75 (196608 outputs of 16 channels 3.58 / 3.80, 262144 4.06 / 3.96), 64 12.3 / 11.1; with four 64 take
+  // 10.8; with two at stride 2 64 images of 112 x 112 x 64 12.5 instead of 11.2.
+  const size_t row = (size_t)W * C, image = row * H, reach = mode == 0 ? 0x7fffffffUL : 0x40000000UL;
+  const bool three = R == 3 && S == 3, two = R == 2 && S == 2 && mode == 0;
+  if ((three || two) && (image < reach || row * (size_t)R < reach)) {
+    const int no = three && stride == 1 && total / 16 > 3 * 1024 * 64 ? 2 : 1;
+    auto kernel = two ? pool_strip_kernel<0, 2, 1>
+                  : no == 2 ? (mode == 0 ? pool_strip_kernel<0, 3, 2> : pool_strip_kernel<1, 3, 2>)
+                            : (mode == 0 ? pool_strip_kernel<0, 3, 1> : pool_strip_kernel<1, 3, 1>);
+    const int images = image < reach ? (int)((reach - 1) / image) : 1;
+    const int band = image < reach ? Ho : (int)(((reach - 1) / row - R) / stride) + 1;
+    for (int n = 0; n < N; n += images)
+      for (int ho = 0; ho < Ho; ho += band) {
+        const int first = ho * stride - pad, top = first > 0 ? first : 0;      // the launch's first row of the image
+        PoolParams p;
+        p.H = H - top; p.W = W; p.stride = stride; p.pad_h = top - first; p.pad_w = pad;
+        p.Ho = Ho - ho < band ? Ho - ho : band; p.Wo = Wo; p.C = C;
+        const int some = N - n < images ? N - n : images;
+        const size_t bytes = (some - 1) * image + (size_t)p.H * row;
+        p.x_bytes = (int)(bytes < reach ? bytes : reach - 1);
+        p.strips = (Wo + no - 1) / no;
+        p.total = (unsigned)((size_t)some * p.Ho * p.strips * (C / 16));
+        p.by_c = q8::make_fast_div((unsigned)(C / 16));
+        p.by_strip = q8::make_fast_div((unsigned)p.strips);
+        p.by_row = q8::make_fast_div((unsigned)p.Ho);
+        p.m = m; p.inv_count = inv_count;
+        p.y = y + ((size_t)n * Ho + ho) * Wo * out_cs;
+        p.out_cs = out_cs; p.out_off = out_off;
+        hipLaunchKernelGGL(kernel, dim3((p.total + kThreads - 1) / kThreads), dim3(kThreads), 0,
+                           (hipStream_t)stream, x + (size_t)n * image + (size_t)top * row, p);
+      }
     return true;
   }
   size_t vb = (total / 16 + kThreads - 1) / kThreads;

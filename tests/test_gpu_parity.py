@@ -1191,6 +1191,12 @@ def test_maximum_and_ops_of_other_streams(B, case):
     ((1, 1, 1, 16), (3, 1, 1), 0), ((2, 2, 1, 48), (3, 1, 2), 0), ((1, 5, 6, 16), (3, 1, 0), 0),
     ((3, 7, 4, 32), (3, 1, 1), 16), ((1, 3, 3, 16), (3, 2, 2), 0), ((2, 6, 9, 48), (3, 2, 1), 0),
     ((2, 9, 8, 16), (2, 2, 0), 16), ((1, 5, 7, 32), (2, 2, 0), 1), ((1, 5, 5, 16), (3, 3, 0), 0),
+    ((2, 7, 8, 32), (3, 3, 1), 16), ((1, 11, 6, 16), (3, 5, 2), 0), ((1, 6, 7, 48), (2, 1, 1), 0), ((3, 8, 9, 16), (2, 3, 1), 0),
+    # two outputs a lane: many maps of one, two, an odd and an even number of columns
+    ((66000, 3, 1, 16), (3, 1, 1), 0), ((35000, 3, 2, 16), (3, 1, 1), 16), ((14000, 3, 5, 16), (3, 1, 1), 0),
+    ((9000, 3, 4, 16), (3, 1, 2), 0), ((40000, 4, 5, 16), (3, 1, 0), 0),
+    # any other window
+    ((1, 9, 7, 32), (1, 2, 0), 0), ((2, 8, 9, 16), (5, 2, 2), 16), ((1, 12, 12, 16), (11, 1, 5), 0),
 ])
 def test_pool_i8_strips(B, shape, win, extra, mode, m):
     """Windows at every edge of the image, odd rests of a strip, a slice of a wider tensor, and one output row
@@ -1214,6 +1220,24 @@ def test_pool_i8_strips(B, shape, win, extra, mode, m):
     if mode == "max" and m == 1.0:
         got = host(B.maxpool_i8(dev(x), R, R, stride, pad, Ho, Wo))
         assert np.array_equal(got, orc.maxpool_i8(x, R, R, stride, pad, Ho, Wo))
+
+
+@pytest.mark.parametrize("mode,stride,shape", [("avg", 1, (3, 20, 16384, 2048)), ("avg", 2, (1, 40, 16384, 2048)),
+                                               ("max", 3, (1, 70, 16384, 2048))])
+def test_pool_i8_beyond_the_reach_of_a_launch(B, mode, stride, shape):
+    """Tensors of more bytes than a launch's offsets reach: image by image or in bands of rows, the same as
+    pieces of the padded tensor."""
+    N, H, W, C = shape
+    x = torch.randint(-128, 128, shape, dtype=torch.int8, device="cuda")
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    got = B.pool_i8(x, mode, 3, 3, stride, 1, Ho, Wo)
+    padded = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1), value=-128 if mode == "max" else 0)
+    step = 1024
+    for n in range(N):
+        for a in range(0, Wo, step):
+            some = min(step, Wo - a)
+            piece = padded[n:n + 1, :, a * stride:(a + some - 1) * stride + 3].contiguous()
+            assert torch.equal(B.pool_i8(piece, mode, 3, 3, stride, 0, Ho, some), got[n:n + 1, :, a:a + some]), (n, a)
 
 
 def test_pool_f32(B):
