@@ -332,8 +332,8 @@ bool pool_i8_vec_launch(const int8_t* x, int N, int H, int W, int C, int mode, i
   // buffer ends where the taps outside the image are sent, so larger tensors go image by image or in bands of
   // rows.  (As the kernel for any window: 3 x 3 with stride 3 on one image of 35 x 35 x 288 4.3 us instead of 2.6.)
   // Two outputs a lane where windows share columns and more than three wavefronts of one output would
-  // stand on a SIMD, one otherwise: one and two, 3 x 3 mean, one image of 35 x 35 x 288 2.64 / 2.96, eight
-  // 3.53 / 3.75 (196608 outputs of 16 channels 3.58 / 3.80, 262144 4.06 / 3.96), 64 12.3 / 11.1; with four 64 take
+  // stand on a SIMD, one otherwise: one and two, 3 x 3 mean, one image of 35 x 35 x 288 2.61 / 2.96, eight
+  // 3.52 / 3.79 (196608 outputs of 16 channels 3.58 / 3.80, 262144 4.06 / 3.96), 64 12.3 / 11.1; with four 64 take
   // 10.8; with two at stride 2 64 images of 112 x 112 x 64 12.5 instead of 11.2.
   const size_t row = (size_t)W * C, image = row * H, reach = mode == 0 ? 0x7fffffffUL : 0x40000000UL;
   const bool three = R == 3 && S == 3, two = R == 2 && S == 2 && mode == 0;
