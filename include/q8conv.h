@@ -385,6 +385,11 @@ const char *q8_group_variant(const q8_op *ops, int n_ops);
  * if they would go one after the other.                                                   */
 const char *q8_block_variant(const q8_op *ops);
 
+/* For programs that mark blocks: 1 if three ops are estimated shorter as one launch than as three, of which the
+ * first may share its own with the n_beside (at most 7) independent ops beside.  0 otherwise, and where they
+ * are no block.                                                                           */
+int q8_block_pays(const q8_op *block, const q8_op *beside, int n_beside);
+
 /* Tests and tuning only: three Q8_OP_CONV ops that form a bottleneck block (see q8_run_ops) as one launch of
  * the given build (0 .. q8_num_bottleneck_builds() - 1).  Q8_EUNSUPPORTED if the ops are no such
  * block or the build does not take its sizes.                                             */

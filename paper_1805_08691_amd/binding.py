@@ -36,7 +36,7 @@ EXPORTS = [
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant",
-    "q8_block_variant", "q8_num_bottleneck_builds", "q8_bottleneck_build_name", "q8_run_bottleneck", "q8_joined_op", "q8_conv_estimate_us",
+    "q8_block_variant", "q8_block_pays", "q8_num_bottleneck_builds", "q8_bottleneck_build_name", "q8_run_bottleneck", "q8_joined_op", "q8_conv_estimate_us",
     "q8_conv_f32_ref", "q8_conv_f32_observed", "q8_conv_f32_observed_spread", "q8_calibrate_fold", "q8_conv_f32_variant", "q8_maxpool_i8", "q8_maxpool_f32", "q8_pool_i8", "q8_pool_f32",
 ]
 
@@ -155,6 +155,7 @@ lib.q8_group_variant.restype = C.c_char_p
 lib.q8_group_variant.argtypes = [_vp, _i]
 lib.q8_block_variant.restype = C.c_char_p
 lib.q8_block_variant.argtypes = [_vp]
+lib.q8_block_pays.argtypes = [_vp, _vp, _i]
 lib.q8_num_bottleneck_builds.argtypes = []
 lib.q8_bottleneck_build_name.restype = C.c_char_p
 lib.q8_bottleneck_build_name.argtypes = [_i]

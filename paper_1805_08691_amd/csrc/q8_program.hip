@@ -68,30 +68,46 @@ int run_one(const q8_op& o, void* stream) {
   }
 }
 
-// The build for a block of three layers, -1: three launches.  The estimates of single launches miss what
-// three dependent ones take in a row by a factor that goes with the map (measured / estimated at 1 to 32 images:
-// 14 x 14 pixels 1.03 ... 0.8, 28 x 28 1.02 ... 1.09, 56 x 56 0.9 ... 1.24), so each kind of block has its own.
+// The build for a block of three layers, -1: three launches.  shared: what the first layer's share of a launch
+// with others takes less than a launch of its own; null: the block is marked, whoever marked it has asked.
+// The estimates are of launches by themselves.  Inside a network (six blocks in a row with filters of their own; 486
+// such networks of 64 to 1024 outer channels on 7 x 7 to 56 x 56 pixels, half of them with a projection beside each
+// first layer) one launch and three lie apart from them by what goes with the middle channels and the launches
+// replaced:
+//  * no projection: below 1.15 of the three launches' estimate no block on 64 channels loses, below 0.95 none on 128.
+//    (28 x 28 x 512 on one image, 0.96, gains 4 % there and costs ResNet-50 201.9 -> 204.2 us.)  256: three launches
+//    are estimated up to a sixth too long while the last layer has at most two tiles of 64 x 64 per CU (1024 -> 256
+//    -> 1024 on 14 x 14, 8 images 1.07 of their time at an estimated 0.89, 11 images 0.97 at 0.93);
+//  * a projection: of 60, 87 and 96 on 64, 128 and 256 channels 0, 5 (up to 7 %) and 13 (up to 12 %) lose. Where the
+//    first layer counted as a launch of its own, 2, 13 and 42 did, up to 29 %.
+// ResNet-50, 8 images 295 -> 286 us, unsigned 319.5 -> 314.8.
 // Unsigned or per-channel blocks of one or two images stay three launches: 9.7 us and 8.5 by themselves, but inside
 // ResNet-50 209.0 and 211.9 with three of them (plain codes 203.0 and 200.9); two images unsigned 247.1 with three
 // launches and 249.0, per channel 247.3 and 247.2; three per channel 303.6 and 275.6.
-int block_choose(const q8_op* ops, const ConvParams* p) {
-  float us = 0.0f, single = 0.0f;
+int block_choose(const q8_op* ops, const ConvParams* p, const float* shared) {
+  float us = 0.0f, three = 0.0f;
   const int build = bneck_applicable(p[0], p[1], p[2]) ? pick_bneck(p[0], p[1], p[2], &us) : -1;
   if (build < 0) return -1;
   if (p[0].N <= 2 && (is_extended(p[0]) || is_extended(p[1]) || is_extended(p[2]))) return -1;
   for (int i = 0; i < 3; ++i) {
     float t = 0.0f;
     conv_choose(&ops[i].d, p[i], &t);
-    single += t;
+    three += t;
   }
-  return us < (p[0].K == 64 ? 1.15f : 0.95f) * single ? build : -1;
+  const long tiles = ((p[2].M + 63L) / 64) * ((p[2].K + 63) / 64);
+  float most = (p[0].K == 64 ? 1.15f : 0.95f) * three;
+  if (shared && *shared > 0.0f)
+    most = fminf(most, (p[0].K == 256 ? 0.9f : 1.05f) * (three - *shared));
+  else if (shared && p[0].K == 256 && tiles <= 512)
+    most = 0.88f * three;
+  return us < most ? build : -1;
 }
-int block_fill(const q8_op* ops, ConvParams* p) {
+int block_fill(const q8_op* ops, ConvParams* p, const float* shared = nullptr) {
   for (int i = 0; i < 3; ++i) {
     bool empty = false;
     if (ops[i].kind != Q8_OP_CONV || conv_fill_op(&ops[i], p[i], &empty) != Q8_OK || empty) return -1;
   }
-  return block_choose(ops, p);
+  return block_choose(ops, p, shared);
 }
 
 // How the convolutions of a run of independent ops are launched: in part or in whole together, as
@@ -108,6 +124,7 @@ struct GroupPlan {
   const ConvParams* set[kSets][kMaxGroup];
   int count[kSets] = {}, build[kSets], member[kMaxGroup] = {};
   int chosen[2] = {-1, -1};            // sets to launch together
+  float less = 0.0f;                   // what that takes less than every layer on its own
 
   void choose(const q8_op* ops, int n) {
     const int first = first_direct_variant(), last = first + num_direct_variants();
@@ -146,8 +163,25 @@ struct GroupPlan {
       if (saved[kLargeTiled] > 0.0f) chosen[0] = kLargeTiled;
       if (saved[kSmallDirect] > 0.0f) chosen[1] = kSmallDirect;
     }
+    for (int s : chosen)
+      if (s >= 0) less += saved[s];
   }
 };
+
+// What the convolutions among independent ops take less together than on their own.
+float group_less(const q8_op* ops, int n) {
+  GroupPlan g;
+  int m = 0;
+  q8_op convs[kMaxGroup];
+  for (int i = 0; i < n && m < kMaxGroup; ++i) {
+    bool empty = false;
+    if (ops[i].kind != Q8_OP_CONV || conv_fill_op(&ops[i], g.p[m], &empty) != Q8_OK || empty) continue;
+    g.waiting[m] = true;
+    convs[m++] = ops[i];
+  }
+  g.choose(convs, m);
+  return g.less;
+}
 
 // A run of independent ops on one stream.  Ops in front of a refused one are enqueued, those behind
 // it are not: the convolutions, whose arguments are checked without a launch, therefore go behind
@@ -356,6 +390,20 @@ extern "C" const char* q8_block_variant(const q8_op* ops) {
   q8::ConvParams p[3];
   const int build = ops ? q8::block_fill(ops, p) : -1;
   return build >= 0 ? q8::bneck_build_name(build) : "single launches";
+}
+
+extern "C" int q8_block_pays(const q8_op* block, const q8_op* beside, int n_beside) {
+  if (!block || n_beside < 0 || n_beside >= q8::kMaxGroup || (n_beside && !beside)) return 0;
+  q8::ConvParams p[3];
+  float shared = 0.0f;
+  if (n_beside) {
+    q8_op all[q8::kMaxGroup];
+    all[0] = block[0];
+    for (int i = 0; i < n_beside; ++i) all[i + 1] = beside[i];
+    shared = q8::group_less(all, n_beside + 1) - q8::group_less(beside, n_beside);
+  }
+  if (!(shared > 0.0f)) shared = 0.0f;
+  return q8::block_fill(block, p, &shared) >= 0;
 }
 
 extern "C" int q8_num_bottleneck_builds(void) { return q8::num_bneck_builds(); }

@@ -471,6 +471,37 @@ def test_bottleneck_blocks_that_one_launch_takes():
     assert B.lib.q8_run_bottleneck(None, 0, None) == -1 and name(None) == "single launches"
 
 
+def test_blocks_that_pay_inside_a_network():
+    """What a program asks before it marks a block: three layers by themselves as the library would launch them,
+    but for wide blocks of few tiles, and the first one's share of a launch with others counted."""
+    def pays(ops, *beside):
+        return B.lib.q8_block_pays(ops, (B.Op * len(beside))(*beside), len(beside))
+
+    def projection(ops, K, **fields):
+        o = B.Op.from_buffer_copy(ops[0])
+        d = ops[0].d
+        o.d, o.w, o.bias, o.y = B.ConvDesc(d.N, d.H, d.W, d.C, K, 1, 1), 1 << 50, 1 << 51, 1 << 52
+        for name, value in fields.items():
+            setattr(o, name, value)
+        return o
+    one = lambda ops: B.lib.q8_block_variant(ops) != b"single launches"
+    for kw, alone, beside in ((dict(), 1, 1), (dict(N=1), 1, 1), (dict(mid=128, C=256, H=20, K2=256, N=2), 1, 0),
+                              (dict(mid=128, C=256, H=20, K2=256, N=1), 1, 0), (dict(mid=128, C=256, H=20, K2=256, N=12), 1, 1),
+                              (dict(mid=256, C=256, H=14, K2=256, N=5), 1, 0), (dict(mid=256, C=512, H=14, K2=512, N=23), 1, 1)):
+        ops = _block(**kw)
+        assert one(ops) and pays(ops) == alone and pays(ops, projection(ops, ops[2].d.K)) == beside, kw
+        # a layer that shares nothing with the first one's launch, and one that is none
+        assert pays(ops, projection(ops, 64, kind=B.OP_POOL)) == alone
+        assert pays(ops, projection(ops, ops[2].d.K, flags=B.OPF_REAL, y_f32=None)) == alone
+    for N, wide in ((8, 0), (9, 0), (11, 1), (16, 1)):     # two tiles of 64 x 64 a CU in the last layer end at 2048 pixels
+        ops = _block(mid=256, C=1024, H=14, K2=1024, N=N)
+        assert one(ops) and pays(ops) == wide
+    assert not pays(_block(o1_x=1 << 39)) and not pays(_block(mid=256, C=1024, H=14, N=1, K2=1024))
+    ops = _block()
+    assert B.lib.q8_block_pays(None, None, 0) == B.lib.q8_block_pays(ops, None, 1) == B.lib.q8_block_pays(ops, ops, 8) == 0
+    assert B.lib.q8_block_pays(ops, None, -1) == 0
+
+
 def _layer_and_maximum(n=1, kind=B.OP_MAXPOOL, **change):
     """n layers of the block-tiled 3x3 kernel, then the 2x2 maxima over their outputs, the last one's first, each pair
     on a stream index of its own, at made-up addresses (nothing is launched)."""

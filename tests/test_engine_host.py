@@ -287,3 +287,15 @@ def test_a_block_whose_inner_values_leave_is_none(recorded):
         ops = step(None, {name: torch.empty(eng.act[name].shape)} if name else None)
         assert sum(bool(o.flags & B.OPF_BLOCK) for o in ops) == marked
         assert all(o.group for o in ops) == (not marked)
+
+
+@pytest.mark.parametrize("batch, pipelines, blocks", [
+    (1, 1, "2a 2b 2c"), (8, 1, "2a 2b 2c 3a 3b 3c 3d"), (13, 1, "2a 2b 2c 3a 3b 3c 3d 4b 4c 4d 4e 4f"),
+    (13, 2, "2a 2b 2c 3a 3b 3c 3d 4a 4b 4c 4d 4e 4f")])
+def test_blocks_of_resnet50(recorded, batch, pipelines, blocks):
+    """The blocks that are marked: a projection's launch, which a first layer would share, counts on one pipeline."""
+    net = wl.resnet50()
+    eng, _ = recorded(net, batch)
+    levels = eng._levels(net.ops, batch, lambda o: o.dst) if pipelines == 1 else None
+    found = eng._blocks(net.ops, {}, batch, levels)
+    assert " ".join(net.ops[i].name[3:5] for i in sorted(found)) == blocks
