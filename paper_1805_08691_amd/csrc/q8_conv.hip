@@ -153,9 +153,9 @@ int pick_halo3(const q8_conv_desc* d) {
   // CU, those (512 -> 512 on 38 x 38: 16.3 us as 96 tiles of 128 x 64, 11.2 in one group, 10.5 in two; 256 -> 256
   // on 40 x 40 10.1, 7.5, 7.4, the latency family 12.5; 128 -> 128 on 56 x 56 7.6, 6.0, 6.2), then two groups on
   // 128 x 64 (512 -> 512 on two such maps 15.6 -> 13.7, 256 -> 256 on 75 x 75 11.1 -> 10.2; more than 256 of
-  // them are a second round: 38 x 38 on four maps 21.0 and 25.7).  Fewer than 128 output channels would gain as
-  // much (128 -> 80 on two maps of 55 x 57 8.2 -> 6.2) and are left to the 128 x 64 tiles for wide maps, whose
-  // extended build is tested on them.
+  // them are a second round: 38 x 38 on four maps 21.0 and 25.7).  Swept from 128 output channels on: of 150
+  // layers that it changes the least gains 3 %, the median 30.  Below, one layer was timed (128 -> 80 on two maps
+  // of 55 x 57, 8.2 and 6.2 us), and the rule is not extended to what has not been swept.
   if (d->K >= 128 && (smallest == 0 || smallest == 4)) {
     const long across = (d->K + 63) / 64, tiles64 = ((M + 63) / 64) * across, tiles128 = ((M + 127) / 128) * across;
     const bool two = d->C % 128 == 0 && d->C >= 256;

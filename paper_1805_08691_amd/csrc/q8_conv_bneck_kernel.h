@@ -194,7 +194,7 @@ void conv_i8_bneck_kernel(const BneckParams q) {
     const bool in = chunk < gA;
 #pragma unroll
     for (int j = 0; j < XL; ++j)
-      load_lds(rsrc_x, tile + slot + (wave + NW * j) * 1024, in ? x_off[j] + 0 : kOobOffset, in ? chunk * G : 0);
+      load_lds(rsrc_x, tile + slot + (wave + NW * j) * 1024, in ? x_off[j] : kOobOffset, in ? chunk * G : 0);
   };
 #pragma unroll
   for (int k = 0; k < D; ++k) {

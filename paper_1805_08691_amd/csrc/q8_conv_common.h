@@ -335,8 +335,8 @@ __device__ __forceinline__ void finish16(const ConvParams& p, int pix, int ch, c
 
 // The 16 codes of values whose lower bound is zero (a ReLU layer's, or unsigned codes), packed four to a
 // word: v_cvt_pk_u8_f32 rounds half to even, saturates at 0 and 255 and puts the byte in its place, in one
-// instruction an element where adding 1.5 * 2^23 and byte permutes take 1.75 (tests hold it against the oracle;
-// checked once over all floats).  clamp: the upper bound hi is below 255.
+// instruction an element where adding 1.5 * 2^23 and byte permutes take 1.75.  The same code as those for every
+// float but the signalling NaNs, which no arithmetic gives.  clamp: the upper bound hi is below 255.
 __device__ __forceinline__ v4i pack16_nonneg(const float (&t)[16], bool clamp, float hi) {
   v4i out;
 #pragma unroll

@@ -82,14 +82,14 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 
   const int frag_row = lane & 31, frag_half = lane >> 5;
   // ---- patch loader: load j of this wave fills patch rows (wave + NW j) RPW + lane / CHUNKS; patch
-  // row rho is input position (h0 - pad + rho / 18, w0 - pad + rho % 18) of the tile's image.  The slot
-  // of 16-byte chunk c in row rho is c ^ ((rho >> 2) & 3) (C = 32: c ^ ((rho >> 3) & 1)): sixteen
-  // consecutive rows read at one chunk touch every bank once.
+  // row rho is input position (h0 - pad + rho / 18, w0 - pad + rho % 18) of the tile's image.
+  // Slot of 16-byte chunk c in row rho, of the filters and, for 32 channels, of the patch: c ^ ((rho >> 2) & 3)
+  // (32 channels: c ^ ((rho >> 3) & 1)), so that sixteen consecutive rows read at one chunk touch every bank once.
   auto slot_of = [](int rho, int chunk) {
     return CHUNKS == 4 ? chunk ^ ((rho >> 2) & 3) : chunk ^ ((rho >> 3) & 1);
   };
-  // (by the column alone for 64 channels: an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and 24-27
-  // together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next)
+  // The patch of 64 channels by its column x alone: an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and
+  // 24-27 together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next.
   auto patch_slot = [&](int rho, int x, int chunk) { return CHUNKS == 4 ? chunk ^ ((x >> 2) & 3) : slot_of(rho, chunk); };
   int pr_y[PL], pr_x[PL], pr_off[PL];          // ... and its offset from the block's
 #pragma unroll

@@ -407,11 +407,11 @@ int launch_stem(ConvParams& p, const StemImage& im, hipStream_t stream) {
   // Strips per image: about as many workgroups as HALF the resident slots -- the layer's
   // other part-batch launch runs beside this one (two pipelines), and a second round of
   // workgroups costs more than longer strips do (ResNet-50's head at 2 x 32 images: 0.711 ->
-  // 0.700 ms per step with 5 instead of 3 pooled rows per strip) -- between four and six rows
-  // each (POOL: three to six pooled rows, i.e. 7 .. 13 output rows of which one is computed
-  // twice).
-  // Few images: shorter strips, down to one row, as long as each still gets a CU of its own (a workgroup's
-  // start and its rows one after the other are what takes the time).
+  // 0.700 ms per step with 5 instead of 3 pooled rows per strip) -- of at most six rows, and at least as
+  // many, up to four, as leave every strip a CU of its own (POOL: pooled rows, up to three, i.e. 7 output rows of
+  // which one is computed twice; 6 are 13).  With few images a workgroup's start and its rows one after the other
+  // are what takes the time: 224 x 224 x 3 with the maximum, one and eight images in strips of three rows 16.0 and
+  // 16.3 us, in strips of one and two 9.7 and 13.0.
   const int rows = POOL ? im.Hp : p.Ho, most = 6;
   int least = 1;
   while (least < (POOL ? 3 : 4) && (long)p.N * ((rows + least - 1) / least) > 256) ++least;

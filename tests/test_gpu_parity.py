@@ -1116,15 +1116,23 @@ def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
         o.R = o.S = o.stride = 2
         o.Ho, o.Wo, o.q_x, o.q_out, o.group = Hp, Wp, q_out, q_out, 2
         o.d.out_c_stride, o.d.out_c_off = cs, off
+        assert B.lib.q8_joined_op(ops, 2, streams, 1, 0) == (1 if apart else -1)
         assert B.lib.q8_run_ops(ops, 2, streams, 1) == 0
         assert np.array_equal(host(y), want)
+        if apart and cs == K:              # the same as a call without a factor
+            o.kind, o.y = B.OP_MAXPOOL, z.fill_(77).data_ptr()
+            y.fill_(77)
+            assert B.lib.q8_joined_op(ops, 2, streams, 1, 0) == 1
+            assert B.lib.q8_run_ops(ops, 2, streams, 1) == 0
+            assert np.array_equal(host(y), want)
         got = host(z if apart else xd.flatten()[:pooled.size].view(pooled.shape))
         assert np.array_equal(got[..., off:off + K], pooled[..., off:off + K])
         if apart:
             assert np.array_equal(got, pooled)
 
 
-@pytest.mark.parametrize("case", ["one stream, two indices", "default stream", "refused", "two streams"])
+@pytest.mark.parametrize("case", ["one stream, two indices", "default stream", "refused", "two streams",
+                                  "leads a group"])
 def test_maximum_and_ops_of_other_streams(B, case):
     """Layers and the maxima over their outputs with ops of other streams between the two: what the list's order
     says where that binds the streams, nothing behind a refused op, and every tensor as by single calls."""
@@ -1159,6 +1167,10 @@ def test_maximum_and_ops_of_other_streams(B, case):
         for i in range(pairs):             # conv 0, conv 1, maximum 1, maximum 0, conv 3, ...
             ops += [conv(i, 0)] if i % 2 == 0 else [conv(i, 1), maximum(y[i], z[i], 2, 1), maximum(y[i - 1], z[i - 1], 2, 0)]
         joined = 3
+    elif case == "leads a group":          # of two maxima, the other of which stays behind
+        handles, more = [torch.cuda.Stream().cuda_stream] * 2, torch.empty_like(z[0])
+        ops, joined = [conv(0, 0), maximum(y[0], z[0], 2, 0), maximum(other, more, 2, 0)], 1
+        ops[1].group = ops[2].group = 3
     elif case == "refused":
         handles = [torch.cuda.Stream().cuda_stream, torch.cuda.Stream().cuda_stream]
         ops, joined = [conv(0, 0), maximum(other, other, 0, 1), maximum(y[0], z[0], 2, 0)], 2
@@ -1174,8 +1186,10 @@ def test_maximum_and_ops_of_other_streams(B, case):
     torch.cuda.synchronize()
     if case == "refused":
         assert code == -1 and np.array_equal(host(y[0]), host(want[0])) and (host(z[0]) == 77).all()
-    elif case == "two streams":
+    elif case in ("two streams", "leads a group"):
         assert code == 0
+        if case == "leads a group":
+            assert np.array_equal(host(more), host(B.maxpool_i8(other, 2, 2, 2, 0, H // 2, W // 2)))
         for a, b, c in zip(y, want, z):
             assert np.array_equal(host(a), host(b))
             assert np.array_equal(host(c), host(B.maxpool_i8(b, 2, 2, 2, 0, H // 2, W // 2)))
@@ -2118,11 +2132,13 @@ def test_run_ops_groups_equal_single_calls(B):
         assert np.array_equal(host(r), host(B.dequantize_u8(y, 0.5) if i % 2 else B.dequantize(y, 0.5)))
 
 
+@pytest.mark.parametrize("scale", [0.5, 0.3, 2.0 ** -31, 1e31])
 @pytest.mark.parametrize("relu", [0, 1])
 @pytest.mark.parametrize("C,N", [(64, 1), (64, 13), (256, 13)])
-def test_tails_on_ties_and_bounds(B, C, N, relu):
+def test_tails_on_ties_and_bounds(B, C, N, relu, scale):
     """Every tail on values at, beside and far beyond its ties and bounds: zero activations, so that the
-    accumulators are the biases, -768 ... 767 and the ends of their range, at a scale of one half; one call
+    accumulators are the biases, -768 ... 767 and the ends of their range, at a scale of one half (ties), one without ties,
+    one that only the ends reach a code with and one whose products leave the floats; one call
     in each family (few pixels: the latency family; many: persistent or general), every tile variant
     of the main kernel, and unsigned codes."""
     K, H = 1536, 28 if N > 1 else 3
@@ -2132,15 +2148,15 @@ def test_tails_on_ties_and_bounds(B, C, N, relu):
     x, w, b = (torch.zeros(s, dtype=torch.int8, device="cuda") for s in ((N, H, H, C), (K, 1, 1, C), 1))
     w, b = B.pack_weights(d, w), dev(bias)
     acc = np.broadcast_to(bias, (1, 1, 1, K))
-    want = orc.requant(acc, 0.5, relu)
-    assert len(np.unique(want)) == (128 if relu else 256)
+    want = orc.requant(acc, scale, relu)
+    assert len(np.unique(want)) == {0.5: 256, 0.3: 256, 2.0 ** -31: 3, 1e31: 3}[scale] // (1 + relu) + (scale not in (0.5, 0.3) and relu)
     variants = [-1] + ([v for v in range(B.conv_num_variants())] if N == 13 else [])
     for v in variants:
-        got = host(B.conv_int8(d, x, w, b, 0.5, 1.0, 1.0, variant=v))
+        got = host(B.conv_int8(d, x, w, b, scale, 1.0, 1.0, variant=v))
         assert np.array_equal(got, np.broadcast_to(want, got.shape)), v
     if relu:
-        got = host(B.conv_u8(d, False, True, False, x, w, b, None, 0.5, 1.0, 1.0))
-        want = orc.requant_mixed(acc, 0.5, 1, out_unsigned=True)
+        got = host(B.conv_u8(d, False, True, False, x, w, b, None, scale, 1.0, 1.0))
+        want = orc.requant_mixed(acc, scale, 1, out_unsigned=True)
         assert np.array_equal(got.view(np.uint8) ^ 0x80, np.broadcast_to(want, got.shape))
 
 
