@@ -78,6 +78,146 @@ def measured_traffic(kernel, net_name, batch):
     return None
 
 
+def launches_of(eng, x, dequant, fused_deq):
+    """The launches of one step as they are enqueued, in order: [{kind, name (of the layers), variant, run,
+    ops, bytes, row (what the table prints)}].  A step that the engine plans is taken apart as q8_run_ops does:
+    marked blocks, groups that share a launch, a maximum in its layer's launch, else op by op; other steps
+    layer by layer."""
+    import ctypes
+    from paper_1805_08691_amd import binding as B
+    net, units = eng.net, []
+
+    def unit(kind, run, layers=(), variant="", n=0, extra=0):
+        u = dict(kind=kind, run=run, name="+".join(o.name for o in layers), variant=variant, ops=0, bytes=extra)
+        for o in layers:
+            s, d = net.tensors[o.src], net.tensors[o.dst]
+            if o.kind == "conv":
+                ops, byts = conv_work(net, o, n)
+                if o.dst in fused_deq:           # also writes the fp32 values of its codes
+                    byts += 4 * n * d.H * d.W * o.K
+                u["ops"] += ops
+            else:
+                byts = n * (s.H * s.W + d.H * d.W) * s.C
+            u["bytes"] += byts
+        if layers:
+            o = layers[0]
+            u["row"] = (dict(C=o.C, K=o.K, R=o.R, S=o.S, stride=o.stride, H=net.tensors[o.src].H) if o.kind == "conv"
+                        else dict(mode=o.mode, H=net.tensors[o.src].H, C=net.tensors[o.src].C, R=o.R, stride=o.stride))
+        units.append(u)
+
+    def head(run, n):                            # reads the fp32 image, writes the pooled tensor
+        conv, pool = eng.head
+        t, out = net.tensors[net.input], net.tensors[(pool or conv).dst]
+        unit("conv", run, [conv], "conv_i8_stem_kernel<Q" + (",pool>" if pool else ">"), n)
+        units[-1]["bytes"] = (4 * n * t.H * t.W * t.C + n * out.H * out.W * conv.K
+                              + conv.K * conv.R * conv.S * conv.C + 4 * conv.K)
+
+    if not eng._plannable(x, dequant):
+        unit("quantize", lambda: eng.quantize_input(x))
+        for o in net.ops:
+            if o.name in eng.paired or o.name in eng.dualed or (eng.head and o is eng.head[1]):
+                continue                         # in the launch of the layer in front of it
+            for lo, n in eng.parts:
+                run = lambda o=o, lo=lo, n=n: eng.run_ops([o], lo, n)
+                if eng.head and o is eng.head[0]:
+                    def run(o=o, lo=lo, n=n):
+                        eng._x = x
+                        eng.run_ops([o], lo, n)
+                        eng._x = None
+                    head(run, n)
+                elif o.kind == "conv":
+                    more = [q for q in (eng.pairs.get(o.name), eng.duals.get(o.name)) if q]
+                    moved = 2 * n * net.tensors[o.dst].H * net.tensors[o.dst].W * o.K    # the tensor between a pair
+                    unit("conv", run, [o] + more, B.conv_variant(eng.conv_desc(o, n)) +
+                         "+pair" * (o.name in eng.pairs), n, -moved * (o.name in eng.pairs))
+                else:
+                    unit("pool", run, [o], n=n)
+        if eng.head:
+            units.pop(0)
+        for name, buf in dequant.items():
+            unit("dequantize", lambda name=name, buf=buf: eng.dequantize(name, out=buf))
+        return units
+
+    segments, _, _, n_parts = next(iter(eng._plans.values()))[0]
+    filters = {eng.wq[o.name][0].data_ptr(): o for o in net.convs()}
+    pools = {}                                   # (address read, address written) -> layer
+    for o in net.ops:
+        if o.kind == "pool":
+            for lo, n in eng.parts + [(0, eng.N)]:
+                pools[eng.act[o.src][lo:].data_ptr(), eng.act[o.dst][lo:].data_ptr()] = o
+    apart = (ctypes.c_void_p * n_parts)(*range(64, 64 + n_parts))      # for what may go ahead of what
+
+    def emit(ops):
+        array = (B.Op * len(ops))(*ops)
+
+        def run():
+            here = (ctypes.c_void_p * n_parts)(*[B._stream()] * n_parts)
+            B._check(B.lib.q8_run_ops(array, len(ops), here, n_parts))
+        o = ops[0]
+        if o.kind in (B.OP_QUANTIZE, B.OP_QUANTIZE_PAD, B.OP_QUANTIZE_IMAGE):
+            return unit("quantize", run)
+        if o.kind == B.OP_DEQUANTIZE:
+            return unit("dequantize", run)
+        layers = [filters.get(q.w) or pools[q.x, q.y] for q in ops]
+        if o.kind == B.OP_HEAD:
+            return head(run, o.d.N)
+        if o.kind != B.OP_CONV:
+            return unit("pool", run, layers, n=o.d.N)
+        variant = B.conv_variant(o.d) + "+D" * (layers[0].dst in fused_deq)
+        extra = 0
+        if len(ops) == 3 and o.flags & B.OPF_BLOCK:          # the tensors between are written and not read
+            variant = B.lib.q8_block_variant(array).decode()
+            extra = -sum(o.d.N * net.tensors[q.dst].H * net.tensors[q.dst].W * q.K for q in layers[:2])
+        elif len(ops) == 2 and layers[1].kind == "pool" and not o.group == ops[1].group != 0:
+            variant += "+max"
+            extra = -o.d.N * net.tensors[layers[0].dst].H * net.tensors[layers[0].dst].W * layers[0].K
+        elif len(ops) > 1:
+            variant = "group: " + B.lib.q8_group_variant(array, len(ops)).decode()
+        unit("conv", run, layers, variant, o.d.N, extra)
+
+    for ops in segments:
+        joined = set()
+        i = 0
+        while i < len(ops):
+            o, j = ops[i], i + 1
+            if i in joined:
+                i = j
+                continue
+            if o.kind == B.OP_CONV and o.flags & B.OPF_BLOCK:
+                j = i + 3
+                three = (B.Op * 3)(*ops[i:j])
+                if B.lib.q8_block_variant(three) == b"single launches":
+                    for q in three:
+                        emit([q])
+                else:
+                    emit(three)
+            else:
+                while o.group and j < len(ops) and j - i < 8 and ops[j].group == o.group and \
+                        ops[j].stream == o.stream:
+                    j += 1
+                together = (B.Op * (j - i))(*ops[i:j])
+                k = B.lib.q8_joined_op(ops, len(ops), apart, n_parts, i) if j == i + 1 else -1
+                if k >= 0:
+                    joined.add(k)
+                    emit([o, ops[k]])
+                elif j > i + 1 and not any(q.kind != B.OP_CONV for q in together) and \
+                        B.lib.q8_group_variant(together, j - i) != b"single launches":
+                    emit(together)
+                else:                            # poolings of a group go in front of its convolutions
+                    convs = [q for q in together if q.kind == B.OP_CONV]
+                    for q in together:
+                        if q.kind != B.OP_CONV:
+                            emit([q])
+                    shared = (B.Op * len(convs))(*convs)
+                    if len(convs) > 1 and B.lib.q8_group_variant(shared, len(convs)) != b"single launches":
+                        emit(convs)
+                    else:
+                        for q in convs:
+                            emit([q])
+            i = j
+    return units
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -239,27 +379,27 @@ def main():
     ms_per_step = elapsed / args.steps * 1e3
     images_per_s = N * args.steps / elapsed
 
-    # the same launches on ONE stream (the half-batch pipelines one after the other): the
-    # total the per-launch intervals below must add up to
-    serial_us = ms_per_step * 1e3
-    if graph is not None and eng.n_streams > 1:
-        g1 = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(g1):
-            eng.run_step(x, dequant, serial=True)
-        for _ in range(3):
-            g1.replay()
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(20):
-            g1.replay()
-        torch.cuda.synchronize()
-        serial_us = (time.perf_counter() - t0) / 20 * 1e6
+    # ---------------- the step's launches, one by one ---------------------------------------
+    fused_deq = {k: v for k, v in dequant.items() if eng._dequant_writer(k)}
+    units = launches_of(eng, x, dequant, fused_deq)
+    # all of them on ONE stream (the part-batch pipelines' launches in turn): the total the
+    # per-launch intervals below must add up to
+    g1 = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g1):
+        for u in units:
+            u["run"]()
+    for _ in range(3):
+        g1.replay()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(20):
+        g1.replay()
+    torch.cuda.synchronize()
+    serial_us = (time.perf_counter() - t0) / 20 * 1e6
 
     # ---------------- per-launch durations with HIP events on the launch stream ------------
     # The host enqueues a whole chained pass behind a spin kernel so the GPU runs the
-    # layers back to back; events between launches give each kernel's duration.
-    ops_list = [o for o in net.ops]
-    fused_deq = {k: v for k, v in dequant.items() if eng._dequant_writer(k)}
+    # launches back to back; events between them give each kernel's duration.
     reps = 7
     # an event record costs GPU time of its own: measure the interval between back-to-back
     # records on the busy stream and take it off every interval below
@@ -269,27 +409,16 @@ def main():
         e.record()
     torch.cuda.synchronize()
     ev_cost = float(np.median([evs[i].elapsed_time(evs[i + 1]) * 1e3 for i in range(32)]))
-    dur = np.zeros((reps, len(ops_list) + 2))
+    dur = np.zeros((reps, len(units)))
     for r in range(reps):
-        ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(ops_list) + 3)]
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(units) + 1)]
         torch.cuda._sleep(20_000_000)
         ev[0].record()
-        eng.set_input(x)                  # Eq. Q now, or inside the first layer's launches
-        eng._deq = dict(fused_deq)        # Eq. D inside the last layer's launches, or below
-        ev[1].record()
-        for i, op in enumerate(ops_list):
-            # the launches of one layer (one per half-batch when split) back to back on
-            # this stream; the interval is divided by their number below
-            for lo, n in (eng.parts if i >= eng.n_unsplit else [(0, N)]):
-                eng.run_ops([op], lo, n)
-            ev[i + 2].record()
-        for name, buf in dequant.items():
-            if name not in fused_deq:
-                eng.dequantize(name, out=buf)
-        ev[-1].record()
-        eng._x, eng._deq = None, {}
+        for i, u in enumerate(units):
+            u["run"]()
+            ev[i + 1].record()
         torch.cuda.synchronize()
-        for i in range(len(ops_list) + 2):
+        for i in range(len(units)):
             dur[r, i] = ev[i].elapsed_time(ev[i + 1]) * 1e3      # us
     raw = np.median(dur, axis=0)
     # between busy kernels a record costs less than between empty ones: take off the amount
@@ -300,32 +429,30 @@ def main():
         f"each launch interval: sum {med.sum():.1f} us vs one-stream step {serial_us:.1f} us "
         f"(timed step, {eng.n_streams} stream(s): {ms_per_step * 1e3:.1f} us)")
 
-    # ---------------- the same launches cold: caches flushed before every layer -------------
-    # A 1 GiB device copy (four times the 256 MB last-level cache) runs before each layer's
-    # launches, so activations, residual and filters come from HBM.
-    cold = np.zeros(len(ops_list))
+    # ---------------- the same launches cold: caches flushed before every one ---------------
+    # A 1 GiB device copy (four times the 256 MB last-level cache) runs before each
+    # launch, so activations, residual and filters come from HBM.
+    cold = np.zeros(len(units))
     if not args.no_cold:
         flush_src = torch.ones(512 << 20, dtype=torch.int8, device="cuda")
         flush_dst = torch.empty_like(flush_src)
         cold_reps = 5
-        cdur = np.zeros((cold_reps, len(ops_list)))
+        cdur = np.zeros((cold_reps, len(units)))
         for r in range(cold_reps):
-            eng._x = x if eng.head else None
-            eng._deq = dict(fused_deq)
-            e0 = [torch.cuda.Event(enable_timing=True) for _ in ops_list]
-            e1 = [torch.cuda.Event(enable_timing=True) for _ in ops_list]
-            for i, op in enumerate(ops_list):
+            e0 = [torch.cuda.Event(enable_timing=True) for _ in units]
+            e1 = [torch.cuda.Event(enable_timing=True) for _ in units]
+            for i, u in enumerate(units):
                 flush_dst.copy_(flush_src)
                 e0[i].record()
-                for lo, n in (eng.parts if i >= eng.n_unsplit else [(0, N)]):
-                    eng.run_ops([op], lo, n)
+                u["run"]()
                 e1[i].record()
-            eng._x, eng._deq = None, {}
             torch.cuda.synchronize()
-            for i in range(len(ops_list)):
+            for i in range(len(units)):
                 cdur[r, i] = e0[i].elapsed_time(e1[i]) * 1e3
         cold = np.maximum(np.median(cdur, axis=0) - ev_take, 0.0)
         del flush_src, flush_dst
+    for u, us, us_cold in zip(units, med, cold):
+        u["us"], u["cold_us"] = float(us), float(us_cold)
 
     # ---------------- measured ceilings: a plain device copy, a register-resident MFMA loop --
     def timed_us(fn, reps=20):
@@ -361,15 +488,20 @@ def main():
     del big
     n_in = x.numel()
     n_out = out_f32.numel()
-    # with the fused head Eq. Q on the input is not a launch of the step: timed on its own
-    t_qin = timed_us(lambda: eng.quantize_input(x)) if eng.head else float(med[0])
+    # with the fused head Eq. Q on the input is not a launch of the step: timed on its own; Eq. D on the
+    # output likewise where the layer that writes it does that too
+    t_qin, t_out = (next((u["us"] for u in units if u["kind"] == kind), None)
+                    for kind in ("quantize", "dequantize"))
+    q_in_step, d_in_step = t_qin is not None, t_out is not None
+    if not q_in_step:
+        t_qin = timed_us(lambda: eng.quantize_input(x))
+    if not d_in_step and not args.real_output:
+        t_out = timed_us(lambda: eng.dequantize(out_name, out=out_f32))
     passes = {
         "maxabs": dict(bytes=4 * 64 * 112 * 112 * 64, us=round(t_maxabs, 2)),
         "quantize_input": dict(bytes=5 * n_in + n_in // 3, us=round(t_qin, 2),
-                               in_step=not eng.head),
-        "dequantize_output": dict(bytes=5 * n_out, in_step=not fused_deq,
-                                  us=round(timed_us(lambda: eng.dequantize(out_name, out=out_f32))
-                                           if fused_deq else float(med[-1]), 2)),
+                               in_step=q_in_step),
+        "dequantize_output": dict(bytes=5 * n_out, in_step=d_in_step, us=round(t_out or 0.0, 2)),
     }
     if args.real_output:
         del passes["dequantize_output"]
@@ -384,56 +516,27 @@ def main():
     tot_ops = tot_us = tot_bytes = tot_cold = 0.0
     roof_us = 0.0
     helpers = []          # the pooling launches between convolutions (not the paper's method)
-    for i, op in enumerate(ops_list):
-        if eng.head and op is eng.head[1]:
-            continue                      # ran inside the first layer's launch
-        if op.kind != "conv":
-            n_launch = len(eng.parts) if i >= eng.n_unsplit else 1
-            s_t, d_t = net.tensors[op.src], net.tensors[op.dst]
-            byts = N * (s_t.H * s_t.W * s_t.C + d_t.H * d_t.W * s_t.C) / n_launch
-            us = float(med[i + 1]) / n_launch
-            helpers.append(dict(name=op.name, mode=op.mode, H=s_t.H, C=s_t.C, R=op.R, stride=op.stride,
-                                us=round(us, 2), gbs=round(byts / us / 1e3, 1), launches=n_launch))
+    rows = {}             # the launches of the same layers, one per part-batch
+    for u in units:
+        if u["kind"] in ("conv", "pool"):
+            rows.setdefault((u["kind"], u["name"]), []).append(u)
+    for (kind, name), us_ in rows.items():
+        n_launch = len(us_)
+        ops, byts, us, us_cold = (sum(u[k] for u in us_) / n_launch for k in ("ops", "bytes", "us", "cold_us"))
+        if kind == "pool":
+            helpers.append(dict(us_[0]["row"], name=name, us=round(us, 2), gbs=round(byts / us / 1e3, 1),
+                                launches=n_launch))
             continue
-        if op.name in eng.paired or op.name in eng.dualed:
-            continue                      # counted with the layer in front of it
-        n_launch = len(eng.parts) if i >= eng.n_unsplit else 1
-        n_img = eng.parts[0][1] if i >= eng.n_unsplit else N
-        ops, byts = conv_work(net, op, N)
-        if op.name in eng.duals:          # one launch for two layers on the same input
-            ops2, byts2 = conv_work(net, eng.duals[op.name], N)
-            s_t = net.tensors[op.src]
-            ops, byts = ops + ops2, byts + byts2
-        if op.name in eng.pairs:          # one launch for two layers: the tensor between
-            ops2, byts2 = conv_work(net, eng.pairs[op.name], N)     # them is not moved
-            mid = net.tensors[op.dst]
-            ops, byts = ops + ops2, byts + byts2 - 2 * N * mid.H * mid.W * mid.C
-        fused_head = bool(eng.head and op is eng.head[0])
-        if fused_head:                    # reads the fp32 image, writes the pooled tensor
-            t_img = net.tensors[net.input]
-            out_t = net.tensors[eng.head[1].dst] if eng.head[1] else net.tensors[op.dst]
-            byts = (4 * N * t_img.H * t_img.W * t_img.C + N * out_t.H * out_t.W * op.K
-                    + op.K * op.R * op.S * op.C + 4 * op.K)
-        if op.dst in fused_deq:           # also writes the fp32 values of its codes
-            byts += 4 * N * net.tensors[op.dst].H * net.tensors[op.dst].W * op.K
-        ops, byts = ops / n_launch, byts / n_launch          # per launch
-        us = float(med[i + 1]) / n_launch
-        us_cold = float(cold[i]) / n_launch
-        variant = B.conv_variant(eng.conv_desc(op, n_img)) + ("+pair" if op.name in eng.pairs else "")
-        if fused_head:
-            variant += "<Q" + (",pool>" if eng.head[1] else ">")
-        if op.dst in fused_deq:
-            variant += "+D"
+        variant = us_[0]["variant"]
         bound = "mfma" if ops / byts > RIDGE else "hbm"
         t_roof = max(ops / (PEAK_INT8_TOPS * 1e12), byts / (PEAK_HBM_GBS * 1e9)) * 1e6
-        layers.append(dict(name=op.name, C=op.C, K=op.K, R=op.R, S=op.S, stride=op.stride,
-                           H=net.tensors[op.src].H, variant=variant, us=round(us, 2),
+        layers.append(dict(us_[0]["row"], name=name, variant=variant, us=round(us, 2), launches=n_launch,
                            cold_us=round(us_cold, 2),
                            tops=round(ops / us / 1e6, 1), gbs=round(byts / us / 1e3, 1),
                            bound=bound, roof_us=round(t_roof, 2), frac=round(t_roof / us, 3)))
-        v = by_variant.setdefault(variant, dict(ops=0.0, us=0.0, bytes=0.0, launches=0))
-        v["ops"] += ops * n_launch; v["us"] += us * n_launch; v["bytes"] += byts * n_launch
-        v["launches"] += n_launch
+        for u in us_:
+            v = by_variant.setdefault(u["variant"], dict(ops=0.0, us=0.0, bytes=0.0, launches=0))
+            v["ops"] += u["ops"]; v["us"] += u["us"]; v["bytes"] += u["bytes"]; v["launches"] += 1
         tot_ops += ops * n_launch; tot_us += us * n_launch; tot_bytes += byts * n_launch
         roof_us += t_roof * n_launch
         tot_cold += us_cold * n_launch
@@ -441,7 +544,7 @@ def main():
         log("{name:22s} {mode}-pool {R}x{R}/{stride} H={H:<3d} C={C:<4d} {us:8.2f} us {gbs:7.1f} GB/s x{launches}"
             .format(**Hh))
     for L in layers:
-        log("{name:22s} C={C:<4d} K={K:<4d} {R}x{S}/{stride} H={H:<3d} {variant:30s} {us:8.2f} us "
+        log("{name:22s} C={C:<4d} K={K:<4d} {R}x{S}/{stride} H={H:<3d} {variant:30s} {us:8.2f} us x{launches} "
             "(cold {cold_us:7.2f}) {tops:7.1f} TOP/s {gbs:7.1f} GB/s  {bound:4s} roof {roof_us:6.2f} us frac {frac:.3f}"
             .format(**L))
     dom_name, dom = max(by_variant.items(), key=lambda kv: kv[1]["us"])
@@ -451,7 +554,7 @@ def main():
     agg_tops = tot_ops / tot_us / 1e6
     log(f"conv kernels: sum {tot_us:.1f} us per pass, {agg_tops:.1f} TOP/s aggregate "
         f"({100 * agg_tops / PEAK_INT8_TOPS:.1f}% of int8 MFMA peak), "
-        f"roofline sum {roof_us:.1f} us; quantize {med[0]:.1f} us; dequantize {med[-1]:.1f} us; "
+        f"roofline sum {roof_us:.1f} us; "
         f"graph step {ms_per_step * 1e3:.1f} us")
 
     # the kernel with the largest share of the step; its launches together decide which
