@@ -12,7 +12,7 @@
 // images 692 -> 645 us, 16 354 -> 320, 13 unsigned 428 -> 400, 4 296 -> 267.
 //
 // What bounds it, in clocks of a strip of four rows of 14 pixels (two pixel tiles a wavefront): 4400 until the
-// first operands are there; layer A 10100 and B 12900, the filters at 45 bytes a clock into LDS (matrix
+// first operands are there; layer A 10100 and B 12900, filters and input at 34 and 46 bytes a clock into LDS (matrix
 // instructions 6300 and 9500); the tails of A and B 5600; layer C 11500, vector instructions of its
 // tail (a matrix and a vector instruction of one wavefront hardly overlap, those of two do, so rounds stay
 // a block of the one and then of the other).

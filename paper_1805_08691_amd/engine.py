@@ -798,9 +798,10 @@ class Engine:
         """Bottleneck blocks that the library estimates shorter as one launch on ``n`` images: {index of the last
         layer: (1x1, 3x3)}.  ``levels``: counting what the first layer would share with its level's
         other layers; None (several pipelines, where launches of the others fill what a launch
-        leaves idle): the three layers by themselves (ResNet-50 at 160 pixels, 44 images 386 us, counted 391).  Only the block itself reads its inner tensors, and nothing behind its first
-        layer writes over what it reads or writes: it can then run where its last layer has its place.  A
-        layer belongs to one block (the first where one's last layer could begin another)."""
+        leaves idle): the three layers by themselves (ResNet-50 at 160 pixels, 44 images 386 us, counted 391).
+        Only the block itself reads its inner tensors, and nothing behind its first layer writes over what it
+        reads or writes: it can then run where its last layer has its place.  A layer belongs to one block
+        (the first where one's last layer could begin another)."""
         at = {o.dst: i for i, o in enumerate(ops)}
         found, taken = {}, set()
         for i, c in enumerate(ops):
@@ -840,14 +841,15 @@ class Engine:
         """Concurrent pipelines hide one launch's latency and tail behind the other's work, and cost
         a second set of launches (in a recorded graph also a dependency per launch): worth it
         where the layers' time on the whole batch is well above the latencies of the layers and of the
-        levels they form (at least a launch each).  Measured (us with one and with two): ResNet-50 16 images
-        357 / 374, 19: 392 / 387, 20: 390 / 395, 24: 468 / 437; Inception-v3 17 images 553 / 574, 18: 610 /
-        545, at 235 pixels 30 images 570 / 579, 32: 597 / 559; the detector 2 images 286 / 288, 4: 359 /
-        350, 5: 392 / 401, 6: 484 / 442.  Layers with unsigned codes or per-channel scales cannot
-        share a launch, so a level counts as its layers: ResNet-50 20 images 424 / 432 and 430 / 434, 21: 463 /
-        466 and 478 / 462, 22: 492 / 470 and 500 / 482; at 160 pixels 40 images 423 / 451 and 438 / 452, 48:
-        517 / 494 and 518 / 502."""
-        if self.N < 4:           # (unequal parts: the detector 3 images 291 / 330 us at 286 pixels)
+        levels they form (at least a launch each).  Measured (us with one and with two; the rule was fitted
+        before bottleneck blocks were one launch and counts their layers as three): ResNet-50 16 images
+        320 / 334, 19: 357 / 357, 21: 367 / 379, 22: 387 / 382, 24: 406 / 409, 28: 477 / 459; Inception-v3 17
+        images 553 / 555, 18: 593 / 549, at 235 pixels 28 images 561 / 565, 32: 569 / 560; the detector 2 images
+        264 / 272, 4: 361 / 340, 5: 395 / 396, 6: 471 / 430.  Layers with unsigned codes or per-channel scales
+        cannot share a launch, so a level counts as its layers: ResNet-50 16 images 341 / 361 and 344 / 361, 20:
+        406 / 398 and 404 / 392, 22: 448 / 428 and 446 / 420; at 160 pixels 40 images 406 / 397 and 407 / 391,
+        48: 480 / 446 and 487 / 453."""
+        if self.N < 4:           # (unequal parts: the detector 3 images 291 / 330 us at 286 pixels, 336 / 326 at 300)
             return False
         us, depth = 0.0, {}
         for o in ops:
