@@ -462,7 +462,8 @@ def test_bottleneck_blocks_that_one_launch_takes():
               dict(o1_y=taken[0].y), dict(o2_y=taken[1].y + 64), dict(o0_y=taken[0].w), dict(o2_residual=taken[0].y),
               dict(o1_dil_h=2, o1_pad_h=2), dict(o1_pad_w=0), dict(o1_stride_h=2), dict(o2_pad_h=1), dict(o0_R=3, o0_pad_h=1),
               dict(o0_residual=taken[0].x, o0_q_res=0.1), dict(o2_out_c_stride=260), dict(o2_out_c_stride=264, o2_out_c_off=8),
-              dict(o2_flags=B.OPF_DEQUANT, o2_y_f32=None), dict(o0_flags=B.OPF_OUT_U8), dict(o1_kind=B.OP_POOL),
+              dict(o2_flags=B.OPF_DEQUANT, o2_y_f32=None), dict(o2_flags=B.OPF_DEQUANT, o2_y_f32=1 << 46),
+              dict(o0_flags=B.OPF_REAL, o0_y_f32=1 << 46), dict(o0_flags=B.OPF_OUT_U8), dict(o1_kind=B.OP_POOL),
               dict(mid=32, C=64, K2=64), dict(mid=64, K2=96), dict(C=48), dict(H=86), dict(mid=256, C=1024, H=14, N=1, K2=1024)]
     for change in single:
         assert name(_block(**change)) == "single launches", change
@@ -528,7 +529,9 @@ def test_maxima_that_join_their_layer():
         for change in (dict(o1_R=3), dict(o1_S=1), dict(o1_stride=1), dict(o1_pad=1), dict(o1_Ho=76), dict(o1_C=48), dict(o1_H=148),
                        dict(o1_x=1 << 40), dict(o1_y=1 << 40), dict(o1_y=(1 << 40) + (1 << 33)), dict(o1_y=None),
                        dict(o1_y=(1 << 40) + (3 << 33) + 1024), dict(o1_y=(1 << 45) + 8), dict(o0_out_c_stride=128),
-                       dict(o0_out_c_stride=128, o0_out_c_off=64), dict(o0_flags=B.OPF_OUT_U8), dict(o0_flags=B.OPF_DEQUANT),
+                       dict(o0_out_c_stride=128, o0_out_c_off=64), dict(o0_flags=B.OPF_OUT_U8),
+                       dict(o0_flags=B.OPF_DEQUANT, o0_y_f32=1 << 46), dict(o0_flags=B.OPF_REAL, o0_y_f32=1 << 46),
+                       dict(o0_residual=1 << 46, o0_q_res=0.1), dict(o0_flags=B.OPF_PER_CHANNEL, o0_aux=1 << 46),
                        dict(o0_q_out=-1.0), dict(o1_kind=B.OP_QUANTIZE)):
             assert joined(_layer_and_maximum(kind=kind, **change), 64) == -1, change
     for change in (dict(o1_mode=1), dict(o1_q_x=0.2), dict(o1_q_x=float("nan"), o1_q_out=float("nan")),
