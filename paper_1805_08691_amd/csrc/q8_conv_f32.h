@@ -63,8 +63,12 @@ __device__ __forceinline__ void observe_block(const F32Params& p, float m_sum, f
 }  // namespace
 
 // The tiled kernel on LDS (q8_conv_f32_lds.hip).
-int pick_f32_lds(long M, int K, int rsc);
+int pick_f32_lds(long M, int K, int rsc, float* us);    // us: its estimate
 int launch_f32_lds(int build, F32Params& p, hipStream_t stream);
 const char* f32_lds_name(int build);
+// The tiled kernel on the bf16 matrix instructions (q8_conv_f32_split.hip).
+bool f32_split_pays(long M, int K, int rsc, float lds_us);
+int launch_f32_split(F32Params& p, hipStream_t stream);
+const char* f32_split_name(long M, int K);
 
 }  // namespace q8

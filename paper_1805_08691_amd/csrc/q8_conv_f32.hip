@@ -453,8 +453,11 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.M = (int)M; p.rsc = d->R * d->S * d->C;
   p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
   p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
-  if (f32_lds_takes(d, per_img, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16))
-    return launch_f32_lds(pick_f32_lds(M, d->K, p.rsc), p, stream);
+  if (f32_lds_takes(d, per_img, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16)) {
+    float us;
+    const int build = pick_f32_lds(M, d->K, p.rsc, &us);
+    return f32_split_pays(M, d->K, p.rsc, us) ? launch_f32_split(p, stream) : launch_f32_lds(build, p, stream);
+  }
   return kF32Builds[pick_f32(M, d->K)].launch(p, stream);
 }
 
@@ -501,8 +504,11 @@ const char* q8_conv_f32_variant(const q8_conv_desc* d) {
   if (!q8::f32_desc_sane(d)) return "unsupported";
   const long per_img = (long)q8_conv_out_h(d) * q8_conv_out_w(d), M = d->N * per_img;
   if (M > 0 && !q8::f32_tiled(d, M, per_img)) return "conv_f32_any_kernel";
-  if (M > 0 && q8::f32_lds_takes(d, per_img, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off))
-    return q8::f32_lds_name(q8::pick_f32_lds(M, d->K, d->R * d->S * d->C));
+  if (M > 0 && q8::f32_lds_takes(d, per_img, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off)) {
+    float us;
+    const int rsc = d->R * d->S * d->C, build = q8::pick_f32_lds(M, d->K, rsc, &us);
+    return q8::f32_split_pays(M, d->K, rsc, us) ? q8::f32_split_name(M, d->K) : q8::f32_lds_name(build);
+  }
   const q8::F32Build& b = q8::kF32Builds[q8::pick_f32(M, d->K)];
   return b.name[d->C % (16 * b.nc) == 0 ? 2 : d->C % 4 == 0 ? 1 : 0];
 }

@@ -340,7 +340,7 @@ constexpr int kNumF32Lds = sizeof(kF32LdsBuilds) / sizeof(kF32LdsBuilds[0]);
 // that the busiest CU gets (256 operations a clock at 2.4 GHz; 91 % of that are reached) and 0.6 us
 // for each tile's own prologue and tail.  Fitted to ResNet-50's layers at batch 8 (deeper rings change
 // nothing; two groups on 64 x 64 tiles, and 32 x 32 by two, are nowhere the best by more than 2 %).
-int pick_f32_lds(long M, int K, int rsc) {
+int pick_f32_lds(long M, int K, int rsc, float* us_out) {
   int best = 0;
   float least = 0.0f;
   for (int v = 0; v < kNumF32Lds; ++v) {
@@ -350,6 +350,7 @@ int pick_f32_lds(long M, int K, int rsc) {
     const float us = 4.5f + (n < 8.0f ? ceilf(n) : n) * tile * (b.bp * b.bc == 1024 ? 1.05f : 1.0f) + 0.6f * n;
     if (v == 0 || us < least) { best = v; least = us; }
   }
+  *us_out = least;
   return best;
 }
 int launch_f32_lds(int build, F32Params& p, hipStream_t stream) {

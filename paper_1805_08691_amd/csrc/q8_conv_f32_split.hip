@@ -1,0 +1,369 @@
+// fp32 convolution of calibration on the bf16 matrix instructions: C % 32 == 0, K % 64 == 0, aligned rows.
+//
+// v_mfma_f32_32x32x16_bf16 does 16 times the products per clock that the fp32 instruction does, and its
+// products and sums are fp32.  A value of 24 significant bits is exactly the sum of three bf16 values h + m + l, each
+// rounded to nearest (|m| <= 2^-9 |x|, |l| <= 2^-18 |x|), and of the nine products of two such sums six are taken: hh,
+// hm + mh, hl + lh, mm.  What is left out is below 2^-26 of a product, an eighth of an fp32 product's own rounding
+// error.  hh goes into one accumulator (one rounding for 16 products, where the fp32 instruction has
+// eight), the other five into a second one of 2^-8 of its size.
+//
+// Against 64 bits the result is half as far off as the fp32 builds' (2-norms: 14 x 14 x 256 3x3 1.1e-7 and
+// 2.2e-7, 7 x 7 x 512 3x3 1.5e-7 and 3.0e-7; over the 106 layers of the package's networks nowhere further off).
+//
+// What bounds it: splitting, 11 vector instructions for two values, behind the LDS reads.  A wavefront issues one of them in
+// 8 clocks, two on a SIMD one in 4.3 (subtractions 2.5); four of them behind an MFMA of 35 clocks are free, eight cost
+// 9.  So a wavefront has four MFMA tiles, for which it splits four fragments, and two wavefronts share a SIMD.
+// (v_dot2_f32_bf16 would subtract without unpacking, but runs on the matrix pipe.  One or two tiles a wavefront are
+// 10 to 40 % slower on large layers; 128 x 128 tiles of four wavefronts, where each fragment is split twice too, 5 %
+// faster there, but with one chain per value further off than the fp32 builds.)  Where tiles are few the operands'
+// way into LDS bounds the layer instead, and the fp32 builds with their smaller tiles stay (f32_split_pays).  Batch 8,
+// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 385 and 318, 38 x 38 512 -> 512 3x3 433 and 323 (107 % of
+// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 200 and 153, 28 x 28 128 -> 128 24.8 and 19.8.
+//
+// The split is exact for zero and for 2^-110 <= |x| < 3.38e38.  Results that are not finite, or below 2^-90
+// and not zero, are therefore summed again in fp32: infinities, NaNs and values that bf16 rounds to infinity
+// give what the fp32 sum gives.
+#include "q8_conv_f32.h"
+#include "q8_conv_ring_kernel.h"
+
+namespace q8 {
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kSplitStep = 64;       // bytes of a row per reduction step
+constexpr int kSplitStages = 2;      // steps of a wavefront's ring
+
+struct Split3 { v8bf h, m, l; };
+
+__device__ __forceinline__ Split3 split3(v4f lo, v4f hi) {
+  v4u h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = e < 2 ? lo[2 * e] : hi[2 * e - 4], b = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
+    const unsigned ph = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{a, b}, v2bf));
+    const float ra = a - __uint_as_float(ph << 16), rb = b - __uint_as_float(ph & 0xffff0000u);
+    const unsigned pm = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{ra, rb}, v2bf));
+    const float sa = ra - __uint_as_float(pm << 16), sb = rb - __uint_as_float(pm & 0xffff0000u);
+    h[e] = ph;
+    m[e] = pm;
+    l[e] = __builtin_bit_cast(unsigned, __builtin_convertvector(v2f{sa, sb}, v2bf));
+  }
+  return {__builtin_bit_cast(v8bf, h), __builtin_bit_cast(v8bf, m), __builtin_bit_cast(v8bf, l)};
+}
+
+// One output value's sum in fp32.
+__device__ __forceinline__ float f32_sum(const F32Params& p, int pix, int k) {
+  const int n = fast_div(pix, p.by_img.m, p.by_img.s), rem = pix - n * (p.Ho * p.Wo);
+  const int ho = fast_div(rem, p.by_row.m, p.by_row.s), wo = rem - ho * p.Wo;
+  float v = 0.0f;
+  for (int r = 0; r < p.R; ++r) {
+    const int hi = ho * p.sh - p.ph + r * p.dh;
+    if (hi < 0 || hi >= p.H) continue;
+    for (int s = 0; s < p.S; ++s) {
+      const int wi = wo * p.sw - p.pw + s * p.dw;
+      if (wi < 0 || wi >= p.W) continue;
+      const float* x = p.x + (((size_t)n * p.H + hi) * p.W + wi) * p.C;
+      const float* w = p.w + ((size_t)k * p.R * p.S + r * p.S + s) * p.C;
+      for (int c = 0; c < p.C; ++c) v = fmaf(x[c], w[c], v);
+    }
+  }
+  return v;
+}
+
+// A worwave owns 64 pixels x 64 channels.  Its KW wavefronts take equal runs of the reduction steps, each with a ring of
+// two steps and all four 32 x 32 tiles, and add their sums through LDS in a fixed order; they do not meet before.
+template <int KW>
+__global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Params p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int ST = kSplitStages, T = 2, B = T * 32, BK = kSplitStep, LOADS = B / 16;    // (loads of either operand)
+  constexpr int A_BYTES = B * BK, STAGE_BYTES = 2 * B * BK;
+  constexpr int QUADS = T * T * 4, OWN = QUADS / KW;        // groups of 4 channels of a lane; those that it finishes
+  static_assert(QUADS % KW == 0, "the wavefronts finish equal parts");
+  extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
+  const int nblk = p.n_ptiles * p.n_ctiles;
+  int bid = blockIdx.x;
+  {   // every XCD takes a contiguous run of tiles, channel tile fastest (shared activations)
+    const int xcd = bid % kNumXcd, idx = bid / kNumXcd, base = nblk / kNumXcd, rem = nblk % kNumXcd;
+    bid = xcd * base + (xcd < rem ? xcd : rem) + idx;
+  }
+  const int ptile = bid / p.n_ctiles, ctile = bid - ptile * p.n_ctiles;
+  const int pix0 = ptile * B, ch0 = ctile * B;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  // The descriptor starts at the tile's first image, less the first padding rows (see conv_f32_lds_kernel).
+  const int c_bytes = p.C * 4, x_shift = (p.ph * p.W + p.pw) * c_bytes;
+  const int n0 = fast_div(pix0, p.by_img.m, p.by_img.s);
+  const long img = (long)p.H * p.W * p.C;
+  const long x_left = ((long)p.N - n0) * img * 4 + x_shift;
+  const int8_t* const x_base = reinterpret_cast<const int8_t*>(p.x + n0 * img) - x_shift;
+  const int x_bytes = (int)(x_left < 0x7fffffffL ? x_left : 0x7fffffffL), w_bytes = p.K * p.rsc * 4;
+
+  // ---- loader: lane l of a load fills row l / 4, slot l % 4 (swizzled)
+  const int lrow = lane >> 2;
+  int a_off[LOADS], b_hi[LOADS], b_wi[LOADS], b_off[LOADS];
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) {
+    const int row = j * 16 + lrow;
+    const int c = ch0 + (row & ~31) + row_to_channel(row & 31);
+    a_off[j] = c < p.K ? c * p.rsc * 4 + swz<4>(row, lane & 3) * 16 : kOobOffset;
+  }
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) {
+    const int row = j * 16 + lrow, px = pix0 + row;
+    b_hi[j] = -(1 << 29);                // a pixel beyond M: every tap outside the image
+    b_wi[j] = b_off[j] = 0;
+    if (px < p.M) {
+      const int n = fast_div(px, p.by_img.m, p.by_img.s);
+      const int rem = px - n * (p.Ho * p.Wo);
+      const int ho = fast_div(rem, p.by_row.m, p.by_row.s);
+      b_hi[j] = ho * p.sh - p.ph;
+      b_wi[j] = (rem - ho * p.Wo) * p.sw - p.pw;
+      b_off[j] = (((n - n0) * p.H + b_hi[j]) * p.W + b_wi[j]) * c_bytes + x_shift + swz<4>(row, lane & 3) * 16;
+    }
+  }
+  int8_t* const ring = lds + wave * ST * STAGE_BYTES;
+  // this group's steps, and where the next one to request lies in the reduction
+  const int n_st = p.rsc / (BK / 4), n_mine = (n_st + KW - 1) / KW;
+  int st = wave * n_mine;
+  const int st_end = min(st + n_mine, n_st);
+  const int dw_step = p.dw * c_bytes, dh_step = p.dh * p.W * c_bytes - p.S * dw_step;
+  int tap = fast_div(st * (BK / 4), p.by_c.m, p.by_c.s), tap_c = st * BK - tap * c_bytes;
+  int tap_r = fast_div(tap, p.by_s.m, p.by_s.s), tap_s = tap - tap_r * p.S;
+  int tap_delta = (tap_r * p.dh * p.W + tap_s * p.dw) * c_bytes;
+  int b_voff[LOADS];
+  auto refresh_tap = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+      const bool in = ((unsigned)(b_hi[j] + tap_r * p.dh) < (unsigned)p.H) &
+                      ((unsigned)(b_wi[j] + tap_s * p.dw) < (unsigned)p.W);
+      b_voff[j] = in ? b_off[j] : kOobOffset;
+    }
+  };
+  refresh_tap();
+  // The loads of the next step into `buf`.  Behind the group's last step the descriptors are empty: zeros, so that
+  // every step counts the same loads.
+  auto request = [&](int buf) __attribute__((always_inline)) {
+    int8_t* const stage = ring + buf * STAGE_BYTES;
+    const bool any = st < st_end;
+    const __amdgpu_buffer_rsrc_t rsrc_w =
+        __builtin_amdgcn_make_buffer_rsrc((void*)p.w, 0, any ? w_bytes : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_x =
+        __builtin_amdgcn_make_buffer_rsrc((void*)x_base, 0, any ? x_bytes : 0, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc_w, (__attribute__((address_space(3))) void*)(stage + j * 1024), 16, a_off[j],
+          any ? st * BK : 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc_x, (__attribute__((address_space(3))) void*)(stage + A_BYTES + j * 1024), 16,
+          b_voff[j], any ? tap_delta + tap_c : 0, 0, 0);
+    ++st;
+    tap_c += BK;
+    if (tap_c == c_bytes) {
+      tap_c = 0;
+      ++tap_s;
+      tap_delta += dw_step;
+      if (tap_s == p.S) {
+        tap_s = 0;
+        ++tap_r;
+        tap_delta += dh_step;
+      }
+      refresh_tap();
+    }
+  };
+  const int frag = (lane & 31) * BK + swz<4>(lane & 31, lane >> 5) * 16;
+  int a_frag[2], b_frag[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    a_frag[h] = wave * ST * STAGE_BYTES + (frag ^ (h * 32));
+    b_frag[h] = wave * ST * STAGE_BYTES + ((A_BYTES + frag) ^ (h * 32));
+    asm volatile("" : "+v"(a_frag[h]));    // in registers: the reads then add an immediate
+    asm volatile("" : "+v"(b_frag[h]));
+  }
+  v16f acc[T][T], low[T][T];
+#pragma unroll
+  for (int j = 0; j < T; ++j)
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][i][e] = low[j][i][e] = 0.0f;
+  v4f af[T][2], bf[T][2];
+  auto read = [&](int off) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) af[i][h] = *reinterpret_cast<const v4f*>(lds + a_frag[h] + off + i * 32 * BK);
+#pragma unroll
+      for (int j = 0; j < T; ++j) bf[j][h] = *reinterpret_cast<const v4f*>(lds + b_frag[h] + off + j * 32 * BK);
+    }
+  };
+  auto meet = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // the fragments this wavefront has asked for are in registers
+    asm volatile("" ::: "memory");
+  };
+#pragma unroll
+  for (int i = 0; i < ST; ++i) request(i);
+  wait_vmcnt<(ST - 1) * 2 * LOADS>();
+  meet();
+  read(0);
+  using std::integral_constant;
+  // One step: its values are in registers or on their way.  Then its buffer is filled again, and the next step's values
+  // are read while the last MFMAs run.  Fragments are split beside the MFMAs that do not need them yet: 1.5 % off.
+  auto step = [&](auto buf_c) __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf_c)::value;
+    wait_vmcnt<(ST - 2) * 2 * LOADS>();
+    meet();
+    Split3 a[T], b[T];
+    auto mma = [&](int i, int j, int t) __attribute__((always_inline)) {     // product t of tile (i, j)
+      v16f& sum = t == 2 ? acc[j][i] : low[j][i];
+      const v8bf& u = t == 0 || t == 4 ? a[i].m : t == 1 ? a[i].l : a[i].h;
+      const v8bf& v = t == 0 || t == 5 ? b[j].m : t == 3 ? b[j].l : b[j].h;
+      sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u, v, sum, 0, 0, 0);
+    };
+    a[0] = split3(af[0][0], af[0][1]);
+    b[0] = split3(bf[0][0], bf[0][1]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) mma(0, 0, t);
+    a[1] = split3(af[1][0], af[1][1]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) mma(1, 0, t);
+    b[1] = split3(bf[1][0], bf[1][1]);
+    __builtin_amdgcn_sched_barrier(0);
+    request(BUF);
+    read((BUF + 1) % ST * STAGE_BYTES);
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int i = 0; i < T; ++i) mma(i, 1, t);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto pass = [&](auto self, int n, auto buf_c) __attribute__((always_inline)) -> void {
+    constexpr int BUF = decltype(buf_c)::value;
+    if constexpr (BUF < ST) {
+      if (BUF < n) {
+        step(buf_c);
+        self(self, n, integral_constant<int, BUF + 1>{});
+      }
+    }
+  };
+  int left = n_mine;
+  for (; left >= ST; left -= ST) pass(pass, ST, integral_constant<int, 0>{});
+  pass(pass, left, integral_constant<int, 0>{});
+  wait_vmcnt<0>();                       // (the loads of steps behind the last: LDS is used again)
+
+  // ---- the tail: quad q of a lane is channels 4 (q % 4) .. of its 16 in channel tile q / 4 % T, pixel tile q / 4 / T
+  __syncthreads();
+  float* const xch = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int q = 0; q < QUADS; ++q) {
+    v4f v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[e] = acc[q / 4 / T][q / 4 % T][4 * (q % 4) + e] + low[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
+    *reinterpret_cast<v4f*>(xch + ((wave * QUADS + q) * 64 + lane) * 4) = v;
+  }
+  __syncthreads();
+  v4f own[OWN];
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
+    own[o] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int g = 0; g < KW; ++g)
+      own[o] += *reinterpret_cast<const v4f*>(xch + ((g * QUADS + wave * OWN + o) * 64 + lane) * 4);
+  }
+  auto pixel_of = [&](int o) { return pix0 + (wave * OWN + o) / 4 / T * 32 + (lane & 31); };
+  auto channel_of = [&](int o) {
+    const int q = wave * OWN + o;
+    return ch0 + q / 4 % T * 32 + 16 * (lane >> 5) + 4 * (q % 4);
+  };
+  // what the split cannot vouch for, again in fp32
+  bool refine = false;
+#pragma unroll
+  for (int o = 0; o < OWN; ++o)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = fabsf(own[o][e]);
+      refine |= !(a < INFINITY && (a >= 0x1p-90f || a == 0.0f));
+    }
+  if (refine) {
+    for (int i = 0; i < OWN * 4; ++i) {
+      const int pix = pixel_of(i / 4), k = channel_of(i / 4) + i % 4;
+      if (pix >= p.M || k >= p.K) continue;
+      const float v = f32_sum(p, pix, k);
+#pragma unroll
+      for (int o = 0; o < OWN; ++o)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) own[o][e] = i == o * 4 + e ? v : own[o][e];
+    }
+  }
+  float m_sum = 0.0f, m_out = 0.0f;
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
+    const int pix = pixel_of(o), ch = channel_of(o);
+    if (pix >= p.M || ch >= p.K) continue;         // (K % 16 == 0: all of a quad's channels or none)
+    v4f v = own[o];
+    if (p.b) v += *reinterpret_cast<const v4f*>(p.b + ch);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m_sum = fmaxf(m_sum, fabsf(v[e]));
+    if (p.res) v += *reinterpret_cast<const v4f*>(p.res + (size_t)pix * p.K + ch);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (p.relu) v[e] = fmaxf(v[e], 0.0f);
+      m_out = fmaxf(m_out, fabsf(v[e]));
+    }
+    *reinterpret_cast<v4f*>(p.y + (size_t)pix * p.out_cs + p.out_off + ch) = v;
+  }
+  __syncthreads();
+  observe_block<KW>(p, m_sum, m_out, reinterpret_cast<float*>(lds));
+#endif
+}
+
+template <int KW>
+int launch_split(F32Params& p, hipStream_t stream) {
+  constexpr int kLdsBytes = KW * kSplitStages * 2 * 64 * kSplitStep;
+  static_assert(kLdsBytes >= KW * 4 * 4096, "the exchange fits the rings");
+  p.n_ptiles = (p.M + 63) / 64;
+  p.n_ctiles = (p.K + 63) / 64;
+  const long nblk = (long)p.n_ptiles * p.n_ctiles;
+  if (nblk > 0x7fffffffL) return Q8_EUNSUPPORTED;
+  auto kernel = conv_f32_split_kernel<KW>;
+  if constexpr (kLdsBytes > 65536) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (attr != hipSuccess) return Q8_EHIP;
+  }
+  hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(KW * 64), kLdsBytes, stream, p);
+  return q8_launch_status();
+}
+
+}  // namespace
+
+// Whether the layer is faster here than with the builds of q8_conv_f32_lds.hip, by their estimate (which is
+// low, by up to a quarter: hence the 1.1) and one fitted to the layers of the package's networks at 1, 3 and 8 images.
+// n: 64 x 64 tiles per CU.  Up to one eight wavefronts share a tile; two workgroups of four wavefronts fit a CU.
+// Of 106 layers none is slower by it; those that change take 0.74 to 0.97 of their time.  K % 64: tiles are full.
+bool f32_split_pays(long M, int K, int rsc, float lds_us) {
+  if (K % 64) return false;
+  const float n = (float)((M + 63) / 64) * (float)(K / 64) / 256.0f;
+  const float step = n <= 1.0f ? 0.139f : n <= 2.0f ? 0.29f : fmaxf(0.49f, 0.182f * n);
+  return (n <= 1.0f ? 7.0f : 9.0f) + 1.1f * n + step * (float)(rsc / 16) < 1.1f * lds_us;
+}
+int launch_f32_split(F32Params& p, hipStream_t stream) {
+  const long tiles = (p.M + 63L) / 64 * ((p.K + 63) / 64);
+  return tiles <= 256 ? launch_split<8>(p, stream) : launch_split<4>(p, stream);
+}
+const char* f32_split_name(long M, int K) {
+  return (M + 63) / 64 * ((K + 63) / 64) <= 256 ? "conv_f32_split_kernel<8>" : "conv_f32_split_kernel<4>";
+}
+
+}  // namespace q8

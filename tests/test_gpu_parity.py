@@ -1941,6 +1941,67 @@ def test_conv_f32_lds_builds(B, build, geom, res, slice_):
     assert np.all(abs(ref - want) <= bound)
 
 
+# the builds on the bf16 matrix instructions: tails in pixels, a step count that the wavefronts do not divide, stride,
+# row and column filters, slices, residuals, several images a tile
+@pytest.mark.parametrize("build,geom,res,slice_", [
+    ("8", (3, 33, 31, 64, 192, 3, 3, 1, 1), True, (0, 0)),
+    ("8", (4, 61, 67, 64, 128, 3, 3, 2, 1), False, (140, 8)),
+    ("4", (6, 65, 67, 32, 64, 5, 5, 1, 1), False, (0, 0)),
+    ("4", (7, 37, 35, 128, 320, 1, 3, 1, 1), True, (0, 0)),
+    ("4", (3, 49, 51, 1024, 192, 1, 1, 1, 1), False, (0, 0))])
+def test_conv_f32_split_builds(B, build, geom, res, slice_):
+    """Sums at least as near to 64 bits as the bound of n fp32 products and sums; what bf16 cannot hold, or
+    holds with fewer bits, as the fp32 sum gives it."""
+    N, H, W, Cc, K, R, S, st, dil = geom
+    g = torch.Generator(device="cuda").manual_seed(13)
+    rand = lambda *s: torch.randn(s, device="cuda", generator=g)
+    ph, pw = dil * (R - 1) // 2, dil * (S - 1) // 2
+    desc = B.ConvDesc(N, H, W, Cc, K, R, S, st, st, ph, pw, dil, dil, relu=int(not res), out_c_stride=slice_[0],
+                      out_c_off=slice_[1])
+    assert B.conv_f32_variant(desc) == f"conv_f32_split_kernel<{build}>"
+    x, w, b = rand(N, H, W, Cc), rand(K, R, S, Cc), rand(K)
+    r = rand(N, desc.Ho, desc.Wo, K) if res else None
+
+    def fp64(x, w):
+        x = torch.nn.functional.pad(x.double(), (0, 0, pw, pw, ph, ph))
+        y = torch.zeros(N * desc.Ho * desc.Wo, K, dtype=torch.float64, device="cuda")
+        for i in range(R):
+            for j in range(S):
+                v = x[:, i * dil:i * dil + (desc.Ho - 1) * st + 1:st, j * dil:j * dil + (desc.Wo - 1) * st + 1:st]
+                y += v.reshape(-1, Cc) @ w[:, i, j].double().t().contiguous()
+        return y.view(N, desc.Ho, desc.Wo, K)
+    pre = fp64(x, w) + b.double()
+    want = pre + r if res else pre.clamp(min=0)
+    # any order of n fp32 products and sums: |error| <= (n + 2) 2^-24 sum |x||w| (+ |b| + |r|)
+    bound = (R * S * Cc + 4) * 2.0 ** -24 * (fp64(x.abs(), w.abs()) + b.abs() + (r.abs() if res else 0))
+    spread = torch.zeros((2, 3 * B.SLOT_STRIDE), device="cuda")
+    out = torch.full((N, desc.Ho, desc.Wo, slice_[0] or K), -7.0, device="cuda")
+    B.conv_f32_observed(desc, x, w, b, r, out, spread[0], spread[1], 3)
+    lo = slice_[1]
+    got = out[..., lo:lo + K]
+    assert bool(((got - want).abs() <= bound).all())
+    assert bool((out[..., :lo] == -7).all()) and bool((out[..., lo + K:] == -7).all())
+    m = host(B.calibrate_fold(spread, torch.empty(2, device="cuda")))
+    assert m[1] == float(got.abs().max()) and abs(m[0] - float(pre.abs().max())) <= float(bound.max())
+    if slice_ != (0, 0):
+        return
+    # the 2-norm of the error: six rounded products of bf16 pieces and their sums stay within that of fp32's, about
+    # sqrt(n) roundings of 2^-25 on values whose squares add up to the result's
+    assert float((got - want).norm()) <= (R * S * Cc) ** 0.5 * 2.0 ** -25 * float(pre.norm())
+    plain = desc
+    plain.relu = 0
+    huge = x.clone()
+    huge[0, 0, 0, 1], huge[0, 5, 6, 3], huge[N - 1, H - 1, W - 1, 0] = 3.4e38, -torch.inf, torch.nan
+    for xs, ws in ((huge, w * 2.0 ** -12), (x * 2.0 ** -100, w * 2.0 ** -20)):
+        got = B.conv_f32_ref(plain, xs, ws)
+        want = fp64(xs, ws).float()
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+        fine = want.isfinite()
+        err = ((got.double() - fp64(xs, ws)).abs()[fine] <= (R * S * Cc + 4) * 2.0 ** -24 *
+               fp64(xs.abs(), ws.abs())[fine] + 2.0 ** -149 * (R * S * Cc + 1))
+        assert bool(err.all())
+
+
 @pytest.mark.parametrize("channels", [(64, 64), (12, 8)])       # a build on LDS, a register-fed one
 def test_conv_f32_observed_raises_the_first_value_of_a_slot(B, channels):
     """A slot of any length holds one maximum, in its first value, unless copies are asked for."""
