@@ -19,6 +19,8 @@ using q8::quant1_fast;
 
 constexpr int kThreads = 256;
 constexpr int kMaxBlocks = 256 * 8;   // 256 CUs x 8 resident blocks
+constexpr int kInFlight = 8;          // 16-byte vectors of a lane per chunk
+constexpr size_t kCachedBytes = (size_t)1 << 28;      // the memory-side cache
 
 inline int blocks_for(size_t work_items) {
   size_t b = (work_items + kThreads - 1) / kThreads;
@@ -28,20 +30,23 @@ inline int blocks_for(size_t work_items) {
 }
 
 // ---------------------------------------------------------------- max-abs ----------
-// One running maximum per tensor.  Every block owns one contiguous run of 16-byte vectors
-// and walks it with sixteen independent non-temporal loads in flight per lane (measured on
-// 205 MB and on 1 GiB: 7.0 TB/s this way against 5.3 - 6.3 TB/s when all blocks sweep the
-// tensor together in grid-sized strides); a wavefront folds with lane shuffles, the four
+// One running maximum per tensor.  A block takes chunks of eight 16-byte vectors per lane, round robin, so
+// that what the chip reads at one time lies together: 8.2 TB/s from the memory-side cache on 26 MB (one contiguous
+// run per block with sixteen loads in flight: 10.6 us there and 2.8 so; 51 MB 13.0 and 8.6, 103 MB 20.8 and
+// 15.9, 205 MB 30.4 and 30.0).  Plain loads: what stays in that cache is what Eq. Q reads next (205 MB, both passes:
+// 75.6 -> 67.7 us).  RUNS: a tensor larger than that cache, in contiguous runs and non-temporal loads as
+// before (1 GiB: 153 us, 170 round robin).  A wavefront folds with lane shuffles, the four
 // wavefronts of a block fold through LDS, and one atomic per block updates the result.
 // |x| >= 0, so the IEEE bit pattern orders like an unsigned integer.
 typedef float f4_nt __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float abs4max(f4_nt v) {
   return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
 }
+template <bool RUNS>
 __global__ __launch_bounds__(kThreads) void maxabs_kernel(const float* __restrict__ x,
                                                           size_t n, size_t head,
                                                           unsigned* __restrict__ out) {
-  constexpr int U = 16;
+  constexpr int U = RUNS ? 16 : kInFlight;
   float m = 0.0f;
   const size_t tid = (size_t)blockIdx.x * kThreads + threadIdx.x;
   // scalar head (until 16-byte alignment) and tail
@@ -50,18 +55,32 @@ __global__ __launch_bounds__(kThreads) void maxabs_kernel(const float* __restric
   if (tid < head) m = fabsf(x[tid]);
   if (tid < n - tail0) m = fmaxf(m, fabsf(x[tail0 + tid]));
   const f4_nt* __restrict__ x4 = reinterpret_cast<const f4_nt*>(x + head);
-  const size_t per = (body + gridDim.x - 1) / gridDim.x;
-  const size_t lo = (size_t)blockIdx.x * per;
-  const size_t hi = lo + per < body ? lo + per : body;
-  size_t i = lo + threadIdx.x;
-  for (; i + (U - 1) * kThreads < hi; i += U * kThreads) {
-    f4_nt v[U];
+  if constexpr (RUNS) {
+    const size_t per = (body + gridDim.x - 1) / gridDim.x;
+    const size_t lo = (size_t)blockIdx.x * per;
+    const size_t hi = lo + per < body ? lo + per : body;
+    size_t i = lo + threadIdx.x;
+    for (; i + (U - 1) * kThreads < hi; i += U * kThreads) {
+      f4_nt v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kThreads);
+      for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(x4 + i + u * kThreads);
 #pragma unroll
-    for (int u = 0; u < U; ++u) m = fmaxf(m, abs4max(v[u]));
+      for (int u = 0; u < U; ++u) m = fmaxf(m, abs4max(v[u]));
+    }
+    for (; i < hi; i += kThreads) m = fmaxf(m, abs4max(__builtin_nontemporal_load(x4 + i)));
+  } else {
+    const size_t chunks = body / (U * kThreads);
+    for (size_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+      const size_t i = c * (U * kThreads) + threadIdx.x;
+      f4_nt v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = x4[i + u * kThreads];
+#pragma unroll
+      for (int u = 0; u < U; ++u) m = fmaxf(m, abs4max(v[u]));
+    }
+    for (size_t i = chunks * (U * kThreads) + tid; i < body; i += (size_t)gridDim.x * kThreads)
+      m = fmaxf(m, abs4max(x4[i]));
   }
-  for (; i < hi; i += kThreads) m = fmaxf(m, abs4max(__builtin_nontemporal_load(x4 + i)));
 
   for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
   __shared__ float wave_max[kThreads / 64];
@@ -79,17 +98,17 @@ __global__ __launch_bounds__(kThreads) void maxabs_kernel(const float* __restric
 }
 
 // ---------------------------------------------------------------- Q ---------------
-// Bound by memory: 4 bytes read and 1 written per value.  Like maxabs_kernel every block owns one
-// contiguous run and keeps eight 16-byte loads per lane in flight; the IEEE division of Eq. Q only
-// runs next to a tie (quant1_fast), where before it ran for every value and bounded the kernel
-// (51 M values: 66 us and 3.9 TB/s).  U8: codes 0..255 stored minus 128.  FAST = false: a factor
-// whose reciprocal is not a normal number, every value divided.
+// Bound by memory: 4 bytes read and 1 written per value.  Chunks round robin as in maxabs_kernel (one contiguous run
+// per block: 51 M values 40.4 us and 38.1 so, 6.4 M 8.4 and 4.9, 0.8 M 5.6 and 2.9; behind maxabs_kernel and with the
+// values' 205 MB written back between passes 64 us and 38).  The IEEE division of Eq. Q only runs next to a tie
+// (quant_fast), where before it ran for every value and bounded the kernel.  U8: codes 0..255 stored minus 128.
+// FAST = false: a factor whose reciprocal is not a normal number, every value divided.
 template <bool U8, bool FAST>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* __restrict__ r,
                                                             size_t n, size_t head, float q,
                                                             float lo, float hi,
                                                             int8_t* __restrict__ z) {
-  constexpr int U = 8, kSub = U8 ? 128 : 0;
+  constexpr int U = kInFlight, kSub = U8 ? 128 : 0;
   const float iq = __fdiv_rn(1.0f, q);
   auto Q = [&](float v) { return (FAST ? quant1_fast(v, q, iq, lo, hi) : quant1(v, q, lo, hi)) - kSub; };
   const size_t tid = (size_t)blockIdx.x * kThreads + threadIdx.x;
@@ -99,22 +118,26 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float* __restr
   if (tid < n - tail0) z[tail0 + tid] = (int8_t)Q(r[tail0 + tid]);
   const f4_nt* __restrict__ r4 = reinterpret_cast<const f4_nt*>(r + head);
   unsigned* __restrict__ z4 = reinterpret_cast<unsigned*>(z + head);
-  const size_t per = (body + gridDim.x - 1) / gridDim.x;
-  const size_t first = (size_t)blockIdx.x * per;
-  const size_t end = first + per < body ? first + per : body;
-  size_t i = first + threadIdx.x;
-  for (; i + (U - 1) * kThreads < end; i += U * kThreads) {
+  auto Q4 = [&](f4_nt v) {
+    if constexpr (FAST) {
+      const float x[4] = {v[0], v[1], v[2], v[3]};
+      int k[4];
+      q8::quant_fast(x, q, iq, lo, hi, k);
+      return pack4(k[0] - kSub, k[1] - kSub, k[2] - kSub, k[3] - kSub);
+    } else {
+      return pack4(Q(v[0]), Q(v[1]), Q(v[2]), Q(v[3]));
+    }
+  };
+  const size_t chunks = body / (U * kThreads);
+  for (size_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+    const size_t i = c * (U * kThreads) + threadIdx.x;
     f4_nt v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = r4[i + u * kThreads];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      z4[i + u * kThreads] = pack4(Q(v[u][0]), Q(v[u][1]), Q(v[u][2]), Q(v[u][3]));
+    for (int u = 0; u < U; ++u) z4[i + u * kThreads] = Q4(v[u]);
   }
-  for (; i < end; i += kThreads) {
-    const f4_nt v = r4[i];
-    z4[i] = pack4(Q(v[0]), Q(v[1]), Q(v[2]), Q(v[3]));
-  }
+  for (size_t i = chunks * (U * kThreads) + tid; i < body; i += (size_t)gridDim.x * kThreads) z4[i] = Q4(r4[i]);
 }
 
 // NHWC with the channel count padded from C to Cp (Cp == 4 and C <= 4): one thread
@@ -159,13 +182,12 @@ __global__ __launch_bounds__(kThreads) void quantize_image_kernel(const float* _
     const f4_a4 a = *reinterpret_cast<const f4_a4*>(src);
     const f4_a4 b = *reinterpret_cast<const f4_a4*>(src + 4);
     const f4_a4 c = *reinterpret_cast<const f4_a4*>(src + 8);
-    const float iq = __fdiv_rn(1.0f, q);
-    auto Q = [&](float v) { return quant1_fast(v, q, iq, lo, hi); };
+    const float x[12] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3], c[0], c[1], c[2], c[3]};
+    int k[12];
+    q8::quant_fast(x, q, __fdiv_rn(1.0f, q), lo, hi, k);
     u4_a4 o;
-    o[0] = pack4(Q(a[0]), Q(a[1]), Q(a[2]), 0);
-    o[1] = pack4(Q(a[3]), Q(b[0]), Q(b[1]), 0);
-    o[2] = pack4(Q(b[2]), Q(b[3]), Q(c[0]), 0);
-    o[3] = pack4(Q(c[1]), Q(c[2]), Q(c[3]), 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = pack4(k[3 * e], k[3 * e + 1], k[3 * e + 2], 0);
     *reinterpret_cast<u4_a4*>(dst) = o;
     return;
   }
@@ -283,6 +305,12 @@ __global__ void requant_scales_kernel(float q_x, const float* __restrict__ q_w, 
 
 // Eq. D on a list of tensors in one launch (the outputs of a network): a block takes 4096 codes of
 // one tensor.  add: 128 for unsigned codes stored minus 128, else 0.
+//
+// Bound by memory: 1 byte read and 4 written per value, 6.4 to 7 TB/s.  A list whose values would fill a quarter of the
+// memory-side cache is written past it (PAST, non-temporal stores): 103 MB of values 19.9 us and 17.1, 51 MB 10.4
+// and 8.9, 205 MB 37.6 and 37.3, but max-abs, Eq. Q and this one in turn on 205 MB 134 us and 105 for the three, as
+// the next pass does not have to wait for these values to be written back.  (Who reads all of them
+// next pays 1.5 to 3 us of it back: 103 MB 36.4 and 38.2 both.)
 constexpr int kDeqBlock = 4096, kDeqMax = 16;
 struct DeqList {
   int n;
@@ -294,6 +322,7 @@ struct DeqList {
     int add, first;      // first block of the tensor
   } t[kDeqMax];
 };
+template <bool PAST>
 __global__ __launch_bounds__(kThreads) void dequantize_list_kernel(const DeqList l) {
   int k = 0;
   for (int i = 1; i < l.n; ++i) k = (int)blockIdx.x >= l.t[i].first ? i : k;
@@ -312,12 +341,11 @@ __global__ __launch_bounds__(kThreads) void dequantize_list_kernel(const DeqList
   for (int u = 0; u < kDeqBlock / (4 * kThreads); ++u) {
     const size_t i = base + ((size_t)u * kThreads + threadIdx.x) * 4;
     if (i + 4 <= n) {
-      float4 o;
-      o.x = __fmul_rn(q, (float)((int)(int8_t)(w[u] & 0xff) + add));
-      o.y = __fmul_rn(q, (float)((int)(int8_t)((w[u] >> 8) & 0xff) + add));
-      o.z = __fmul_rn(q, (float)((int)(int8_t)((w[u] >> 16) & 0xff) + add));
-      o.w = __fmul_rn(q, (float)((int)(int8_t)(w[u] >> 24) + add));
-      *reinterpret_cast<float4*>(r + i) = o;
+      f4_nt o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = __fmul_rn(q, (float)((int)(int8_t)(w[u] >> (8 * e)) + add));
+      if constexpr (PAST) __builtin_nontemporal_store(o, reinterpret_cast<f4_nt*>(r + i));
+      else *reinterpret_cast<f4_nt*>(r + i) = o;
     } else {
       for (size_t j = i; j < n && j < i + 4; ++j) r[j] = __fmul_rn(q, (float)((int)z[j] + add));
     }
@@ -330,35 +358,6 @@ __global__ __launch_bounds__(kThreads) void dequantize_u8_kernel(const int8_t* _
   const size_t nthreads = (size_t)gridDim.x * kThreads;
   for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += nthreads)
     r[i] = __fmul_rn(q, (float)((int)z[i] + 128));
-}
-
-__global__ __launch_bounds__(kThreads) void dequantize_vec_kernel(const int8_t* __restrict__ z,
-                                                                  size_t n4, float q,
-                                                                  float4* __restrict__ r) {
-  // every block owns one contiguous run of 4-code groups (see maxabs_kernel), four groups
-  // per lane in flight
-  constexpr int U = 4;
-  const unsigned* __restrict__ z4 = reinterpret_cast<const unsigned*>(z);
-  const size_t per = (n4 + gridDim.x - 1) / gridDim.x;
-  const size_t lo = (size_t)blockIdx.x * per;
-  const size_t hi = lo + per < n4 ? lo + per : n4;
-  auto one = [&](size_t i, unsigned w) {
-    float4 o;
-    o.x = __fmul_rn(q, (float)(int8_t)(w & 0xff));
-    o.y = __fmul_rn(q, (float)(int8_t)((w >> 8) & 0xff));
-    o.z = __fmul_rn(q, (float)(int8_t)((w >> 16) & 0xff));
-    o.w = __fmul_rn(q, (float)(int8_t)(w >> 24));
-    r[i] = o;
-  };
-  size_t i = lo + threadIdx.x;
-  for (; i + (U - 1) * kThreads < hi; i += U * kThreads) {
-    unsigned w[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = z4[i + u * kThreads];
-#pragma unroll
-    for (int u = 0; u < U; ++u) one(i + u * kThreads, w[u]);
-  }
-  for (; i < hi; i += kThreads) one(i, z4[i]);
 }
 
 // ---------------------------------------------------------------- Eq. BN ----------
@@ -399,7 +398,9 @@ int dequantize_list(const q8_op* ops, int n, hipStream_t stream) {
   size_t blocks = 0;
   auto flush = [&]() -> int {
     if (l.n == 0) return Q8_OK;
-    hipLaunchKernelGGL(dequantize_list_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, l);
+    const bool past = blocks * kDeqBlock >= kCachedBytes / 16;
+    hipLaunchKernelGGL((past ? dequantize_list_kernel<true> : dequantize_list_kernel<false>), dim3((unsigned)blocks),
+                       dim3(kThreads), 0, stream, l);
     l.n = 0;
     blocks = 0;
     return q8_launch_status();
@@ -460,10 +461,11 @@ int q8_calibrate_maxabs(const float* x_dev, size_t n, float* maxabs_dev, void* s
   if (n == 0) return Q8_OK;
   Q8_REQUIRE(x_dev != nullptr, Q8_EINVAL);
   Q8_REQUIRE(q8_aligned(x_dev, 4) && q8_aligned(maxabs_dev, 4), Q8_EALIGN);
-  size_t head = head_elems(x_dev, 4, n);
-  int blocks = blocks_for((n + 15) / 16);
-  hipLaunchKernelGGL(maxabs_kernel, dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, x_dev, n,
-                     head, reinterpret_cast<unsigned*>(maxabs_dev));
+  const size_t head = head_elems(x_dev, 4, n);
+  const bool runs = n > kCachedBytes / 4;
+  const int blocks = blocks_for((n + 15) / 16);
+  hipLaunchKernelGGL((runs ? maxabs_kernel<true> : maxabs_kernel<false>), dim3(blocks), dim3(kThreads), 0,
+                     (hipStream_t)stream, x_dev, n, head, reinterpret_cast<unsigned*>(maxabs_dev));
   return q8_launch_status();
 }
 
@@ -558,19 +560,9 @@ int q8_dequantize(const int8_t* z_dev, size_t n, float q, float* r_dev, void* st
   Q8_REQUIRE(z_dev != nullptr && r_dev != nullptr, Q8_EINVAL);
   Q8_REQUIRE(q8_aligned(r_dev, 4), Q8_EALIGN);
   if (deq_listable(z_dev, n, r_dev)) {
-    if (n < (size_t)kMaxBlocks * kDeqBlock) {      // below that the blocks' runs are short anyway
-      q8_op o{};
-      o.x = z_dev; o.n = n; o.q_x = q; o.y_f32 = r_dev;
-      return q8::dequantize_list(&o, 1, (hipStream_t)stream);
-    }
-    size_t n4 = n / 4;
-    if (n4)
-      hipLaunchKernelGGL(dequantize_vec_kernel, dim3(blocks_for(n4 / 2 + 1)), dim3(kThreads), 0,
-                         (hipStream_t)stream, z_dev, n4, q, reinterpret_cast<float4*>(r_dev));
-    if (n & 3)   // ragged tail: the scalar path of the generic kernel (head = all)
-      hipLaunchKernelGGL(dequantize_kernel, dim3(1), dim3(kThreads), 0, (hipStream_t)stream,
-                         z_dev + 4 * n4, n & 3, n & 3, q, r_dev + 4 * n4);
-    return q8_launch_status();
+    q8_op o{};
+    o.x = z_dev; o.n = n; o.q_x = q; o.y_f32 = r_dev;
+    return q8::dequantize_list(&o, 1, (hipStream_t)stream);
   }
   size_t mis = reinterpret_cast<uintptr_t>(z_dev) & 3;
   size_t head = mis ? 4 - mis : 0;

@@ -1941,6 +1941,32 @@ def test_conv_f32_lds_builds(B, build, geom, res, slice_):
     assert np.all(abs(ref - want) <= bound)
 
 
+# the streaming passes: chunks of 8192 values per block (a ragged last one, none at all, more than the grid has
+# blocks), addresses that are 4-byte aligned only, lists around a quarter of the cache, a tensor beyond it
+@pytest.mark.parametrize("n,shift", [(5, 0), (8191, 1), (8192, 0), (8193, 3), (24576 + 7, 2), (2048 * 8192 + 4099, 0),
+                                     (2**24 - 1, 0), (2**24 + 1, 1), (2**26 + 8195, 0)])
+def test_streaming_passes(B, n, shift):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    buf = torch.randn(n + shift, device="cuda", generator=g)
+    x, q = buf[shift:], 0.043
+    k = torch.randint(0, n, (257,), device="cuda", generator=g)
+    x[k] = (torch.randint(-140, 140, (257,), device="cuda", generator=g) + 0.5) * q       # ties and clamped codes
+    x[n // 2], x[n - 1] = torch.inf, -9.25
+    for unsigned in (False, True):
+        # the IEEE quotient (by a tensor: torch multiplies by a number's reciprocal), half to even
+        want = torch.round(x / torch.full((1,), q, device="cuda"))
+        want = want.clamp(0, 255) - 128 if unsigned else want.clamp(-128, 127)
+        z = B.quantize_u8(x, q) if unsigned else B.quantize(x, q, 7)
+        assert torch.equal(z, want.to(torch.int8))
+        r = torch.empty(n + shift, device="cuda")[shift:]
+        r = B.dequantize_u8(z, q, out=r) if unsigned else B.dequantize(z, q, out=r)
+        assert torch.equal(r, (z.float() + (128 if unsigned else 0)) * q)
+    x[n // 2] = 8.0
+    slot = torch.zeros(1, device="cuda")
+    B.calibrate_maxabs(x, slot)
+    assert float(slot) == 9.25
+
+
 # the builds on the bf16 matrix instructions: tails in pixels, a step count that the wavefronts do not divide, stride,
 # row and column filters, slices, residuals, several images a tile
 @pytest.mark.parametrize("build,geom,res,slice_", [
