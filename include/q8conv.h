@@ -406,10 +406,13 @@ int q8_joined_op(const q8_op *ops, int n_ops, void *const *streams, int n_stream
  * layers.  0 if the layer is unsupported.                                               */
 float q8_conv_estimate_us(const q8_conv_desc *d);
 
-/* Name of the kernel variant (tile shape) q8_conv_int8 picks for this geometry, as it
+/* Name of the kernel variant (tile shape) picked for this geometry, as it
  * appears in a profiler's kernel trace; "unsupported" if the call would be rejected.
  * For measurement code that groups launches by kernel.                              */
 const char *q8_conv_variant(const q8_conv_desc *d);
+/* The same for a call of q8_conv_int8: some layers of more than 10 us take another tile in a
+ * launch that has the chip to itself than in a planned step (q8_run_ops).            */
+const char *q8_conv_call_variant(const q8_conv_desc *d);
 
 /* q8_conv_int8 that also applies Eq. D to its own output in the same launch, for a layer whose
  * output leaves the quantised domain as fp32 AND is kept as codes: besides z_y it writes

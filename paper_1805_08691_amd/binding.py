@@ -32,7 +32,7 @@ EXPORTS = [
     "q8_conv_chain_workspace_bytes", "q8_conv_chain_int8",
     "q8_conv_chain_static_workspace_limit", "q8_conv_chain_int8_static",
     "q8_conv_chain_static_status",
-    "q8_conv_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
+    "q8_conv_variant", "q8_conv_call_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant",
@@ -142,6 +142,8 @@ lib.q8_quantize_u8.argtypes = [_vp, _sz, _f, _vp, _vp]
 lib.q8_dequantize_u8.argtypes = [_vp, _sz, _f, _vp, _vp]
 lib.q8_conv_variant.restype = C.c_char_p
 lib.q8_conv_variant.argtypes = [_dp]
+lib.q8_conv_call_variant.restype = C.c_char_p
+lib.q8_conv_call_variant.argtypes = [_dp]
 lib.q8_conv_num_variants.argtypes = []
 lib.q8_conv_variant_name.restype = C.c_char_p
 lib.q8_conv_variant_name.argtypes = [_i]
@@ -524,6 +526,10 @@ def conv_estimate_us(desc):
 
 def conv_variant(desc):
     return lib.q8_conv_variant(C.byref(desc)).decode()
+
+
+def conv_call_variant(desc):
+    return lib.q8_conv_call_variant(C.byref(desc)).decode()
 
 
 def conv_num_variants():

@@ -31,7 +31,7 @@ int pick_direct(long M, int K, int red_len, float* us);
 bool direct_applicable(const ConvParams& p);
 bool p3_variant_takes(int variant, const ConvParams& p);
 bool pw_variant_takes(int variant, const ConvParams& p);
-int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us);
+int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us, bool alone = false);
 int launch_stem_image(ConvParams& p, const StemImage& im, int pool, bool dry_run, hipStream_t stream);
 int first_split_variant();
 int num_split_variants();
@@ -298,14 +298,62 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
   return tiles128 <= 512 ? 11 : 1;
 }
 
+// us of a layer on one of the main kernel's larger tiles, by the workgroups per CU w and the reduction steps s:
+// base + chain s max(1, w) + tile w + round s ceil(w).  Least squares over 1050 layers of 1 to 64 images, 7 to 150
+// rows, 48 to 2048 channels and 1 to 25 taps; the errors of a build are 9 to 12 % (root of the mean square).
+struct TileCost { int variant, bp, bc; float base, chain, tile, round; };
+constexpr int kTiledCosts = 6;
+constexpr TileCost kTileCosts[2][kTiledCosts] = {          // C % 64 == 0; other channel counts
+    {{1, 128, 128, 5.20f, 0.050f, 1.314f, 0.177f}, {8, 128, 64, 4.46f, 0.150f, 0.522f, 0.044f},
+     {9, 128, 64, 4.33f, 0.073f, 0.776f, 0.086f}, {11, 128, 128, 4.72f, -0.018f, 1.605f, 0.208f},
+     {13, 256, 128, 6.16f, -0.281f, 3.105f, 0.612f}, {25, 128, 192, 6.47f, 0.077f, 1.672f, 0.206f}},
+    {{1, 128, 128, 5.15f, 0.037f, 0.810f, 0.274f}, {8, 128, 64, 4.53f, 0.144f, 0.307f, 0.099f},
+     {9, 128, 64, 4.29f, 0.035f, 0.560f, 0.172f}, {11, 128, 128, 4.26f, -0.067f, 1.280f, 0.329f},
+     {13, 256, 128, 5.19f, -0.311f, 3.300f, 0.699f}, {25, 128, 192, 6.21f, 0.083f, 1.373f, 0.285f}}};
+
+// Another tile for a layer launched by a call of its own (plain codes) that takes more than 10 us, where the estimates
+// say so clearly.  The rules of pick_tiled go by the number of 128 x 128 tiles; what a large layer takes is whole
+// rounds of tiles, and how much of a tile lies beyond K.  Among the 376 layers drawn above that the main kernel has,
+// 111 change: 0.96 to 1.6 times the speed, 1.12 on average (3x3 80 -> 192 on 71 x 71 x 64 74.6 -> 64.0 us, on 128 x
+// 192 tiles; 5x5 640 -> 128 on 86 x 85 x 6 138 -> 96 and 3x3 288 -> 80 on 116 x 113 x 24 162 -> 124, on 256 x 128).
+// Below 10 us the choice measured inside the networks stays, their filters then come from HBM.  Not in a planned
+// step, where a second pipeline's workgroups fill what a round leaves and do not fit beside the largest
+// tiles: with these there SSD300 on 64 images took 2243 us, without 2168, Inception-v3 991 and 971.
+//
+// 3x3 on 256 x 256 tiles: per round 1.85 times what 256 x 128 take, so where the rounds are fewer by more than that
+// (us, 256 x 128 and these: 512 -> 512 on 38 x 38 x 64, 5.6 and 2.8 tiles per CU, 186 and 173; 19 x 19 x 64, 1.4 and
+// 0.7, 58.8 and 52.9; 704 -> 704 on 86 x 89 x 2 80 and 71; but 38 x 38 x 32, 2.8 and 1.4, 97 and 106), from 0.55
+// tiles per CU on (256 -> 256 on 74 x 74 x 7, 0.59, 36.6 on 128 x 64 and 33.2; 512 on 19 x 19 x 12, 0.13, 22.9 and 50).
+int retile(const q8_conv_desc* d, int tiled, long M) {
+  const int first_halo = q8::num_ring_variants();
+  auto tiles = [&](long bp, long bc) { return (float)((M + bp - 1) / bp * ((d->K + bc - 1) / bc)) / 256.0f; };
+  if (tiled >= first_halo) {
+    if (tiled > first_halo + 4 || tiled == first_halo + 3) return tiled;
+    const int tail = d->K % 256;
+    const float n = tiles(256, 256);
+    const bool fits = d->W <= 127 && d->K > 128 && (tail == 0 || tail > 128);
+    return fits && n >= 0.55f && 1.85f * ceilf(n) <= ceilf(tiles(256, 128)) ? first_halo + 17 : tiled;
+  }
+  const float steps = (float)((d->R * d->S * d->C + 63) / 64);
+  float least = 1e30f, now = 0.0f;
+  int best = tiled;
+  for (const TileCost& t : kTileCosts[d->C % 64 == 0 ? 0 : 1]) {
+    const float w = tiles(t.bp, t.bc);
+    const float us = t.base + t.tile * w + steps * (t.chain * fmaxf(1.0f, w) + t.round * ceilf(w));
+    if (t.variant == tiled) now = us;
+    if (t.variant > 8 && us < least) { best = t.variant; least = us; }
+  }
+  return now > 10.0f && least < 0.93f * now ? best : tiled;
+}
+
 // Layers with few tiles: the latency family (q8_conv_direct_kernel.h) where its estimate is below
 // that of the tiled build.  The tiled estimates are fits to the same launches: a chain of reduction
 // steps fed at 28 bytes per clock and CU behind 3.6 us of launch, prologue and tail; the 3x3 family
 // by its 64-channel chunks, the 3x3 blocks by their rounds (block_tiles_us).  The pointwise family is only
 // chosen for sizes far above this.
-// ext: unsigned codes or per-channel scales (the extended builds).
+// ext: unsigned codes or per-channel scales (the extended builds); alone: a call of its own on plain codes (retile).
 int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float* est_us = nullptr,
-                 bool persistent = true) {
+                 bool persistent = true, bool alone = false) {
   const int tiled = pick_tiled(d, forced, persistent);
   if (est_us)
     *est_us = 4.0f + (float)d->N * (float)d->H * (float)d->W * (float)d->K * (float)(d->R * d->S * d->C) * 2e-9f;
@@ -337,7 +385,8 @@ int pick_variant(const q8_conv_desc* d, bool ext = false, int forced = -1, float
   const int direct = q8::pick_direct(M, d->K, red_len, &us);
   const bool take_direct = us < 0.95f * tiled_us;
   if (est_us) *est_us = take_direct ? us : tiled_us;
-  return take_direct ? q8::first_direct_variant() + direct : tiled;
+  if (take_direct) return q8::first_direct_variant() + direct;
+  return blocks || !alone ? tiled : retile(d, tiled, M);
 }
 
 }  // namespace
@@ -630,7 +679,7 @@ int conv_launch(const q8_conv_desc* d, const U8Flags& u, const int8_t* z_x, cons
     return q8::launch_pair_variant(p, s);
   }
   float us = 0.0f;
-  int variant = u.variant >= 0 ? pick_variant(d, false, u.variant) : q8::conv_choose(d, p, &us);
+  int variant = u.variant >= 0 ? pick_variant(d, false, u.variant) : q8::conv_choose(d, p, &us, true);
   p.n_split = 1;
   p.ws_counters = nullptr;
   p.ws_slabs = nullptr;
@@ -695,10 +744,11 @@ bool persistent_takes(const q8_conv_desc* d, const ConvParams& p) {
   return v < first_pw_variant() || v >= first_split_variant() || pw_variant_takes(v - first_pw_variant(), p);
 }
 // What one layer would be launched as on its own, and the estimate; launches it.
-int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us) {
+int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us, bool alone) {
   *us = 0.0f;
   const bool persistent = persistent_takes(d, p);
-  const int v = pick_variant(d, is_extended(p), -1, us, persistent);
+  const bool ext = is_extended(p);
+  const int v = pick_variant(d, ext, -1, us, persistent, alone && !ext && !p.y_f32 && !p.y_deq);
   return v >= first_direct_variant() && v < kRegBase && !direct_applicable(p) ? pick_tiled(d, -1, persistent) : v;
 }
 // Whether a layer may join a group launch of the main kernel (plain codes only).  1: its tiled choice
@@ -987,12 +1037,14 @@ float q8_conv_estimate_us(const q8_conv_desc* d) {
   return us;
 }
 
-const char* q8_conv_variant(const q8_conv_desc* d) {
+static const char* variant_name(const q8_conv_desc* d, bool alone) {
   if (!desc_sane(d) || conv_mode(d) < 0) return "unsupported";
-  const int variant = pick_variant(d);
+  const int variant = pick_variant(d, false, -1, nullptr, true, alone);
   return variant >= kRegBase ? q8::reg_variant_name(variant - kRegBase)
                              : q8::stream_variant_name(variant);
 }
+const char* q8_conv_variant(const q8_conv_desc* d) { return variant_name(d, false); }
+const char* q8_conv_call_variant(const q8_conv_desc* d) { return variant_name(d, true); }
 
 }  // extern "C"
 

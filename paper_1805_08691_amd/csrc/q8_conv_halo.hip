@@ -54,6 +54,8 @@ const HaloVariant kHaloVariants[] = {
       HaloShape<2, 2, 1, 1, 3>::max_w() },                      // 15: 64 x 64
     { "conv_i8_halo3_kernel<2,2,2,1,5,2>", &launch_halo3_or_generic<2, 2, 2, 1, 5, 2>, 128, 64,
       HaloShape<2, 2, 2, 1, 5, 2>::max_w() },                   // 16: 128 x 64, two groups, maps up to 95 wide
+    // wavefronts of 64 pixels x 128 channels: fewer LDS reads and pixels' loads per product
+    Q8_HALO_ROW(4, 2, 2, 4, 4)     // 17: 256 x 256, eight wavefronts, maps up to 127 wide
 };
 #undef Q8_HALO_ROW
 constexpr int kNumHaloVariants = sizeof(kHaloVariants) / sizeof(kHaloVariants[0]);

@@ -29,6 +29,7 @@ const RingVariant kRingVariants[] = {
     Q8_RING_ROW(22, 2, 2, 1, 2, 128, 4)    // 22: 64 x 128, 128 reduction bytes per step
     Q8_RING_ROW(23, 2, 2, 2, 1, 128, 4)    // 23: 128 x 64, 128 reduction bytes per step
     Q8_RING_ROW(24, 2, 2, 1, 1, 128, 8)    // 24: 64 x 64, 128 bytes per step, deep ring (128 KB)
+    Q8_RING_ROW(25, 2, 2, 2, 3, 64, 3)     // 25: 128 x 192
 };
 #undef Q8_RING_ROW
 constexpr int kNumRingVariants = sizeof(kRingVariants) / sizeof(kRingVariants[0]);

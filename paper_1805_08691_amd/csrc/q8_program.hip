@@ -5,7 +5,7 @@
 
 namespace q8 {
 int conv_fill_op(const q8_op* o, ConvParams& p, bool* empty);
-int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us);
+int conv_choose(const q8_conv_desc* d, const ConvParams& p, float* us, bool alone = false);
 int conv_launch_chosen(int variant, ConvParams& p, hipStream_t s);
 int first_direct_variant();
 int num_direct_variants();

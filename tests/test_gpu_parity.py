@@ -2636,6 +2636,29 @@ def test_conv_extended_builds(B, idx):
     assert np.array_equal(host(got), orc.requant_pc(acc, m, True, res_s, np.float32(0.4)))
 
 
+# layers that a call of its own takes in other tiles than a planned step: tails in pixels and channels, a residual,
+# channel counts that are no multiple of 64, a column filter, a stride
+RETILED = [
+    ("ring_kernel<2,2,2,3,64,3>", dict(N=16, H=71, W=69, C=80, K=180, R=3, S=3), False),
+    ("ring_kernel<2,2,2,1,64,4>", dict(N=5, H=61, W=67, C=320, K=176, R=1, S=7, pad_w=3), True),
+    ("ring_kernel<4,2,2,2,64,3>", dict(N=1, H=119, W=117, C=272, K=400, R=5, S=5, pad_h=2, pad_w=2), False),
+    ("halo3_kernel<4,2,2,4,4>", dict(N=14, H=37, W=39, C=256, K=500, R=3, S=3, pad_h=1, pad_w=1), True)]
+
+
+@pytest.mark.parametrize("idx", range(len(RETILED)))
+def test_conv_retiled(B, idx):
+    kernel, geom, with_res = RETILED[idx]
+    d = B.ConvDesc(relu=1, **geom)
+    assert B.conv_call_variant(d) == "conv_i8_" + kernel != B.conv_variant(d)
+    g = torch.Generator(device="cuda").manual_seed(idx)
+    codes = lambda *s: torch.randint(-128, 128, s, dtype=torch.int8, device="cuda", generator=g)
+    x, w = codes(d.N, d.H, d.W, d.C), B.pack_weights(d, codes(d.K, d.R, d.S, d.C))
+    b = torch.randint(-20000, 20000, (d.K,), dtype=torch.int32, device="cuda", generator=g)
+    args = (d, x, w, b, 0.02, 0.0004, 0.03, codes(d.N, d.Ho, d.Wo, d.K) if with_res else None, 0.02)
+    got, want = B.conv_int8(*args), B.conv_int8(*args, variant=7)       # 64 x 64 tiles
+    assert torch.equal(got, want) and 0 < int(want.float().std()) < 127
+
+
 # the block-tiled 3x3 kernel: blocks that end inside the map in both directions, one row and one column,
 # padding 0 and 1, 32 and 64 channels in, 16 to 64 out (blocks of 16 x 16 up to 32), images of several
 # tiles and tiles beyond one per workgroup, slices; the last one with unsigned codes at the border, too (those
