@@ -204,18 +204,19 @@ def _stream():
     return _raw_stream(_device())
 
 
-# The layer calls go through _q8call, which does what _ptr and _stream do without the interpreter:
-# 3.4 us of host time a call instead of 5.6, of which the launch itself is 2.3.
+# The layer calls and the passes go through _q8call, which does what _ptr and _stream do without the interpreter:
+# 3.4 us of host time a call instead of 5.6, of which the launch itself is 2.3 (max-abs, Eq. Q and Eq. D of a
+# small tensor 12.5 us for the three, now 9.2).
 _q8call.bind(_ptr, _device, _raw_stream, ConvDesc, torch.int8, torch.int32, torch.float32, torch.uint8,
              *(C.cast(f, C.c_void_p).value for f in (
                  lib.q8_conv_int8, lib.q8_conv_u8, lib.q8_conv_int8_per_channel,
-                 lib.q8_conv_int8_real_output, lib.q8_conv_f32_observed_spread)))
+                 lib.q8_conv_int8_real_output, lib.q8_conv_f32_observed_spread, lib.q8_calibrate_maxabs,
+                 lib.q8_quantize, lib.q8_dequantize)))
 
 
 def calibrate_maxabs(x, maxabs):
     """maxabs[0] = max(maxabs[0], max|x|); ``maxabs`` is a 1-element fp32 device tensor."""
-    _check(lib.q8_calibrate_maxabs(_ptr(x, torch.float32), x.numel(),
-                                   _ptr(maxabs, torch.float32), _stream()))
+    _check(_q8call.maxabs(x, maxabs))
 
 
 def qfactor(max_abs, p):
@@ -224,8 +225,7 @@ def qfactor(max_abs, p):
 
 def quantize(r, q, p, out=None):
     z = out if out is not None else torch.empty(r.shape, dtype=torch.int8, device=r.device)
-    _check(lib.q8_quantize(_ptr(r, torch.float32), r.numel(), q, p, _ptr(z, torch.int8),
-                           _stream()))
+    _check(_q8call.quantize(r, q, p, z))
     return z
 
 
@@ -258,8 +258,7 @@ def quantize_bias(b, q_x, q_w, out=None):
 
 def dequantize(z, q, out=None):
     r = out if out is not None else torch.empty(z.shape, dtype=torch.float32, device=z.device)
-    _check(lib.q8_dequantize(_ptr(z, torch.int8), z.numel(), q, _ptr(r, torch.float32),
-                             _stream()))
+    _check(_q8call.dequantize(z, q, r))
     return r
 
 

@@ -15,8 +15,8 @@
 namespace {
 
 PyObject *g_ptr, *g_device, *g_stream, *g_desc_type, *g_int8, *g_int32, *g_float32, *g_uint8;
-void* g_fn[5];
-enum { kInt8, kU8, kPerChannel, kReal, kF32 };
+void* g_fn[8];
+enum { kInt8, kU8, kPerChannel, kReal, kF32, kMaxabs, kQuantize, kDequantize };
 
 // One call's arguments, read in order; `ok` turns false with a Python exception set.
 struct Args {
@@ -71,7 +71,7 @@ struct Args {
     if (PyErr_Occurred()) ok = false;
     return ok ? static_cast<T*>(p) : nullptr;
   }
-  int8_t* i8(int i) { return tensor<int8_t>(i, at::kChar, g_int8); }
+  int8_t* i8(int i, long* n = nullptr) { return tensor<int8_t>(i, at::kChar, g_int8, n); }
   int32_t* i32(int i) { return tensor<int32_t>(i, at::kInt, g_int32); }
   float* f32(int i, long* n = nullptr) { return tensor<float>(i, at::kFloat, g_float32, n); }
   float factor(int i) {
@@ -209,15 +209,55 @@ PyObject* conv_f32(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// bind(_ptr, get_device, get_stream, ConvDesc, int8, int32, float32, uint8, five addresses)
+// (x, maximum)
+PyObject* maxabs(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (!count(n, 2)) return nullptr;
+  Args g{args};
+  long len = 0;
+  const float* x = g.f32(0, &len);
+  float* m = g.f32(1);
+  void* s = g.stream();
+  return finish(g, [&] { return ((decltype(&q8_calibrate_maxabs))g_fn[kMaxabs])(x, (size_t)len, m, s); });
+}
+
+// (r, q, p, z)
+PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (!count(n, 4)) return nullptr;
+  Args g{args};
+  long len = 0;
+  const float* r = g.f32(0, &len);
+  const float q = g.factor(1);
+  if (g.ok && !PyLong_Check(args[2])) {
+    PyErr_SetString(PyExc_TypeError, "p: an int");
+    g.ok = false;
+  }
+  const int p = g.flag(2);
+  int8_t* z = g.i8(3);
+  void* s = g.stream();
+  return finish(g, [&] { return ((decltype(&q8_quantize))g_fn[kQuantize])(r, (size_t)len, q, p, z, s); });
+}
+
+// (z, q, r)
+PyObject* dequantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (!count(n, 3)) return nullptr;
+  Args g{args};
+  long len = 0;
+  const int8_t* z = g.i8(0, &len);
+  const float q = g.factor(1);
+  float* r = g.f32(2);
+  void* s = g.stream();
+  return finish(g, [&] { return ((decltype(&q8_dequantize))g_fn[kDequantize])(z, (size_t)len, q, r, s); });
+}
+
+// bind(_ptr, get_device, get_stream, ConvDesc, int8, int32, float32, uint8, eight addresses)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
-  if (!count(n, 13)) return nullptr;
+  if (!count(n, 16)) return nullptr;
   PyObject** keep[] = {&g_ptr, &g_device, &g_stream, &g_desc_type, &g_int8, &g_int32, &g_float32, &g_uint8};
   for (int i = 0; i < 8; ++i) {
     Py_INCREF(args[i]);
     *keep[i] = args[i];
   }
-  for (int i = 0; i < 5; ++i) {
+  for (int i = 0; i < 8; ++i) {
     g_fn[i] = PyLong_AsVoidPtr(args[8 + i]);
     if (PyErr_Occurred()) return nullptr;
   }
@@ -226,7 +266,8 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
 
 #define Q8_METHOD(F) {#F, (PyCFunction)(void (*)(void))F, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {Q8_METHOD(conv_int8), Q8_METHOD(conv_u8), Q8_METHOD(conv_per_channel),
-                         Q8_METHOD(conv_real), Q8_METHOD(conv_f32), Q8_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
+                         Q8_METHOD(conv_real), Q8_METHOD(conv_f32), Q8_METHOD(maxabs), Q8_METHOD(quantize),
+                         Q8_METHOD(dequantize), Q8_METHOD(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_q8call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

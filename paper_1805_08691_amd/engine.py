@@ -334,7 +334,7 @@ class Engine:
             if op.dst not in keys:
                 keys.append(op.dst)
         spread = torch.zeros((len(keys), MAX_COPIES * B.SLOT_STRIDE), dtype=torch.float32, device=self.dev)
-        slot = dict(zip(keys, spread))
+        slot = dict(zip(keys, spread.unbind()))
         n_batches = 0
         for x in batches:
             B.calibrate_maxabs(x.contiguous(), slot[self.net.input][:1])
@@ -343,8 +343,9 @@ class Engine:
         if not n_batches:
             raise ValueError("calibrate: no batches")     # every factor would be 1
         vals = B.calibrate_fold(spread, torch.empty(len(keys), device=self.dev)).cpu().numpy()
-        q = {k: B.qfactor(float(v), 8 if k in self.unsigned else P_ACT)
-             for k, v in zip(keys, vals)}
+        # qfactor of every key: one fp32 division, 1 for a maximum that is not positive
+        levels = np.array([255 if k in self.unsigned else 2 ** P_ACT - 1 for k in keys], dtype=np.float32)
+        q = dict(zip(keys, np.where(vals > 0, vals / levels, np.float32(1)).tolist()))
         for op in self.net.ops:
             if (op.kind == "conv" and op.res is not None and not self.unsigned
                     and not self.own_sum_factor):
