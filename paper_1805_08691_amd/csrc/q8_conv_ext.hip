@@ -20,7 +20,7 @@ int halo_ext(ConvParams& p, hipStream_t stream) {
 
 template <int TC, int KS>
 int pw_ext(ConvParams& p, hipStream_t stream) {
-  return pw_applicable<TC, KS>(p) ? launch_pw<TC, KS, 1>(p, stream) : Q8_EUNSUPPORTED;
+  return pw_applicable<TC, KS, 1>(p) ? launch_pw<TC, KS, 1>(p, stream) : Q8_EUNSUPPORTED;
 }
 
 }  // namespace

@@ -28,6 +28,8 @@
 namespace q8 {
 namespace {
 
+constexpr int kNonTemporal = 2;          // cache policy of a buffer store
+
 template <int TC, int KS>
 struct PwShape {
   static constexpr int NW = 4, WP = 2, WC = 2, TP = 2;
@@ -38,13 +40,17 @@ struct PwShape {
   static constexpr int LDS_BYTES = A_BYTES + 2 * B_BYTES + 2 * S_BYTES;
 };
 
-template <int TC, int KS, int EXT>
+// DEQ: Eq. D of the codes beside them, from the staging tile too: 16 bytes a lane, whole rows of the channel tile, past
+// the caches (nobody in the step reads them).  64 -> 256 with a residual on 56 x 56 x 32 images, 103 MB of values: 29.7
+// us as two launches, 22.4 as one; its 160 MB take 25 of a copy from and to HBM.
+template <int TC, int KS, int EXT, bool DEQ = false>
 __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = PwShape<TC, KS>;
   constexpr int NW = Sh::NW, WP = Sh::WP, TP = Sh::TP, BP = Sh::BP, BC = Sh::BC;
   constexpr int SLOTS = BC / 16;
-  constexpr int STORES = BP * SLOTS / (NW * 64);
+  constexpr int CODE_STORES = BP * SLOTS / (NW * 64), VALUE_STORES = DEQ ? CODE_STORES * 4 : 0;
+  constexpr int STORES = CODE_STORES + VALUE_STORES;
   constexpr int A_LOADS = KS * BC / 16 / NW, B_LOADS = KS * BP / 16 / NW, R_LOADS = BP * BC / 1024 / NW;
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int8_t* const lds_a = lds;
@@ -153,9 +159,9 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 
   // Copy-out of a tile: its first pixel and channel are the base of the buffer, so an offset is one
   // row and slot; a lane outside the map or the channels is sent out of range.
-  int st_off[STORES], st_row[STORES];
+  int st_off[CODE_STORES], st_row[CODE_STORES];
 #pragma unroll
-  for (int k = 0; k < STORES; ++k) {
+  for (int k = 0; k < CODE_STORES; ++k) {
     const int c = tid + k * NW * 64;
     st_row[k] = c / SLOTS;
     st_off[k] = ch0 + (c % SLOTS) * 16 < p.K ? st_row[k] * p.out_cs + (c % SLOTS) * 16 : kOobOffset;
@@ -246,11 +252,28 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
       const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(
           (void*)(p.y + (size_t)pix0 * p.out_cs + p.out_off + ch0), 0, 0x7fffffff, 0x00020000);
 #pragma unroll
-      for (int k = 0; k < STORES; ++k) {
+      for (int k = 0; k < CODE_STORES; ++k) {
         const int row = st_row[k], g = (tid + k * NW * 64) % SLOTS;
         const v4i codes =
             *reinterpret_cast<const v4i*>(stage + row * BC + ((g ^ swz_out<SLOTS>(row)) << 4));
         __builtin_amdgcn_raw_buffer_store_b128(codes, rsrc_y, pix0 + row < M ? st_off[k] : kOobOffset, 0, 0);
+      }
+      if constexpr (DEQ) {
+        const __amdgpu_buffer_rsrc_t rsrc_d = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(p.y_deq + (size_t)pix0 * p.out_cs + p.out_off + ch0), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int k = 0; k < VALUE_STORES; ++k) {
+          const int c = tid + k * NW * 64, row = c / (SLOTS * 4), quad = c % (SLOTS * 4);
+          const unsigned codes = *reinterpret_cast<const unsigned*>(
+              stage + row * BC + (((quad >> 2) ^ swz_out<SLOTS>(row)) << 4) + (quad & 3) * 4);
+          v4i v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[e] = __builtin_bit_cast(int, p.q_deq * (float)(int8_t)(codes >> (8 * e)));
+          __builtin_amdgcn_raw_buffer_store_b128(
+              v, rsrc_d, pix0 + row < M && ch0 + quad * 4 < p.K ? (row * p.out_cs + quad * 4) * 4 : kOobOffset, 0,
+              kNonTemporal);
+        }
       }
     }
     // the copy-out's LDS reads are done before anyone requests the tile after next into
@@ -262,22 +285,25 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 #endif
 }
 
-template <int TC, int KS>
+template <int TC, int KS, int EXT = 0>
 bool pw_applicable(const ConvParams& p) {
   const bool pointwise = p.R == 1 && p.S == 1 && p.stride_h == 1 && p.stride_w == 1 &&
                          p.pad_h == 0 && p.pad_w == 0;
   return pointwise && p.S4 == 0 && p.C == KS * 64 && (p.K & 15) == 0 && p.vec16 && !p.acc_dump &&
-         !p.y_f32 && !p.y_deq && !p.w2 &&
+         !p.y_f32 && !p.w2 && (!p.y_deq || (!EXT && p.f32_vec4 && p.out_cs < 0x7fffffff / 512)) &&
          (!p.res || (p.res_bytes > 0 && (long)p.M * p.res_cs < 0x7fffffffL)) &&
          (long)p.M * p.in_cs < 0x7fffffffL && p.out_cs < 0x7fffffff / 128;
 }
 
-template <int TC, int KS, int EXT>
+template <int TC, int KS, int EXT, bool DEQ = false>
 int launch_pw(ConvParams& p, hipStream_t stream) {
+  if constexpr (!EXT && !DEQ) {
+    if (p.y_deq) return launch_pw<TC, KS, EXT, true>(p, stream);
+  }
   using Sh = PwShape<TC, KS>;
   p.n_ptiles = (p.M + Sh::BP - 1) / Sh::BP;
   p.n_ctiles = (p.K + Sh::BC - 1) / Sh::BC;
-  auto kernel = conv_i8_pw_kernel<TC, KS, EXT>;
+  auto kernel = conv_i8_pw_kernel<TC, KS, EXT, DEQ>;
   if constexpr (Sh::LDS_BYTES > 65536) {
     static const hipError_t attr = hipFuncSetAttribute(
         reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -731,13 +731,16 @@ class Engine:
         if with_x and self.head:
             ops = [o for o in ops if o is not self.head[1]]
         fused = {name: self._dequant_writer(name) for name in names}
-        # Eq. D inside the launch that writes the tensor: asked for, or free (a launch of the
-        # latency family finishes four channels per lane whatever it writes)
-        for name in names:
-            w = self._dequant_writer(name, any_engine=True)
-            if fused[name] is None and w is not None and \
-                    "direct" in B.conv_variant(self.conv_desc(w, self.N)):
-                fused[name] = w
+        # Eq. D inside the launch that writes the tensor: asked for, free (a launch of the
+        # latency family finishes four channels per lane whatever it writes), or a saved pass (the pointwise family
+        # writes the values in whole rows from LDS: bottleneck block on 56 x 56, 32 images 69 -> 62 us, 64 images
+        # 141 -> 132), here where that is worth more than the layer's block in one launch (256 channels, us with
+        # the block and so: 75 thousand pixels 49.6 / 48.9, 102 thousand 67.5 / 62.0, 150 thousand 105.9 / 100.0; 48
+        # thousand 36.0 / 36.7, 12.5 thousand 18.4 / 22.2), below where it ends no such block
+        could = {name: self._dequant_writer(name, any_engine=True) for name in names}
+        writes = lambda w, family: w is not None and family in B.conv_variant(self.conv_desc(w, self.N))
+        fused.update({name: w for name, w in could.items() if fused[name] is None and (
+            writes(w, "direct") or (writes(w, "pw_kernel") and self.act[name].numel() >= 1 << 24))})
         fused = {name: w for name, w in fused.items() if w is not None}
         parts = self.parts
         if len(parts) > 1 and not self._pipelines_pay(ops):
@@ -775,6 +778,8 @@ class Engine:
         levels = self._levels(ops, parts[0][1], dst_of)
         blocks = self._blocks(ops, fused, parts[0][1], levels if len(parts) == 1 else None)
         inside = {i for pair in blocks.values() for i in pair}
+        fused.update({name: w for name, w in could.items() if name not in fused and writes(w, "pw_kernel") and
+                      ops.index(w) not in inside | blocks.keys()})
         for level, members in enumerate(levels):
             for k in list(range(1, len(parts))) + [0]:
                 for i in sorted(members):

@@ -2636,6 +2636,31 @@ def test_conv_extended_builds(B, idx):
     assert np.array_equal(host(got), orc.requant_pc(acc, m, True, res_s, np.float32(0.4)))
 
 
+# the pointwise family with Eq. D beside its codes: each build, tails in pixels and in the channel tile, slices, with and
+# without a residual; values that are 4-byte aligned only, which that family does not take
+@pytest.mark.parametrize("pixels,C,K,cs,off,shift", [
+    (40961, 64, 80, 0, 0, 0), (40961, 64, 64, 96, 16, 0), (41999, 128, 80, 0, 0, 0), (61441, 128, 272, 0, 0, 0),
+    (128129, 256, 368, 400, 32, 0), (40961, 64, 80, 0, 0, 1)])
+def test_pointwise_with_dequantized_output(B, pixels, C, K, cs, off, shift):
+    d = B.ConvDesc(1, 1, pixels, C, K, 1, 1, relu=1, out_c_stride=cs, out_c_off=off)
+    assert "pw_kernel" in B.conv_variant(d)
+    g = torch.Generator(device="cuda").manual_seed(K)
+    codes = lambda *s: torch.randint(-128, 128, s, dtype=torch.int8, device="cuda", generator=g)
+    x, w, q_out = codes(1, 1, pixels, C), B.pack_weights(d, codes(K, 1, 1, C)), 0.03
+    b = torch.randint(-20000, 20000, (K,), dtype=torch.int32, device="cuda", generator=g)
+    for res in (None, codes(1, 1, pixels, K)):
+        args = (x, w, b, 0.02, 0.0004, q_out, res, 0.02)
+        want = torch.full((1, 1, pixels, cs or K), 77, dtype=torch.int8, device="cuda")
+        B.conv_int8(d, *args, out=want)
+        got, values = torch.full_like(want, 77), torch.full((want.numel() + shift,), -5.0, device="cuda")[shift:]
+        values = values.view(want.shape)
+        B.conv_int8_dequantized(d, *args, out=got, out_f32=values)
+        assert torch.equal(got, want)
+        expect = torch.full_like(values, -5.0)
+        expect[..., off:off + K] = want[..., off:off + K].float() * q_out
+        assert torch.equal(values, expect)
+
+
 # layers that a call of its own takes in other tiles than a planned step: tails in pixels and channels, a residual,
 # channel counts that are no multiple of 64, a column filter, a stride
 RETILED = [
