@@ -1266,6 +1266,29 @@ def test_pool_f32(B):
         assert np.allclose(got, want, rtol=1e-6, atol=1e-6), mode
 
 
+# four channels a lane: slices, one pixel, a window that leaves the image, rows and images that end inside a block;
+# channels and places that are no multiples of four take a value per lane
+@pytest.mark.parametrize("shape,C,R,stride,pad,cs,off", [
+    ((1, 1, 1), 4, 3, 1, 1, 0, 0), ((3, 17, 15), 20, 3, 2, 1, 48, 28), ((5, 9, 11), 64, 2, 2, 0, 0, 0),
+    ((2, 7, 9), 12, 5, 3, 2, 24, 12), ((2, 17, 15), 6, 3, 1, 1, 0, 0), ((2, 17, 15), 8, 3, 1, 1, 19, 3)])
+def test_pool_f32_builds(B, shape, C, R, stride, pad, cs, off):
+    (N, H, W), g = shape, torch.Generator(device="cuda").manual_seed(C)
+    Ho, Wo = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    x = torch.randn((N, H, W, C), device="cuda", generator=g)
+    for mode in ("max", "avg"):
+        p = torch.nn.functional.pad(x, (0, 0, pad, pad, pad, pad), value=-torch.inf if mode == "max" else 0.0)
+        want = torch.full((N, Ho, Wo, C), -3.402823466e38 if mode == "max" else 0.0, device="cuda")
+        for r in range(R):                      # in the kernel's order: the same sums
+            for s in range(R):
+                v = p[:, r:r + (Ho - 1) * stride + 1:stride, s:s + (Wo - 1) * stride + 1:stride]
+                want = torch.maximum(want, v) if mode == "max" else want + v
+        want = want if mode == "max" else want / torch.full((1,), float(R * R), device="cuda")
+        out = torch.full((N, Ho, Wo, cs or C), -7.0, device="cuda")
+        B.pool_f32(x, mode, R, R, stride, pad, Ho, Wo, out=out, out_c_off=off)
+        assert torch.equal(out[..., off:off + C], want)
+        assert bool((out[..., :off] == -7).all()) and bool((out[..., off + C:] == -7).all())
+
+
 def _oracle_pipeline(cfg_id, batch, calib_library):
     cfg = wl.CONFIGS[cfg_id]
     net = cfg["make"]()
