@@ -67,7 +67,7 @@ int pick_f32_lds(long M, int K, int rsc, float* us);    // us: its estimate
 int launch_f32_lds(int build, F32Params& p, hipStream_t stream);
 const char* f32_lds_name(int build);
 // The tiled kernel on the bf16 matrix instructions (q8_conv_f32_split.hip).
-bool f32_split_pays(long M, int K, int rsc, float lds_us);
+bool f32_split_pays(long M, int K, int rsc, float lds_us, bool lds);
 int launch_f32_split(F32Params& p, hipStream_t stream);
 const char* f32_split_name(long M, int K);
 

@@ -2,9 +2,9 @@
 // activations calibration measures, with the max-abs of what it computes taken on the way.
 // A helper around the quantised path, not part of it.
 //
-// This file: the register-fed builds, for channel counts and alignments that those on LDS
-// (q8_conv_f32_lds.hip) do not take, and the host side.  What bounds them: on large layers the fp32
-// matrix rate (122 of the 153 TF a library product of 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at
+// This file: the register-fed builds, for channel counts and alignments that those on LDS and on the
+// bf16 instructions (q8_conv_f32_lds.hip, q8_conv_f32_split.hip) do not take, and the host side.
+// What bounds them: on large layers the fp32 matrix rate (122 of the 153 TF a library product of 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at
 // batch 64); on small maps the operand loads, 11 to 14 bytes per clock and CU.  16 reduction bytes
 // per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments straight into the MFMA's
 // register layout (16 rows x 64 bytes a load), two stages ahead of the one it computes: no LDS and no
@@ -414,14 +414,27 @@ bool f32_tiled(const q8_conv_desc* d, long M, long per_img) {
            d->H > (1 << 28) || (long)d->R * d->dil_h > (1 << 28));
 }
 
+// Whether the padding fits the 32-bit offsets of the builds whose descriptor starts at the image's first tap, pad_h
+// rows and pad_w pixels in front of it, on both sides of the map, its columns too, which the register-fed builds do not
+// count (in a descriptor of more than 2^31 - 1 bytes the out-of-range offset would lie inside).
+bool f32_pad_fits(const q8_conv_desc* d, long per_img) {
+  return f32_reach(d, per_img) + ((long)d->pad_h * d->W + 2L * d->pad_w) * d->C * 4 <= 0x7fffffffL;
+}
 // Whether the builds on LDS take the layer: whole 128-byte pieces of a tap, whole groups of a lane's
-// channels, output (residual, bias) rows of 16-byte accesses.  Their descriptor starts at the image's
-// first tap, pad_h rows and pad_w pixels in front of it, so the padding has to fit the 32-bit offsets
-// on both sides of the map, its columns too, which the other builds do not count (in a descriptor of
-// more than 2^31 - 1 bytes the out-of-range offset would lie inside).
+// channels, output (residual, bias) rows of 16-byte accesses.
 bool f32_lds_takes(const q8_conv_desc* d, long per_img, int out_cs, int out_off) {
-  return d->C % 32 == 0 && d->K % 16 == 0 && out_cs % 4 == 0 && out_off % 4 == 0 &&
-         f32_reach(d, per_img) + ((long)d->pad_h * d->W + 2L * d->pad_w) * d->C * 4 <= 0x7fffffffL;
+  return d->C % 32 == 0 && d->K % 16 == 0 && out_cs % 4 == 0 && out_off % 4 == 0 && f32_pad_fits(d, per_img);
+}
+
+// The layer's build, among those on LDS (0 ..), the ones on the bf16 matrix instructions (-1), or register-fed (-2).
+// aligned: activations and filters are; rows: so are output (residual, bias) rows.
+int pick_f32_tiled(const q8_conv_desc* d, long M, long per_img, int out_cs, int out_off, bool aligned, bool rows) {
+  if (!aligned || d->C % 16 || !f32_pad_fits(d, per_img)) return -2;
+  const int rsc = d->R * d->S * d->C;
+  const bool lds = rows && f32_lds_takes(d, per_img, out_cs, out_off);
+  float us;
+  const int build = pick_f32_lds(M, d->K, rsc, &us);
+  return f32_split_pays(M, d->K, rsc, us, lds) ? -1 : lds ? build : -2;
 }
 
 int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float* b, const float* res,
@@ -453,11 +466,10 @@ int conv_f32(const q8_conv_desc* d, const float* x, const float* w, const float*
   p.M = (int)M; p.rsc = d->R * d->S * d->C;
   p.by_img = make_fast_div((unsigned)per_img); p.by_row = make_fast_div((unsigned)p.Wo);
   p.by_c = make_fast_div((unsigned)d->C); p.by_s = make_fast_div((unsigned)d->S);
-  if (f32_lds_takes(d, per_img, out_cs, out_off) && p.vec_y && p.vec_b && q8_aligned(x, 16) && q8_aligned(w, 16)) {
-    float us;
-    const int build = pick_f32_lds(M, d->K, p.rsc, &us);
-    return f32_split_pays(M, d->K, p.rsc, us) ? launch_f32_split(p, stream) : launch_f32_lds(build, p, stream);
-  }
+  const int build = pick_f32_tiled(d, M, per_img, out_cs, out_off, q8_aligned(x, 16) && q8_aligned(w, 16),
+                                   p.vec_y && p.vec_b);
+  if (build >= 0) return launch_f32_lds(build, p, stream);
+  if (build == -1) return launch_f32_split(p, stream);
   return kF32Builds[pick_f32(M, d->K)].launch(p, stream);
 }
 
@@ -504,11 +516,10 @@ const char* q8_conv_f32_variant(const q8_conv_desc* d) {
   if (!q8::f32_desc_sane(d)) return "unsupported";
   const long per_img = (long)q8_conv_out_h(d) * q8_conv_out_w(d), M = d->N * per_img;
   if (M > 0 && !q8::f32_tiled(d, M, per_img)) return "conv_f32_any_kernel";
-  if (M > 0 && q8::f32_lds_takes(d, per_img, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off)) {
-    float us;
-    const int rsc = d->R * d->S * d->C, build = q8::pick_f32_lds(M, d->K, rsc, &us);
-    return q8::f32_split_pays(M, d->K, rsc, us) ? q8::f32_split_name(M, d->K) : q8::f32_lds_name(build);
-  }
+  const int build = M > 0 ? q8::pick_f32_tiled(d, M, per_img, d->out_c_stride ? d->out_c_stride : d->K, d->out_c_off,
+                                               true, true) : -2;
+  if (build >= 0) return q8::f32_lds_name(build);
+  if (build == -1) return q8::f32_split_name(M, d->K);
   const q8::F32Build& b = q8::kF32Builds[q8::pick_f32(M, d->K)];
   return b.name[d->C % (16 * b.nc) == 0 ? 2 : d->C % 4 == 0 ? 1 : 0];
 }

@@ -1,4 +1,4 @@
-// fp32 convolution of calibration on the bf16 matrix instructions: C % 32 == 0, K % 64 == 0, aligned rows.
+// fp32 convolution of calibration on the bf16 matrix instructions: C % 16 == 0, aligned activations and filters.
 //
 // v_mfma_f32_32x32x16_bf16 does 16 times the products per clock that the fp32 instruction does, and its
 // products and sums are fp32.  A value of 24 significant bits is exactly the sum of three bf16 values h + m + l, each
@@ -310,18 +310,34 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
 #pragma unroll
   for (int o = 0; o < OWN; ++o) {
     const int pix = pixel_of(o), ch = channel_of(o);
-    if (pix >= p.M || ch >= p.K) continue;         // (K % 16 == 0: all of a quad's channels or none)
+    if (pix >= p.M || ch >= p.K) continue;
     v4f v = own[o];
-    if (p.b) v += *reinterpret_cast<const v4f*>(p.b + ch);
+    float* const y = p.y + (size_t)pix * p.out_cs + p.out_off + ch;
+    const float* const res = p.res ? p.res + (size_t)pix * p.K + ch : nullptr;
+    auto relu_max = [&](float u) {
+      if (p.relu) u = fmaxf(u, 0.0f);
+      m_out = fmaxf(m_out, fabsf(u));
+      return u;
+    };
+    if (p.vec_y && p.vec_b && ch + 4 <= p.K) {
+      if (p.b) v += *reinterpret_cast<const v4f*>(p.b + ch);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m_sum = fmaxf(m_sum, fabsf(v[e]));
-    if (p.res) v += *reinterpret_cast<const v4f*>(p.res + (size_t)pix * p.K + ch);
+      for (int e = 0; e < 4; ++e) m_sum = fmaxf(m_sum, fabsf(v[e]));
+      if (res) v += *reinterpret_cast<const v4f*>(res);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (p.relu) v[e] = fmaxf(v[e], 0.0f);
-      m_out = fmaxf(m_out, fabsf(v[e]));
+      for (int e = 0; e < 4; ++e) v[e] = relu_max(v[e]);
+      *reinterpret_cast<v4f*>(y) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (ch + e >= p.K) continue;
+        float u = v[e];
+        if (p.b) u += p.b[ch + e];
+        m_sum = fmaxf(m_sum, fabsf(u));
+        if (res) u += res[e];
+        y[e] = relu_max(u);
+      }
     }
-    *reinterpret_cast<v4f*>(p.y + (size_t)pix * p.out_cs + p.out_off + ch) = v;
   }
   __syncthreads();
   observe_block<KW>(p, m_sum, m_out, reinterpret_cast<float*>(lds));
@@ -352,11 +368,14 @@ int launch_split(F32Params& p, hipStream_t stream) {
 // low, by up to a quarter: hence the 1.1) and one fitted to the layers of the package's networks at 1, 3 and 8 images.
 // n: 64 x 64 tiles per CU.  Up to one eight wavefronts share a tile; two workgroups of four wavefronts fit a CU.
 // Of 106 layers none is slower by it; those that change take 0.74 to 0.97 of their time.  K % 64: tiles are full.
-bool f32_split_pays(long M, int K, int rsc, float lds_us) {
-  if (K % 64) return false;
-  const float n = (float)((M + 63) / 64) * (float)(K / 64) / 256.0f;
+// Layers that those builds do not take (`lds` false) run register-fed, in 1.5 to 1.8 times that estimate where
+// they are long: 3x3 80 -> 192 on 71 x 71 x 8 150 us, 84 here; 512 -> 84 on 38 x 38 x 8 172, 102.
+bool f32_split_pays(long M, int K, int rsc, float lds_us, bool lds) {
+  if (lds && K % 64) return false;
+  const float n = (float)((M + 63) / 64) * (float)((K + 63) / 64) / 256.0f;
   const float step = n <= 1.0f ? 0.139f : n <= 2.0f ? 0.29f : fmaxf(0.49f, 0.182f * n);
-  return (n <= 1.0f ? 7.0f : 9.0f) + 1.1f * n + step * (float)(rsc / 16) < 1.1f * lds_us;
+  const float us = (n <= 1.0f ? 7.0f : 9.0f) + 1.1f * n + step * (float)(rsc / 16);
+  return lds ? us < 1.1f * lds_us : us > 30.0f && us < 1.5f * lds_us;
 }
 int launch_f32_split(F32Params& p, hipStream_t stream) {
   const long tiles = (p.M + 63L) / 64 * ((p.K + 63) / 64);

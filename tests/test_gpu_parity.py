@@ -1997,7 +1997,11 @@ def test_streaming_passes(B, n, shift):
     ("8", (4, 61, 67, 64, 128, 3, 3, 2, 1), False, (140, 8)),
     ("4", (6, 65, 67, 32, 64, 5, 5, 1, 1), False, (0, 0)),
     ("4", (7, 37, 35, 128, 320, 1, 3, 1, 1), True, (0, 0)),
-    ("4", (3, 49, 51, 1024, 192, 1, 1, 1, 1), False, (0, 0))])
+    ("4", (3, 49, 51, 1024, 192, 1, 1, 1, 1), False, (0, 0)),
+    # layers that are no multiples of the LDS builds' pieces: 16 channels, rows of 4- and of 8-byte accesses
+    ("4", (5, 47, 49, 80, 180, 5, 5, 1, 1), True, (0, 0)),
+    ("8", (2, 41, 43, 304, 126, 3, 3, 1, 1), True, (0, 0)),
+    ("8", (2, 43, 41, 304, 84, 3, 3, 1, 1), False, (91, 6))])
 def test_conv_f32_split_builds(B, build, geom, res, slice_):
     """Sums at least as near to 64 bits as the bound of n fp32 products and sums; what bf16 cannot hold, or
     holds with fewer bits, as the fp32 sum gives it."""
