@@ -244,6 +244,11 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
         d->W <= 240 && d->stride_h <= 2 && d->stride_w <= 2 &&
         (long)d->N * ho * wo >= 128L * 256 && wo >= 64)
       return q8::first_stem_variant();
+    // ... and with up to four taps and rows, which need no LDS (q8_conv_taps4.hip), from where that is more than a
+    // launch: 4096 to 90000 pixels take either kernel the same time by themselves, in SSD-300 and Inception-v3 on one
+    // image this one 3 us less; from there on it takes 0.5 to 0.85 of the other's
+    if (d->S <= 4 && d->R <= 4 && d->K <= 64 && (d->K & 15) == 0 && (long)d->N * ho * wo >= 4096)
+      return q8::first_stem_variant() + 1;
     return d->K <= 64 ? 8 : 4;   // short reduction: small tiles, many per CU
   }
   const long M = (long)d->N * out_extent(d->H, d->pad_h, d->dil_h, d->R, d->stride_h) *

@@ -5,6 +5,7 @@
 #include "q8_conv_stem_kernel.h"
 
 namespace q8 {
+int launch_taps4_or_generic(ConvParams& p, hipStream_t stream);      // q8_conv_taps4.hip
 namespace {
 
 int launch_stem_or_generic(ConvParams& p, hipStream_t stream) {
@@ -25,6 +26,7 @@ struct StemVariant {
 };
 const StemVariant kStemVariants[] = {
     {"conv_i8_stem_kernel", &launch_stem_or_generic},
+    {"conv_i8_taps4_kernel", &launch_taps4_or_generic},
 };
 constexpr int kNumStemVariants = sizeof(kStemVariants) / sizeof(kStemVariants[0]);
 

@@ -329,6 +329,26 @@ def test_conv_image_row_family(B, idx):
         _run_conv_case(B, geom, relu=True, with_res=False, with_bias=True, seed=7777, dump_acc=False)
 
 
+# 4-channel images with up to four rows and taps: runs of 32 pixels that end inside a row, an image, the
+# tensor; fewer rows, taps and channels than the operand has; more runs than wavefronts; any stride
+@pytest.mark.parametrize("geom", [
+    (3, 15, 17, 3, 64, 3, 3, 1, 1), (1, 4, 5, 1, 16, 4, 4, 1, 1), (5, 33, 31, 4, 48, 2, 4, 2, 3),
+    (2, 29, 27, 2, 32, 3, 1, 2, 2), (1, 3, 3, 3, 64, 3, 3, 1, 1), (7, 152, 151, 3, 64, 3, 3, 1, 1),
+    (2, 23, 301, 3, 32, 1, 2, 1, 5)])
+def test_conv_few_taps(B, geom):
+    geom = dict(zip(("N", "H", "W", "C", "K", "R", "S", "stride_h", "stride_w"), geom))
+    d = B.ConvDesc(**geom, relu=1, in_c_stride=4)
+    names = [B.lib.q8_conv_variant_name(v).decode() for v in range(B.conv_num_variants())]
+    v = names.index("conv_i8_taps4_kernel")
+    if d.N * d.Ho * d.Wo >= 4096:
+        assert B.conv_variant(d) == names[v]
+    for k in range(2):
+        _run_conv_case(B, geom, relu=bool(k), with_res=False, with_bias=bool(k), seed=7500 + k, variant=v,
+                       out_pad=32 * k, out_off=16 * k, dump_acc=False)
+    # what it does not take: a residual, accumulators as well, output rows of no 16 bytes
+    _run_conv_case(B, geom, relu=True, with_res=True, with_bias=True, seed=7510, variant=v, out_pad=7, out_off=3)
+
+
 HEAD_CASES = [   # image (N, H, W, C), filter, strides, padding = the zero frame around the image
     dict(N=2, H=37, W=41, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, pad_h=3, pad_w=3),
     dict(N=3, H=224, W=224, C=3, K=64, R=7, S=7, stride_h=2, stride_w=2, pad_h=3, pad_w=3),  # ResNet-50
@@ -2625,7 +2645,9 @@ EXT_CASES = [
     ("halo3_kernel<2,2,1,1,3,2,9>", dict(N=1, H=39, W=37, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1)),
     ("halo3_kernel<2,2,1,1,3,1,9>", dict(N=1, H=55, W=63, C=192, K=144, R=3, S=3, pad_h=1, pad_w=1)),
     ("halo3_kernel<2,2,2,1,4,2>", dict(N=2, H=39, W=38, C=256, K=528, R=3, S=3, pad_h=1, pad_w=1)),
-    ("halo3_kernel<2,2,2,1,5,2>", dict(N=1, H=66, W=95, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1))]
+    ("halo3_kernel<2,2,2,1,5,2>", dict(N=1, H=66, W=95, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1)),
+    ("taps4_kernel", dict(N=8, H=135, W=137, C=3, K=64, R=3, S=3, in_c_stride=4)),
+    ("taps4_kernel", dict(N=19, H=49, W=35, C=3, K=48, R=4, S=4, stride_h=3, stride_w=2, in_c_stride=4))]
 
 
 @pytest.mark.parametrize("idx", range(len(EXT_CASES)))
