@@ -1,6 +1,6 @@
 // The block-tiled build of the persistent 3x3 family (Eq. x / Eq. A' of arxiv 1805.08691):
-// 3x3, stride 1, padding 0 or 1, C = 64 or 32 input channels, K <= 64 output channels, maps of any
-// width.
+// 3x3, stride 1, padding 0 or 1, C = 64 or 32 input channels, maps of any width.  A workgroup has 64 output channels
+// (32 where K <= 32); layers of more are as many sets of walkers.
 //
 // The persistent 3x3 kernel (q8_conv_p3_kernel.h) cuts the output into runs of 128 consecutive
 // pixels; the activations such a run reads are the run plus a whole map row on either side, so
@@ -19,7 +19,8 @@
 // (tap row, tile) pairs of a tap column.  30 LDS reads a tile and wavefront instead of 54, and nobody
 // waits for a tile's stores.  64 -> 64 on 300 x 300 x 32 images 160 -> 133 us, on 56 x 56 x 32 9.2 -> 8.9;
 // 32 -> 64 on 147 x 147 x 32 34.5 us in the general kernel (half a step per tap), 20.5 here, 32 -> 32 29.2 and
-// 15.6 (48 MB: 9.3 us of a copy).
+// 15.6 (48 MB: 9.3 us of a copy).  More than 64 channels, the best general build and this one: 64 -> 128 on
+// 150 x 150 x 32 73.1 and 58.4, 64 -> 256 on 56 x 56 x 32 24.0 and 19.6, 32 -> 96 on 112 x 112 x 32 29.2 and 21.5.
 //
 // POOL: the 2x2 maximum with stride 2 behind the layer in the same launch.  Blocks begin on even rows and columns,
 // so every window lies in one staging tile: two rows of it in the lane that stores them, the other two in a lane
@@ -71,6 +72,10 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_p = wave % WP, wave_c = wave / WP;
   const int H = p.H, W = p.W, Ho = p.Ho, Wo = p.Wo, pad = p.pad_h;
+  // Every workgroup is a walker of its own over tiles walker, + walkers, ..., with 64 (32) channels from ch0 on;
+  // those of one tile's channels are on the same XCD, a place apart.
+  const int ch_tiles = (p.K + BC - 1) / BC, place = blockIdx.x / kNumXcd;
+  const int ch0 = place % ch_tiles * BC, walkers = gridDim.x / ch_tiles;
   const int tiles_w = p.n_ctiles, tiles_img = ((Ho + TH - 1) / TH) * tiles_w;
 
   const __amdgpu_buffer_rsrc_t rsrc_w =
@@ -129,23 +134,23 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   for (int l = 0; l < Sh::A_LOADS; l += NW) {
     if (l + wave < Sh::A_LOADS) {
       const int row = ((l + wave) * Sh::RPW) % BC + lane / CHUNKS, tap = (l + wave) * Sh::RPW / BC;
-      const int ch = (row & ~31) + row_to_channel(row & 31);
+      const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
       const int off = ch < p.K ? ch * p.red_len + slot_of(row, lane % CHUNKS) * 16 : kOobOffset;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * CB, 0, 0);
     }
   }
-  int tile = blockIdx.x;
+  int tile = place / ch_tiles * kNumXcd + blockIdx.x % kNumXcd;
   if (tile < p.n_ptiles) issue_patch(tile, 0);
   v16i bias_v;
   {
     int b[16];
-    load_bias16(p, wave_c * 32 + 16 * frag_half, b);
+    load_bias16(p, ch0 + wave_c * 32 + 16 * frag_half, b);
 #pragma unroll
     for (int e = 0; e < 16; ++e) bias_v[e] = b[e];
   }
   float scales[16] = {};
-  if (EXT && p.m_vec) load_scale16(p, wave_c * 32 + 16 * frag_half, scales);
+  if (EXT && p.m_vec) load_scale16(p, ch0 + wave_c * 32 + 16 * frag_half, scales);
 
   // patch offsets of this lane's fragments, the same in every tile: fragment q of tap column s is the
   // two block rows from row 2 TP wave_p + q on, shifted by s columns
@@ -185,10 +190,9 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
       af[t][h] = *reinterpret_cast<const v4i*>(filters + t * (BC * CB) + (wave_c * 32 + frag_row) * CB +
                                                slot_of(frag_row, 2 * h + frag_half) * 16);
   meet();
-  // every workgroup is a walker of its own: tiles blockIdx.x, + gridDim.x, ...
-  for (int it = 0; tile < p.n_ptiles; ++it, tile += gridDim.x) {
+  for (int it = 0; tile < p.n_ptiles; ++it, tile += walkers) {
     const int buf = it & 1;
-    const int next = tile + gridDim.x;
+    const int next = tile + walkers;
     // the other patch buffer is free: every wave passed the barrier behind the last tile
     // This tile's patch has landed; younger than it are the last tile's STORES stores (always issued,
     // lanes outside the map out of range) and the next patch: nobody waits for the stores.
@@ -214,7 +218,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
         const int r_lo = h < 0, r_hi = h + 3 <= H ? 3 : 2, s_lo = w < 0, s_hi = w + 3 <= W ? 3 : 2;
         const int idx = h + pad < Ho && w + pad < Wo ? ((r_lo * 4 + r_hi) * 4 + s_lo) * 4 + s_hi : 0;
         int b[16];
-        load_start16(p, idx, wave_c * 32 + 16 * frag_half, b);
+        load_start16(p, idx, ch0 + wave_c * 32 + 16 * frag_half, b);
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = b[e];
       }
@@ -253,8 +257,8 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
     {
       int n, h0, w0;
       tile_origin(tile, n, h0, w0);
-      const int origin = ((n * Ho + h0) * Wo + w0) * p.out_cs + p.out_off;
-      const bool in = (w0 + out_x < Wo) & (out_g * 16 < p.K);
+      const int origin = ((n * Ho + h0) * Wo + w0) * p.out_cs + p.out_off + ch0;
+      const bool in = (w0 + out_x < Wo) & (ch0 + out_g * 16 < p.K);
       v4i codes[STORES];
 #pragma unroll
       for (int k = 0; k < STORES; ++k) {
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
                                                (unsigned)larger(even, beside ? even1 : even), 0x07030501u);
         }
         const int hp = (h0 + out_y) / 2, wp = (w0 + out_x) / 2;
-        int off = ((n * pool.Hp + hp) * pool.Wp + wp) * pool.cs + out_g * 16;
+        int off = ((n * pool.Hp + hp) * pool.Wp + wp) * pool.cs + ch0 + out_g * 16;
         asm volatile("" : "+v"(off));
         off = in & (out_x % 2 == 0) & (hp < pool.Hp) & (wp < pool.Wp) ? off : kOobOffset;
         __builtin_amdgcn_raw_buffer_store_b128(most, rsrc_p, off, 0, 0);
@@ -303,8 +307,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 
 inline bool p3b_applicable(const ConvParams& p) {
   return p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 && p.dil_w == 1 &&
-         p.pad_h == p.pad_w && p.pad_h <= 1 && (p.C == 64 || p.C == 32) && p.S4 == 0 && p.K <= 64 &&
-         (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
+         p.pad_h == p.pad_w && p.pad_h <= 1 && (p.C == 64 || p.C == 32) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
          (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
@@ -330,9 +333,15 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
       per_cu = 1;
     return per_cu * cus;
   }();
-  // as many workgroups as stay resident, every one with the same number of tiles (+- 1)
-  const int passes = (p.n_ptiles + resident - 1) / resident;
-  const int grid = (p.n_ptiles + passes - 1) / passes;
+  // as many workgroups as stay resident, every one with the same number of tiles (+- 1); with several channel
+  // tiles the walkers fill whole rows of XCDs (those of more than are resident follow them)
+  const int ch_tiles = (p.K + Sh::BC - 1) / Sh::BC, most = resident / ch_tiles / kNumXcd * kNumXcd;
+  const int places = ch_tiles == 1 ? resident : most < kNumXcd ? kNumXcd : most;
+  const int passes = (p.n_ptiles + places - 1) / places;
+  int walkers = (p.n_ptiles + passes - 1) / passes;
+  if (ch_tiles > 1) walkers = (walkers + kNumXcd - 1) / kNumXcd * kNumXcd;
+  if ((long)walkers * ch_tiles > 0x7fffffffL) return Q8_EUNSUPPORTED;
+  const int grid = walkers * ch_tiles;
   hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), Sh::LDS_BYTES, stream, p, pool);
   return q8_launch_status();
 }

@@ -1097,6 +1097,8 @@ def test_pool_i8(B, mode, shape, win, m, slice_):
     ((1, 299, 301), 64, 48, 1, True, (80, 16)),    # the last windows hold one row and column; into a slice
     ((5, 149, 163), 32, 64, 1, True, (64, 0)),
     ((2, 149, 151), 32, 32, 0, False, (32, 0)),    # 16 x 16 blocks
+    ((3, 149, 151), 64, 144, 1, True, (176, 16)),  # several channel tiles, the last with 16 of 64
+    ((5, 149, 163), 32, 96, 1, False, (96, 0)),
 ])
 def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
     """The block-tiled 3x3 kernel with the 2x2 maximum in its launch: both tensors as by two calls, nothing
@@ -2646,6 +2648,9 @@ EXT_CASES = [
     ("halo3_kernel<2,2,1,1,3,1,9>", dict(N=1, H=55, W=63, C=192, K=144, R=3, S=3, pad_h=1, pad_w=1)),
     ("halo3_kernel<2,2,2,1,4,2>", dict(N=2, H=39, W=38, C=256, K=528, R=3, S=3, pad_h=1, pad_w=1)),
     ("halo3_kernel<2,2,2,1,5,2>", dict(N=1, H=66, W=95, C=256, K=272, R=3, S=3, pad_h=1, pad_w=1)),
+    ("p3b_kernel", dict(N=12, H=57, W=59, C=64, K=144, R=3, S=3)),
+    ("p3b_kernel", dict(N=12, H=55, W=57, C=32, K=144, R=3, S=3, pad_h=1, pad_w=1)),
+    ("p3b_kernel", dict(N=1, H=183, W=181, C=64, K=528, R=3, S=3, pad_h=1, pad_w=1)),
     ("taps4_kernel", dict(N=8, H=135, W=137, C=3, K=64, R=3, S=3, in_c_stride=4)),
     ("taps4_kernel", dict(N=19, H=49, W=35, C=3, K=48, R=4, S=4, stride_h=3, stride_w=2, in_c_stride=4))]
 
