@@ -174,7 +174,10 @@ __global__ __launch_bounds__(kThreads) void quantize_image_kernel(const float* _
   const unsigned item = blockIdx.x * blockDim.x + threadIdx.x;
   const unsigned row = item / per_row;        // n * H + h
   if (row >= (unsigned)n_rows) return;
-  const int w = (int)(item - row * per_row) * GROUP;
+  // (A row's last group of four ends with it, over pixels of the group before: the same codes twice.  Pixel by
+  // pixel it held up its whole wavefront: 299 x 299 x 64 images 24.0 us, 18.2 so; 300 x 300 18.1.)
+  int w = (int)(item - row * per_row) * GROUP;
+  if (GROUP == 4 && W >= 4) w = min(w, W - 4);
   const int n = (int)(row / (unsigned)H), h = (int)row - n * H;
   const float* src = r + ((size_t)row * W + w) * C;
   unsigned* dst = z + ((size_t)n * Hs + top + h) * Ws + left + w;

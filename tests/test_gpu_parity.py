@@ -620,6 +620,18 @@ def test_conv_image_in_zero_frame(B, geom):
     assert np.array_equal(host(got), want)
 
 
+# rows whose last four pixels are not a group of their own, and rows of fewer
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 6, 7, 9, 75, 299])
+def test_quantize_image_rows(B, W):
+    rng = np.random.default_rng(W)
+    r = (rng.standard_normal((3, 5, W, 3)) * 2).astype(np.float32)
+    want = np.full((3, 8, W + 3, 4), 77, np.int8)
+    want[:, 2:7, 1:1 + W, :3], want[:, 2:7, 1:1 + W, 3] = orc.Q(r, np.float32(0.021), 7), 0
+    frame = torch.full(want.shape, 77, dtype=torch.int8, device="cuda")
+    B.quantize_image(dev(r), 0.021, 7, frame, 2, 1)
+    assert np.array_equal(host(frame), want)
+
+
 # ------------------------------------------------------------------ unsigned activations
 def _stored(u8):
     """unsigned codes -> the stored form (code - 128 in an int8 byte)."""
