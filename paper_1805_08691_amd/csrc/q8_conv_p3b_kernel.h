@@ -1,5 +1,5 @@
 // The block-tiled build of the persistent 3x3 family (Eq. x / Eq. A' of arxiv 1805.08691):
-// 3x3, stride 1, padding 0 or 1, C = 64 or 32 input channels, maps of any width.  A workgroup has 64 output channels
+// 3x3, stride 1, padding 0 or 1, C = 32, 64 or 128 input channels (128: plain codes), maps of any width.  A workgroup has 64 output channels
 // (32 where K <= 32); layers of more are as many sets of walkers.
 //
 // The persistent 3x3 kernel (q8_conv_p3_kernel.h) cuts the output into runs of 128 consecutive
@@ -14,13 +14,14 @@
 //
 // What bounds it is the LDS: a fragment of 1 KB per MFMA of 32 clocks and wavefront is all that four
 // wavefronts can read.  So a wavefront keeps its 32 channels' filters in registers for the whole launch
-// (72 of them, 36 where C = 32), and an MFMA tile being two rows of the block, the rows that tap
+// (72 of them, 36 where C = 32, 144 where C = 128: all of the 256 that two wavefronts per SIMD leave each), and an MFMA tile being two rows of the block, the rows that tap
 // row r reads for one tile are those that row r - 2 reads for the next: five fragments serve the six
 // (tap row, tile) pairs of a tap column.  30 LDS reads a tile and wavefront instead of 54, and nobody
 // waits for a tile's stores.  64 -> 64 on 300 x 300 x 32 images 160 -> 133 us, on 56 x 56 x 32 9.2 -> 8.9;
 // 32 -> 64 on 147 x 147 x 32 34.5 us in the general kernel (half a step per tap), 20.5 here, 32 -> 32 29.2 and
 // 15.6 (48 MB: 9.3 us of a copy).  More than 64 channels, the best general build and this one: 64 -> 128 on
-// 150 x 150 x 32 73.1 and 58.4, 64 -> 256 on 56 x 56 x 32 24.0 and 19.6, 32 -> 96 on 112 x 112 x 32 29.2 and 21.5.
+// 150 x 150 x 32 73.1 and 58.4, 64 -> 256 on 56 x 56 x 32 24.0 and 19.6, 32 -> 96 on 112 x 112 x 32 29.2 and 21.5,
+// 128 -> 128 on 150 x 150 x 32 128 and 101 (2.1 POP/s).
 //
 // POOL: the 2x2 maximum with stride 2 behind the layer in the same launch.  Blocks begin on even rows and columns,
 // so every window lies in one staging tile: two rows of it in the lane that stores them, the other two in a lane
@@ -44,7 +45,8 @@ struct P3bShape {
   static constexpr int PATCH_BYTES = PL * NW * 1024;
   static constexpr int S_BYTES = BP * BC;                        // staging: codes out
   // (the filters pass through LDS on their way to the registers, behind the first patch buffer)
-  static constexpr int A_BYTES = 9 * BC * CB, A_LOADS = A_BYTES / 1024;
+  static constexpr int A_TAPS = CB <= 64 ? 9 : 3;                // at a time: 128 channels' nine would leave one workgroup a CU
+  static constexpr int A_BYTES = A_TAPS * BC * CB, A_LOADS = A_BYTES / 1024;
   static constexpr int LDS_BYTES = PATCH_BYTES + (PATCH_BYTES + S_BYTES > A_BYTES ? PATCH_BYTES + S_BYTES : A_BYTES);
 };
 
@@ -91,11 +93,13 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   // Slot of 16-byte chunk c in row rho, of the filters and, for 32 channels, of the patch: c ^ ((rho >> 2) & 3)
   // (32 channels: c ^ ((rho >> 3) & 1)), so that sixteen consecutive rows read at one chunk touch every bank once.
   auto slot_of = [](int rho, int chunk) {
-    return CHUNKS == 4 ? chunk ^ ((rho >> 2) & 3) : chunk ^ ((rho >> 3) & 1);
+    return CHUNKS == 8 ? chunk ^ ((rho >> 1) & 7) : CHUNKS == 4 ? chunk ^ ((rho >> 2) & 3) : chunk ^ ((rho >> 3) & 1);
   };
-  // The patch of 64 channels by its column x alone: an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and
+  // The patch of 64 and more channels by its column x alone (128: two columns fill the banks): an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and
   // 24-27 together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next.
-  auto patch_slot = [&](int rho, int x, int chunk) { return CHUNKS == 4 ? chunk ^ ((x >> 2) & 3) : slot_of(rho, chunk); };
+  auto patch_slot = [&](int rho, int x, int chunk) {
+    return CHUNKS == 8 ? chunk ^ ((x >> 1) & 7) : CHUNKS == 4 ? chunk ^ ((x >> 2) & 3) : slot_of(rho, chunk);
+  };
   int pr_y[PL], pr_x[PL], pr_off[PL];          // ... and its offset from the block's
 #pragma unroll
   for (int j = 0; j < PL; ++j) {
@@ -130,16 +134,19 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   };
 
   int8_t* const filters = lds + Sh::PATCH_BYTES;
+  auto load_filters = [&](int tap0) {
 #pragma unroll
-  for (int l = 0; l < Sh::A_LOADS; l += NW) {
-    if (l + wave < Sh::A_LOADS) {
-      const int row = ((l + wave) * Sh::RPW) % BC + lane / CHUNKS, tap = (l + wave) * Sh::RPW / BC;
-      const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
-      const int off = ch < p.K ? ch * p.red_len + slot_of(row, lane % CHUNKS) * 16 : kOobOffset;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * CB, 0, 0);
+    for (int l = 0; l < Sh::A_LOADS; l += NW) {
+      if (l + wave < Sh::A_LOADS) {
+        const int row = ((l + wave) * Sh::RPW) % BC + lane / CHUNKS, tap = tap0 + (l + wave) * Sh::RPW / BC;
+        const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
+        const int off = ch < p.K ? ch * p.red_len + slot_of(row, lane % CHUNKS) * 16 : kOobOffset;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * CB, 0, 0);
+      }
     }
-  }
+  };
+  load_filters(0);
   int tile = place / ch_tiles * kNumXcd + blockIdx.x % kNumXcd;
   if (tile < p.n_ptiles) issue_patch(tile, 0);
   v16i bias_v;
@@ -154,11 +161,13 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 
   // patch offsets of this lane's fragments, the same in every tile: fragment q of tap column s is the
   // two block rows from row 2 TP wave_p + q on, shifted by s columns
-  int b_foff[3][NQ][NH];
+  // (from 64 channels on a slot is the column's alone, so the block's rows are a constant apart)
+  constexpr int NQO = CHUNKS >= 4 ? 1 : NQ;
+  int b_foff[3][NQO][NH];
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
+    for (int q = 0; q < NQO; ++q)
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
         const int rho = (wave_p * TP * 2 + q + (frag_row >> 4)) * PW + (frag_row & 15) + s;
@@ -181,15 +190,19 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   };
   // ---- the filters of this wavefront's 32 channels: fragment (tap, half) holds 16 bytes
   v4i af[9][NH];
-  wait_vmcnt<0>();
-  meet();
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+  for (int t0 = 0; t0 < 9; t0 += Sh::A_TAPS) {
+    if (t0) load_filters(t0);
+    wait_vmcnt<0>();
+    meet();
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
-      af[t][h] = *reinterpret_cast<const v4i*>(filters + t * (BC * CB) + (wave_c * 32 + frag_row) * CB +
-                                               slot_of(frag_row, 2 * h + frag_half) * 16);
-  meet();
+    for (int t = 0; t < Sh::A_TAPS; ++t)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        af[t0 + t][h] = *reinterpret_cast<const v4i*>(filters + t * (BC * CB) + (wave_c * 32 + frag_row) * CB +
+                                                      slot_of(frag_row, 2 * h + frag_half) * 16);
+    meet();
+  }
   for (int it = 0; tile < p.n_ptiles; ++it, tile += walkers) {
     const int buf = it & 1;
     const int next = tile + walkers;
@@ -230,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
       for (int h = 0; h < NH; ++h) {
         v4i bf[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) bf[q] = *reinterpret_cast<const v4i*>(pbase + b_foff[s][q][h]);
+        for (int q = 0; q < NQ; ++q) bf[q] = *reinterpret_cast<const v4i*>(pbase + b_foff[s][NQO == 1 ? 0 : q][h] + (NQO == 1 ? q * PW * CB : 0));
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -307,7 +320,8 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 
 inline bool p3b_applicable(const ConvParams& p) {
   return p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 && p.dil_w == 1 &&
-         p.pad_h == p.pad_w && p.pad_h <= 1 && (p.C == 64 || p.C == 32) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
+         p.pad_h == p.pad_w && p.pad_h <= 1 &&
+         (p.C == 64 || p.C == 32 || (p.C == 128 && !is_extended(p))) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
          (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
@@ -349,6 +363,8 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
 template <int EXT>
 int launch_p3b(ConvParams& p, hipStream_t stream) {
   if (p.C == 64) return launch_p3b_build<64, 2, EXT>(p, stream);
+  if constexpr (!EXT)
+    if (p.C == 128) return launch_p3b_build<128, 2, 0>(p, stream);
   if constexpr (!EXT) {                  // (the extended builds are kept to K > 32)
     if (p.K <= 32) return launch_p3b_build<32, 1, 0>(p, stream);
   }

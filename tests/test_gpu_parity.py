@@ -1111,6 +1111,8 @@ def test_pool_i8(B, mode, shape, win, m, slice_):
     ((2, 149, 151), 32, 32, 0, False, (32, 0)),    # 16 x 16 blocks
     ((3, 149, 151), 64, 144, 1, True, (176, 16)),  # several channel tiles, the last with 16 of 64
     ((5, 149, 163), 32, 96, 1, False, (96, 0)),
+    ((1, 299, 301), 128, 80, 1, False, (80, 0)),
+    ((1, 299, 301), 128, 80, 0, True, (112, 16)),
 ])
 def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
     """The block-tiled 3x3 kernel with the 2x2 maximum in its launch: both tensors as by two calls, nothing
