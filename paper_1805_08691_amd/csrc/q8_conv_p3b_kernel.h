@@ -1,5 +1,6 @@
 // The block-tiled build of the persistent 3x3 family (Eq. x / Eq. A' of arxiv 1805.08691):
-// 3x3, stride 1, padding 0 or 1, C = 32, 64 or 128 input channels (128: plain codes), maps of any width.  A workgroup has 64 output channels
+// 3x3, stride 1, padding 0 or 1, C = 32, 64, 80, 96 or 128 input channels (above 64:
+// plain codes), maps of any width.  A workgroup has 64 output channels
 // (32 where K <= 32); layers of more are as many sets of walkers.
 //
 // The persistent 3x3 kernel (q8_conv_p3_kernel.h) cuts the output into runs of 128 consecutive
@@ -21,7 +22,8 @@
 // 32 -> 64 on 147 x 147 x 32 34.5 us in the general kernel (half a step per tap), 20.5 here, 32 -> 32 29.2 and
 // 15.6 (48 MB: 9.3 us of a copy).  More than 64 channels, the best general build and this one: 64 -> 128 on
 // 150 x 150 x 32 73.1 and 58.4, 64 -> 256 on 56 x 56 x 32 24.0 and 19.6, 32 -> 96 on 112 x 112 x 32 29.2 and 21.5,
-// 128 -> 128 on 150 x 150 x 32 128 and 101 (2.1 POP/s).
+// 128 -> 128 on 150 x 150 x 32 128 and 101 (2.1 POP/s).  80 and 96 channels have the patch of 128 with chunks of
+// zeros, and three quarters of its products: 80 -> 192 on 71 x 71 x 32 37.7 (the build chosen before: 43) and 30.1.
 //
 // POOL: the 2x2 maximum with stride 2 behind the layer in the same launch.  Blocks begin on even rows and columns,
 // so every window lies in one staging tile: two rows of it in the lane that stores them, the other two in a lane
@@ -58,13 +60,16 @@ struct P3bPool {
 
 // p.n_ptiles = tiles in all (N * tiles_h * tiles_w); div_img and div_row divide a tile's number by the
 // tiles of an image and of a row of them, n_ctiles (set by launch_p3b).
-template <int CB, int WC, int EXT, bool POOL = false>
+// NH: 32-byte halves of a tap that an MFMA takes; fewer than CB has where C is 80 or 96 (chunks beyond C are zeros).
+template <int CB, int WC, int EXT, bool POOL = false, int NH = CB / 32>
 __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p, const P3bPool pool) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = P3bShape<CB, WC>;
   constexpr int NW = Sh::NW, WP = Sh::WP, TP = Sh::TP, BP = Sh::BP, BC = Sh::BC, CHUNKS = Sh::CHUNKS;
   constexpr int TH = Sh::TH, TW = Sh::TW, PW = Sh::PW, PL = Sh::PL;
-  constexpr int SLOTS = BC / 16, NH = CB / 32, NQ = 2 * TP + 1;
+  constexpr int SLOTS = BC / 16, NQ = 2 * TP + 1;
+  constexpr bool WHOLE = NH == CB / 32;
+  const int tap_bytes = WHOLE ? CB : p.C;
   constexpr int STORES = BP * SLOTS / (NW * 64), ALL_STORES = STORES + POOL;
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int8_t* const patch = lds;
@@ -106,7 +111,9 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
     const int rho = (wave + NW * j) * Sh::RPW + lane / CHUNKS;
     pr_y[j] = rho < Sh::PATCH_PIX ? rho / PW : -4096;            // beyond the patch: never inside
     pr_x[j] = rho % PW;
-    pr_off[j] = (pr_y[j] * W + pr_x[j]) * p.in_cs + patch_slot(rho, pr_x[j], lane % CHUNKS) * 16;
+    const int chunk = patch_slot(rho, pr_x[j], lane % CHUNKS) * 16;
+    if (!WHOLE && chunk >= p.C) pr_y[j] = -4096;
+    pr_off[j] = (pr_y[j] * W + pr_x[j]) * p.in_cs + chunk;
   }
   // tile number -> image and block origin
   auto tile_origin = [&](int tile, int& n, int& h0, int& w0) {
@@ -140,9 +147,10 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
       if (l + wave < Sh::A_LOADS) {
         const int row = ((l + wave) * Sh::RPW) % BC + lane / CHUNKS, tap = tap0 + (l + wave) * Sh::RPW / BC;
         const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
-        const int off = ch < p.K ? ch * p.red_len + slot_of(row, lane % CHUNKS) * 16 : kOobOffset;
+        const int chunk = slot_of(row, lane % CHUNKS) * 16;
+        const int off = ch < p.K && (WHOLE || chunk < p.C) ? ch * p.red_len + chunk : kOobOffset;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * CB, 0, 0);
+            rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * tap_bytes, 0, 0);
       }
     }
   };
@@ -321,11 +329,11 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 inline bool p3b_applicable(const ConvParams& p) {
   return p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 && p.dil_w == 1 &&
          p.pad_h == p.pad_w && p.pad_h <= 1 &&
-         (p.C == 64 || p.C == 32 || (p.C == 128 && !is_extended(p))) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
+         (p.C == 64 || p.C == 32 || ((p.C == 128 || p.C == 96 || p.C == 80) && !is_extended(p))) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
          (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
-template <int CB, int WC, int EXT, bool POOL = false>
+template <int CB, int WC, int EXT, bool POOL = false, int NH = CB / 32>
 int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}) {
   using Sh = P3bShape<CB, WC>;
   const long tiles_w = (p.Wo + Sh::TW - 1) / Sh::TW, tiles_h = (p.Ho + Sh::TH - 1) / Sh::TH;
@@ -336,7 +344,7 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
   const FastDiv img = make_fast_div((unsigned)(tiles_h * tiles_w)), row = make_fast_div((unsigned)tiles_w);
   p.div_img_m = img.m; p.div_img_s = img.s;
   p.div_row_m = row.m; p.div_row_s = row.s;
-  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT, POOL>;
+  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT, POOL, NH>;
   static const int resident = [&]() {
     int per_cu = 0, dev = 0, cus = 256;
     hipDeviceProp_t prop;
@@ -363,8 +371,10 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
 template <int EXT>
 int launch_p3b(ConvParams& p, hipStream_t stream) {
   if (p.C == 64) return launch_p3b_build<64, 2, EXT>(p, stream);
-  if constexpr (!EXT)
+  if constexpr (!EXT) {
     if (p.C == 128) return launch_p3b_build<128, 2, 0>(p, stream);
+    if (p.C > 64) return launch_p3b_build<128, 2, 0, false, 3>(p, stream);
+  }
   if constexpr (!EXT) {                  // (the extended builds are kept to K > 32)
     if (p.K <= 32) return launch_p3b_build<32, 1, 0>(p, stream);
   }

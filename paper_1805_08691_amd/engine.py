@@ -867,7 +867,7 @@ class Engine:
             return us > 8.5 * len(ops)
         if self.unsigned or self.per_channel:
             return us > 7.7 * len(ops)
-        return us > 5.38 * len(ops) + 2.2 * levels
+        return us > 5.31 * len(ops) + 2.2 * levels   # (5.38 before 3x3 layers of 80 channels ran, and are estimated, on blocks)
 
     def _plannable(self, x, dequant):
         """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and

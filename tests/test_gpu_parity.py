@@ -1113,6 +1113,8 @@ def test_pool_i8(B, mode, shape, win, m, slice_):
     ((5, 149, 163), 32, 96, 1, False, (96, 0)),
     ((1, 299, 301), 128, 80, 1, False, (80, 0)),
     ((1, 299, 301), 128, 80, 0, True, (112, 16)),
+    ((3, 149, 167), 80, 144, 0, False, (144, 0)),  # filters and patches of less than their rows
+    ((2, 149, 167), 96, 80, 1, True, (80, 0)),
 ])
 def test_maximum_behind_a_layer(B, shape, C, K, pad, ceil, slice_):
     """The block-tiled 3x3 kernel with the 2x2 maximum in its launch: both tensors as by two calls, nothing
