@@ -71,9 +71,18 @@ struct Args {
     if (PyErr_Occurred()) ok = false;
     return ok ? static_cast<T*>(p) : nullptr;
   }
-  int8_t* i8(int i, long* n = nullptr) { return tensor<int8_t>(i, at::kChar, g_int8, n); }
+  // A tensor whose elements count: None has no number of them, and is none of length 0.
+  template <typename T>
+  T* counted(int i, at::ScalarType type, PyObject* dtype, long* elements) {
+    if (ok && a[i] == Py_None) {
+      Py_XDECREF(PyObject_GetAttrString(a[i], "numel"));       // the exception that this raises
+      ok = false;
+    }
+    return tensor<T>(i, type, dtype, elements);
+  }
+  int8_t* i8(int i) { return tensor<int8_t>(i, at::kChar, g_int8); }
   int32_t* i32(int i) { return tensor<int32_t>(i, at::kInt, g_int32); }
-  float* f32(int i, long* n = nullptr) { return tensor<float>(i, at::kFloat, g_float32, n); }
+  float* f32(int i) { return tensor<float>(i, at::kFloat, g_float32); }
   float factor(int i) {
     if (!ok) return 0.0f;
     const double v = PyFloat_AsDouble(a[i]);
@@ -214,7 +223,7 @@ PyObject* maxabs(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (!count(n, 2)) return nullptr;
   Args g{args};
   long len = 0;
-  const float* x = g.f32(0, &len);
+  const float* x = g.counted<float>(0, at::kFloat, g_float32, &len);
   float* m = g.f32(1);
   void* s = g.stream();
   return finish(g, [&] { return ((decltype(&q8_calibrate_maxabs))g_fn[kMaxabs])(x, (size_t)len, m, s); });
@@ -225,7 +234,7 @@ PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (!count(n, 4)) return nullptr;
   Args g{args};
   long len = 0;
-  const float* r = g.f32(0, &len);
+  const float* r = g.counted<float>(0, at::kFloat, g_float32, &len);
   const float q = g.factor(1);
   if (g.ok && !PyLong_Check(args[2])) {
     PyErr_SetString(PyExc_TypeError, "p: an int");
@@ -242,7 +251,7 @@ PyObject* dequantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (!count(n, 3)) return nullptr;
   Args g{args};
   long len = 0;
-  const int8_t* z = g.i8(0, &len);
+  const int8_t* z = g.counted<int8_t>(0, at::kChar, g_int8, &len);
   const float q = g.factor(1);
   float* r = g.f32(2);
   void* s = g.stream();

@@ -353,6 +353,47 @@ def test_layer_calls_raise_for_tensors_without_storage():
     assert len(seen) == 5
 
 
+@pytest.fixture
+def passes():
+    """Max-abs, Eq. Q and Eq. D of the binding on host memory; the list of what reaches the library."""
+    import torch
+    seen = []
+
+    def ptr(t, dtype=None):                     # the checks of the binding, without a device
+        if t is None:
+            return None
+        assert t.is_contiguous() and t.dtype is dtype
+        return t.data_ptr()
+    vp, sz = C.c_void_p, C.c_size_t
+    recorders = [C.CFUNCTYPE(C.c_int, *types)(lambda *a: seen.append(a) or 0) for types in (
+        (vp, sz, vp, vp), (vp, sz, C.c_float, C.c_int, vp, vp), (vp, sz, C.c_float, vp, vp))]
+    types = (B.ConvDesc, torch.int8, torch.int32, torch.float32, torch.uint8)
+    layers = [C.cast(f, vp).value for f in (B.lib.q8_conv_int8, B.lib.q8_conv_u8, B.lib.q8_conv_int8_per_channel,
+                                            B.lib.q8_conv_int8_real_output, B.lib.q8_conv_f32_observed_spread)]
+    bind = lambda *f: B._q8call.bind(*f[:3], *types, *layers, *(C.cast(p, vp).value for p in f[3:]))
+    bind(ptr, lambda: 0, lambda device: 0, *recorders)
+    yield seen
+    bind(B._ptr, B._device, B._raw_stream, B.lib.q8_calibrate_maxabs, B.lib.q8_quantize, B.lib.q8_dequantize)
+
+
+def test_passes_need_the_tensor_that_they_read(passes):
+    """None has no elements to count: refused, and not taken for a tensor of length 0."""
+    import torch
+    z, r, slot = torch.zeros(6, dtype=torch.int8), torch.zeros(6), torch.zeros(1)
+    for call in (lambda t: B.calibrate_maxabs(t, slot), lambda t: B.quantize(t, 0.5, 7, out=z),
+                 lambda t: B.dequantize(t, 0.5, out=r)):
+        with pytest.raises(AttributeError):
+            call(None)
+    assert not passes
+    B.calibrate_maxabs(r, slot), B.quantize(r, 0.5, 7, out=z), B.dequantize(z, 0.25, out=r)
+    a, b, c = r.data_ptr(), z.data_ptr(), slot.data_ptr()
+    assert passes == [(a, 6, c, None), (a, 6, 0.5, 7, b, None), (b, 6, 0.25, a, None)]
+    with pytest.raises(AssertionError):
+        B.quantize(z, 0.5, 7, out=z)
+    B.calibrate_maxabs(r[:0], slot)                # empty: the library's own answer
+    assert passes[3][1:3] == (0, c)
+
+
 def test_layer_calls_take_flags_as_int_does():
     d = B.ConvDesc(1, 4, 4, 16, 16, 1, 1)
     for bad in (None, "no number", []):
