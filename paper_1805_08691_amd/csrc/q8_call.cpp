@@ -83,11 +83,45 @@ struct Args {
   int8_t* i8(int i) { return tensor<int8_t>(i, at::kChar, g_int8); }
   int32_t* i32(int i) { return tensor<int32_t>(i, at::kInt, g_int32); }
   float* f32(int i) { return tensor<float>(i, at::kFloat, g_float32); }
+  // The number inside an object of that ctypes type; null, with the exception as it is, for any other.
+  static PyObject* boxed(PyObject* v, const char* type) {
+    PyObject *kind, *error, *trace;
+    PyErr_Fetch(&kind, &error, &trace);
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    PyObject* t = ctypes ? PyObject_GetAttrString(ctypes, type) : nullptr;
+    PyObject* n = t && PyObject_IsInstance(v, t) == 1 ? PyObject_GetAttrString(v, "value") : nullptr;
+    Py_XDECREF(ctypes);
+    Py_XDECREF(t);
+    PyErr_Clear();
+    if (!n) {
+      PyErr_Restore(kind, error, trace);
+      return nullptr;
+    }
+    Py_XDECREF(kind);
+    Py_XDECREF(error);
+    Py_XDECREF(trace);
+    return n;
+  }
+  // As ctypes takes a c_float: whatever has __float__ or __index__, and its own objects.
   float factor(int i) {
     if (!ok) return 0.0f;
-    const double v = PyFloat_AsDouble(a[i]);
-    if (v == -1.0 && PyErr_Occurred()) ok = false;
+    double v = PyFloat_AsDouble(a[i]);
+    if (v == -1.0 && PyErr_Occurred()) {
+      PyObject* n = boxed(a[i], "c_float");
+      if (n) v = PyFloat_AsDouble(n);
+      Py_XDECREF(n);
+    }
+    if (PyErr_Occurred()) ok = false;
     return (float)v;
+  }
+  int integer(int i) {                       // ... and a c_int: whatever has __index__
+    if (!ok) return 0;
+    PyObject* n = PyNumber_Index(a[i]);
+    if (!n) n = boxed(a[i], "c_int");
+    const int v = n ? (int)PyLong_AsUnsignedLongMask(n) : 0;
+    Py_XDECREF(n);
+    if (PyErr_Occurred()) ok = false;
+    return v;
   }
   int flag(int i) {
     if (!ok) return 0;
@@ -236,11 +270,7 @@ PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
   long len = 0;
   const float* r = g.counted<float>(0, at::kFloat, g_float32, &len);
   const float q = g.factor(1);
-  if (g.ok && !PyLong_Check(args[2])) {
-    PyErr_SetString(PyExc_TypeError, "p: an int");
-    g.ok = false;
-  }
-  const int p = g.flag(2);
+  const int p = g.integer(2);
   int8_t* z = g.i8(3);
   void* s = g.stream();
   return finish(g, [&] { return ((decltype(&q8_quantize))g_fn[kQuantize])(r, (size_t)len, q, p, z, s); });

@@ -394,6 +394,25 @@ def test_passes_need_the_tensor_that_they_read(passes):
     assert passes[3][1:3] == (0, c)
 
 
+def test_passes_take_numbers_as_ctypes_does(passes):
+    import numpy as np
+    import torch
+    r, z = torch.zeros(4), torch.zeros(4, dtype=torch.int8)
+    for p in (7, True, np.int64(7), np.uint8(3), torch.tensor(5), 2**32 + 6, C.c_int(4)):
+        B.quantize(r, 0.5, p, out=z)
+    assert [a[3] for a in passes] == [7, 1, 7, 3, 5, 6, 4]
+    for p in (7.0, np.float32(7), None, "7", C.c_float(7)):
+        with pytest.raises(TypeError):
+            B.quantize(r, 0.5, p, out=z)
+    passes.clear()
+    for q in (0.5, 2, np.float32(0.5), np.int64(3), torch.tensor(0.25), C.c_float(0.125)):
+        B.quantize(r, q, 7, out=z), B.dequantize(z, q, out=r)
+    assert [a[2] for a in passes] == [0.5, 0.5, 2, 2, 0.5, 0.5, 3, 3, 0.25, 0.25, 0.125, 0.125]
+    for q in (None, "0.5", 1j):
+        with pytest.raises(TypeError):
+            B.dequantize(z, q, out=r)
+
+
 def test_layer_calls_take_flags_as_int_does():
     d = B.ConvDesc(1, 4, 4, 16, 16, 1, 1)
     for bad in (None, "no number", []):
