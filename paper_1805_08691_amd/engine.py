@@ -847,11 +847,13 @@ class Engine:
         """Concurrent pipelines hide one launch's latency and tail behind the other's work, and cost
         a second set of launches (in a recorded graph also a dependency per launch): worth it
         where the layers' time on the whole batch is well above the latencies of the layers and of the
-        levels they form (at least a launch each).  Measured (us with one and with two; the rule was fitted
-        before bottleneck blocks were one launch and counts their layers as three): ResNet-50 16 images
-        320 / 334, 19: 357 / 357, 21: 367 / 379, 22: 387 / 382, 24: 406 / 409, 28: 477 / 459; Inception-v3 17
-        images 553 / 555, 18: 593 / 549, at 235 pixels 28 images 561 / 565, 32: 569 / 560; the detector 2 images
-        264 / 272, 4: 361 / 340, 5: 395 / 396, 6: 471 / 430.  Layers with unsigned codes or per-channel scales
+        levels they form (at least a launch each).  Fitted to both times of 285 steps around the crossing
+        (ResNet-50 at 160 to 224 pixels, Inception-v3 at 235 to 299, the detector at 268 to 300): by the choice the
+        steps take 1.002, 1.002 and 1.02 of the better one's time, 1.08 at worst.  A bottleneck block counts as its
+        three layers though it is one launch.  us with one and with two: ResNet-50 18 images 325 / 326, 20: 358 / 354,
+        22: 386 / 377, at 176 pixels 28 images 377 / 349, at 160 pixels 36 images 332 / 333; Inception-v3 17 images
+        558 / 557, 18: 575 / 527, at 279 pixels 20 images 497 / 544, at 235 pixels 30 images 553 / 549, 32: 559 / 546;
+        the detector 4 images 336 / 326, 5: 361 / 383, 6: 432 / 412.  Layers with unsigned codes or per-channel scales
         cannot share a launch, so a level counts as its layers: ResNet-50 16 images 341 / 361 and 344 / 361, 20:
         406 / 398 and 404 / 392, 22: 448 / 428 and 446 / 420; at 160 pixels 40 images 406 / 397 and 407 / 391,
         48: 480 / 446 and 487 / 453."""
@@ -867,7 +869,7 @@ class Engine:
             return us > 8.5 * len(ops)
         if self.unsigned or self.per_channel:
             return us > 7.7 * len(ops)
-        return us > 5.31 * len(ops) + 2.2 * levels   # (5.38 before 3x3 layers of 80 channels ran, and are estimated, on blocks)
+        return us > 5.59 * len(ops) + 1.6 * levels
 
     def _plannable(self, x, dequant):
         """Not with the multi-layer kernels, and only for a batch of exactly the net's shape and

@@ -221,7 +221,10 @@ def test_pipelines_of_per_channel_layers_follow_the_unsigned_rule():
     (wl.resnet50, 224, 16, False), (wl.resnet50, 224, 21, True), (wl.resnet50, 160, 32, False),
     (wl.resnet50, 160, 48, True), (wl.inception_v3, 299, 17, False), (wl.inception_v3, 299, 18, True),
     (wl.inception_v3, 235, 28, False), (wl.inception_v3, 235, 32, True), (wl.ssd300_vgg16, 300, 2, False),
-    (wl.ssd300_vgg16, 300, 4, True), (wl.ssd300_vgg16, 270, 3, False)])
+    (wl.ssd300_vgg16, 300, 4, True), (wl.ssd300_vgg16, 270, 3, False),
+    # times of one and of two, us: 377 and 349, 361 and 341, 341 and 332; 497 and 544, 583 and 546
+    (wl.resnet50, 176, 28, True), (wl.resnet50, 180, 25, True), (wl.resnet50, 196, 20, True),
+    (wl.inception_v3, 279, 20, False), (wl.inception_v3, 259, 26, True)])
 def test_pipelines_of_layers_that_share_launches(net, image, batch, two):
     """The batches around the measured crossings (the fused head as a deployed model has it)."""
     assert _two_pipelines(net(image=image), batch, fuse_head=True) == two
