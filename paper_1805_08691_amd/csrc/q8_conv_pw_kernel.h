@@ -28,7 +28,7 @@
 namespace q8 {
 namespace {
 
-constexpr int kNonTemporal = 2;          // cache policy of a buffer store
+constexpr int kNonTemporal = 2;          // cache policy of a buffer store (0: through the caches)
 
 template <int TC, int KS>
 struct PwShape {
@@ -40,10 +40,14 @@ struct PwShape {
   static constexpr int LDS_BYTES = A_BYTES + 2 * B_BYTES + 2 * S_BYTES;
 };
 
-// DEQ: Eq. D of the codes beside them, from the staging tile too: 16 bytes a lane, whole rows of the channel tile, past
-// the caches (nobody in the step reads them).  64 -> 256 with a residual on 56 x 56 x 32 images, 103 MB of values: 29.7
-// us as two launches, 22.4 as one; its 160 MB take 25 of a copy from and to HBM.
-template <int TC, int KS, int EXT, bool DEQ = false>
+// DEQ: Eq. D of the codes beside them, from the staging tile too: 16 bytes a lane, whole rows of the channel tile.
+// 64 -> 256 with a residual on 56 x 56 x 32 images, 103 MB of values: 32.6 us as two launches, 25.3 as one; its 160 MB
+// take 25 of a copy from and to HBM.  2: past the caches, where q8_past_cache says so.  us through the caches and past
+// them, for this launch alone, with a max-abs of the values behind it, with a pass behind it that reads and writes them:
+// 64 -> 256, 10 MB of values 6.0 / 5.6, 11.7 / 11.9, 12.5 / 12.6; 40 MB 11.9 / 11.0, 22.5 / 23.6, 25.1 / 27.8; 67 MB
+// 17.4 / 16.4, 28.7 / 30.2, 37.4 / 39.5; 206 MB 67.4 / 48.0, 86.4 / 83.0, 143 / 137; 128 -> 512, 51 MB 14.6 / 14.3,
+// 25.3 / 27.0, 31.3 / 33.2; 103 MB 27.0 / 26.1, 43.4 / 45.7, 57.0 / 58.1.
+template <int TC, int KS, int EXT, int DEQ = 0>
 __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = PwShape<TC, KS>;
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(256) void conv_i8_pw_kernel(const ConvParams p) {
             v[e] = __builtin_bit_cast(int, p.q_deq * (float)(int8_t)(codes >> (8 * e)));
           __builtin_amdgcn_raw_buffer_store_b128(
               v, rsrc_d, pix0 + row < M && ch0 + quad * 4 < p.K ? (row * p.out_cs + quad * 4) * 4 : kOobOffset, 0,
-              kNonTemporal);
+              DEQ == 2 ? kNonTemporal : 0);
         }
       }
     }
@@ -295,10 +299,12 @@ bool pw_applicable(const ConvParams& p) {
          (long)p.M * p.in_cs < 0x7fffffffL && p.out_cs < 0x7fffffff / 128;
 }
 
-template <int TC, int KS, int EXT, bool DEQ = false>
+template <int TC, int KS, int EXT, int DEQ = 0>
 int launch_pw(ConvParams& p, hipStream_t stream) {
   if constexpr (!EXT && !DEQ) {
-    if (p.y_deq) return launch_pw<TC, KS, EXT, true>(p, stream);
+    if (p.y_deq)
+      return q8_past_cache((size_t)p.M * p.K * sizeof(float)) ? launch_pw<TC, KS, EXT, 2>(p, stream)
+                                                              : launch_pw<TC, KS, EXT, 1>(p, stream);
   }
   using Sh = PwShape<TC, KS>;
   p.n_ptiles = (p.M + Sh::BP - 1) / Sh::BP;

@@ -20,7 +20,6 @@ using q8::quant1_fast;
 constexpr int kThreads = 256;
 constexpr int kMaxBlocks = 256 * 8;   // 256 CUs x 8 resident blocks
 constexpr int kInFlight = 8;          // 16-byte vectors of a lane per chunk
-constexpr size_t kCachedBytes = (size_t)1 << 28;      // the memory-side cache
 
 inline int blocks_for(size_t work_items) {
   size_t b = (work_items + kThreads - 1) / kThreads;
@@ -310,10 +309,12 @@ __global__ void requant_scales_kernel(float q_x, const float* __restrict__ q_w, 
 // one tensor.  add: 128 for unsigned codes stored minus 128, else 0.
 //
 // Bound by memory: 1 byte read and 4 written per value, 6.4 to 7 TB/s.  A list whose values would fill a quarter of the
-// memory-side cache is written past it (PAST, non-temporal stores): 103 MB of values 19.9 us and 17.1, 51 MB 10.4
-// and 8.9, 205 MB 37.6 and 37.3, but max-abs, Eq. Q and this one in turn on 205 MB 134 us and 105 for the three, as
-// the next pass does not have to wait for these values to be written back.  (Who reads all of them
-// next pays 1.5 to 3 us of it back: 103 MB 36.4 and 38.2 both.)
+// memory-side cache is written past it (PAST, non-temporal stores).  us through the cache and past it, for this launch
+// alone, with a max-abs of the values behind it, with a pass behind it that reads and writes them: 80 MB of values
+// 16.7 / 14.5, 30.8 / 31.6, 43.3 / 43.1; 100 MB 20.0 / 18.3, 36.0 / 37.3, 50.7 / 50.0; 150 MB 28.5 / 27.8, 50.8 / 52.5,
+// 74.8 / 72.3; 205 MB 38.1 / 37.5, 67.8 / 71.3, 115.7 / 115.8; 300 MB 66.8 / 53.8, 117.9 / 100.8, 169.6 / 166.3.  And
+// max-abs, Eq. Q and this one in turn on 205 MB 134 and 105 for the three: the next pass does not have to
+// wait for these values to be written back.
 constexpr int kDeqBlock = 4096, kDeqMax = 16;
 struct DeqList {
   int n;
@@ -401,7 +402,7 @@ int dequantize_list(const q8_op* ops, int n, hipStream_t stream) {
   size_t blocks = 0;
   auto flush = [&]() -> int {
     if (l.n == 0) return Q8_OK;
-    const bool past = blocks * kDeqBlock >= kCachedBytes / 16;
+    const bool past = q8_past_cache(blocks * kDeqBlock * sizeof(float));
     hipLaunchKernelGGL((past ? dequantize_list_kernel<true> : dequantize_list_kernel<false>), dim3((unsigned)blocks),
                        dim3(kThreads), 0, stream, l);
     l.n = 0;
@@ -465,7 +466,7 @@ int q8_calibrate_maxabs(const float* x_dev, size_t n, float* maxabs_dev, void* s
   Q8_REQUIRE(x_dev != nullptr, Q8_EINVAL);
   Q8_REQUIRE(q8_aligned(x_dev, 4) && q8_aligned(maxabs_dev, 4), Q8_EALIGN);
   const size_t head = head_elems(x_dev, 4, n);
-  const bool runs = n > kCachedBytes / 4;
+  const bool runs = n > kQ8CacheBytes / 4;
   const int blocks = blocks_for((n + 15) / 16);
   hipLaunchKernelGGL((runs ? maxabs_kernel<true> : maxabs_kernel<false>), dim3(blocks), dim3(kThreads), 0,
                      (hipStream_t)stream, x_dev, n, head, reinterpret_cast<unsigned*>(maxabs_dev));

@@ -2710,7 +2710,9 @@ def test_conv_extended_builds(B, idx):
 # without a residual; values that are 4-byte aligned only, which that family does not take
 @pytest.mark.parametrize("pixels,C,K,cs,off,shift", [
     (40961, 64, 80, 0, 0, 0), (40961, 64, 64, 96, 16, 0), (41999, 128, 80, 0, 0, 0), (61441, 128, 272, 0, 0, 0),
-    (128129, 256, 368, 400, 32, 0), (40961, 64, 80, 0, 0, 1)])
+    (128129, 256, 368, 400, 32, 0), (40961, 64, 80, 0, 0, 1),
+    # the last size that is written through the caches, and the first past them
+    (65535, 64, 256, 0, 0, 0), (65536, 64, 256, 272, 16, 0), (52427, 128, 320, 336, 0, 0), (52429, 128, 320, 0, 0, 0)])
 def test_pointwise_with_dequantized_output(B, pixels, C, K, cs, off, shift):
     d = B.ConvDesc(1, 1, pixels, C, K, 1, 1, relu=1, out_c_stride=cs, out_c_off=off)
     assert "pw_kernel" in B.conv_variant(d)
