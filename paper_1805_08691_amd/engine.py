@@ -730,21 +730,24 @@ class Engine:
         ops = list(net.ops)
         if with_x and self.head:
             ops = [o for o in ops if o is not self.head[1]]
+        parts = self.parts
+        if len(parts) > 1 and not self._pipelines_pay(ops):
+            parts = [(0, self.N)]
         fused = {name: self._dequant_writer(name) for name in names}
         # Eq. D inside the launch that writes the tensor: asked for, free (a launch of the
         # latency family finishes four channels per lane whatever it writes), or a saved pass (the pointwise family
         # writes the values in whole rows from LDS: bottleneck block on 56 x 56, 32 images 69 -> 62 us, 64 images
         # 141 -> 132), here where that is worth more than the layer's block in one launch (256 channels, us with
         # the block and so: 75 thousand pixels 49.6 / 48.9, 102 thousand 67.5 / 62.0, 150 thousand 105.9 / 100.0; 48
-        # thousand 36.0 / 36.7, 12.5 thousand 18.4 / 22.2), below where it ends no such block
+        # thousand 36.0 / 36.7, 12.5 thousand 18.4 / 22.2), below where it ends no such block.  By the launch of every
+        # part: half a batch may run on another family, whose tail writes the values four at a time
         could = {name: self._dequant_writer(name, any_engine=True) for name in names}
-        writes = lambda w, family: w is not None and family in B.conv_variant(self.conv_desc(w, self.N))
+        writes = lambda w, family: w is not None and all(
+            family in B.conv_variant(self.conv_desc(w, n)) for _, n in parts)
         fused.update({name: w for name, w in could.items() if fused[name] is None and (
-            writes(w, "direct") or (writes(w, "pw_kernel") and self.act[name].numel() >= 1 << 24))})
+            writes(w, "direct") or
+            (writes(w, "pw_kernel") and self.N * self.act[name].shape[1:].numel() >= 1 << 24))})
         fused = {name: w for name, w in fused.items() if w is not None}
-        parts = self.parts
-        if len(parts) > 1 and not self._pipelines_pay(ops):
-            parts = [(0, self.N)]
         x_slots, out_slots = [], []
 
         def add(into, o, stream=0, group=0):

@@ -155,6 +155,26 @@ def test_planned_step_takes_buffers_longer_than_the_batch(recorded):
         step(None, {out: r[:1]})
 
 
+@pytest.mark.parametrize("H, batch, pipelines, together", [(90, 4, 1, True), (90, 4, 2, False), (128, 4, 2, True),
+                                                           (40, 4, 1, False)])
+def test_values_beside_the_codes_are_by_the_launches_of_the_parts(recorded, H, batch, pipelines, together):
+    """Eq. D joins a 1x1 layer where each part's launch is of the family that writes whole rows: 256 -> 1024 is from
+    32 thousand pixels on, 90 x 90 on four images, and two of those are on the general kernel."""
+    net = wl.Network("wide", "x")
+    net.tensor("x", H, H, 256)
+    net.tensor("y", H, H, 1024)
+    wl._conv(net, "a", "x", 1024, 1, 1, dst="y")
+    net.outputs = ["y"]
+    eng, _ = recorded(net, batch)
+    eng.parts = [(0, batch // 2), (batch // 2, batch - batch // 2)]
+    eng._pipelines_pay = lambda ops: pipelines == 2
+    (_, layers, behind), _, values, _ = eng._plan(False, ("y",))
+    assert [o.d.N for o in layers] == [batch // pipelines] * pipelines
+    assert [bool(o.flags & B.OPF_DEQUANT) for o in layers] == [together] * pipelines
+    assert [o.kind for o in behind] == ([] if together else [B.OP_DEQUANTIZE])
+    assert len(values) == (pipelines if together else 1)
+
+
 def test_planned_step_needs_no_factor_of_a_real_valued_output(recorded):
     net = wl.bottleneck_block()
     out = net.outputs[0]

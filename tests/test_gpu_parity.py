@@ -1431,6 +1431,66 @@ def test_run_step_one_and_two_pipelines_and_serial(B):
         assert np.array_equal(got, host(eng.dequantize(o)))       # fused or not: the same bits
 
 
+@pytest.mark.parametrize("batch, pipelines", [(21, 1), (22, 1), (43, 2)])
+def test_run_step_values_in_the_last_layers_launch(B, batch, pipelines):
+    """A bottleneck block whose output has 2^24 values or more: Eq. D leaves with the last layer's codes, and the
+    block is three launches.  One image less: the block in one launch, and Eq. D behind it."""
+    from paper_1805_08691_amd.engine import Engine
+    net, params, x, _, q, *_ = _oracle_pipeline(2, 2, True)
+    o = net.outputs[0]
+    eng = Engine(net, batch, n_streams=2)
+    eng._pipelines_pay = lambda ops: pipelines == 2
+    eng.load_params(params)
+    eng.fold()
+    eng.set_factors(q)
+    eng.quantize_weights()
+    eng.allocate()
+    long = eng.act[o].numel() >= 1 << 24
+    assert long == (batch > 20)
+    segments = eng._plan(True, (o,))[0]
+    assert [op.kind for op in segments[2]] == ([] if long else [B.OP_DEQUANTIZE])
+    flags = [op.flags for op in segments[1]]
+    assert len(flags) == 3 * pipelines
+    assert sum(bool(f & B.OPF_DEQUANT) for f in flags) == (pipelines if long else 0)
+    assert sum(bool(f & B.OPF_BLOCK) for f in flags) == (0 if long else pipelines)
+    batches = dev(np.concatenate([x] * (batch // 2 + 1))[:batch])
+    batches *= torch.linspace(0.2, 1.0, batch, device="cuda").view(-1, 1, 1, 1)
+    got = []
+    for serial in (True, False):
+        eng.act[o].fill_(55)
+        out = torch.full(eng.act[o].shape, -7.0, device="cuda")
+        eng.run_step(batches, {o: out}, serial=serial)
+        torch.cuda.synchronize()
+        got.append((eng.act[o].clone(), out))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert torch.equal(got[1][1], got[1][0].float() * torch.full((1,), q[o], device="cuda"))
+    assert len(torch.unique(got[1][0])) > 16
+
+
+def test_run_step_values_of_a_layer_in_no_block(B):
+    """A 1x1 layer that ends no block writes its values beside the codes at any size of its family."""
+    from paper_1805_08691_amd.engine import Engine
+    net = wl.Network("wide", "x")
+    net.tensor("x", 40, 40, 64)
+    net.tensor("y", 40, 40, 256)
+    wl._conv(net, "a", "x", 256, 1, 1, dst="y")
+    net.outputs = ["y"]
+    eng = Engine(net, 8)
+    eng.load_params({op.name: wl.conv_params(2, i, op) for i, op in enumerate(net.convs())})
+    eng.fold()
+    x = torch.randn((8, 40, 40, 64), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    eng.calibrate([x])
+    eng.quantize_weights()
+    eng.allocate()
+    segments = eng._plan(True, ("y",))[0]
+    assert [op.flags for op in segments[1]] == [B.OPF_DEQUANT] and not segments[2]
+    out = torch.empty(eng.act["y"].shape, device="cuda")
+    eng.run_step(x, {"y": out})
+    values, codes = out.clone(), eng.act["y"].clone()
+    eng.run_step(x, {"y": out}, serial=True)
+    assert torch.equal(values, out) and torch.equal(codes, eng.act["y"]) and len(torch.unique(codes)) > 16
+
+
 def test_planned_step_follows_the_engine(B):
     """The planned step equals the layer-by-layer one (``serial``) with the pipelines forced, after
     a factor was set between two steps, and for a batch longer than the engine's."""
