@@ -17,12 +17,13 @@
 // 10 to 40 % slower on large layers; 128 x 128 tiles of four wavefronts, where each fragment is split twice too, 5 %
 // faster there, but with one chain per value further off than the fp32 builds.)  Where tiles are few the operands'
 // way into LDS bounds the layer instead, and the fp32 builds with their smaller tiles stay (f32_split_pays).  Batch 8,
-// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 385 and 318, 38 x 38 512 -> 512 3x3 433 and 323 (107 % of
-// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 200 and 153, 28 x 28 128 -> 128 24.8 and 19.8.
+// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 393 and 342, 38 x 38 512 -> 512 3x3 429 and 329 (105 % of
+// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 199 and 159, 28 x 28 128 -> 128 21.3 and 18.3.
 //
-// The split is exact for zero and for 2^-110 <= |x| < 3.38e38.  Results that are not finite, or below 2^-90
-// and not zero, are therefore summed again in fp32: infinities, NaNs and values that bf16 rounds to infinity
-// give what the fp32 sum gives.
+// The split is exact for zero and for 2^-110 <= |x| < 3.38e38.  Where results are not finite, or below 2^-90
+// and not zero, the workgroup therefore runs its reduction a second time on the fp32 instruction: infinities, NaNs and
+// values that bf16 rounds to infinity give what the fp32 sum gives.  A layer with such sums in every tile takes 2.1
+// times its time (28 x 28 128 -> 128 of NaNs 18 and 42 us).
 #include "q8_conv_f32.h"
 #include "q8_conv_ring_kernel.h"
 
@@ -56,26 +57,7 @@ __device__ __forceinline__ Split3 split3(v4f lo, v4f hi) {
   return {__builtin_bit_cast(v8bf, h), __builtin_bit_cast(v8bf, m), __builtin_bit_cast(v8bf, l)};
 }
 
-// One output value's sum in fp32.
-__device__ __forceinline__ float f32_sum(const F32Params& p, int pix, int k) {
-  const int n = fast_div(pix, p.by_img.m, p.by_img.s), rem = pix - n * (p.Ho * p.Wo);
-  const int ho = fast_div(rem, p.by_row.m, p.by_row.s), wo = rem - ho * p.Wo;
-  float v = 0.0f;
-  for (int r = 0; r < p.R; ++r) {
-    const int hi = ho * p.sh - p.ph + r * p.dh;
-    if (hi < 0 || hi >= p.H) continue;
-    for (int s = 0; s < p.S; ++s) {
-      const int wi = wo * p.sw - p.pw + s * p.dw;
-      if (wi < 0 || wi >= p.W) continue;
-      const float* x = p.x + (((size_t)n * p.H + hi) * p.W + wi) * p.C;
-      const float* w = p.w + ((size_t)k * p.R * p.S + r * p.S + s) * p.C;
-      for (int c = 0; c < p.C; ++c) v = fmaf(x[c], w[c], v);
-    }
-  }
-  return v;
-}
-
-// A worwave owns 64 pixels x 64 channels.  Its KW wavefronts take equal runs of the reduction steps, each with a ring of
+// A workgroup owns 64 pixels x 64 channels.  Its KW wavefronts take equal runs of the reduction steps, each with a ring of
 // two steps and all four 32 x 32 tiles, and add their sums through LDS in a fixed order; they do not meet before.
 template <int KW>
 __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Params p) {
@@ -127,16 +109,15 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       b_off[j] = (((n - n0) * p.H + b_hi[j]) * p.W + b_wi[j]) * c_bytes + x_shift + swz<4>(row, lane & 3) * 16;
     }
   }
+  // Behind the rings: whether some sum is taken again.
+  int* const redo = reinterpret_cast<int*>(lds + KW * ST * STAGE_BYTES);
+  if (threadIdx.x == 0) *redo = 0;       // (a barrier follows before anyone sets it)
   int8_t* const ring = lds + wave * ST * STAGE_BYTES;
   // this group's steps, and where the next one to request lies in the reduction
   const int n_st = p.rsc / (BK / 4), n_mine = (n_st + KW - 1) / KW;
-  int st = wave * n_mine;
-  const int st_end = min(st + n_mine, n_st);
+  const int st_end = min((wave + 1) * n_mine, n_st);
   const int dw_step = p.dw * c_bytes, dh_step = p.dh * p.W * c_bytes - p.S * dw_step;
-  int tap = fast_div(st * (BK / 4), p.by_c.m, p.by_c.s), tap_c = st * BK - tap * c_bytes;
-  int tap_r = fast_div(tap, p.by_s.m, p.by_s.s), tap_s = tap - tap_r * p.S;
-  int tap_delta = (tap_r * p.dh * p.W + tap_s * p.dw) * c_bytes;
-  int b_voff[LOADS];
+  int st, tap_c, tap_r, tap_s, tap_delta, b_voff[LOADS];
   auto refresh_tap = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
@@ -145,7 +126,15 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       b_voff[j] = in ? b_off[j] : kOobOffset;
     }
   };
-  refresh_tap();
+  auto begin = [&]() __attribute__((always_inline)) {
+    st = wave * n_mine;
+    const int tap = fast_div(st * (BK / 4), p.by_c.m, p.by_c.s);
+    tap_c = st * BK - tap * c_bytes;
+    tap_r = fast_div(tap, p.by_s.m, p.by_s.s);
+    tap_s = tap - tap_r * p.S;
+    tap_delta = (tap_r * p.dh * p.W + tap_s * p.dw) * c_bytes;
+    refresh_tap();
+  };
   // The loads of the next step into `buf`.  Behind the group's last step the descriptors are empty: zeros, so that
   // every step counts the same loads.
   auto request = [&](int buf) __attribute__((always_inline)) {
@@ -189,12 +178,6 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
     asm volatile("" : "+v"(b_frag[h]));
   }
   v16f acc[T][T], low[T][T];
-#pragma unroll
-  for (int j = 0; j < T; ++j)
-#pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[j][i][e] = low[j][i][e] = 0.0f;
   v4f af[T][2], bf[T][2];
   auto read = [&](int off) __attribute__((always_inline)) {
 #pragma unroll
@@ -209,18 +192,28 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
     __builtin_amdgcn_s_waitcnt(0xc07f);  // the fragments this wavefront has asked for are in registers
     asm volatile("" ::: "memory");
   };
-#pragma unroll
-  for (int i = 0; i < ST; ++i) request(i);
-  wait_vmcnt<(ST - 1) * 2 * LOADS>();
-  meet();
-  read(0);
   using std::integral_constant;
   // One step: its values are in registers or on their way.  Then its buffer is filled again, and the next step's values
   // are read while the last MFMAs run.  Fragments are split beside the MFMAs that do not need them yet: 1.5 % off.
-  auto step = [&](auto buf_c) __attribute__((always_inline)) {
+  // FP32: the products of the fp32 instruction instead.
+  auto step = [&](auto buf_c, auto fp32_c) __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf_c)::value;
+    constexpr bool FP32 = decltype(fp32_c)::value;
     wait_vmcnt<(ST - 2) * 2 * LOADS>();
     meet();
+    if constexpr (FP32) {
+#pragma unroll
+      for (int j = 0; j < T; ++j)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e / 4][e % 4], bf[j][e / 4][e % 4], acc[j][i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      request(BUF);
+      read((BUF + 1) % ST * STAGE_BYTES);
+      return;
+    }
     Split3 a[T], b[T];
     auto mma = [&](int i, int j, int t) __attribute__((always_inline)) {     // product t of tile (i, j)
       v16f& sum = t == 2 ? acc[j][i] : low[j][i];
@@ -247,70 +240,78 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       for (int i = 0; i < T; ++i) mma(i, 1, t);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto pass = [&](auto self, int n, auto buf_c) __attribute__((always_inline)) -> void {
+  auto pass = [&](auto self, int n, auto buf_c, auto fp32_c) __attribute__((always_inline)) -> void {
     constexpr int BUF = decltype(buf_c)::value;
     if constexpr (BUF < ST) {
       if (BUF < n) {
-        step(buf_c);
-        self(self, n, integral_constant<int, BUF + 1>{});
+        step(buf_c, fp32_c);
+        self(self, n, integral_constant<int, BUF + 1>{}, fp32_c);
       }
     }
   };
-  int left = n_mine;
-  for (; left >= ST; left -= ST) pass(pass, ST, integral_constant<int, 0>{});
-  pass(pass, left, integral_constant<int, 0>{});
-  wait_vmcnt<0>();                       // (the loads of steps behind the last: LDS is used again)
-
-  // ---- the tail: quad q of a lane is channels 4 (q % 4) .. of its 16 in channel tile q / 4 % T, pixel tile q / 4 / T
-  __syncthreads();
+  // The whole reduction, its sums into the exchange.  Quad q of a lane is channels 4 (q % 4) .. of its 16 in channel
+  // tile q / 4 % T, pixel tile q / 4 / T; a wavefront finishes quads wave * OWN .., of one channel and one pixel tile.
   float* const xch = reinterpret_cast<float*>(lds);
+  auto reduce = [&](auto fp32_c) __attribute__((always_inline)) {
+    constexpr bool FP32 = decltype(fp32_c)::value;
 #pragma unroll
-  for (int q = 0; q < QUADS; ++q) {
-    v4f v;
+    for (int j = 0; j < T; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      v[e] = acc[q / 4 / T][q / 4 % T][4 * (q % 4) + e] + low[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
-    *reinterpret_cast<v4f*>(xch + ((wave * QUADS + q) * 64 + lane) * 4) = v;
-  }
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][i][e] = low[j][i][e] = 0.0f;
+    begin();
+#pragma unroll
+    for (int i = 0; i < ST; ++i) request(i);
+    wait_vmcnt<(ST - 1) * 2 * LOADS>();
+    meet();
+    read(0);
+    int left = n_mine;
+    for (; left >= ST; left -= ST) pass(pass, ST, integral_constant<int, 0>{}, fp32_c);
+    pass(pass, left, integral_constant<int, 0>{}, fp32_c);
+    wait_vmcnt<0>();                     // (the loads of steps behind the last: LDS is used again)
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+      v4f v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
+        if constexpr (!FP32) v[e] += low[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
+      }
+      *reinterpret_cast<v4f*>(xch + ((wave * QUADS + q) * 64 + lane) * 4) = v;
+    }
+  };
+  auto total = [&](int o) {
+    v4f v = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int g = 0; g < KW; ++g)
+      v += *reinterpret_cast<const v4f*>(xch + ((g * QUADS + wave * OWN + o) * 64 + lane) * 4);
+    return v;
+  };
+  reduce(std::false_type{});
   __syncthreads();
   v4f own[OWN];
 #pragma unroll
-  for (int o = 0; o < OWN; ++o) {
-    own[o] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int g = 0; g < KW; ++g)
-      own[o] += *reinterpret_cast<const v4f*>(xch + ((g * QUADS + wave * OWN + o) * 64 + lane) * 4);
-  }
+  for (int o = 0; o < OWN; ++o) own[o] = total(o);
   auto pixel_of = [&](int o) { return pix0 + (wave * OWN + o) / 4 / T * 32 + (lane & 31); };
   auto channel_of = [&](int o) {
     const int q = wave * OWN + o;
     return ch0 + q / 4 % T * 32 + 16 * (lane >> 5) + 4 * (q % 4);
   };
-  // what the split cannot vouch for, again in fp32
-  bool refine = false;
+  unsigned again = 0;                    // what the split cannot vouch for
 #pragma unroll
   for (int o = 0; o < OWN; ++o)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float a = fabsf(own[o][e]);
-      refine |= !(a < INFINITY && (a >= 0x1p-90f || a == 0.0f));
+      again |= a < INFINITY && (a >= 0x1p-90f || a == 0.0f) ? 0u : 1u << (o * 4 + e);
     }
-  if (refine) {
-    for (int i = 0; i < OWN * 4; ++i) {
-      const int pix = pixel_of(i / 4), k = channel_of(i / 4) + i % 4;
-      if (pix >= p.M || k >= p.K) continue;
-      const float v = f32_sum(p, pix, k);
-#pragma unroll
-      for (int o = 0; o < OWN; ++o)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) own[o][e] = i == o * 4 + e ? v : own[o][e];
-    }
-  }
+  if (again) *redo = 1;
   float m_sum = 0.0f, m_out = 0.0f;
-#pragma unroll
-  for (int o = 0; o < OWN; ++o) {
+  auto finish = [&](int o) __attribute__((always_inline)) {
     const int pix = pixel_of(o), ch = channel_of(o);
-    if (pix >= p.M || ch >= p.K) continue;
+    if (pix >= p.M || ch >= p.K) return;
     v4f v = own[o];
     float* const y = p.y + (size_t)pix * p.out_cs + p.out_off + ch;
     const float* const res = p.res ? p.res + (size_t)pix * p.K + ch : nullptr;
@@ -338,16 +339,32 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
         y[e] = relu_max(u);
       }
     }
-  }
+  };
+#pragma unroll
+  for (int o = 0; o < OWN; ++o)
+    if (!(again >> (o * 4) & 15)) finish(o);
   __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*redo)) {
+    reduce(std::true_type{});
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) {
+      const v4f v = total(o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) own[o][e] = again >> (o * 4 + e) & 1 ? v[e] : own[o][e];
+      if (again >> (o * 4) & 15) finish(o);
+    }
+    __syncthreads();
+  }
   observe_block<KW>(p, m_sum, m_out, reinterpret_cast<float*>(lds));
 #endif
 }
 
 template <int KW>
 int launch_split(F32Params& p, hipStream_t stream) {
-  constexpr int kLdsBytes = KW * kSplitStages * 2 * 64 * kSplitStep;
-  static_assert(kLdsBytes >= KW * 4 * 4096, "the exchange fits the rings");
+  constexpr int kRingBytes = KW * kSplitStages * 2 * 64 * kSplitStep, kFlagBytes = 4;
+  static_assert(kRingBytes == KW * 4 * 4096, "the exchange fits the rings");
+  constexpr int kLdsBytes = kRingBytes + kFlagBytes;
   p.n_ptiles = (p.M + 63) / 64;
   p.n_ctiles = (p.K + 63) / 64;
   const long nblk = (long)p.n_ptiles * p.n_ctiles;

@@ -2153,6 +2153,33 @@ def test_conv_f32_split_builds(B, build, geom, res, slice_):
         assert bool(err.all())
 
 
+@pytest.mark.parametrize("geom", [(8, 28, 28, 128, 128), (4, 41, 43, 256, 192)])      # eight wavefronts a tile, four
+def test_conv_f32_split_is_no_slower_than_the_fp32_instruction_where_it_sums_again(B, geom):
+    """Sums that are no numbers are taken again by the whole workgroup, 16 + 5 instructions' time for 5: a layer of
+    them stays within four times its time, also where only few of a tile's sums are such."""
+    N, H, W, Cc, K = geom
+    g = torch.Generator(device="cuda").manual_seed(5)
+    d = B.ConvDesc(N, H, W, Cc, K, 3, 3, pad_h=1, pad_w=1)
+    assert B.conv_f32_variant(d).startswith("conv_f32_split_kernel")
+    x, w = torch.randn((N, H, W, Cc), device="cuda", generator=g), torch.randn((K, 3, 3, Cc), device="cuda", generator=g)
+    few, y = x.clone(), torch.empty((N, H, W, K), device="cuda")
+    few[:, ::4, ::4, 7] = torch.nan
+
+    def us(t):
+        took = []
+        for _ in range(7):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(4):
+                B.conv_f32_observed(d, t, w, None, None, y, None, None)
+            b.record()
+            b.synchronize()
+            took.append(a.elapsed_time(b))
+        return sorted(took)[3]
+    plain = us(x)
+    assert us(few) < 4 * plain and us(torch.full_like(x, torch.nan)) < 4 * plain and bool(y.isnan().all())
+
+
 @pytest.mark.parametrize("channels", [(64, 64), (12, 8)])       # a build on LDS, a register-fed one
 def test_conv_f32_observed_raises_the_first_value_of_a_slot(B, channels):
     """A slot of any length holds one maximum, in its first value, unless copies are asked for."""
