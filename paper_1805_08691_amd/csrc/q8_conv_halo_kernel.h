@@ -314,6 +314,13 @@ __device__ __forceinline__ void conv_tile_halo3(const ConvParams& p, const int p
   for (; chunk + 1 < n_chunks; ++chunk) {
     Q8_MID(0); Q8_MID(1); Q8_MID(2); Q8_MID(3); Q8_MID(4); Q8_MID(5); Q8_MID(6); Q8_MID(7); Q8_MID(8);
   }
+  if constexpr (TC * TP > 4) {
+    // (Eight MFMA tiles a wavefront: the last chunk's addresses made in front of the loop would not fit the registers;
+    // reloaded, each waits for the filter slabs in flight too.  512 -> 512 on 38 x 38 x 64 193 us, 190 so; 74 x 74 x 7
+    // on 256 channels 34.5, 33.6.)
+#pragma unroll
+    for (int j = 0; j < TP; ++j) asm volatile("" : "+v"(prow[j]), "+v"(pmask[j]));
+  }
   Q8_END(0); Q8_END(1); Q8_END(2); Q8_END(3); Q8_END(4); Q8_END(5); Q8_END(6); Q8_END(7); Q8_END(8);
 #undef Q8_MID
 #undef Q8_END

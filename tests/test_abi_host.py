@@ -3,6 +3,7 @@ rejects bad arguments before anything is launched (so these run without a GPU)."
 import ctypes as C
 import os
 import re
+import struct
 
 import pytest
 
@@ -606,3 +607,30 @@ def test_maxima_that_join_their_layer():
     # ... unless they are ordered with it: the same stream under another index, the legacy default stream's two names
     assert joined(two, 64, 64) == -1 and joined(two, 64, 64, first=1) == 2 and joined(two, None, 1) == -1
     assert joined(two, 64) == -1 and joined(two, 64, 128, first=4) == -1
+
+
+def _kernels():
+    """Metadata of every kernel in the library: the note of each code object of its offload bundles."""
+    msgpack = pytest.importorskip("msgpack")
+    data, magic = open(B.lib._name, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__"
+    for bundle in (m.start() for m in re.finditer(magic, data)):
+        at = bundle + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", data, at - 8)[0]):
+            offset, size, n = struct.unpack_from("<QQQ", data, at)
+            triple, at, elf = data[at + 24:at + 24 + n], at + 24 + n, data[bundle + offset:bundle + offset + size]
+            if b"gfx950" not in triple:
+                continue
+            headers, = struct.unpack_from("<Q", elf, 32)
+            each, count = struct.unpack_from("<HH", elf, 54)
+            for h in range(headers, headers + each * count, each):
+                if struct.unpack_from("<I", elf, h)[0] == 4:                       # PT_NOTE
+                    note, = struct.unpack_from("<Q", elf, h + 8)
+                    name, length = struct.unpack_from("<II", elf, note)
+                    text = note + 12 + (name + 3) // 4 * 4
+                    yield from msgpack.unpackb(elf[text:text + length])["amdhsa.kernels"]
+
+
+def test_tiles_of_the_3x3_family_stay_in_registers():
+    """A register reloaded from scratch waits for every load in flight, the filters requested ahead among them."""
+    found = {k[".name"]: k[".private_segment_fixed_size"] for k in _kernels() if "conv_i8_halo3_kernel" in k[".name"]}
+    assert len(found) >= 18 and not {n: size for n, size in found.items() if size}
