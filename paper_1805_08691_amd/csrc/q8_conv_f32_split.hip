@@ -17,13 +17,16 @@
 // 10 to 40 % slower on large layers; 128 x 128 tiles of four wavefronts, where each fragment is split twice too, 5 %
 // faster there, but with one chain per value further off than the fp32 builds.)  Where tiles are few the operands'
 // way into LDS bounds the layer instead, and the fp32 builds with their smaller tiles stay (f32_split_pays).  Batch 8,
-// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 393 and 342, 38 x 38 512 -> 512 3x3 429 and 329 (105 % of
-// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 199 and 159, 28 x 28 128 -> 128 21.3 and 18.3.
+// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 386 and 355, 38 x 38 512 -> 512 3x3 430 and 346 (100 % of
+// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 198 and 164, 28 x 28 128 -> 128 23.5 and 19.1.
 //
-// The split is exact for zero and for 2^-110 <= |x| < 3.38e38.  Where results are not finite, or below 2^-90
-// and not zero, the workgroup therefore runs its reduction a second time on the fp32 instruction: infinities, NaNs and
-// values that bf16 rounds to infinity give what the fp32 sum gives.  A layer with such sums in every tile takes 2.1
-// times its time (28 x 28 128 -> 128 of NaNs 18 and 42 us).
+// The split is exact for zero and for 2^-110 <= |x| < 3.38e38; of smaller values it loses up to 2^-134 each, of a
+// denormal perhaps all.  So it holds for a sum of at least 2^-60 whose operands are below 2^32 (2^-42 of the sum is lost
+// for each product at worst), and for a sum of zero without denormal operands.  Where a workgroup has other sums
+// (infinities, NaNs and values that bf16 rounds to infinity among them) it runs its reduction a second time on
+// the fp32 instruction, for what the fp32 sum gives; where it has zeros it looks through its operands first.  Noting
+// the largest operand is one instruction for two values and costs 2 % (337 us of the 346 above).  75 x 75 128 -> 256 180 us, with a zero
+// in every tile 218 to 256, of NaNs or of values below 2^-60 326 to 377; the fp32 builds 190 to 210.
 #include "q8_conv_f32.h"
 #include "q8_conv_ring_kernel.h"
 
@@ -38,6 +41,7 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitStep = 64;       // bytes of a row per reduction step
 constexpr int kSplitStages = 2;      // steps of a wavefront's ring
+constexpr float kSplitLeast = 0x1p-60f, kSplitLargest = 0x1p32f;
 
 struct Split3 { v8bf h, m, l; };
 
@@ -109,9 +113,11 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       b_off[j] = (((n - n0) * p.H + b_hi[j]) * p.W + b_wi[j]) * c_bytes + x_shift + swz<4>(row, lane & 3) * 16;
     }
   }
-  // Behind the rings: whether some sum is taken again.
-  int* const redo = reinterpret_cast<int*>(lds + KW * ST * STAGE_BYTES);
-  if (threadIdx.x == 0) *redo = 0;       // (a barrier follows before anyone sets it)
+  // Behind the rings, what some lane has found: a sum that is taken again, a large operand, a sum of zero, a denormal.
+  enum { kAgain, kLarge, kZero, kDenormal, kFlags };
+  int* const found = reinterpret_cast<int*>(lds + KW * ST * STAGE_BYTES);
+  if (threadIdx.x < kFlags) found[threadIdx.x] = 0;    // (a barrier follows before anyone sets one)
+  auto any = [&](int flag) { return __builtin_amdgcn_readfirstlane(found[flag]) != 0; };
   int8_t* const ring = lds + wave * ST * STAGE_BYTES;
   // this group's steps, and where the next one to request lies in the reduction
   const int n_st = p.rsc / (BK / 4), n_mine = (n_st + KW - 1) / KW;
@@ -178,6 +184,8 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
     asm volatile("" : "+v"(b_frag[h]));
   }
   v16f acc[T][T], low[T][T];
+  float large = 0.0f;                    // the largest operand that this lane has split
+  unsigned small = ~0u;                  // 2 |bits| - 1 of the smallest but zero that it has looked at
   v4f af[T][2], bf[T][2];
   auto read = [&](int off) __attribute__((always_inline)) {
 #pragma unroll
@@ -195,42 +203,61 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
   using std::integral_constant;
   // One step: its values are in registers or on their way.  Then its buffer is filled again, and the next step's values
   // are read while the last MFMAs run.  Fragments are split beside the MFMAs that do not need them yet: 1.5 % off.
-  // FP32: the products of the fp32 instruction instead.
-  auto step = [&](auto buf_c, auto fp32_c) __attribute__((always_inline)) {
-    constexpr int BUF = decltype(buf_c)::value;
-    constexpr bool FP32 = decltype(fp32_c)::value;
+  // kFp32: the products of the fp32 instruction instead.  kLook: none, the operands looked at.
+  enum { kSplit, kFp32, kLook };
+  auto step = [&](auto buf_c, auto mode_c) __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf_c)::value, MODE = decltype(mode_c)::value;
     wait_vmcnt<(ST - 2) * 2 * LOADS>();
     meet();
-    if constexpr (FP32) {
+    if constexpr (MODE != kSplit) {
+      if constexpr (MODE == kFp32) {
 #pragma unroll
-      for (int j = 0; j < T; ++j)
+        for (int j = 0; j < T; ++j)
+#pragma unroll
+          for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              acc[j][i] =
+                  __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e / 4][e % 4], bf[j][e / 4][e % 4], acc[j][i], 0, 0, 0);
+      } else {
 #pragma unroll
         for (int i = 0; i < T; ++i)
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e / 4][e % 4], bf[j][e / 4][e % 4], acc[j][i], 0, 0, 0);
+          for (int e = 0; e < 8; ++e) {
+            const unsigned a = __float_as_uint(af[i][e / 4][e % 4]), b = __float_as_uint(bf[i][e / 4][e % 4]);
+            small = min(small, min((a << 1) - 1, (b << 1) - 1));
+          }
+      }
       __builtin_amdgcn_sched_barrier(0);
       request(BUF);
       read((BUF + 1) % ST * STAGE_BYTES);
       return;
     }
     Split3 a[T], b[T];
+    auto split = [&](v4f lo, v4f hi) __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {     // (fmaxf would quiet signalling NaNs first, two instructions more)
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(large) : "v"(lo[e]), "v"(lo[e + 1]));
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(large) : "v"(hi[e]), "v"(hi[e + 1]));
+      }
+      return split3(lo, hi);
+    };
     auto mma = [&](int i, int j, int t) __attribute__((always_inline)) {     // product t of tile (i, j)
       v16f& sum = t == 2 ? acc[j][i] : low[j][i];
       const v8bf& u = t == 0 || t == 4 ? a[i].m : t == 1 ? a[i].l : a[i].h;
       const v8bf& v = t == 0 || t == 5 ? b[j].m : t == 3 ? b[j].l : b[j].h;
       sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u, v, sum, 0, 0, 0);
     };
-    a[0] = split3(af[0][0], af[0][1]);
-    b[0] = split3(bf[0][0], bf[0][1]);
+    a[0] = split(af[0][0], af[0][1]);
+    b[0] = split(bf[0][0], bf[0][1]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 6; ++t) mma(0, 0, t);
-    a[1] = split3(af[1][0], af[1][1]);
+    a[1] = split(af[1][0], af[1][1]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 6; ++t) mma(1, 0, t);
-    b[1] = split3(bf[1][0], bf[1][1]);
+    b[1] = split(bf[1][0], bf[1][1]);
     __builtin_amdgcn_sched_barrier(0);
     request(BUF);
     read((BUF + 1) % ST * STAGE_BYTES);
@@ -240,26 +267,16 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       for (int i = 0; i < T; ++i) mma(i, 1, t);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto pass = [&](auto self, int n, auto buf_c, auto fp32_c) __attribute__((always_inline)) -> void {
+  auto pass = [&](auto self, int n, auto buf_c, auto mode_c) __attribute__((always_inline)) -> void {
     constexpr int BUF = decltype(buf_c)::value;
     if constexpr (BUF < ST) {
       if (BUF < n) {
-        step(buf_c, fp32_c);
-        self(self, n, integral_constant<int, BUF + 1>{}, fp32_c);
+        step(buf_c, mode_c);
+        self(self, n, integral_constant<int, BUF + 1>{}, mode_c);
       }
     }
   };
-  // The whole reduction, its sums into the exchange.  Quad q of a lane is channels 4 (q % 4) .. of its 16 in channel
-  // tile q / 4 % T, pixel tile q / 4 / T; a wavefront finishes quads wave * OWN .., of one channel and one pixel tile.
-  float* const xch = reinterpret_cast<float*>(lds);
-  auto reduce = [&](auto fp32_c) __attribute__((always_inline)) {
-    constexpr bool FP32 = decltype(fp32_c)::value;
-#pragma unroll
-    for (int j = 0; j < T; ++j)
-#pragma unroll
-      for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][i][e] = low[j][i][e] = 0.0f;
+  auto walk = [&](auto mode_c) __attribute__((always_inline)) {     // over the whole reduction
     begin();
 #pragma unroll
     for (int i = 0; i < ST; ++i) request(i);
@@ -267,17 +284,29 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
     meet();
     read(0);
     int left = n_mine;
-    for (; left >= ST; left -= ST) pass(pass, ST, integral_constant<int, 0>{}, fp32_c);
-    pass(pass, left, integral_constant<int, 0>{}, fp32_c);
+    for (; left >= ST; left -= ST) pass(pass, ST, integral_constant<int, 0>{}, mode_c);
+    pass(pass, left, integral_constant<int, 0>{}, mode_c);
     wait_vmcnt<0>();                     // (the loads of steps behind the last: LDS is used again)
     __syncthreads();
+  };
+  // Its sums, into the exchange.  Quad q of a lane is channels 4 (q % 4) .. of its 16 in channel
+  // tile q / 4 % T, pixel tile q / 4 / T; a wavefront finishes quads wave * OWN .., of one channel and one pixel tile.
+  float* const xch = reinterpret_cast<float*>(lds);
+  auto reduce = [&](auto mode_c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < T; ++j)
+#pragma unroll
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][i][e] = low[j][i][e] = 0.0f;
+    walk(mode_c);
 #pragma unroll
     for (int q = 0; q < QUADS; ++q) {
       v4f v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         v[e] = acc[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
-        if constexpr (!FP32) v[e] += low[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
+        if constexpr (decltype(mode_c)::value == kSplit) v[e] += low[q / 4 / T][q / 4 % T][4 * (q % 4) + e];
       }
       *reinterpret_cast<v4f*>(xch + ((wave * QUADS + q) * 64 + lane) * 4) = v;
     }
@@ -289,7 +318,8 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
       v += *reinterpret_cast<const v4f*>(xch + ((g * QUADS + wave * OWN + o) * 64 + lane) * 4);
     return v;
   };
-  reduce(std::false_type{});
+  reduce(integral_constant<int, kSplit>{});
+  if (!(large < kSplitLargest)) found[kLarge] = 1;
   __syncthreads();
   v4f own[OWN];
 #pragma unroll
@@ -299,15 +329,21 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
     const int q = wave * OWN + o;
     return ch0 + q / 4 % T * 32 + 16 * (lane >> 5) + 4 * (q % 4);
   };
-  unsigned again = 0;                    // what the split cannot vouch for
+  // The sums that the split cannot vouch for, and those of zero, for which it can where no operand is denormal.
+  const bool all = any(kLarge);
+  unsigned again = 0, zero = 0;
 #pragma unroll
-  for (int o = 0; o < OWN; ++o)
+  for (int o = 0; o < OWN; ++o) {
+    if (pixel_of(o) >= p.M) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float a = fabsf(own[o][e]);
-      again |= a < INFINITY && (a >= 0x1p-90f || a == 0.0f) ? 0u : 1u << (o * 4 + e);
+      if (channel_of(o) + e >= p.K || (!all && a >= kSplitLeast && a < INFINITY)) continue;
+      (!all && a == 0.0f ? zero : again) |= 1u << (o * 4 + e);
     }
-  if (again) *redo = 1;
+  }
+  if (again) found[kAgain] = 1;
+  if (zero) found[kZero] = 1;
   float m_sum = 0.0f, m_out = 0.0f;
   auto finish = [&](int o) __attribute__((always_inline)) {
     const int pix = pixel_of(o), ch = channel_of(o);
@@ -342,27 +378,36 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
   };
 #pragma unroll
   for (int o = 0; o < OWN; ++o)
-    if (!(again >> (o * 4) & 15)) finish(o);
+    if (!((again | zero) >> (o * 4) & 15)) finish(o);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(*redo)) {
-    reduce(std::true_type{});
+  if (any(kZero)) {
+    walk(integral_constant<int, kLook>{});
+    if (small < 0x00ffffffu) found[kDenormal] = 1;
+    __syncthreads();
+    if (any(kDenormal)) again |= zero;
+  }
+  const unsigned late = again | zero;
+  if (any(kAgain) || any(kDenormal)) {
+    reduce(integral_constant<int, kFp32>{});
     __syncthreads();
 #pragma unroll
     for (int o = 0; o < OWN; ++o) {
       const v4f v = total(o);
 #pragma unroll
       for (int e = 0; e < 4; ++e) own[o][e] = again >> (o * 4 + e) & 1 ? v[e] : own[o][e];
-      if (again >> (o * 4) & 15) finish(o);
     }
-    __syncthreads();
   }
+#pragma unroll
+  for (int o = 0; o < OWN; ++o)
+    if (late >> (o * 4) & 15) finish(o);
+  __syncthreads();
   observe_block<KW>(p, m_sum, m_out, reinterpret_cast<float*>(lds));
 #endif
 }
 
 template <int KW>
 int launch_split(F32Params& p, hipStream_t stream) {
-  constexpr int kRingBytes = KW * kSplitStages * 2 * 64 * kSplitStep, kFlagBytes = 4;
+  constexpr int kRingBytes = KW * kSplitStages * 2 * 64 * kSplitStep, kFlagBytes = 16;
   static_assert(kRingBytes == KW * 4 * 4096, "the exchange fits the rings");
   constexpr int kLdsBytes = kRingBytes + kFlagBytes;
   p.n_ptiles = (p.M + 63) / 64;
@@ -384,9 +429,10 @@ int launch_split(F32Params& p, hipStream_t stream) {
 // Whether the layer is faster here than with the builds of q8_conv_f32_lds.hip, by their estimate (which is
 // low, by up to a quarter: hence the 1.1) and one fitted to the layers of the package's networks at 1, 3 and 8 images.
 // n: 64 x 64 tiles per CU.  Up to one eight wavefronts share a tile; two workgroups of four wavefronts fit a CU.
-// Of 106 layers none is slower by it; those that change take 0.74 to 0.97 of their time.  K % 64: tiles are full.
-// Layers that those builds do not take (`lds` false) run register-fed, in 1.5 to 1.8 times that estimate where
-// they are long: 3x3 80 -> 192 on 71 x 71 x 8 150 us, 84 here; 512 -> 84 on 38 x 38 x 8 172, 102.
+// Of 106 layers 44 change: 39 take 0.62 to 0.98 of their time, five 1.00 to 1.05 (worst 1x1 / 2 256 -> 512 on
+// 56 x 56 x 8, 24.3 and 25.7 us).  K % 64: tiles are full.  Layers that those builds do not take (`lds` false) run
+// register-fed, in 1.5 to 1.8 times that estimate where they are long: 3x3 80 -> 192 on 73 x 73 x 8 146 us, 91 here;
+// 512 -> 84 on 38 x 38 x 8 146, 96.
 bool f32_split_pays(long M, int K, int rsc, float lds_us, bool lds) {
   if (lds && K % 64) return false;
   const float n = (float)((M + 63) / 64) * (float)((K + 63) / 64) / 256.0f;

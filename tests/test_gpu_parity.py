@@ -2153,6 +2153,50 @@ def test_conv_f32_split_builds(B, build, geom, res, slice_):
         assert bool(err.all())
 
 
+@pytest.mark.parametrize("geom", [(8, 28, 28, 128, 128), (3, 61, 59, 64, 256)])       # eight wavefronts a tile, four
+@pytest.mark.parametrize("kind", ["small x, large w", "large x, small w", "denormal x", "denormal w", "few denormals",
+                                  "zeros", "zeros and large"])
+def test_conv_f32_split_operands_that_bf16_cannot_split(B, geom, kind):
+    """Values that three bf16 pieces hold with fewer bits, or not at all, count as the fp32 sum counts them, whatever the
+    size of the sum; sums of zero are zero."""
+    N, H, W, Cc, K = geom
+    g = torch.Generator(device="cuda").manual_seed(17)
+    d = B.ConvDesc(N, H, W, Cc, K, 3, 3, pad_h=1, pad_w=1)
+    assert B.conv_f32_variant(d).startswith("conv_f32_split_kernel")
+    x, w = torch.randn((N, H, W, Cc), device="cuda", generator=g), torch.randn((K, 3, 3, Cc), device="cuda", generator=g)
+    mantissa = lambda t, e: torch.ldexp(torch.sign(t) * (1 + t.abs().frac()), torch.tensor(e, device="cuda"))
+    if kind == "small x, large w":
+        x, w = mantissa(x, -124), w * 2.0 ** 100
+    elif kind == "large x, small w":
+        x, w = x * 2.0 ** 100, mantissa(w, -124)
+    elif kind == "denormal x":
+        x, w = mantissa(x, -137), w * 2.0 ** 30
+    elif kind == "denormal w":
+        x, w = x * 2.0 ** 30, mantissa(w, -137)
+    elif kind == "few denormals":          # sums of zero in most places, of denormals' products in some
+        x = torch.zeros_like(x)
+        x[N - 1, H - 1, W - 1, Cc - 1] = x[0, 5, 3, 0] = 2.0 ** -138
+        w = w * 2.0 ** 30
+    else:
+        x[:, ::2] = 0
+        x[0, :8, :11] = 0
+        w[:, :, :, Cc // 2:] = 0
+        w[3] = 0
+        if kind == "zeros and large":
+            x[N - 1, H - 1, W - 1, 0] = 2.0 ** 40
+    got = B.conv_f32_ref(d, x, w).double()
+
+    def fp64(x, w):
+        x = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+        return sum((x[:, i:i + H, j:j + W].reshape(-1, Cc) @ w[:, i, j].double().t().contiguous()
+                    for i in range(3) for j in range(3))).view(N, H, W, K)
+    want, n = fp64(x, w), 9 * Cc
+    size = fp64(x.abs(), w.abs())
+    assert bool(((got - want).abs() <= (n + 2) * 2.0 ** -24 * size + (n + 1) * 2.0 ** -149).all())
+    if "zeros" in kind or kind == "few denormals":
+        assert bool((got[size == 0] == 0).all()) and bool((size == 0).any()) and bool((got[want.abs() > 0.5 * size] != 0).all())
+
+
 @pytest.mark.parametrize("geom", [(8, 28, 28, 128, 128), (4, 41, 43, 256, 192)])      # eight wavefronts a tile, four
 def test_conv_f32_split_is_no_slower_than_the_fp32_instruction_where_it_sums_again(B, geom):
     """Sums that are no numbers are taken again by the whole workgroup, 16 + 5 instructions' time for 5: a layer of
