@@ -213,20 +213,23 @@ float ring_tiles_us(const q8_conv_desc* d, long M, int bp, int bc) {
 }
 
 // us of the block-tiled 3x3 kernel (q8_conv_p3b_kernel.h); 0: not one of its layers (3x3, stride 1,
-// padding 0 or 1, 128, 96, 80, 64 or 32 channels, many pixels).  What its tiles take is the same however
+// padding 0 or 1, 32 to 128 channels in sixteens, many pixels).  What its tiles take is the same however
 // much of them lies on the map, so it is rounds of 512 of them, two per CU: 64 channels 5.3 us up to 512 tiles,
 // 7.4 up to 1000, 13.4 at 1710 and 25 at 4940; 128 channels 7.7 up to 512, 11.9 up to 1000,
 // 28.8 at 3040; 32 channels 4.2, 6.4 at 1000 and 17 at 4940.
 float block_tiles_us(const q8_conv_desc* d) {
   if (d->R != 3 || d->S != 3 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != d->pad_w || d->pad_h > 1 ||
-      d->dil_h != 1 || d->dil_w != 1 || (d->C != 128 && d->C != 96 && d->C != 80 && d->C != 64 && d->C != 32) || (d->K & 15) != 0 ||
+      d->dil_h != 1 || d->dil_w != 1 || !q8::p3b_channels(d->C, false) || (d->K & 15) != 0 ||
       (long)d->N * d->H * d->W < 128L * 256)
     return 0.0f;
   const int rows = d->C == 32 && d->K <= 32 ? 16 : 8;
   const long tiles = (long)d->N * ((out_extent(d->H, d->pad_h, 1, 3, 1) + rows - 1) / rows) *
                      ((out_extent(d->W, d->pad_w, 1, 3, 1) + 15) / 16) * ((d->K + 63) / 64);
   const float rounds = (float)((tiles + 511) / 512);
-  return d->C == 128 ? 3.9f + 4.05f * rounds : d->C > 64 ? 3.7f + 3.2f * rounds : d->C == 64 ? 3.0f + 2.25f * rounds : 2.75f + 1.47f * rounds;
+  return d->C > 96   ? 3.9f + 4.05f * rounds
+         : d->C > 64 ? 3.7f + 3.2f * rounds
+         : d->C > 32 ? 3.0f + 2.25f * rounds
+                     : 2.75f + 1.47f * rounds;
 }
 
 // Among the tiled kernels.  `forced`: -1, or a variant of the main kernel to use where that kernel
@@ -266,6 +269,8 @@ int pick_tiled(const q8_conv_desc* d, int forced = -1, bool persistent = true) {
   // 901 thousand pixels, 80 to 368 channels: 64 -> 128 on 150 x 150 x 32 73.1 us and 58.4; between 0.7 and 0.8
   // they take the same: 64 -> 96 on 35 x 35 x 32 7.0 and 7.2, and that one joins its level's launch).  80 and 96
   // channels: 0.79 to 0.99 in seven layers chosen, 1.14 in one that is not (80 -> 96 on 181 x 181 x 2 11.0 and 12.5).
+  // 48 and 112 channels by the same rules: 0.72 to 1.01 and 0.61 to 0.86 in 56 layers chosen of 95 (48 -> 64 on 150 x
+  // 150 x 8 14.0 and 10.7, 112 -> 128 there 33.4 and 26.6; on 19 x 19 x 64, not chosen, 6.6 and 7.3, 8.4 and 11.1).
   // 128 channels: against the tiles of the 3x3 family, which get to 1.72 POP/s on such layers (us, the best other build
   // and the blocks: 128 -> 128 on 150 x 150 x 32 128 and 101, x 8 35.7 and 28.8, 75 x 75 x 32 33.9 and 31.4, 128 -> 256
   // there 64.0 and 53.3, 128 -> 64 on 60 x 60 x 24 11.0 and 12.1, 28 x 28 x 64 11.4 and 12.3; in no layer of 15 chosen slower).

@@ -426,6 +426,10 @@ __device__ __forceinline__ v4i codes16_build(const P& p, const int (&v)[16],
     return has_res ? codes16_fast<true>(p, v, rw, mv) : codes16_fast<false>(p, v, rw, mv);
   }
 }
+// Input channels that the block-tiled 3x3 kernel has builds for (q8_conv_p3b_kernel.h).
+inline bool p3b_channels(int C, bool ext) {
+  return ext ? C == 32 || C == 64 : C >= 32 && C <= 128 && C % 16 == 0;
+}
 __host__ __device__ inline bool is_extended(const ConvParams& p) {
   return p.in_u8 || p.out_u8 || p.res_u8 || p.m_vec != nullptr;
 }

@@ -45,11 +45,7 @@ bool p3b_pooled_takes(const ConvParams& p, size_t bytes) {
 }
 int launch_p3b_pooled(ConvParams& p, int8_t* y, int Hp, int Wp, int cs, int bytes, hipStream_t stream) {
   const P3bPool pool{y, bytes, Hp, Wp, cs};
-  if (p.C == 128) return launch_p3b_build<128, 2, 0, true>(p, stream, pool);
-  if (p.C > 64) return launch_p3b_build<128, 2, 0, true, 3>(p, stream, pool);
-  if (p.C == 64) return launch_p3b_build<64, 2, 0, true>(p, stream, pool);
-  if (p.K <= 32) return launch_p3b_build<32, 1, 0, true>(p, stream, pool);
-  return launch_p3b_build<32, 2, 0, true>(p, stream, pool);
+  return launch_p3b<0, true>(p, stream, pool);
 }
 const char* p3_variant_name(int variant) {
   return variant >= 0 && variant < kNumP3Variants ? kP3Variants[variant].name : "unsupported";

@@ -1,7 +1,7 @@
 // The block-tiled build of the persistent 3x3 family (Eq. x / Eq. A' of arxiv 1805.08691):
-// 3x3, stride 1, padding 0 or 1, C = 32, 64, 80, 96 or 128 input channels (above 64:
-// plain codes), maps of any width.  A workgroup has 64 output channels
-// (32 where K <= 32); layers of more are as many sets of walkers.
+// 3x3, stride 1, padding 0 or 1, 32 to 128 input channels in sixteens, maps of any width.  Extended layers: 32 and 64
+// channels (128 would keep 36 registers of a lane in scratch; 80 and 96 fit, with 248, and are not built).
+// A workgroup has 64 output channels (32 where K <= 32); layers of more are as many sets of walkers.
 //
 // The persistent 3x3 kernel (q8_conv_p3_kernel.h) cuts the output into runs of 128 consecutive
 // pixels; the activations such a run reads are the run plus a whole map row on either side, so
@@ -60,16 +60,17 @@ struct P3bPool {
 
 // p.n_ptiles = tiles in all (N * tiles_h * tiles_w); div_img and div_row divide a tile's number by the
 // tiles of an image and of a row of them, n_ctiles (set by launch_p3b).
-// NH: 32-byte halves of a tap that an MFMA takes; fewer than CB has where C is 80 or 96 (chunks beyond C are zeros).
-template <int CB, int WC, int EXT, bool POOL = false, int NH = CB / 32>
+// NH: 32-byte halves of a tap that an MFMA takes.  PART: C <= 32 NH channels where the patch has CB, the chunks beyond
+// C are zeros.
+template <int CB, int WC, int EXT, bool POOL, int NH, bool PART>
 __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p, const P3bPool pool) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using Sh = P3bShape<CB, WC>;
   constexpr int NW = Sh::NW, WP = Sh::WP, TP = Sh::TP, BP = Sh::BP, BC = Sh::BC, CHUNKS = Sh::CHUNKS;
   constexpr int TH = Sh::TH, TW = Sh::TW, PW = Sh::PW, PL = Sh::PL;
   constexpr int SLOTS = BC / 16, NQ = 2 * TP + 1;
-  constexpr bool WHOLE = NH == CB / 32;
-  const int tap_bytes = WHOLE ? CB : p.C;
+  static_assert(NH <= CB / 32 && (PART || NH == CB / 32), "the halves lie in the patch, without PART all of them");
+  const int tap_bytes = PART ? p.C : CB;
   constexpr int STORES = BP * SLOTS / (NW * 64), ALL_STORES = STORES + POOL;
   extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
   int8_t* const patch = lds;
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
     pr_y[j] = rho < Sh::PATCH_PIX ? rho / PW : -4096;            // beyond the patch: never inside
     pr_x[j] = rho % PW;
     const int chunk = patch_slot(rho, pr_x[j], lane % CHUNKS) * 16;
-    if (!WHOLE && chunk >= p.C) pr_y[j] = -4096;
+    if (PART && chunk >= p.C) pr_y[j] = -4096;
     pr_off[j] = (pr_y[j] * W + pr_x[j]) * p.in_cs + chunk;
   }
   // tile number -> image and block origin
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
         const int row = ((l + wave) * Sh::RPW) % BC + lane / CHUNKS, tap = tap0 + (l + wave) * Sh::RPW / BC;
         const int ch = ch0 + (row & ~31) + row_to_channel(row & 31);
         const int chunk = slot_of(row, lane % CHUNKS) * 16;
-        const int off = ch < p.K && (WHOLE || chunk < p.C) ? ch * p.red_len + chunk : kOobOffset;
+        const int off = ch < p.K && (!PART || chunk < p.C) ? ch * p.red_len + chunk : kOobOffset;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rsrc_w, (__attribute__((address_space(3))) void*)(filters + (l + wave) * 1024), 16, off, tap * tap_bytes, 0, 0);
       }
@@ -328,14 +329,14 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
 
 inline bool p3b_applicable(const ConvParams& p) {
   return p.R == 3 && p.S == 3 && p.stride_h == 1 && p.stride_w == 1 && p.dil_h == 1 && p.dil_w == 1 &&
-         p.pad_h == p.pad_w && p.pad_h <= 1 &&
-         (p.C == 64 || p.C == 32 || ((p.C == 128 || p.C == 96 || p.C == 80) && !is_extended(p))) && p.S4 == 0 && (p.K & 15) == 0 && p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 &&
-         (long)p.M * p.out_cs < 0x7fffffffL;
+         p.pad_h == p.pad_w && p.pad_h <= 1 && p3b_channels(p.C, is_extended(p)) && p.S4 == 0 && (p.K & 15) == 0 &&
+         p.vec16 && !p.res && !p.acc_dump && !p.y_f32 && !p.y_deq && !p.w2 && (long)p.M * p.out_cs < 0x7fffffffL;
 }
 
-template <int CB, int WC, int EXT, bool POOL = false, int NH = CB / 32>
-int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}) {
+template <int CB, int WC, int EXT, bool POOL, int NH = CB / 32, bool PART = NH != CB / 32>
+int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool) {
   using Sh = P3bShape<CB, WC>;
+  if (PART ? p.C > 32 * NH || p.C % 16 != 0 : p.C != CB) return Q8_EUNSUPPORTED;
   const long tiles_w = (p.Wo + Sh::TW - 1) / Sh::TW, tiles_h = (p.Ho + Sh::TH - 1) / Sh::TH;
   const long tiles = (long)p.N * tiles_h * tiles_w;
   if (tiles > 0x7fffffffL) return Q8_EUNSUPPORTED;
@@ -344,7 +345,7 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
   const FastDiv img = make_fast_div((unsigned)(tiles_h * tiles_w)), row = make_fast_div((unsigned)tiles_w);
   p.div_img_m = img.m; p.div_img_s = img.s;
   p.div_row_m = row.m; p.div_row_s = row.s;
-  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT, POOL, NH>;
+  auto kernel = conv_i8_p3b_kernel<CB, WC, EXT, POOL, NH, PART>;
   static const int resident = [&]() {
     int per_cu = 0, dev = 0, cus = 256;
     hipDeviceProp_t prop;
@@ -368,17 +369,20 @@ int launch_p3b_build(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}
   return q8_launch_status();
 }
 
-template <int EXT>
-int launch_p3b(ConvParams& p, hipStream_t stream) {
-  if (p.C == 64) return launch_p3b_build<64, 2, EXT>(p, stream);
+// The build for p3b_channels: the smallest patch that holds C, and of it the halves that C reaches into.
+template <int EXT, bool POOL = false>
+int launch_p3b(ConvParams& p, hipStream_t stream, const P3bPool& pool = {}) {
   if constexpr (!EXT) {
-    if (p.C == 128) return launch_p3b_build<128, 2, 0>(p, stream);
-    if (p.C > 64) return launch_p3b_build<128, 2, 0, false, 3>(p, stream);
+    if (p.C > 112) return launch_p3b_build<128, 2, 0, POOL>(p, stream, pool);
+    if (p.C > 96) return launch_p3b_build<128, 2, 0, POOL, 4, true>(p, stream, pool);
+    if (p.C > 64) return launch_p3b_build<128, 2, 0, POOL, 3>(p, stream, pool);
+    if (p.C > 32 && p.C < 64) return launch_p3b_build<64, 2, 0, POOL, 2, true>(p, stream, pool);
   }
+  if (p.C > 32) return launch_p3b_build<64, 2, EXT, POOL>(p, stream, pool);
   if constexpr (!EXT) {                  // (the extended builds are kept to K > 32)
-    if (p.K <= 32) return launch_p3b_build<32, 1, 0>(p, stream);
+    if (p.K <= 32) return launch_p3b_build<32, 1, 0, POOL>(p, stream, pool);
   }
-  return launch_p3b_build<32, 2, EXT>(p, stream);
+  return launch_p3b_build<32, 2, EXT, POOL>(p, stream, pool);
 }
 
 }  // namespace

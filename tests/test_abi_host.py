@@ -609,6 +609,11 @@ def test_maxima_that_join_their_layer():
     assert joined(two, 64) == -1 and joined(two, 64, 128, first=4) == -1
 
 
+@pytest.mark.parametrize("C", range(32, 144, 16))
+def test_block_tiles_take_any_channels_in_sixteens(C):
+    assert B.conv_variant(B.ConvDesc(8, 150, 150, C, 64, 3, 3, 1, 1, 1, 1)) == "conv_i8_p3b_kernel"
+
+
 def _kernels():
     """Metadata of every kernel in the library: the note of each code object of its offload bundles."""
     msgpack = pytest.importorskip("msgpack")

@@ -2958,6 +2958,20 @@ def test_conv_pointwise_rule(B, build, size, with_res):
     assert np.array_equal(host(got), orc.requant_pc(acc, one, True, r, m_r))
 
 
+@pytest.mark.parametrize("geom", [
+    dict(N=2, H=11, W=19, C=48, K=16, pad_h=1, pad_w=1), dict(N=1, H=1, W=1, C=48, K=80, pad_h=1, pad_w=1),
+    dict(N=13, H=53, W=51, C=48, K=144, pad_h=0, pad_w=0), dict(N=2, H=9, W=33, C=112, K=64, pad_h=1, pad_w=1),
+    dict(N=3, H=17, W=18, C=112, K=16, pad_h=0, pad_w=0), dict(N=8, H=147, W=35, C=112, K=80, pad_h=1, pad_w=1)])
+def test_conv_block_tiles_of_channels_that_fill_no_patch(B, geom):
+    """48 of 64 and 112 of 128: chunks of zeros in every half of the patch that is multiplied, or in its last one."""
+    geom = dict(geom, R=3, S=3)
+    names = [B.lib.q8_conv_variant_name(v).decode() for v in range(B.conv_num_variants())]
+    _run_conv_case(B, geom, relu=geom["pad_h"] == 1, with_res=False, with_bias=True, seed=geom["C"] + geom["K"],
+                   variant=names.index("conv_i8_p3b_kernel"), out_pad=16, out_off=16, dump_acc=False)
+    if geom["N"] > 4:
+        test_maximum_behind_a_layer(B, (3, 149, 167), geom["C"], 64 if geom["C"] < 64 else 80, geom["pad_h"], True, (96, 16))
+
+
 @pytest.mark.parametrize("C,pad", [(32, 1), (64, 0)])
 def test_conv_block_tiles_with_a_residual(B, C, pad):
     """A layer that the block-tiled kernel is chosen for by its sizes but cannot take: the general kernel,
