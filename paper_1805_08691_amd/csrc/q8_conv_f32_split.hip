@@ -17,16 +17,17 @@
 // 10 to 40 % slower on large layers; 128 x 128 tiles of four wavefronts, where each fragment is split twice too, 5 %
 // faster there, but with one chain per value further off than the fp32 builds.)  Where tiles are few the operands'
 // way into LDS bounds the layer instead, and the fp32 builds with their smaller tiles stay (f32_split_pays).  Batch 8,
-// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 386 and 355, 38 x 38 512 -> 512 3x3 430 and 346 (100 % of
-// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 198 and 164, 28 x 28 128 -> 128 23.5 and 19.1.
+// the fp32 builds' and these (us): 150 x 150 128 -> 128 3x3 376 and 334, 38 x 38 512 -> 512 3x3 413 and 330 (105 % of
+// the fp32 matrix rate), 19 x 19 512 -> 1024 dilated 199 and 157, 28 x 28 128 -> 128 23.0 and 18.8.
 //
 // The split is exact for zero and for 2^-110 <= |x| < 3.38e38; of smaller values it loses up to 2^-134 each, of a
 // denormal perhaps all.  So it holds for a sum of at least 2^-60 whose operands are below 2^32 (2^-42 of the sum is lost
 // for each product at worst), and for a sum of zero without denormal operands.  Where a workgroup has other sums
 // (infinities, NaNs and values that bf16 rounds to infinity among them) it runs its reduction a second time on
-// the fp32 instruction, for what the fp32 sum gives; where it has zeros it looks through its operands first.  Noting
-// the largest operand is one instruction for two values and costs 2 % (337 us of the 346 above).  75 x 75 128 -> 256 180 us, with a zero
-// in every tile 218 to 256, of NaNs or of values below 2^-60 326 to 377; the fp32 builds 190 to 210.
+// the fp32 instruction, for what the fp32 sum gives; where it has zeros it looks through its operands first.  Noting the
+// largest operand, one instruction for two values, and the barrier behind which all know take 1.8 % (323 us of the 330
+// above).  75 x 75 128 -> 256 177 us, with a zero in every tile 218 to 245, of NaNs or of values below 2^-60 326 to
+// 364; the fp32 builds 190 to 210.
 #include "q8_conv_f32.h"
 #include "q8_conv_ring_kernel.h"
 
@@ -332,22 +333,58 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
   // The sums that the split cannot vouch for, and those of zero, for which it can where no operand is denormal.
   const bool all = any(kLarge);
   unsigned again = 0, zero = 0;
+  float least = INFINITY, none = 0.0f;   // none: no number where some sum is infinite or none
 #pragma unroll
-  for (int o = 0; o < OWN; ++o) {
-    if (pixel_of(o) >= p.M) continue;
+  for (int o = 0; o < OWN; ++o)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float a = fabsf(own[o][e]);
-      if (channel_of(o) + e >= p.K || (!all && a >= kSplitLeast && a < INFINITY)) continue;
-      (!all && a == 0.0f ? zero : again) |= 1u << (o * 4 + e);
+      least = fminf(least, fabsf(own[o][e]));
+      none = fmaf(own[o][e], 0.0f, none);
+    }
+  if (all || !(least >= kSplitLeast) || none != 0.0f) {
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) {
+      if (pixel_of(o) >= p.M) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = fabsf(own[o][e]);
+        if (channel_of(o) + e >= p.K || (!all && a >= kSplitLeast && a < INFINITY)) continue;
+        (!all && a == 0.0f ? zero : again) |= 1u << (o * 4 + e);
+      }
+    }
+    if (again) found[kAgain] = 1;
+    if (zero) found[kZero] = 1;
+  }
+  __syncthreads();
+  const bool some_again = any(kAgain), some_zero = any(kZero);
+  if (some_again | some_zero) {
+    bool second = some_again;
+    if (some_zero) {
+      walk(integral_constant<int, kLook>{});
+      if (small < 0x00ffffffu) found[kDenormal] = 1;
+      __syncthreads();
+      if (any(kDenormal)) {
+        again |= zero;
+        second = true;
+      }
+    }
+    if (second) {
+      reduce(integral_constant<int, kFp32>{});
+      __syncthreads();
+#pragma unroll
+      for (int o = 0; o < OWN; ++o) {
+        const v4f v = total(o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) own[o][e] = again >> (o * 4 + e) & 1 ? v[e] : own[o][e];
+      }
+      __syncthreads();
     }
   }
-  if (again) found[kAgain] = 1;
-  if (zero) found[kZero] = 1;
   float m_sum = 0.0f, m_out = 0.0f;
-  auto finish = [&](int o) __attribute__((always_inline)) {
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
     const int pix = pixel_of(o), ch = channel_of(o);
-    if (pix >= p.M || ch >= p.K) return;
+    if (pix >= p.M || ch >= p.K) continue;
     v4f v = own[o];
     float* const y = p.y + (size_t)pix * p.out_cs + p.out_off + ch;
     const float* const res = p.res ? p.res + (size_t)pix * p.K + ch : nullptr;
@@ -375,32 +412,7 @@ __global__ __launch_bounds__(KW * 64, 2) void conv_f32_split_kernel(const F32Par
         y[e] = relu_max(u);
       }
     }
-  };
-#pragma unroll
-  for (int o = 0; o < OWN; ++o)
-    if (!((again | zero) >> (o * 4) & 15)) finish(o);
-  __syncthreads();
-  if (any(kZero)) {
-    walk(integral_constant<int, kLook>{});
-    if (small < 0x00ffffffu) found[kDenormal] = 1;
-    __syncthreads();
-    if (any(kDenormal)) again |= zero;
   }
-  const unsigned late = again | zero;
-  if (any(kAgain) || any(kDenormal)) {
-    reduce(integral_constant<int, kFp32>{});
-    __syncthreads();
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-      const v4f v = total(o);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) own[o][e] = again >> (o * 4 + e) & 1 ? v[e] : own[o][e];
-    }
-  }
-#pragma unroll
-  for (int o = 0; o < OWN; ++o)
-    if (late >> (o * 4) & 15) finish(o);
-  __syncthreads();
   observe_block<KW>(p, m_sum, m_out, reinterpret_cast<float*>(lds));
 #endif
 }
@@ -429,10 +441,10 @@ int launch_split(F32Params& p, hipStream_t stream) {
 // Whether the layer is faster here than with the builds of q8_conv_f32_lds.hip, by their estimate (which is
 // low, by up to a quarter: hence the 1.1) and one fitted to the layers of the package's networks at 1, 3 and 8 images.
 // n: 64 x 64 tiles per CU.  Up to one eight wavefronts share a tile; two workgroups of four wavefronts fit a CU.
-// Of 106 layers 44 change: 39 take 0.62 to 0.98 of their time, five 1.00 to 1.05 (worst 1x1 / 2 256 -> 512 on
-// 56 x 56 x 8, 24.3 and 25.7 us).  K % 64: tiles are full.  Layers that those builds do not take (`lds` false) run
-// register-fed, in 1.5 to 1.8 times that estimate where they are long: 3x3 80 -> 192 on 73 x 73 x 8 146 us, 91 here;
-// 512 -> 84 on 38 x 38 x 8 146, 96.
+// Of 106 layers 44 change: 41 take 0.59 to 0.99 of their time, three 1.00 to 1.02 (worst 1x1 512 -> 2048 on 7 x 7 x 8,
+// 12.5 and 12.8 us).  K % 64: tiles are full.  Layers that those builds do not take (`lds` false) run
+// register-fed, in 1.5 to 1.8 times that estimate where they are long: 3x3 80 -> 192 on 73 x 73 x 8 145 us, 86 here;
+// 512 -> 84 on 38 x 38 x 8 146, 94.
 bool f32_split_pays(long M, int K, int rsc, float lds_us, bool lds) {
   if (lds && K % 64) return false;
   const float n = (float)((M + 63) / 64) * (float)((K + 63) / 64) / 256.0f;
