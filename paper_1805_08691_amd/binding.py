@@ -32,7 +32,8 @@ EXPORTS = [
     "q8_conv_chain_workspace_bytes", "q8_conv_chain_int8",
     "q8_conv_chain_static_workspace_limit", "q8_conv_chain_int8_static",
     "q8_conv_chain_static_status",
-    "q8_conv_variant", "q8_conv_call_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant", "q8_sum_factor",
+    "q8_conv_variant", "q8_conv_call_variant", "q8_conv_num_variants", "q8_conv_variant_name", "q8_conv_int8_variant",
+    "q8_sum_factor",
     "q8_conv_workspace_bytes", "q8_conv_workspace_bytes_variant",
     "q8_conv_image_f32_supported", "q8_conv_image_f32_int8", "q8_conv_int8_dequantized",
     "q8_probe_mfma_i8", "q8_run_ops", "q8_group_variant",

@@ -20,7 +20,8 @@ SOURCES = ["q8_conv_ring.hip", "q8_conv_ring_ext.hip", "q8_conv_ring_pair.hip", 
            "q8_conv_chain.hip", "q8_conv_bneck.hip",
            "q8_conv_halo.hip", "q8_conv_dual.hip", "q8_conv_pw.hip", "q8_conv_split.hip", "q8_conv_p3.hip", "q8_conv_stem.hip",
            "q8_conv_taps4.hip",
-           "q8_conv_f32.hip", "q8_conv_f32_lds.hip", "q8_conv_f32_split.hip", "q8_conv_direct.hip", "q8_program.hip", "q8_conv_ext.hip",
+           "q8_conv_f32.hip", "q8_conv_f32_lds.hip", "q8_conv_f32_split.hip", "q8_conv_direct.hip",
+           "q8_program.hip", "q8_conv_ext.hip",
            "q8_conv.hip", "q8_conv_reg.hip", "q8_elementwise.hip", "q8_helpers.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

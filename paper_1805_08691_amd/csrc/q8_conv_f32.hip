@@ -4,8 +4,8 @@
 //
 // This file: the register-fed builds, for channel counts and alignments that those on LDS and on the
 // bf16 instructions (q8_conv_f32_lds.hip, q8_conv_f32_split.hip) do not take, and the host side.
-// What bounds them: on large layers the fp32 matrix rate (122 of the 153 TF a library product of 8192 x 8192 x 8192 reaches, 28 x 28 x 512 3x3 at
-// batch 64); on small maps the operand loads, 11 to 14 bytes per clock and CU.  16 reduction bytes
+// What bounds them: on large layers the fp32 matrix rate (122 of the 153 TF a library product of 8192 x 8192 x 8192
+// reaches, 28 x 28 x 512 3x3 at batch 64); on small maps the operand loads, 11 to 14 bytes per clock and CU.  16 reduction bytes
 // per lane feed four MFMAs of 32 clocks, so a wavefront loads its fragments straight into the MFMA's
 // register layout (16 rows x 64 bytes a load), two stages ahead of the one it computes: no LDS and no
 // barrier inside the loop.  ResNet-50 calibration on 8 images: 13.9 ms with the max-abs as passes over

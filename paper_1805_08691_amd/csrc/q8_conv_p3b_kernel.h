@@ -15,15 +15,17 @@
 //
 // What bounds it is the LDS: a fragment of 1 KB per MFMA of 32 clocks and wavefront is all that four
 // wavefronts can read.  So a wavefront keeps its 32 channels' filters in registers for the whole launch
-// (72 of them, 36 where C = 32, 144 where C = 128: all of the 256 that two wavefronts per SIMD leave each), and an MFMA tile being two rows of the block, the rows that tap
+// (72 of them, 36 where C = 32, 144 where C = 128: all of the 256 that two wavefronts per SIMD leave
+// each), and an MFMA tile being two rows of the block, the rows that tap
 // row r reads for one tile are those that row r - 2 reads for the next: five fragments serve the six
 // (tap row, tile) pairs of a tap column.  30 LDS reads a tile and wavefront instead of 54, and nobody
 // waits for a tile's stores.  64 -> 64 on 300 x 300 x 32 images 160 -> 133 us, on 56 x 56 x 32 9.2 -> 8.9;
 // 32 -> 64 on 147 x 147 x 32 34.5 us in the general kernel (half a step per tap), 20.5 here, 32 -> 32 29.2 and
 // 15.6 (48 MB: 9.3 us of a copy).  More than 64 channels, the best general build and this one: 64 -> 128 on
 // 150 x 150 x 32 73.1 and 58.4, 64 -> 256 on 56 x 56 x 32 24.0 and 19.6, 32 -> 96 on 112 x 112 x 32 29.2 and 21.5,
-// 128 -> 128 on 150 x 150 x 32 128 and 101 (2.1 POP/s).  80 and 96 channels have the patch of 128 with chunks of
-// zeros, and three quarters of its products: 80 -> 192 on 71 x 71 x 32 37.7 (the build chosen before: 43) and 30.1.
+// 128 -> 128 on 150 x 150 x 32 128 and 101 (2.1 POP/s).  Counts that fill no patch (48 of
+// 64; 80, 96 and 112 of 128) have chunks of zeros in it, 80 and 96 three quarters of the products: 80 -> 192 on 71 x 71
+// x 32 37.7 (the build chosen before: 43) and 30.1, 48 -> 64 on 150 x 150 x 8 14.0 and 10.7, 112 -> 128 there 33.4 and 26.6.
 //
 // POOL: the 2x2 maximum with stride 2 behind the layer in the same launch.  Blocks begin on even rows and columns,
 // so every window lies in one staging tile: two rows of it in the lane that stores them, the other two in a lane
@@ -101,8 +103,8 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
   auto slot_of = [](int rho, int chunk) {
     return CHUNKS == 8 ? chunk ^ ((rho >> 1) & 7) : CHUNKS == 4 ? chunk ^ ((rho >> 2) & 3) : chunk ^ ((rho >> 3) & 1);
   };
-  // The patch of 64 and more channels by its column x alone (128: two columns fill the banks): an LDS read of 16 bytes serves lanes 0-3, 12-15, 20-23 and
-  // 24-27 together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next.
+  // The patch of 64 and more channels by its column x alone (128: two columns fill the banks): an LDS read of 16
+  // bytes serves lanes 0-3, 12-15, 20-23 and 24-27 together, i.e. columns 0-3 and 12-15 of one block row and 4-11 of the next.
   auto patch_slot = [&](int rho, int x, int chunk) {
     return CHUNKS == 8 ? chunk ^ ((x >> 1) & 7) : CHUNKS == 4 ? chunk ^ ((x >> 2) & 3) : slot_of(rho, chunk);
   };
@@ -252,7 +254,9 @@ __global__ __launch_bounds__(256, 2) void conv_i8_p3b_kernel(const ConvParams p,
       for (int h = 0; h < NH; ++h) {
         v4i bf[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) bf[q] = *reinterpret_cast<const v4i*>(pbase + b_foff[s][NQO == 1 ? 0 : q][h] + (NQO == 1 ? q * PW * CB : 0));
+        for (int q = 0; q < NQ; ++q)
+          bf[q] = *reinterpret_cast<const v4i*>(pbase + b_foff[s][NQO == 1 ? 0 : q][h] +
+                                                (NQO == 1 ? q * PW * CB : 0));
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll

@@ -1,6 +1,7 @@
 // The register-fed tile family of the int8 convolution (Eq. x / Eq. A' of arxiv 1805.08691): a
 // network's first layer with up to four taps per filter row and four filter rows, over a 4-channel
-// image that carries its own padding as a zero frame, K <= 64 output channels (a detector's 3x3 on 300 x 300, Inception-v3's 3x3 / 2 on 299 x 299).
+// image that carries its own padding as a zero frame, K <= 64 output channels (a detector's 3x3
+// on 300 x 300, Inception-v3's 3x3 / 2 on 299 x 299).
 //
 // Four taps x four channels are 16 bytes, half the depth of a 32 x 32 x 32 MFMA, and the 16 bytes that an output
 // pixel reads of image row r are contiguous: lane (pixel, half h) loads those of row h into the operand's register

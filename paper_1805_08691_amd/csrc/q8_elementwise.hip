@@ -488,7 +488,8 @@ int q8_quantize(const float* r_dev, size_t n, float q, int p, int8_t* z_dev, voi
     return q8_launch_status();
   }
   int blocks = blocks_for((n + 15) / 16);
-  hipLaunchKernelGGL((q8_recip_normal(q) ? quantize_kernel<false, true> : quantize_kernel<false, false>), dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, r_dev,
+  hipLaunchKernelGGL((q8_recip_normal(q) ? quantize_kernel<false, true> : quantize_kernel<false, false>), dim3(blocks),
+                     dim3(kThreads), 0, (hipStream_t)stream, r_dev,
                      n, head, q, lo, hi, z_dev);
   return q8_launch_status();
 }
