@@ -337,6 +337,9 @@ constexpr TileCost kTileCosts[2][kTiledCosts] = {          // C % 64 == 0; other
 // rounds of tiles, and how much of a tile lies beyond K.  Among the 376 layers drawn above that the main kernel has,
 // 111 change: 0.96 to 1.6 times the speed, 1.12 on average (3x3 80 -> 192 on 71 x 71 x 64 74.6 -> 64.0 us, on 128 x
 // 192 tiles; 5x5 640 -> 128 on 86 x 85 x 6 138 -> 96 and 3x3 288 -> 80 on 116 x 113 x 24 162 -> 124, on 256 x 128).
+// Not to 9 from 1, not from 8 on up to four steps, and with 0.84 for 0.93 to larger tiles on short reductions and to 13
+// where 1 has more than four rounds: of 893 layers drawn anew that changed, those (103) take 1.006 of their time so (0.81
+// to 1.22; 4x4 48 -> 80 on 133 x 130 x 55 103 and 126 us, 1x1 64 -> 480 on 41 x 101 x 58 73 and 85), the others 0.886.
 // Below 10 us the choice measured inside the networks stays, their filters then come from HBM.  Not in a planned
 // step, where a second pipeline's workgroups fill what a round leaves and do not fit beside the largest
 // tiles: with these there SSD300 on 64 images took 2243 us, without 2168, Inception-v3 991 and 971.
@@ -356,15 +359,18 @@ int retile(const q8_conv_desc* d, int tiled, long M) {
     return fits && n >= 0.55f && 1.85f * ceilf(n) <= ceilf(tiles(256, 128)) ? first_halo + 17 : tiled;
   }
   const float steps = (float)((d->R * d->S * d->C + 63) / 64);
+  if (tiled == 8 && steps <= 4.0f) return tiled;
   float least = 1e30f, now = 0.0f;
   int best = tiled;
   for (const TileCost& t : kTileCosts[d->C % 64 == 0 ? 0 : 1]) {
     const float w = tiles(t.bp, t.bc);
     const float us = t.base + t.tile * w + steps * (t.chain * fmaxf(1.0f, w) + t.round * ceilf(w));
     if (t.variant == tiled) now = us;
-    if (t.variant > 8 && us < least) { best = t.variant; least = us; }
+    if (t.variant > 8 && !(t.variant == 9 && tiled == 1) && us < least) { best = t.variant; least = us; }
   }
-  return now > 10.0f && least < 0.93f * now ? best : tiled;
+  const bool unsure = (tiled == 11 && (best == 13 || best == 25) && steps <= 20.0f) ||
+                      (tiled == 1 && best == 13 && tiles(128, 128) > 4.0f);
+  return now > 10.0f && least < (unsure ? 0.84f : 0.93f) * now ? best : tiled;
 }
 
 // Layers with few tiles: the latency family (q8_conv_direct_kernel.h) where its estimate is below

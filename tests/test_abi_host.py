@@ -639,3 +639,14 @@ def test_tiles_of_the_3x3_family_stay_in_registers():
     """A register reloaded from scratch waits for every load in flight, the filters requested ahead among them."""
     found = {k[".name"]: k[".private_segment_fixed_size"] for k in _kernels() if "conv_i8_halo3_kernel" in k[".name"]}
     assert len(found) >= 18 and not {n: size for n, size in found.items() if size}
+
+
+# calls of their own, us in the planned step's tile and in the larger one that the estimates name: 103 and 126, 73 and 85,
+# 51 and 62, 13 and 14; and the same where the larger tile pays: 75 and 64, 138 and 96
+@pytest.mark.parametrize("geom, larger", [
+    ((55, 133, 130, 48, 80, 4, 4, 1, 1, 1, 1), False), ((58, 41, 101, 64, 480, 2, 2, 1, 1, 0, 0), False),
+    ((35, 94, 97, 736, 80, 1, 1, 1, 1, 0, 0), False), ((57, 34, 34, 640, 400, 1, 1, 2, 2, 0, 0), False),
+    ((64, 71, 71, 80, 180, 3, 3, 1, 1, 0, 0), True), ((6, 86, 85, 640, 128, 5, 5, 1, 1, 2, 2), True)])
+def test_calls_take_larger_tiles_where_they_pay(geom, larger):
+    d = B.ConvDesc(*geom, relu=1)
+    assert (B.conv_call_variant(d) != B.conv_variant(d)) == larger
