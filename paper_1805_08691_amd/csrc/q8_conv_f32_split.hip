@@ -445,8 +445,12 @@ int launch_split(F32Params& p, hipStream_t stream) {
 // 12.5 and 12.8 us).  K % 64: tiles are full.  Layers that those builds do not take (`lds` false) run
 // register-fed, in 1.5 to 1.8 times that estimate where they are long: 3x3 80 -> 192 on 73 x 73 x 8 145 us, 86 here;
 // 512 -> 84 on 38 x 38 x 8 146, 94.
+//
+// Where the reduction is short, or half of every tile lies beyond K, both kernels spend their time elsewhere and these
+// estimates do not hold: of 489 layers drawn and chosen by them the 50 left out here took 1.09 of their time on average
+// (0.86 to 1.33), the others 0.76.
 bool f32_split_pays(long M, int K, int rsc, float lds_us, bool lds) {
-  if (lds && K % 64) return false;
+  if (lds ? K % 64 != 0 || rsc < 16 * 16 : K <= 32 || rsc <= 8 * 16) return false;
   const float n = (float)((M + 63) / 64) * (float)((K + 63) / 64) / 256.0f;
   const float step = n <= 1.0f ? 0.139f : n <= 2.0f ? 0.29f : fmaxf(0.49f, 0.182f * n);
   const float us = (n <= 1.0f ? 7.0f : 9.0f) + 1.1f * n + step * (float)(rsc / 16);

@@ -650,3 +650,15 @@ def test_tiles_of_the_3x3_family_stay_in_registers():
 def test_calls_take_larger_tiles_where_they_pay(geom, larger):
     d = B.ConvDesc(*geom, relu=1)
     assert (B.conv_call_variant(d) != B.conv_variant(d)) == larger
+
+
+# us register-fed or on the fp32 instruction through LDS, and on the bf16 ones
+@pytest.mark.parametrize("geom, split", [
+    ((9, 86, 89, 320, 4, 5, 5, 1, 1, 0, 0, 2, 2), False),          # 279 and 336
+    ((7, 94, 93, 448, 1, 3, 3, 1, 1, 1, 1), False),                # 150 and 171
+    ((6, 140, 137, 160, 384, 1, 1), False),                        # 142 and 179
+    ((19, 124, 125, 48, 128, 1, 1), False),                        # 117 and 122
+    ((8, 38, 38, 512, 84, 3, 3, 1, 1, 1, 1), True),                # 146 and 94
+    ((8, 38, 38, 512, 512, 3, 3, 1, 1, 1, 1), True)])              # 413 and 330
+def test_fp32_layers_go_to_the_bf16_instructions_where_those_pay(geom, split):
+    assert ("split" in B.conv_f32_variant(B.ConvDesc(*geom))) == split
