@@ -30,10 +30,11 @@ inline int blocks_for(size_t work_items) {
 
 // ---------------------------------------------------------------- max-abs ----------
 // One running maximum per tensor.  A block takes chunks of eight 16-byte vectors per lane, round robin, so
-// that what the chip reads at one time lies together: 8.2 TB/s from the memory-side cache on 26 MB (one contiguous
-// run per block with sixteen loads in flight: 10.6 us there and 2.8 so; 51 MB 13.0 and 8.6, 103 MB 20.8 and
-// 15.9, 205 MB 30.4 and 30.0).  Plain loads: what stays in that cache is what Eq. Q reads next (205 MB, both passes:
-// 75.6 -> 67.7 us).  RUNS: a tensor larger than that cache, in contiguous runs and non-temporal loads as
+// that what the chip reads at one time lies together (us of this pass again and again, one contiguous run per block with
+// non-temporal loads and so: 24 MB 3.4 and 3.0, 8 TB/s from the memory-side cache, 36 MB 6.6 and 5.1, 103 MB 16.2 and 15.8,
+// 205 MB 32.1 and 30.2; 40 to 76 MB, a little more than the L2s hold, 2 to 6 % longer, 48 MB 8.0 and 8.5).  Plain loads:
+// what stays in that cache is what Eq. Q reads next (205 MB, both passes: 75.6 -> 67.7 us).  RUNS: a tensor larger than
+// that cache, in contiguous runs and non-temporal loads as
 // before (1 GiB: 153 us, 170 round robin).  A wavefront folds with lane shuffles, the four
 // wavefronts of a block fold through LDS, and one atomic per block updates the result.
 // |x| >= 0, so the IEEE bit pattern orders like an unsigned integer.
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void maxabs_kernel(const float* __restric
 
 // ---------------------------------------------------------------- Q ---------------
 // Bound by memory: 4 bytes read and 1 written per value.  Chunks round robin as in maxabs_kernel (one contiguous run
-// per block: 51 M values 40.4 us and 38.1 so, 6.4 M 8.4 and 4.9, 0.8 M 5.6 and 2.9; behind maxabs_kernel and with the
+// per block: 51 M values 39.8 us and 37.8 so, 16 M 15.3 and 13.2, 6 M 5.1 and 4.8; behind maxabs_kernel and with the
 // values' 205 MB written back between passes 64 us and 38).  The IEEE division of Eq. Q only runs next to a tie
 // (quant_fast), where before it ran for every value and bounded the kernel.  U8: codes 0..255 stored minus 128.
 // FAST = false: a factor whose reciprocal is not a normal number, every value divided.
